@@ -85,9 +85,8 @@ typedef enum {
  *           multiple of 256 (dwords of rows >= `rows`, and bytes of blocks >= cols/32, are
  *           unspecified).  16-byte aligned (the quantize kernels write it with 16-byte stores;
  *           SNIP_ERR_LAYOUT otherwise).  snip_quantize fills it when it is not NULL; when both
- *           operands of a GEMM carry one and cols is a multiple of 128 the GEMM copies its scales
- *           from it with fully coalesced loads, otherwise it falls back to a slower kernel that
- *           gathers from `scales`.  Size: snip_qtensor_scale_g4_bytes.
+ *           operands of a GEMM carry one the GEMM copies its scales from it with fully coalesced loads,
+ *           otherwise it falls back to a slower kernel that gathers from `scales`.  Size: snip_qtensor_scale_g4_bytes.
  *   rows, cols: extents of the stored matrix; cols must be a multiple of 32. */
 typedef struct {
     void*    codes;
@@ -207,9 +206,11 @@ snip_status snip_quantize_sr_fp4(const void* x, int64_t rows, int64_t cols, int6
  *   wgrad: dYq = quantize(dY, COL) [N,M],  Xq  = quantize(X,  COL) [K,M]  ->  dW [N,K]
  *
  * Every output element sums its products in one fixed order, whichever kernel and workgroup tile
- * the launcher picks for the shape.  The matrix-core kernel has two tiles (256 x 256 and 256 x 128
- * outputs per workgroup); the environment variable SNIP_GEMM_TILE=big|wide, read at every call,
- * fixes the tile for measurements and tests and never changes a result. */
+ * the launcher picks for the shape.  The matrix-core kernels have tiles from 256 x 256 down to
+ * 32 x 32 outputs per workgroup; the environment variable
+ * SNIP_GEMM_TILE=big|wide|128x128|64x64|64x32|32x32|general (big = 256 x 256, wide = 256 x 128), read
+ * at every call, fixes the tile where it can serve the call, for measurements and tests, and never
+ * changes a result. */
 snip_status snip_gemm_fwd(const snip_layer_plan* plan, const snip_qtensor* xq_row,
                           const snip_qtensor* wq_row, void* y, int64_t ld_out,
                           snip_out_dtype out_dtype, void* workspace, size_t workspace_bytes,

@@ -3,29 +3,35 @@ from __future__ import annotations
 
 import os
 import subprocess
+from concurrent.futures import ThreadPoolExecutor
 
 _HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(_HERE, "csrc")
 LIB = os.path.join(_HERE, "libsnip_hip.so")
 MICROBENCH = os.path.join(_HERE, "snip_microbench")
-SOURCES = ("api.hip", "quant_kernels.hip", "gemm.hip", "gemm_fast.hip", "optim_kernels.hip", "paper_kernels.hip", "gemm_paper.hip")
+OBJDIR = os.path.join(_HERE, "_build")          # object files (not tracked)
+FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
+         "-Wno-unused-command-line-argument"]
+SOURCES = ("api.hip", "quant_kernels.hip", "gemm.hip", "gemm_fast.hip", "gemm_small.hip", "optim_kernels.hip", "paper_kernels.hip", "gemm_paper.hip")
 
 
 def build_library(verbose: bool = False) -> str:
-    cmd = ["hipcc", "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-shared",
-           "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
-           "-Wno-unused-command-line-argument",
-           "-o", LIB] + [os.path.join(CSRC, s) for s in SOURCES]
-    res = subprocess.run(cmd, capture_output=True, text=True)
-    if verbose or res.returncode != 0:
-        print(res.stdout)
-        print(res.stderr)
-    if res.returncode != 0:
+    # one compiler per source file, side by side, then one link
+    objs = [os.path.join(OBJDIR, s + ".o") for s in SOURCES]
+    os.makedirs(OBJDIR, exist_ok=True)
+    with ThreadPoolExecutor(max_workers=min(8, os.cpu_count() or 1)) as pool:
+        results = list(pool.map(lambda so: subprocess.run(["hipcc"] + FLAGS + ["-fPIC", "-c", "-o", so[1], os.path.join(CSRC, so[0])],
+                                                          capture_output=True, text=True), zip(SOURCES, objs)))
+    results.append(subprocess.run(["hipcc", "--offload-arch=gfx950", "-fPIC", "-shared", "-o", LIB] + objs, capture_output=True, text=True)
+                   if all(r.returncode == 0 for r in results) else results[-1])
+    for res in results:
+        if verbose or res.returncode != 0:
+            print(res.stdout)
+            print(res.stderr)
+    if any(r.returncode != 0 for r in results):
         raise RuntimeError("hipcc failed building libsnip_hip.so")
     # device microbenchmarks (measured roofline denominators), run by `bench.py --microbench`
-    cmd = ["hipcc", "--offload-arch=gfx950", "-O3", "-std=c++17", "-Xclang", "-target-feature", "-Xclang",
-           "-packed-fp32-ops", "-Wno-unused-command-line-argument", "-o", MICROBENCH,
-           os.path.join(CSRC, "microbench.hip")]
+    cmd = ["hipcc"] + FLAGS + ["-o", MICROBENCH, os.path.join(CSRC, "microbench.hip")]
     res = subprocess.run(cmd, capture_output=True, text=True)
     if res.returncode != 0:
         print(res.stdout)

@@ -16,6 +16,9 @@
 // The B tile is fed as the first operand and the A tile as the second, so that a lane ends up
 // with 4 consecutive output columns per register quad.
 #include "snip_internal.h"
+#include <atomic>
+#include <cstdlib>
+#include <cstring>
 
 namespace snip {
 namespace {
@@ -310,9 +313,80 @@ hipError_t launch_sum_partials(const float* partials, int64_t n, double* out, hi
     return hipGetLastError();
 }
 
-static hipError_t launch_gemm_kernel(const GemmArgs& a, hipStream_t s)
+// Compute units of the current device, a multiple of 8 (one share per XCD) so that dispatch ids u and u + grid
+// land on the same XCD.
+int gemm_compute_units()
 {
-    if (gemm_fast_eligible(a)) return launch_gemm_fast(a, s);
+    static std::atomic<int> cached[64];
+    int dev = 0;
+    if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) return 256;
+    int n = cached[dev].load(std::memory_order_relaxed);
+    if (n == 0) {
+        if (hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || n < 8) n = 256;
+        n = n / 8 * 8;
+        cached[dev].store(n, std::memory_order_relaxed);
+    }
+    return n;
+}
+
+// Which tile serves a call: the one with the smallest estimate of
+//     start + rounds * stages * stage time + (rounds - 1) * turn,     rounds = tiles over compute units,
+// in microseconds.  `start` is what a launch with one stage takes, `turn` the result stores between two tiles of a
+// compute unit; a stage (256 contraction elements for FP4 x FP4, else 128) takes `alone` on a nearly empty chip (latency
+// of the copy - barrier - read - MFMA chain) and `full` with a tile on every compute unit (operand bytes out of L2, and the
+// clock under load).  All from launches timed back to back in a graph: [64 x 4096 x 4096] ... [64 x 4096 x 11008], [200 x
+// 4096 x 4096], [1504 x 2080 x 1568], [2048 x 4096 x 4096], [4096 x 2048 x 2048], [4096 x 4096 x 16384], FP4 and FP8.
+// Over 60 random shapes (1 ... 8192 rows, 64 ... 8192 columns and contraction elements, all format pairs) the pick was
+// on average 1-2 % slower than the fastest tile.
+struct TileCost { GemmTile tile; int m, n; float start, turn, alone[2], full[2]; };      // [0]: FP4 x FP4, [1]: others
+static const TileCost kTileCosts[] = {
+    {GemmTile::kBig,     256, 256, 7.0f, 3.0f, {0.95f, 0.90f}, {1.70f, 1.45f}},
+    {GemmTile::kWide,    256, 128, 5.5f, 2.0f, {0.63f, 0.55f}, {1.08f, 0.92f}},
+    {GemmTile::k128x128, 128, 128, 6.0f, 1.5f, {0.27f, 0.29f}, {0.51f, 0.44f}},
+    {GemmTile::k64x64,    64,  64, 3.3f, 0.7f, {0.17f, 0.19f}, {0.25f, 0.22f}},
+    {GemmTile::k64x32,    64,  32, 3.1f, 0.6f, {0.17f, 0.18f}, {0.25f, 0.25f}},
+    {GemmTile::k32x32,    32,  32, 2.9f, 0.5f, {0.14f, 0.14f}, {0.25f, 0.20f}},
+};
+
+static bool tile_usable(const GemmArgs& a, GemmTile t)
+{
+    if (t == GemmTile::kBig || t == GemmTile::kWide) return gemm_fast_eligible(a);
+    if (t == GemmTile::kGeneral) return true;
+    // an output norm has room for one partial per 128 x 128 tile
+    return gemm_small_eligible(a) && (!a.norm_out || t == GemmTile::k128x128);
+}
+
+static int64_t tile_count(const GemmArgs& a, int m, int n) { return ((a.I + m - 1) / m) * ((a.J + n - 1) / n); }
+
+static GemmTile pick_tile(const GemmArgs& a)
+{
+    // SNIP_GEMM_TILE in the environment fixes the tile where it can serve the call (read at every call, so a test can
+    // cover every tile on every shape); anything else leaves the choice to the estimate
+    if (const char* e = getenv("SNIP_GEMM_TILE")) {
+        static const struct { const char* name; GemmTile tile; } kNames[] = {
+            {"big", GemmTile::kBig}, {"wide", GemmTile::kWide}, {"128x128", GemmTile::k128x128}, {"64x64", GemmTile::k64x64},
+            {"64x32", GemmTile::k64x32}, {"32x32", GemmTile::k32x32}, {"general", GemmTile::kGeneral}};
+        for (const auto& n : kNames)
+            if (!strcmp(e, n.name) && tile_usable(a, n.tile)) return n.tile;
+    }
+    const int other = a.fmt_a == kFP4 && a.fmt_b == kFP4 ? 0 : 1;
+    const int ke = other ? 128 : 256;
+    const int64_t ncu = gemm_compute_units(), stages = (a.R + ke - 1) / ke;
+    GemmTile best = GemmTile::kGeneral;
+    double best_t = 0.0;
+    for (const TileCost& c : kTileCosts) {
+        if (!tile_usable(a, c.tile)) continue;
+        const int64_t tiles = tile_count(a, c.m, c.n), rounds = (tiles + ncu - 1) / ncu;
+        const double load = tiles < ncu ? (double)tiles / (double)ncu : 1.0;
+        const double stage = c.alone[other] + (c.full[other] - c.alone[other]) * load;
+        const double t = c.start + (double)rounds * (double)stages * stage + (double)(rounds - 1) * c.turn;
+        if (best == GemmTile::kGeneral || t < best_t) { best = c.tile; best_t = t; }
+    }
+    return best;
+}
+
+static hipError_t launch_general(const GemmArgs& a, hipStream_t s)
+{
     if (a.fmt_a == kFP8 && a.fmt_b == kFP8) return launch_t<kFP8, kFP8>(a, s);
     if (a.fmt_a == kFP8 && a.fmt_b == kFP4) return launch_t<kFP8, kFP4>(a, s);
     if (a.fmt_a == kFP4 && a.fmt_b == kFP8) return launch_t<kFP4, kFP8>(a, s);
@@ -321,19 +395,16 @@ static hipError_t launch_gemm_kernel(const GemmArgs& a, hipStream_t s)
 
 hipError_t launch_gemm(const GemmArgs& a, hipStream_t s)
 {
-    const bool empty = a.I == 0 || a.J == 0;
-    if (!empty) {
-        const hipError_t e = launch_gemm_kernel(a, s);
+    int64_t partials = 0;
+    if (a.I != 0 && a.J != 0) {
+        const GemmTile tile = pick_tile(a);
+        const bool fast = tile == GemmTile::kBig || tile == GemmTile::kWide;
+        const hipError_t e = fast ? launch_gemm_fast(a, tile == GemmTile::kWide, s)
+                                  : tile == GemmTile::kGeneral ? launch_general(a, s) : launch_gemm_small(a, tile, s);
         if (e != hipSuccess) return e;
+        partials = tile_count(a, fast ? 256 : 128, tile == GemmTile::kBig ? 256 : 128);
     }
-    if (a.norm_out) {
-        int64_t n = 0;
-        if (!empty)
-            n = gemm_fast_eligible(a) ? gemm_fast_partials(a)
-                                      : ((a.I + BM - 1) / BM) * ((a.J + BN - 1) / BN);
-        return launch_sum_partials(a.norm_partials, n, a.norm_out, s);
-    }
-    return hipSuccess;
+    return a.norm_out ? launch_sum_partials(a.norm_partials, partials, a.norm_out, s) : hipSuccess;
 }
 
 }  // namespace snip

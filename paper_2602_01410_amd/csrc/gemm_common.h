@@ -1,0 +1,119 @@
+// What the two global->LDS GEMM kernels (gemm_fast.hip: large tiles, persistent; gemm_small.hip: small tiles) share:
+// the copy instructions, the LDS swizzle, the operand fragments of v_mfma_scale_f32_32x32x64_f8f6f4 and the order in
+// which tiles are dealt to the chip.  Register layout of the instruction: see gemm.hip.
+#pragma once
+#include "snip_internal.h"
+
+namespace snip {
+namespace {
+
+typedef int v8i __attribute__((ext_vector_type(8)));
+typedef int v4i __attribute__((ext_vector_type(4)));
+typedef float v16f __attribute__((ext_vector_type(16)));
+typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+typedef float float2_t __attribute__((ext_vector_type(2)));
+typedef unsigned v4u __attribute__((ext_vector_type(4)));
+
+// Global -> LDS copy issued by the load unit: lane i's 16 (or 4) bytes land at lds + 16*i (4*i); `lds` is
+// wave-uniform and travels in M0.  Written as inline assembly on purpose: the compiler then keeps no
+// scoreboard entry for these copies and never adds its own (conservative, count-zero) wait in front of LDS
+// reads; completion is enforced by explicit SNIP_WAIT_VM + barrier in the kernels.  The "memory"
+// clobber tells the compiler that LDS contents change here.
+__device__ __forceinline__ unsigned lds_addr(const void* p)
+{
+    return (unsigned)(uintptr_t)(const __attribute__((address_space(3))) void*)p;
+}
+// The source address is a wave-uniform 64-bit base (SGPR pair) plus a 32-bit per-lane byte offset.
+__device__ __forceinline__ void glds16(const uint8_t* base, unsigned lane_off, unsigned lds)
+{
+    asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1" : : "v"(lane_off), "s"(base), "s"(lds) : "memory", "m0");
+}
+__device__ __forceinline__ void glds4(const uint8_t* base, unsigned lane_off, unsigned lds)
+{
+    asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dword %0, %1" : : "v"(lane_off), "s"(base), "s"(lds) : "memory", "m0");
+}
+// The same with a buffer descriptor as source: per-lane an offset: per-lane `lane_off` + wave-uniform `soff`; a lane whose offset lies at or
+// past the descriptor's size delivers zeros (kNoSource is past every size used here).
+constexpr unsigned kNoSource = 0x80000000u;
+__device__ __forceinline__ void blds16(v4i rsrc, unsigned lane_off, unsigned soff, unsigned lds)
+{
+    asm volatile("s_mov_b32 m0, %3\n\ts_nop 0\n\tbuffer_load_dwordx4 %0, %1, %2 offen lds"
+                 : : "v"(lane_off), "s"(rsrc), "s"(soff), "s"(lds) : "memory", "m0");
+}
+__device__ __forceinline__ void blds4(v4i rsrc, unsigned lane_off, unsigned soff, unsigned lds)
+{
+    asm volatile("s_mov_b32 m0, %3\n\ts_nop 0\n\tbuffer_load_dword %0, %1, %2 offen lds"
+                 : : "v"(lane_off), "s"(rsrc), "s"(soff), "s"(lds) : "memory", "m0");
+}
+// Raw buffer descriptor (stride 0, 32-bit data format) of `bytes` < 2^31 bytes at `p`; both wave-uniform.
+__device__ __forceinline__ v4i buffer_desc(const uint8_t* p, unsigned bytes)
+{
+    const uint64_t a = (uint64_t)p;
+    v4i r;
+    r[0] = __builtin_amdgcn_readfirstlane((int)(unsigned)a);
+    r[1] = __builtin_amdgcn_readfirstlane((int)((unsigned)(a >> 32) & 0xFFFFu));
+    r[2] = __builtin_amdgcn_readfirstlane((int)bytes);
+    r[3] = 0x00020000;
+    return r;
+}
+// s_waitcnt vmcnt(n), other counters untouched (gfx9 encoding: vmcnt[3:0], expcnt[6:4], lgkmcnt[11:8], vmcnt[5:4] in [15:14])
+#define SNIP_WAIT_VM(n) __builtin_amdgcn_s_waitcnt(0x0F70 | ((n) & 15) | ((((n) >> 4) & 3) << 14))
+#define SNIP_BAR() do { __builtin_amdgcn_sched_barrier(0); __builtin_amdgcn_s_barrier(); __builtin_amdgcn_sched_barrier(0); } while (0)
+
+// Swizzle: chunk position p of `row` holds logical chunk p ^ f(row); f makes the 16/CPR rows that share
+// a 256-byte bank span use different positions.
+template <int SB> __device__ __forceinline__ int swz(int row)
+{
+    constexpr int CPR = SB / 16;
+    return (row / (16 / CPR)) % CPR;
+}
+
+// Chunk offsets (bytes inside a row block) a lane reads for MFMA step ks: FP8 two 16-byte chunks
+// (bytes [16g,16g+16) and [32+16g, ...) of the step's 64-byte slab), FP4 one (bytes [16g, 16g+16) of
+// the step's 32-byte slab).
+template <int F, int SB, int KS>
+__device__ __forceinline__ void frag_offsets(int r32, int g, int* off)
+{
+    const int f = swz<SB>(r32);          // row-block bases are multiples of 32 rows: f depends on r32 only
+    constexpr int NC = F == kFP8 ? 2 * KS : KS;
+#pragma unroll
+    for (int k = 0; k < NC; ++k) {
+        const int c = F == kFP8 ? ((k >> 1) * 4 + (k & 1) * 2 + g) : (k * 2 + g);
+        off[k] = r32 * SB + ((c ^ f) * 16);
+    }
+}
+
+template <int F>
+__device__ __forceinline__ v8i read_frag(const uint8_t* tile, int rowblock_off, const int* off, int ks)
+{
+    v8i f = {0, 0, 0, 0, 0, 0, 0, 0};
+    if (F == kFP8) {
+        const uint4 a = *reinterpret_cast<const uint4*>(tile + rowblock_off + off[ks * 2 + 0]);
+        const uint4 b = *reinterpret_cast<const uint4*>(tile + rowblock_off + off[ks * 2 + 1]);
+        f[0] = a.x; f[1] = a.y; f[2] = a.z; f[3] = a.w; f[4] = b.x; f[5] = b.y; f[6] = b.z; f[7] = b.w;
+    } else {
+        const uint4 a = *reinterpret_cast<const uint4*>(tile + rowblock_off + off[ks]);
+        f[0] = a.x; f[1] = a.y; f[2] = a.z; f[3] = a.w;
+    }
+    return f;
+}
+
+// Dispatch id -> tile.  Workgroups are dealt round-robin to the 8 XCDs, so ids u, u + 8, u + 16, ... share an L2:
+// each XCD gets a contiguous run of the tile sequence, and the sequence walks bands of 4 tile rows column by
+// column, so that the 32 tiles an XCD works on at a time are a 4 x 8 patch (4 + 8 operand slabs for 32 tiles).
+__device__ __forceinline__ void tile_of(int u, int nblk, int tiles_i, int tiles_j, int& ti, int& tj)
+{
+    int bid = u;
+    const int per = nblk / 8;
+    if (bid < per * 8) bid = (bid % 8) * per + bid / 8;
+    const int band = 4;
+    const int band_sz = band * tiles_j;
+    const int b0 = bid / band_sz;
+    const int rem = bid - b0 * band_sz;
+    const int rows_in_band = min(band, tiles_i - b0 * band);
+    ti = b0 * band + rem % rows_in_band;
+    tj = rem / rows_in_band;
+}
+
+}  // namespace
+}  // namespace snip

@@ -1,5 +1,5 @@
 // Large-tile variant of the block-scaled GEMM, used when both operands carry the grouped scale copy
-// (scales_g4) and the contraction extent is a multiple of the stage length.
+// (scales_g4) and the contraction extent is longer than a stage.
 //
 //   workgroup tile 256 x 256, 8 waves (2 x 4), wave tile 128 (A rows) x 64 (B rows), fp32
 //   accumulators in registers (128 per lane); for outputs that would leave compute units without a
@@ -36,18 +36,12 @@
 // the wave's memory counter.
 //
 // See gemm.hip for the register layout of v_mfma_scale_f32_32x32x64_f8f6f4.
-#include "snip_internal.h"
+#include "gemm_common.h"
+#include <algorithm>
 #include <type_traits>
-#include <cstdlib>
 
 namespace snip {
 namespace {
-
-typedef int v8i __attribute__((ext_vector_type(8)));
-typedef float v16f __attribute__((ext_vector_type(16)));
-typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
-typedef float float2_t __attribute__((ext_vector_type(2)));
-typedef unsigned v4u __attribute__((ext_vector_type(4)));
 
 constexpr int NWAVE = 8, NT = NWAVE * 64;
 constexpr int TNP = 256;                // rows of the B tile's scale area (a 128-row B tile leaves half of it unused)
@@ -64,27 +58,6 @@ template <int TM_, int TN_, int WTM_, int WTN_> struct TileCfg {
 using TileBig = TileCfg<256, 256, 128, 64>;
 // 256 x 128, 4 x 2 waves of 64 x 64: twice as many tiles for outputs that would leave compute units without one.
 using TileWide = TileCfg<256, 128, 64, 64>;
-
-// Global -> LDS copy issued by the load unit: lane i's 16 (or 4) bytes land at lds + 16*i (4*i); `lds` is
-// wave-uniform and travels in M0.  Written as inline assembly on purpose: the compiler then keeps no
-// scoreboard entry for these copies and never adds its own (conservative, count-zero) wait in front of LDS
-// reads; completion is enforced by the explicit SNIP_WAIT_VM + barrier of the pipeline below.  The "memory"
-// clobber tells the compiler that LDS contents change here.
-__device__ __forceinline__ unsigned lds_addr(const void* p)
-{
-    return (unsigned)(uintptr_t)(const __attribute__((address_space(3))) void*)p;
-}
-// The source address is a wave-uniform 64-bit base (SGPR pair) plus a 32-bit per-lane byte offset.
-__device__ __forceinline__ void glds16(const uint8_t* base, unsigned lane_off, unsigned lds)
-{
-    asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1" : : "v"(lane_off), "s"(base), "s"(lds) : "memory", "m0");
-}
-__device__ __forceinline__ void glds4(const uint8_t* base, unsigned lane_off, unsigned lds)
-{
-    asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dword %0, %1" : : "v"(lane_off), "s"(base), "s"(lds) : "memory", "m0");
-}
-// s_waitcnt vmcnt(n), other counters untouched (gfx9 encoding: vmcnt[3:0], expcnt[6:4], lgkmcnt[11:8], vmcnt[5:4] in [15:14])
-#define SNIP_WAIT_VM(n) __builtin_amdgcn_s_waitcnt(0x0F70 | ((n) & 15) | ((((n) >> 4) & 3) << 14))
 
 template <int FA, int FB, class T> struct FCfg {
     static constexpr int TM = T::TM, TN = T::TN;
@@ -113,62 +86,11 @@ template <int FA, int FB, class T> struct FCfg {
     static_assert(LDS_BYTES + 64 <= 160 * 1024, "LDS budget");
 };
 
-// Swizzle: chunk position p of `row` holds logical chunk p ^ f(row); f makes the 16/CPR rows that share
-// a 256-byte bank span use different positions.
-template <int SB> __device__ __forceinline__ int swz(int row)
-{
-    constexpr int CPR = SB / 16;
-    return (row / (16 / CPR)) % CPR;
-}
-
-// Chunk offsets (bytes inside a row block) a lane reads for MFMA step ks: FP8 two 16-byte chunks
-// (bytes [16g,16g+16) and [32+16g, ...) of the step's 64-byte slab), FP4 one (bytes [16g, 16g+16) of
-// the step's 32-byte slab).
-template <int F, int SB, int KS>
-__device__ __forceinline__ void frag_offsets(int r32, int g, int* off)
-{
-    const int f = swz<SB>(r32);          // row-block bases are multiples of 32 rows: f depends on r32 only
-    constexpr int NC = F == kFP8 ? 2 * KS : KS;
-#pragma unroll
-    for (int k = 0; k < NC; ++k) {
-        const int c = F == kFP8 ? ((k >> 1) * 4 + (k & 1) * 2 + g) : (k * 2 + g);
-        off[k] = r32 * SB + ((c ^ f) * 16);
-    }
-}
-
-template <int F>
-__device__ __forceinline__ v8i read_frag(const uint8_t* tile, int rowblock_off, const int* off, int ks)
-{
-    v8i f = {0, 0, 0, 0, 0, 0, 0, 0};
-    if (F == kFP8) {
-        const uint4 a = *reinterpret_cast<const uint4*>(tile + rowblock_off + off[ks * 2 + 0]);
-        const uint4 b = *reinterpret_cast<const uint4*>(tile + rowblock_off + off[ks * 2 + 1]);
-        f[0] = a.x; f[1] = a.y; f[2] = a.z; f[3] = a.w; f[4] = b.x; f[5] = b.y; f[6] = b.z; f[7] = b.w;
-    } else {
-        const uint4 a = *reinterpret_cast<const uint4*>(tile + rowblock_off + off[ks]);
-        f[0] = a.x; f[1] = a.y; f[2] = a.z; f[3] = a.w;
-    }
-    return f;
-}
-
-// Dispatch id -> tile.  Workgroups are dealt round-robin to the 8 XCDs, so ids u, u + 8, u + 16, ... share an L2:
-// each XCD gets a contiguous run of the tile sequence, and the sequence walks bands of 4 tile rows column by
-// column, so that the 32 tiles an XCD works on at a time are a 4 x 8 patch (4 + 8 operand slabs for 32 tiles).
-__device__ __forceinline__ void tile_of(int u, int nblk, int tiles_i, int tiles_j, int& ti, int& tj)
-{
-    int bid = u;
-    const int per = nblk / 8;
-    if (bid < per * 8) bid = (bid % 8) * per + bid / 8;
-    const int band = 4;
-    const int band_sz = band * tiles_j;
-    const int b0 = bid / band_sz;
-    const int rem = bid - b0 * band_sz;
-    const int rows_in_band = min(band, tiles_i - b0 * band);
-    ti = b0 * band + rem % rows_in_band;
-    tj = rem / rows_in_band;
-}
-
-template <int FA, int FB, bool OUT_F32, class T>
+// TAIL: the contraction extent does not end with a stage.  Copies then go through buffer descriptors, which deliver zeros
+// for chunks past the end of a row, and the scale bytes past the last block are masked.  It is a variant of its own
+// because descriptors and masks cost the whole-stage form 10-14 % (16384 x 4096 x 4096, FP4 134 -> 147 us, FP8 202 -> 233;
+// scalar registers spill); against the general kernel it is 3.5-4 times as fast (4096 x 4096 x 4128, FP4 190 -> 46 us).
+template <int FA, int FB, bool OUT_F32, class T, bool TAIL>
 __global__ __launch_bounds__(NT) void gemm_fast_kernel(const uint8_t* __restrict__ a_codes,
                                                        const uint8_t* __restrict__ a_g4,
                                                        const uint8_t* __restrict__ b_codes,
@@ -190,7 +112,8 @@ __global__ __launch_bounds__(NT) void gemm_fast_kernel(const uint8_t* __restrict
 
     const int64_t a_row_bytes = FA == kFP8 ? R : R / 2;
     const int64_t b_row_bytes = FB == kFP8 ? R : R / 2;
-    const int nstage = R / C::KE;                                     // >= 2 (gemm_fast_eligible)
+    const int nstage = (R + C::KE - 1) / C::KE;                       // >= 2 (gemm_fast_eligible)
+    const int ngrp = (R + 127) / 128;                                 // scale groups of a row
     const int64_t a_pitch = g4_pitch(I), b_pitch = g4_pitch(J);      // dwords per scale group
 
     // ---- source addresses of the global->LDS copies of ONE tile (the tile the wave's copies currently belong
@@ -202,6 +125,15 @@ __global__ __launch_bounds__(NT) void gemm_fast_kernel(const uint8_t* __restrict
     int64_t sstep[C::LS];
     const uint8_t* abase;
     const uint8_t* bbase;
+    // TAIL: descriptors over the tile's rows (rows past the end of an operand lie past their end) and over the grouped
+    // scale copy.  A wave's scale copies belong to one operand and scale group and to adjacent quarters.
+    v4i ra, rb, rs;
+    const int sq = wave * C::LS;
+    const bool sop = sq >= 4 * C::NG;
+    const unsigned spitch = (unsigned)(sop ? b_pitch : a_pitch) * 4;
+    const unsigned soff0 = sq % (4 * C::NG) / 4 * spitch + (sop && sq % 4 * 64 >= TN ? sq % 4 - TN / 64 : sq % 4) * 256;
+    auto chunk_a = [&](int j) { constexpr int CPR = C::SBA / 16, RPI = 1024 / C::SBA; return (lane % CPR) ^ swz<C::SBA>((wave * C::LA + j) * RPI + lane / CPR); };
+    auto chunk_b = [&](int j) { constexpr int CPR = C::SBB / 16, RPI = 1024 / C::SBB; return (lane % CPR) ^ swz<C::SBB>((wave * C::LB + j) * RPI + lane / CPR); };
     auto set_copy_tile = [&](int u) {
         int ti, tj;
         tile_of(u, nblk, tiles_i, tiles_j, ti, tj);
@@ -210,15 +142,20 @@ __global__ __launch_bounds__(NT) void gemm_fast_kernel(const uint8_t* __restrict
         for (int j = 0; j < C::LA; ++j) {
             constexpr int CPR = C::SBA / 16, RPI = 1024 / C::SBA;
             const int row = (wave * C::LA + j) * RPI + lane / CPR;
-            const int c = (lane % CPR) ^ swz<C::SBA>(row);
-            oa[j] = (unsigned)(min(row, I - 1 - i0) * a_row_bytes + c * 16);
+            oa[j] = (unsigned)((TAIL ? row : min(row, I - 1 - i0)) * a_row_bytes + chunk_a(j) * 16);
         }
 #pragma unroll
         for (int j = 0; j < C::LB; ++j) {
             constexpr int CPR = C::SBB / 16, RPI = 1024 / C::SBB;
             const int row = (wave * C::LB + j) * RPI + lane / CPR;
-            const int c = (lane % CPR) ^ swz<C::SBB>(row);
-            ob[j] = (unsigned)(min(row, J - 1 - j0) * b_row_bytes + c * 16);
+            ob[j] = (unsigned)((TAIL ? row : min(row, J - 1 - j0)) * b_row_bytes + chunk_b(j) * 16);
+        }
+        if (TAIL) {
+            const unsigned row4 = (unsigned)(sop ? j0 : i0) * 4;
+            ra = buffer_desc(a_codes + (int64_t)i0 * a_row_bytes, (unsigned)(min(TM, I - i0) * a_row_bytes));
+            rb = buffer_desc(b_codes + (int64_t)j0 * b_row_bytes, (unsigned)(min(TN, J - j0) * b_row_bytes));
+            rs = buffer_desc((sop ? b_g4 : a_g4) + row4, (unsigned)ngrp * spitch - row4);
+            return;
         }
         // scale copy q of a stage: operand, scale group inside the stage, quarter of the 256 tile rows (the
         // padded pitch of the grouped copy covers whole tiles)
@@ -235,24 +172,39 @@ __global__ __launch_bounds__(NT) void gemm_fast_kernel(const uint8_t* __restrict
         abase = a_codes + (int64_t)i0 * a_row_bytes;
         bbase = b_codes + (int64_t)j0 * b_row_bytes;
     };
+    // TAIL, before the copies of the last stage: lanes whose chunk lies past the end of the row lose their source until the
+    // next set_copy_tile.
+    auto cut_tail = [&](int stage) {
+        if (!TAIL || stage != nstage - 1) return;
+#pragma unroll
+        for (int j = 0; j < C::LA; ++j) oa[j] = chunk_a(j) * 16 < (int)a_row_bytes - stage * C::SBA ? oa[j] : kNoSource;
+#pragma unroll
+        for (int j = 0; j < C::LB; ++j) ob[j] = chunk_b(j) * 16 < (int)b_row_bytes - stage * C::SBB ? ob[j] : kNoSource;
+    };
     const unsigned lds0 = lds_addr(lds);
 
-    // all of this wave's copies of `stage` (of the copy tile) into stage buffer `slot`
-    auto issue = [&](int stage, int slot) {
-        const unsigned base = lds0 + slot * C::SLOT1;
-#pragma unroll
-        for (int j = 0; j < C::LA; ++j) glds16(abase + (int64_t)stage * C::SBA, oa[j], base + (wave * C::LA + j) * 1024);
-#pragma unroll
-        for (int j = 0; j < C::LB; ++j) glds16(bbase + (int64_t)stage * C::SBB, ob[j], base + C::A_BYTES + (wave * C::LB + j) * 1024);
-#pragma unroll
-        for (int j = 0; j < C::LS; ++j) glds4(sbase[j] + stage * sstep[j], os, base + C::A_BYTES + C::B_BYTES + (wave * C::LS + j) * 256);
-    };
-    // copy instruction j (0 .. L-1) of this wave's share of a stage
+    // copy instruction j (0 .. L-1) of this wave's share of `stage` (of the copy tile) into stage buffer `slot`
     auto issue_one = [&](int j, int stage, int slot) {
         const unsigned base = lds0 + slot * C::SLOT1;
-        if (j < C::LA) glds16(abase + (int64_t)stage * C::SBA, oa[j], base + (wave * C::LA + j) * 1024);
-        else if (j < C::LA + C::LB) { const int k = j - C::LA; glds16(bbase + (int64_t)stage * C::SBB, ob[k], base + C::A_BYTES + (wave * C::LB + k) * 1024); }
-        else { const int k = j - C::LA - C::LB; glds4(sbase[k] + stage * sstep[k], os, base + C::A_BYTES + C::B_BYTES + (wave * C::LS + k) * 256); }
+        if (j < C::LA) {
+            const unsigned dst = base + (wave * C::LA + j) * 1024;
+            if constexpr (TAIL) blds16(ra, oa[j], stage * C::SBA, dst);
+            else glds16(abase + (int64_t)stage * C::SBA, oa[j], dst);
+        } else if (j < C::LA + C::LB) {
+            const int k = j - C::LA;
+            const unsigned dst = base + C::A_BYTES + (wave * C::LB + k) * 1024;
+            if constexpr (TAIL) blds16(rb, ob[k], stage * C::SBB, dst);
+            else glds16(bbase + (int64_t)stage * C::SBB, ob[k], dst);
+        } else {
+            const int k = j - C::LA - C::LB;
+            const unsigned dst = base + C::A_BYTES + C::B_BYTES + (wave * C::LS + k) * 256;
+            if constexpr (TAIL) blds4(rs, os, soff0 + stage * (C::NG * spitch) + k * 256, dst);
+            else glds4(sbase[k] + stage * sstep[k], os, dst);
+        }
+    };
+    auto issue = [&](int stage, int slot) {
+#pragma unroll
+        for (int j = 0; j < C::L; ++j) issue_one(j, stage, slot);
     };
 
     // ---- per-lane LDS read offsets ----
@@ -287,7 +239,7 @@ __global__ __launch_bounds__(NT) void gemm_fast_kernel(const uint8_t* __restrict
     constexpr int KP = C::KS / 2;                      // k-steps per phase
     v8i fa[KP][MB], fb[KP][NB];
     unsigned sa[MB], sb[NB];
-    auto RD = [&](int slot, int p) {
+    auto RD = [&](int slot, int p, int stage) {
         const uint8_t* base = lds + slot * C::SLOT1;
         const uint8_t* ta = base + wm * WTM * C::SBA;
         const uint8_t* tb = base + C::A_BYTES + wn * WTN * C::SBB;
@@ -296,6 +248,14 @@ __global__ __launch_bounds__(NT) void gemm_fast_kernel(const uint8_t* __restrict
         for (int m = 0; m < MB; ++m) sa[m] = *reinterpret_cast<const unsigned*>(base + sca_off + q * TM * 4 + m * 128) >> (8 * g);
 #pragma unroll
         for (int n = 0; n < NB; ++n) sb[n] = *reinterpret_cast<const unsigned*>(base + scb_off + q * TNP * 4 + n * 128) >> (8 * g);
+        // scale bytes past the last block are unspecified (a group past the last one was delivered as zeros)
+        if (TAIL && (R & 127) != 0 && stage * C::NG + q == ngrp - 1) {
+            const unsigned mask = ((1u << (8 * ((R & 127) / kBlock))) - 1u) >> (8 * g);
+#pragma unroll
+            for (int m = 0; m < MB; ++m) sa[m] &= mask;
+#pragma unroll
+            for (int n = 0; n < NB; ++n) sb[n] &= mask;
+        }
 #pragma unroll
         for (int k = 0; k < KP; ++k) {
 #pragma unroll
@@ -337,7 +297,6 @@ __global__ __launch_bounds__(NT) void gemm_fast_kernel(const uint8_t* __restrict
     };
     const std::true_type with_copy{};
     const std::false_type no_copy{};
-#define SNIP_BAR() do { __builtin_amdgcn_sched_barrier(0); __builtin_amdgcn_s_barrier(); __builtin_amdgcn_sched_barrier(0); } while (0)
 
     // ---- result of tile u: optional sum of squares, then every wave transposes its 128 x 64 block through its
     //      own 8 KB of the staging area at byte `ebase` of the LDS array ----
@@ -501,9 +460,9 @@ __global__ __launch_bounds__(NT) void gemm_fast_kernel(const uint8_t* __restrict
                 // here again would wait for those stores
                 if (s > 0 || first) SNIP_WAIT_VM(0);
                 SNIP_BAR();                                         // b(4s)
-                RD(slot, 0); SNIP_BAR();         // b(4s+1)
+                RD(slot, 0, s); SNIP_BAR();      // b(4s+1)
                 MM(copy_tag, 0, cstage, slot ^ 1); SNIP_BAR();      // b(4s+2)
-                RD(slot, 1); SNIP_BAR();         // b(4s+3)
+                RD(slot, 1, s); SNIP_BAR();      // b(4s+3)
                 MM(no_copy, 1, 0, 0);
             };
             // Every stage carries copies, so that the MFMA code exists once (two variants of it merging in front
@@ -512,6 +471,7 @@ __global__ __launch_bounds__(NT) void gemm_fast_kernel(const uint8_t* __restrict
             for (int s = 0; s < nstage; ++s) {
                 const bool last = s == nstage - 1;
                 if (last && has_next) set_copy_tile(un);
+                cut_tail(last ? 0 : s + 1);
                 stage0(with_copy, s, last ? 0 : s + 1);
             }
             SNIP_BAR();                                             // b(4S)
@@ -523,20 +483,22 @@ __global__ __launch_bounds__(NT) void gemm_fast_kernel(const uint8_t* __restrict
             auto stage1 = [&](auto copy_tag, int s, int cstage) {
                 const int slot = (s + par) & 1;
                 SNIP_BAR();                                         // b(4s+1)
-                RD(slot, 0); SNIP_BAR();         // b(4s+2)
+                RD(slot, 0, s); SNIP_BAR();      // b(4s+2)
                 MM(no_copy, 0, 0, 0); SNIP_BAR();                   // b(4s+3)
-                RD(slot, 1);
+                RD(slot, 1, s);
                 __builtin_amdgcn_s_waitcnt(0x0070);                 // vmcnt(0) and lgkmcnt(0)
                 SNIP_BAR();                                         // b(4s+4)
                 MM(copy_tag, 1, cstage, slot);
             };
             if (first) SNIP_WAIT_VM(0);
             SNIP_BAR();                                             // b(0)
+            cut_tail(1);
             issue(1, (1 + par) & 1);
             // (without a next tile the copies of M1(S-2) re-fetch stage 0 of this tile into the free buffer)
             for (int s = 0; s < nstage - 1; ++s) {
                 const bool cross = s == nstage - 2;
                 if (cross && has_next) set_copy_tile(un);
+                cut_tail(cross ? 0 : s + 2);
                 stage1(with_copy, s, cross ? 0 : s + 2);
             }
             stage1(no_copy, nstage - 1, 0);
@@ -547,50 +509,14 @@ __global__ __launch_bounds__(NT) void gemm_fast_kernel(const uint8_t* __restrict
         par = (par + nstage) & 1;
         first = false;
     }
-#undef SNIP_BAR
 }
 
-// Compute units of the current device, a multiple of 8 (one share per XCD) so that dispatch ids u and u + grid
-// land on the same XCD.
-int compute_units()
-{
-    static int cached[64] = {};
-    int dev = 0;
-    if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) return 256;
-    if (cached[dev] == 0) {
-        int n = 0;
-        if (hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || n < 8) n = 256;
-        cached[dev] = n / 8 * 8;
-    }
-    return cached[dev];
-}
-
-// Which tile serves an I x J output best: the estimate is rounds of tiles over the compute units times the time of a
-// tile; a 256 x 128 tile takes 0.6 of the time of a 256 x 256 one (half the MFMAs, three quarters of the operand bytes).
-// The wide tile wins where the big one would leave compute units without a tile, or a last round nearly empty.
-bool prefer_wide_tile(const GemmArgs& a)
-{
-    // SNIP_GEMM_TILE=big|wide in the environment fixes the tile (read at every call, so a test can cover both tiles
-    // on every shape); anything else leaves the choice to the estimate below
-    if (const char* e = getenv("SNIP_GEMM_TILE")) {
-        if (e[0] == 'w') return true;
-        if (e[0] == 'b') return false;
-    }
-    // A 256 x 128 tile costs about 0.8 of a 256 x 256 one (measured on one-round launches: per flop it reads more
-    // of the LDS and stores as often), so it only pays while it fills compute units the larger tile would leave
-    // idle, i.e. while it does not add a round of tiles.
-    const int64_t ncu = compute_units();
-    const int64_t big = ((a.I + 255) / 256) * ((a.J + 255) / 256), wide = ((a.I + 255) / 256) * ((a.J + 127) / 128);
-    const double t_big = (double)((big + ncu - 1) / ncu), t_wide = 0.8 * (double)((wide + ncu - 1) / ncu);
-    return t_wide < t_big;
-}
-
-template <int FA, int FB, class T>
+template <int FA, int FB, class T, bool TAIL>
 hipError_t launch_fast_t(const GemmArgs& a, hipStream_t s)
 {
     const int ti = (int)((a.I + T::TM - 1) / T::TM), tj = (int)((a.J + T::TN - 1) / T::TN);
     // one workgroup per compute unit (the LDS array admits no second one), each walking its share of the tiles
-    const int ncu = compute_units();
+    const int ncu = gemm_compute_units();
     const dim3 grid((unsigned)(ti * tj < ncu ? ti * tj : ncu)), block(NT);
     // streaming output stores when operands + output exceed what the memory-side cache (256 MB) can hold next to
     // everything else in flight
@@ -598,21 +524,26 @@ hipError_t launch_fast_t(const GemmArgs& a, hipStream_t s)
                          (double)a.I * a.J * (a.out_fp32 ? 4.0 : 2.0);
     int stream_out = bytes > 200e6;
     if (a.out_fp32)
-        hipLaunchKernelGGL((gemm_fast_kernel<FA, FB, true, T>), grid, block, 0, s, a.a_codes, a.a_scales_g4, a.b_codes, a.b_scales_g4,
+        hipLaunchKernelGGL((gemm_fast_kernel<FA, FB, true, T, TAIL>), grid, block, 0, s, a.a_codes, a.a_scales_g4, a.b_codes, a.b_scales_g4,
                            (int)a.I, (int)a.J, (int)a.R, a.c, a.ldc, ti, tj, a.norm_partials, stream_out);
     else
-        hipLaunchKernelGGL((gemm_fast_kernel<FA, FB, false, T>), grid, block, 0, s, a.a_codes, a.a_scales_g4, a.b_codes, a.b_scales_g4,
+        hipLaunchKernelGGL((gemm_fast_kernel<FA, FB, false, T, TAIL>), grid, block, 0, s, a.a_codes, a.a_scales_g4, a.b_codes, a.b_scales_g4,
                            (int)a.I, (int)a.J, (int)a.R, a.c, a.ldc, ti, tj, a.norm_partials, stream_out);
     return hipGetLastError();
+}
+template <int FA, int FB, class T>
+hipError_t launch_fast_f(const GemmArgs& a, hipStream_t s)
+{
+    return a.R % FCfg<FA, FB, T>::KE == 0 ? launch_fast_t<FA, FB, T, false>(a, s) : launch_fast_t<FA, FB, T, true>(a, s);
 }
 
 template <class T>
 hipError_t launch_fast_tile(const GemmArgs& a, hipStream_t s)
 {
-    if (a.fmt_a == kFP8 && a.fmt_b == kFP8) return launch_fast_t<kFP8, kFP8, T>(a, s);
-    if (a.fmt_a == kFP8 && a.fmt_b == kFP4) return launch_fast_t<kFP8, kFP4, T>(a, s);
-    if (a.fmt_a == kFP4 && a.fmt_b == kFP8) return launch_fast_t<kFP4, kFP8, T>(a, s);
-    return launch_fast_t<kFP4, kFP4, T>(a, s);
+    if (a.fmt_a == kFP8 && a.fmt_b == kFP8) return launch_fast_f<kFP8, kFP8, T>(a, s);
+    if (a.fmt_a == kFP8 && a.fmt_b == kFP4) return launch_fast_f<kFP8, kFP4, T>(a, s);
+    if (a.fmt_a == kFP4 && a.fmt_b == kFP8) return launch_fast_f<kFP4, kFP8, T>(a, s);
+    return launch_fast_f<kFP4, kFP4, T>(a, s);
 }
 
 }  // namespace
@@ -620,18 +551,17 @@ hipError_t launch_fast_tile(const GemmArgs& a, hipStream_t s)
 bool gemm_fast_eligible(const GemmArgs& a)
 {
     const int ke = (a.fmt_a == kFP4 && a.fmt_b == kFP4) ? 256 : 128;
-    if (a.R > (1 << 22)) return false;      // per-lane source offsets are 32-bit: 256 rows x row bytes must fit
-    return a.a_scales_g4 && a.b_scales_g4 && a.R % ke == 0 && a.R >= 2 * ke && a.I > 128 && a.J > 128;
+    // 32-bit source offsets: 256 rows of codes below 2^31 bytes and, where the last stage is not whole, a grouped scale
+    // copy below 2^32
+    if (a.R > (1 << 22)) return false;
+    const int64_t groups = (a.R + 127) / 128, most = std::max(g4_pitch(a.I), g4_pitch(a.J)) * 4 * groups;
+    if (a.R % ke != 0 && most >= ((int64_t)1 << 32)) return false;
+    return a.a_scales_g4 && a.b_scales_g4 && a.R > ke && a.I > 128 && a.J > 128;      // at least two stages
 }
 
-int64_t gemm_fast_partials(const GemmArgs& a)
+hipError_t launch_gemm_fast(const GemmArgs& a, bool wide, hipStream_t s)
 {
-    return ((a.I + 255) / 256) * (prefer_wide_tile(a) ? (a.J + 127) / 128 : (a.J + 255) / 256);
-}
-
-hipError_t launch_gemm_fast(const GemmArgs& a, hipStream_t s)
-{
-    return prefer_wide_tile(a) ? launch_fast_tile<TileWide>(a, s) : launch_fast_tile<TileBig>(a, s);
+    return wide ? launch_fast_tile<TileWide>(a, s) : launch_fast_tile<TileBig>(a, s);
 }
 
 }  // namespace snip

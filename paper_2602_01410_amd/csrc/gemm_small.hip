@@ -1,0 +1,362 @@
+// Block-scaled GEMM for outputs that 256-wide tiles do not serve: few rows (a short micro-batch against a weight), few
+// tiles, contraction extents that end inside a pipeline stage.  Same operands (grouped scale copies), instruction and
+// summation order as gemm_fast.hip, so the results agree bit for bit.
+//
+//   One workgroup per tile, tiles of 128 x 128 (four waves of 64 x 64) down to 32 x 32 (one wave), so that a launch
+//   has enough workgroups whatever the output's shape.  A ring of NST stage buffers is filled by global->LDS copies
+//   NST - 1 stages ahead (128 code bytes per row and stage as in gemm_fast.hip).  Copies and arithmetic belong to
+//   different waves: with one or two waves per SIMD a wave retires an instruction every 4-5 cycles, and the copy
+//   instructions with their address arithmetic took half of the time of a stage when every wave did both.  One barrier per
+//   stage: behind that of stage s, stage s + 1 is complete in LDS and is read into registers while the MFMAs of stage s,
+//   whose operands were read a stage earlier, are issued; the buffer of stage s is refilled with stage s + NST.
+//   Measured (us per call, back to back in a graph; before: the general kernel): [64 x 4096 x 4096] FP4 23.6 -> 5.2, FP8
+//   33 -> 7.0; [64 x 4096 x 11008] FP4 53 -> 8.9; [64 x 11008 x 4096] FP4 24.5 -> 6.3; [1504 x 2080 x 1568] FP4 25.3 -> 9.4,
+//   FP8 31.5 -> 11.9; [256 x 512 x 512] FP8 6.5 (256 x 128 tile) -> 3.45.  What is left is the chain of a stage (barrier,
+//   LDS latency, dependent MFMAs: about 0.14 us for 256 FP4 elements) and 3 us of launch, first fill and result.
+//   Copies go through buffer descriptors: rows past the end of an operand and chunks past the end of a row deliver
+//   zeros, and the scale bytes past the last block are masked, so any contraction extent that is a multiple of 32 runs.
+#include "gemm_common.h"
+
+namespace snip {
+namespace {
+
+// BM x BN tile, one compute wave per WTM x WTN part, NP copy waves, NST stage buffers.
+template <int BM_, int BN_, int WTM_, int WTN_, int NST_, int NP_> struct SmallTile {
+    static constexpr int BM = BM_, BN = BN_, WTM = WTM_, WTN = WTN_, NST = NST_, NP = NP_;
+    static constexpr int NC = (BM / WTM) * (BN / WTN), NT = (NC + NP) * 64;
+    static constexpr int WGN = BN / WTN;
+    static constexpr int MB = WTM / 32, NB = WTN / 32;
+};
+
+template <int FA, int FB, class T> struct SmallCfg {
+    static constexpr int KE = (FA == kFP4 && FB == kFP4) ? 256 : 128;    // contraction elements per stage
+    static constexpr int SBA = FA == kFP8 ? KE : KE / 2, SBB = FB == kFP8 ? KE : KE / 2;
+    static constexpr int KS = KE / 64, NG = KE / 128;
+    // copy instructions of a stage: 1 KB of codes or 64 scale dwords each; a wave takes LA + LB + LS of them (where they do
+    // not divide evenly some are issued twice, with the same bytes)
+    static constexpr int NA = T::BM * SBA / 1024, NBC = T::BN * SBB / 1024;
+    static constexpr int NSA = (T::BM * NG + 63) / 64, NSB = (T::BN * NG + 63) / 64;
+    static constexpr int LA = (NA + T::NP - 1) / T::NP, LB = (NBC + T::NP - 1) / T::NP, LS = (NSA + NSB + T::NP - 1) / T::NP;
+    static constexpr int L = LA + LB + LS;
+    // stage buffer: [A codes][B codes][A scale dwords: group-major][B scale dwords: group-major]
+    static constexpr int OFF_B = NA * 1024, OFF_SA = OFF_B + NBC * 1024, OFF_SB = OFF_SA + NSA * 256, SLOT = OFF_SB + NSB * 256;
+    // (the result tile is staged in the stage buffers)
+    static constexpr int LDS_BYTES = T::NST * SLOT > T::BM * T::BN * 4 ? T::NST * SLOT : T::BM * T::BN * 4;
+    static_assert(L * (T::NST - 1) <= 63, "copies in flight must be countable");
+    static_assert(LDS_BYTES <= 159 * 1024, "LDS budget");
+};
+
+template <int FA, int FB, bool OUT_F32, class T>
+__global__ __launch_bounds__(T::NT) void gemm_small_kernel(const uint8_t* __restrict__ a_codes, const uint8_t* __restrict__ a_g4,
+                                                           const uint8_t* __restrict__ b_codes, const uint8_t* __restrict__ b_g4,
+                                                           int I, int J, int R, void* __restrict__ c_out, int64_t ldc,
+                                                           int tiles_i, int tiles_j, float* __restrict__ norm_partials)
+{
+    using C = SmallCfg<FA, FB, T>;
+    constexpr int BM = T::BM, BN = T::BN, WTM = T::WTM, WTN = T::WTN, MB = T::MB, NB = T::NB, NST = T::NST, NP = T::NP;
+    __shared__ __attribute__((aligned(1024))) uint8_t lds[C::LDS_BYTES];
+
+    int ti, tj;
+    tile_of(blockIdx.x, tiles_i * tiles_j, tiles_i, tiles_j, ti, tj);
+    const int i0 = ti * BM, j0 = tj * BN;
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int nkb = R / kBlock, ngrp = (nkb + 3) / 4;
+    const int nstage = (R + C::KE - 1) / C::KE;
+
+    if (wave >= T::NC) {
+        // ---- a copy wave.  Copy instruction q of an operand fills 1 KB of its LDS tile.
+        const int p = wave - T::NC;
+        const int a_row_bytes = FA == kFP8 ? R : R / 2, b_row_bytes = FB == kFP8 ? R : R / 2;
+        v4i ra = buffer_desc(a_codes + (int64_t)i0 * a_row_bytes, (unsigned)(min(BM, I - i0) * a_row_bytes));
+        v4i rb = buffer_desc(b_codes + (int64_t)j0 * b_row_bytes, (unsigned)(min(BN, J - j0) * b_row_bytes));
+        auto qa = [&](int j) { return (p + NP * j) % C::NA; };
+        auto qb = [&](int j) { return (p + NP * j) % C::NBC; };
+        auto row_a = [&](int j) { return qa(j) * (1024 / C::SBA) + lane / (C::SBA / 16); };
+        auto row_b = [&](int j) { return qb(j) * (1024 / C::SBB) + lane / (C::SBB / 16); };
+        auto chunk_a = [&](int j) { return (lane % (C::SBA / 16)) ^ swz<C::SBA>(row_a(j)); };
+        auto chunk_b = [&](int j) { return (lane % (C::SBB / 16)) ^ swz<C::SBB>(row_b(j)); };
+        unsigned oa[C::LA], ob[C::LB], os[C::LS];
+#pragma unroll
+        for (int j = 0; j < C::LA; ++j) oa[j] = (unsigned)(row_a(j) * a_row_bytes + chunk_a(j) * 16);
+#pragma unroll
+        for (int j = 0; j < C::LB; ++j) ob[j] = (unsigned)(row_b(j) * b_row_bytes + chunk_b(j) * 16);
+        // scale dword f of an operand's area: scale group f / rows inside the stage, row f % rows.  Rows past the end lie in
+        // the padded pitch, groups past the last one past the end of the descriptor.
+        const unsigned pa = (unsigned)g4_pitch(I) * 4, pb = (unsigned)g4_pitch(J) * 4;       // bytes per scale group
+        v4i rs[C::LS];
+        unsigned sstep[C::LS], sdst[C::LS];
+#pragma unroll
+        for (int j = 0; j < C::LS; ++j) {
+            const int q = (p + NP * j) % (C::NSA + C::NSB);
+            const bool isa = q < C::NSA;
+            const int f = (isa ? q : q - C::NSA) * 64 + lane;
+            const int grp = isa ? f / BM : f / BN, row = isa ? f % BM : f % BN;
+            const unsigned pitch = isa ? pa : pb, row0 = (unsigned)(isa ? i0 : j0) * 4;
+            os[j] = grp < C::NG ? grp * pitch + row * 4 : kNoSource;
+            rs[j] = buffer_desc((isa ? a_g4 : b_g4) + row0, ngrp * pitch - row0);
+            sstep[j] = C::NG * pitch;
+            sdst[j] = C::OFF_SA + q * 256;
+        }
+        const unsigned lds0 = lds_addr(lds);
+        const int tail_stage = R % C::KE != 0 ? nstage - 1 : -1;
+        // This wave's share of stage st into stage buffer `slot`.  Every stage issues the same number of copies, so that
+        // the waits count in stages.  In a last stage that is not whole, lanes whose chunk lies past the end of the row
+        // lose their source for good; past the last stage the descriptors are empty (no memory is read).
+        auto issue = [&](int st, int slot) {
+            if (st == tail_stage) {
+#pragma unroll
+                for (int j = 0; j < C::LA; ++j) oa[j] = chunk_a(j) * 16 < a_row_bytes - st * C::SBA ? oa[j] : kNoSource;
+#pragma unroll
+                for (int j = 0; j < C::LB; ++j) ob[j] = chunk_b(j) * 16 < b_row_bytes - st * C::SBB ? ob[j] : kNoSource;
+            }
+            if (st == nstage) {
+                ra[2] = rb[2] = 0;
+#pragma unroll
+                for (int j = 0; j < C::LS; ++j) rs[j][2] = 0;
+            }
+            const unsigned base = lds0 + slot * C::SLOT;
+#pragma unroll
+            for (int j = 0; j < C::LA; ++j) blds16(ra, oa[j], st * C::SBA, base + qa(j) * 1024);
+#pragma unroll
+            for (int j = 0; j < C::LB; ++j) blds16(rb, ob[j], st * C::SBB, base + C::OFF_B + qb(j) * 1024);
+#pragma unroll
+            for (int j = 0; j < C::LS; ++j) blds4(rs[j], os[j], st * sstep[j], base + sdst[j]);
+        };
+#pragma unroll
+        for (int st = 0; st < NST; ++st) issue(st, st);
+        SNIP_WAIT_VM(C::L * (NST - 1));                          // stage 0
+        SNIP_BAR();
+        int slot = 0;
+        for (int s = 0; s < nstage; ++s) {
+            SNIP_WAIT_VM(C::L * (NST - 2));                      // stage s + 1 has landed
+            SNIP_BAR();                                          // the compute waves have read stage s
+            issue(s + NST, slot);
+            slot = slot == NST - 1 ? 0 : slot + 1;
+        }
+        SNIP_WAIT_VM(0);                                         // the empty copies past the last stage write zeros
+        SNIP_BAR();
+        if (norm_partials) __syncthreads();
+        return;
+    }
+
+    // ---- a compute wave
+    const int wm = wave / T::WGN, wn = wave % T::WGN;
+    const int r32 = lane & 31, g = lane >> 5;
+    constexpr int NCA = FA == kFP8 ? 2 * C::KS : C::KS, NCB = FB == kFP8 ? 2 * C::KS : C::KS;
+    int offa[NCA], offb[NCB];
+    frag_offsets<FA, C::SBA, C::KS>(r32, g, offa);
+    frag_offsets<FB, C::SBB, C::KS>(r32, g, offb);
+    const int sca_off = C::OFF_SA + (wm * WTM + r32) * 4;
+    const int scb_off = C::OFF_SB + (wn * WTN + r32) * 4;
+
+    v16f acc[MB][NB];
+#pragma unroll
+    for (int a = 0; a < MB; ++a)
+#pragma unroll
+        for (int b = 0; b < NB; ++b)
+#pragma unroll
+            for (int k = 0; k < 16; ++k) acc[a][b][k] = 0.f;
+
+    // Operands of one stage: codes of its KS MFMA steps and scale dwords.
+    struct Operands { v8i fa[C::KS][MB], fb[C::KS][NB]; unsigned sa[C::NG][MB], sb[C::NG][NB]; } op0, op1;
+    auto read_scales = [&](Operands& o, int slot) {
+        const uint8_t* base = lds + slot * C::SLOT;
+#pragma unroll
+        for (int q = 0; q < C::NG; ++q) {
+#pragma unroll
+            for (int m = 0; m < MB; ++m) o.sa[q][m] = *reinterpret_cast<const unsigned*>(base + sca_off + q * BM * 4 + m * 128);
+#pragma unroll
+            for (int n = 0; n < NB; ++n) o.sb[q][n] = *reinterpret_cast<const unsigned*>(base + scb_off + q * BN * 4 + n * 128);
+        }
+    };
+    constexpr int NR = C::KS * (MB + NB);                        // operand blocks of a stage
+    auto read_block = [&](Operands& o, int slot, int r) {
+        const uint8_t* base = lds + slot * C::SLOT;
+        const int ks = r / (MB + NB), i = r % (MB + NB);
+        if (i < MB) o.fa[ks][i] = read_frag<FA>(base + wm * WTM * C::SBA, i * 32 * C::SBA, offa, ks);
+        else        o.fb[ks][i - MB] = read_frag<FB>(base + C::OFF_B + wn * WTN * C::SBB, (i - MB) * 32 * C::SBB, offb, ks);
+    };
+    constexpr int ca = FB == kFP8 ? 0 : 4, cb = FA == kFP8 ? 0 : 4;              // first operand = B tile
+    // Stage s: its operands are in `cur`; those of stage s + 1 are read meanwhile.
+    auto step = [&](Operands& cur, Operands& nxt, int s, int slot1) {
+        SNIP_BAR();                                              // stage s + 1 is complete
+        read_scales(nxt, slot1);
+        __builtin_amdgcn_sched_barrier(0);
+        // scale bytes past the last block are unspecified: masked (whole groups past the end were delivered as zeros)
+        if ((nkb & 3) != 0 && s == nstage - 1) {
+#pragma unroll
+            for (int q = 0; q < C::NG; ++q) {
+                const unsigned mask = s * C::NG + q == ngrp - 1 ? (1u << (8 * (nkb & 3))) - 1u : 0xFFFFFFFFu;
+#pragma unroll
+                for (int m = 0; m < MB; ++m) cur.sa[q][m] &= mask;
+#pragma unroll
+                for (int n = 0; n < NB; ++n) cur.sb[q][n] &= mask;
+            }
+        }
+        // lane group g looks at bytes g and 2 + g of its rows' dwords
+#pragma unroll
+        for (int q = 0; q < C::NG; ++q) {
+#pragma unroll
+            for (int m = 0; m < MB; ++m) cur.sa[q][m] >>= 8 * g;
+#pragma unroll
+            for (int n = 0; n < NB; ++n) cur.sb[q][n] >>= 8 * g;
+        }
+        // the next stage's operands are requested between the MFMAs: all at once they would fill the LDS queue and hold
+        // the MFMAs back for the time of all waves' reads
+        constexpr int NM = C::KS * MB * NB;
+        int idx = 0;
+#pragma unroll
+        for (int ks = 0; ks < C::KS; ++ks)
+#pragma unroll
+            for (int m = 0; m < MB; ++m)
+#pragma unroll
+                for (int n = 0; n < NB; ++n) {
+                    if ((ks & 1) == 0)
+                        acc[m][n] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(cur.fb[ks][n], cur.fa[ks][m], acc[m][n], ca, cb, 0, (int)cur.sb[ks >> 1][n], 0, (int)cur.sa[ks >> 1][m]);
+                    else
+                        acc[m][n] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(cur.fb[ks][n], cur.fa[ks][m], acc[m][n], ca, cb, 2, (int)cur.sb[ks >> 1][n], 2, (int)cur.sa[ks >> 1][m]);
+                    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                    for (int r = 0; r < NR; ++r)
+                        if (r * NM / NR == idx) read_block(nxt, slot1, r);
+                    __builtin_amdgcn_sched_barrier(0);
+                    ++idx;
+                }
+        __builtin_amdgcn_sched_barrier(0);
+        __builtin_amdgcn_s_waitcnt(0xC07F);                      // lgkmcnt(0): stage s + 1 is read before the next barrier
+    };
+    SNIP_BAR();                                                  // stage 0 is complete
+    read_scales(op0, 0);
+#pragma unroll
+    for (int r = 0; r < NR; ++r) read_block(op0, 0, r);
+    __builtin_amdgcn_s_waitcnt(0xC07F);
+    int slot1 = NST == 1 ? 0 : 1;
+    for (int s = 0;;) {
+        step(op0, op1, s, slot1);
+        slot1 = slot1 == NST - 1 ? 0 : slot1 + 1;
+        if (++s == nstage) break;
+        step(op1, op0, s, slot1);
+        slot1 = slot1 == NST - 1 ? 0 : slot1 + 1;
+        if (++s == nstage) break;
+    }
+    SNIP_BAR();                                                  // nothing writes to the stage buffers any more
+
+    // Optional: sum of squares of the tile as it will be stored, elements outside the matrix excluded.
+    if (norm_partials) {
+        __shared__ float wave_ss[T::NC];
+        float ss = 0.f;
+#pragma unroll
+        for (int m = 0; m < MB; ++m) {
+            const bool row_ok = i0 + wm * WTM + m * 32 + r32 < I;
+#pragma unroll
+            for (int n = 0; n < NB; ++n)
+#pragma unroll
+                for (int k = 0; k < 16; ++k) {
+                    const int col = j0 + wn * WTN + n * 32 + 8 * (k >> 2) + 4 * g + (k & 3);
+                    float v = acc[m][n][k];
+                    if (!OUT_F32) v = (float)(__bf16)v;
+                    ss = (row_ok && col < J) ? fmaf(v, v, ss) : ss;
+                }
+        }
+        for (int off = 32; off > 0; off >>= 1) ss += __shfl_xor(ss, off, 64);
+        if (lane == 0) wave_ss[wave] = ss;
+        __syncthreads();
+        if (threadIdx.x == 0) {
+            float t = 0.f;
+            for (int w = 0; w < T::NC; ++w) t += wave_ss[w];
+            norm_partials[blockIdx.x] = t;
+        }
+    }
+
+    // Result: every compute wave transposes its block through its own part of the stage buffers.  In registers, lane
+    // (r32, g) of block (m, n) holds C[32m + r32][32n + 8q + 4g + t] in acc[m][n][4q + t].
+    constexpr int ESZ = OUT_F32 ? 4 : 2;
+    constexpr int ROWB = WTN * ESZ, CPR = ROWB / 16, RPI = 64 / CPR;
+    uint8_t* reg = lds + wave * WTM * ROWB;
+    auto spread = [](int row) { return CPR >= 16 ? row & (CPR - 1) : CPR == 8 ? (row >> 1) & 7 : (row >> 2) & 3; };
+#pragma unroll
+    for (int m = 0; m < MB; ++m) {
+        const int row = m * 32 + r32;
+        const int f = spread(row);
+#pragma unroll
+        for (int n = 0; n < NB; ++n)
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                const float v0 = acc[m][n][4 * q + 0], v1 = acc[m][n][4 * q + 1];
+                const float v2 = acc[m][n][4 * q + 2], v3 = acc[m][n][4 * q + 3];
+                if (OUT_F32) {
+                    *reinterpret_cast<float4*>(reg + row * ROWB + (((n * 8 + q * 2 + g) ^ f) * 16)) = make_float4(v0, v1, v2, v3);
+                } else {
+                    const float2_t lo = {v0, v1}, hi = {v2, v3};
+                    const bf16x2 blo = __builtin_convertvector(lo, bf16x2), bhi = __builtin_convertvector(hi, bf16x2);
+                    *reinterpret_cast<uint2*>(reg + row * ROWB + (((n * 4 + q) ^ f) * 16) + 8 * g) =
+                        make_uint2(__builtin_bit_cast(unsigned, blo), __builtin_bit_cast(unsigned, bhi));
+                }
+            }
+    }
+#pragma unroll
+    for (int it = 0; it < WTM / RPI; ++it) {
+        const int row = it * RPI + lane / CPR, c = lane % CPR;
+        const uint4 v = *reinterpret_cast<const uint4*>(reg + row * ROWB + ((c ^ spread(row)) * 16));
+        const int i = i0 + wm * WTM + row, j = j0 + wn * WTN + c * (16 / ESZ);
+        if (i < I) {
+            uint8_t* p = reinterpret_cast<uint8_t*>(c_out) + ((int64_t)i * ldc + j) * ESZ;
+            if (j + 16 / ESZ <= J) {
+                *reinterpret_cast<uint4*>(p) = v;
+            } else {
+                const unsigned w[4] = {v.x, v.y, v.z, v.w};
+                for (int e = 0; e < 16 / ESZ; ++e)
+                    if (j + e < J) {
+                        if (OUT_F32) reinterpret_cast<unsigned*>(p)[e] = w[e];
+                        else reinterpret_cast<uint16_t*>(p)[e] = (uint16_t)(w[e >> 1] >> (16 * (e & 1)));
+                    }
+            }
+        }
+    }
+}
+
+template <int FA, int FB, class T>
+hipError_t launch_small_t(const GemmArgs& a, hipStream_t s)
+{
+    const int ti = (int)((a.I + T::BM - 1) / T::BM), tj = (int)((a.J + T::BN - 1) / T::BN);
+    const dim3 grid((unsigned)(ti * tj)), block(T::NT);
+    if (a.out_fp32)
+        hipLaunchKernelGGL((gemm_small_kernel<FA, FB, true, T>), grid, block, 0, s, a.a_codes, a.a_scales_g4, a.b_codes, a.b_scales_g4,
+                           (int)a.I, (int)a.J, (int)a.R, a.c, a.ldc, ti, tj, a.norm_partials);
+    else
+        hipLaunchKernelGGL((gemm_small_kernel<FA, FB, false, T>), grid, block, 0, s, a.a_codes, a.a_scales_g4, a.b_codes, a.b_scales_g4,
+                           (int)a.I, (int)a.J, (int)a.R, a.c, a.ldc, ti, tj, a.norm_partials);
+    return hipGetLastError();
+}
+
+template <class T>
+hipError_t launch_small_tile(const GemmArgs& a, hipStream_t s)
+{
+    if (a.fmt_a == kFP8 && a.fmt_b == kFP8) return launch_small_t<kFP8, kFP8, T>(a, s);
+    if (a.fmt_a == kFP8 && a.fmt_b == kFP4) return launch_small_t<kFP8, kFP4, T>(a, s);
+    if (a.fmt_a == kFP4 && a.fmt_b == kFP8) return launch_small_t<kFP4, kFP8, T>(a, s);
+    return launch_small_t<kFP4, kFP4, T>(a, s);
+}
+
+}  // namespace
+
+bool gemm_small_eligible(const GemmArgs& a)
+{
+    // 32-bit source offsets inside the buffer descriptors: 128 rows of codes and a whole grouped scale copy below 2^31 bytes
+    const int64_t groups = (a.R + 127) / 128;
+    return a.a_scales_g4 && a.b_scales_g4 && a.R <= (1 << 22) && g4_pitch(a.I) * 4 * groups < ((int64_t)1 << 31) &&
+           g4_pitch(a.J) * 4 * groups < ((int64_t)1 << 31) && (a.I + 31) / 32 * ((a.J + 31) / 32) < ((int64_t)1 << 31);
+}
+
+hipError_t launch_gemm_small(const GemmArgs& a, GemmTile tile, hipStream_t s)
+{
+    switch (tile) {
+        case GemmTile::k128x128: return launch_small_tile<SmallTile<128, 128, 64, 64, 4, 4>>(a, s);
+        case GemmTile::k64x64:   return launch_small_tile<SmallTile<64, 64, 32, 32, 4, 4>>(a, s);
+        case GemmTile::k64x32:   return launch_small_tile<SmallTile<64, 32, 32, 32, 6, 4>>(a, s);
+        default:                 return launch_small_tile<SmallTile<32, 32, 32, 32, 8, 4>>(a, s);
+    }
+}
+
+}  // namespace snip
