@@ -1,4 +1,5 @@
-"""Build step: compile the HIP sources in csrc/ for gfx950 into libsnip_hip.so (in-tree)."""
+"""Build step: compile the HIP sources in csrc/ for gfx950 into libsnip_hip.so and the
+native half of the Python binding into _snip_binding.so (in-tree)."""
 from __future__ import annotations
 
 import os
@@ -8,11 +9,24 @@ from concurrent.futures import ThreadPoolExecutor
 _HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(_HERE, "csrc")
 LIB = os.path.join(_HERE, "libsnip_hip.so")
+BINDING = os.path.join(_HERE, "_snip_binding.so")
 MICROBENCH = os.path.join(_HERE, "snip_microbench")
 OBJDIR = os.path.join(_HERE, "_build")          # object files (not tracked)
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
          "-Wno-unused-command-line-argument"]
 SOURCES = ("api.hip", "quant_kernels.hip", "gemm.hip", "gemm_fast.hip", "gemm_small.hip", "optim_kernels.hip", "paper_kernels.hip", "gemm_paper.hip")
+
+
+def binding_command():
+    """Host compiler line of the native half of the Python binding (csrc/binding.cpp)."""
+    import sysconfig
+    import torch
+    t = os.path.dirname(torch.__file__)
+    rocm = os.environ.get("ROCM_PATH", "/opt/rocm")
+    return ["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-D__HIP_PLATFORM_AMD__=1", "-DUSE_ROCM=1",
+            f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}", f"-I{t}/include",
+            f"-I{t}/include/torch/csrc/api/include", f"-I{rocm}/include", f"-I{sysconfig.get_paths()['include']}",
+            os.path.join(CSRC, "binding.cpp"), "-o", BINDING, f"-L{t}/lib", "-ltorch_python", "-ltorch_cpu", "-lc10", "-lc10_hip", "-ldl"]
 
 
 def build_library(verbose: bool = False) -> str:
@@ -22,6 +36,7 @@ def build_library(verbose: bool = False) -> str:
     with ThreadPoolExecutor(max_workers=min(8, os.cpu_count() or 1)) as pool:
         results = list(pool.map(lambda so: subprocess.run(["hipcc"] + FLAGS + ["-fPIC", "-c", "-o", so[1], os.path.join(CSRC, so[0])],
                                                           capture_output=True, text=True), zip(SOURCES, objs)))
+    results.append(subprocess.run(binding_command(), capture_output=True, text=True))
     results.append(subprocess.run(["hipcc", "--offload-arch=gfx950", "-fPIC", "-shared", "-o", LIB] + objs, capture_output=True, text=True)
                    if all(r.returncode == 0 for r in results) else results[-1])
     for res in results:

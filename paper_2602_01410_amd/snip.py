@@ -1,8 +1,9 @@
-"""ctypes binding of the C-ABI library declared in include/snip.h.
+"""Binding of the C-ABI library declared in include/snip.h.
 
 Argument marshalling only: every step of the path runs in the library's HIP kernels.  PyTorch
 is used for device memory and for the current stream, nothing else.  There is no fallback: if
-the library has not been built, the first call raises.
+the library has not been built, the first call raises.  The calls of a training step take their
+tensors apart in native code (csrc/binding.cpp); size queries and rare calls go through ctypes.
 """
 from __future__ import annotations
 
@@ -55,10 +56,18 @@ class _PlanC(ctypes.Structure):
 
 
 _handle = None
+_native = None          # csrc/binding.cpp, bound to the library of _handle
+
+
+def _nat():
+    """The native half of this binding: the same calls with tensors and QTensors as arguments."""
+    if _native is None or _handle is None:
+        _lib()
+    return _native
 
 
 def _lib():
-    global _handle
+    global _handle, _native
     if _handle is None:
         if not os.path.exists(LIB_PATH):
             raise RuntimeError(
@@ -120,14 +129,22 @@ def _lib():
         lib.snip_quant_error_stats_noalloc.argtypes = [vp, i64, i64, i64, ci, ci, vp, vp, vp]
         lib.snip_status_string.restype = ctypes.c_char_p
         lib.snip_status_string.argtypes = [ci]
+        from . import _snip_binding
+        _snip_binding.bind(LIB_PATH)
+        _native = _snip_binding
         _handle = lib
     return _handle
 
 
 def _stream(stream) -> int:
     if stream is None:
-        stream = torch.cuda.current_stream()
+        return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
     return stream.cuda_stream if hasattr(stream, "cuda_stream") else int(stream)
+
+
+def _handle_of(stream):
+    """Stream argument of the native calls: None stands for the current stream."""
+    return None if stream is None else _stream(stream)
 
 
 def _alloc_on(stream):
@@ -217,20 +234,17 @@ def _src(x: torch.Tensor):
 def snip_quantize(x: torch.Tensor, fmt: int, axis: int = ROW, rule: int = NO_OVERFLOW,
                   out: Optional[QTensor] = None, stats: Optional[torch.Tensor] = None,
                   workspace: Optional[torch.Tensor] = None, stream=None) -> QTensor:
-    ptr, rows, cols, ld = _src(x)
     if out is None or (stats is not None and workspace is None):
+        _, rows, cols, _ = _src(x)
         with _alloc_on(stream):
             if out is None:
                 sr, sc = (rows, cols) if axis == ROW else (cols, rows)
                 out = alloc_qtensor(sr, sc, fmt, x.device)
             if stats is not None and workspace is None:
                 workspace = alloc_workspace(rows, cols, x.device)
-    q = out.c_struct()
-    _check(_lib().snip_quantize(ptr, rows, cols, ld, fmt, axis, rule, ctypes.byref(q),
-                                stats.data_ptr() if stats is not None else None,
-                                workspace.data_ptr() if workspace is not None else None,
-                                workspace.numel() if workspace is not None else 0, _stream(stream)),
-           "snip_quantize")
+    status = _nat().quantize(x, fmt, axis, rule, out, stats, workspace, _handle_of(stream))
+    if status:
+        raise SnipError(status, "snip_quantize")
     return out
 
 
@@ -240,8 +254,8 @@ def snip_quantize_both(x: torch.Tensor, fmt_row: int, fmt_col: int, rule: int = 
                        workspace: Optional[torch.Tensor] = None, stream=None, both_formats: bool = False):
     """Row-block and column-block quantization of x from one read; returns (out_row, out_col).  With statistics
     outputs and both_formats=True they receive the error sums of both formats, not only of the ones written."""
-    ptr, rows, cols, ld = _src(x)
     if out_row is None or out_col is None or (stats_row is not None and workspace is None):
+        _, rows, cols, _ = _src(x)
         with _alloc_on(stream):
             if out_row is None:
                 out_row = alloc_qtensor(rows, cols, fmt_row, x.device)
@@ -249,28 +263,24 @@ def snip_quantize_both(x: torch.Tensor, fmt_row: int, fmt_col: int, rule: int = 
                 out_col = alloc_qtensor(cols, rows, fmt_col, x.device)
             if stats_row is not None and workspace is None:
                 workspace = alloc_workspace(rows, cols, x.device)
-    qr, qc = out_row.c_struct(), out_col.c_struct()
-    _check(_lib().snip_quantize_both(ptr, rows, cols, ld, rule, ctypes.byref(qr), ctypes.byref(qc),
-                                     stats_row.data_ptr() if stats_row is not None else None,
-                                     stats_col.data_ptr() if stats_col is not None else None,
-                                     1 if both_formats else 0,
-                                     workspace.data_ptr() if workspace is not None else None,
-                                     workspace.numel() if workspace is not None else 0, _stream(stream)),
-           "snip_quantize_both")
+    status = _nat().quantize_both(x, rule, out_row, out_col, stats_row, stats_col, 1 if both_formats else 0, workspace,
+                                  _handle_of(stream))
+    if status:
+        raise SnipError(status, "snip_quantize_both")
     return out_row, out_col
 
 
 def snip_quantize_sr_fp4(x: torch.Tensor, axis: int = ROW, rule: int = NO_OVERFLOW, seed: int = 0,
                          out: Optional[QTensor] = None, stream=None) -> QTensor:
     """FP4 quantization with stochastic rounding; `seed` (64 bit) selects the random byte stream."""
-    ptr, rows, cols, ld = _src(x)
     if out is None:
+        _, rows, cols, _ = _src(x)
         with _alloc_on(stream):
             sr, sc = (rows, cols) if axis == ROW else (cols, rows)
             out = alloc_qtensor(sr, sc, FP4, x.device)
-    q = out.c_struct()
-    _check(_lib().snip_quantize_sr_fp4(ptr, rows, cols, ld, axis, rule, int(seed) & (2 ** 64 - 1), ctypes.byref(q),
-                                       _stream(stream)), "snip_quantize_sr_fp4")
+    status = _nat().quantize_sr_fp4(x, axis, rule, int(seed) & (2 ** 64 - 1), out, _handle_of(stream))
+    if status:
+        raise SnipError(status, "snip_quantize_sr_fp4")
     return out
 
 
@@ -279,15 +289,14 @@ TILE_1x128, BLOCK_128x128 = 1, 128
 
 def snip_quantize_paper(x: torch.Tensor, fmt: int, axis: int = ROW, group: int = TILE_1x128, stream=None):
     """The paper's recipe: returns (codes uint8 [SR, SC or SC/2], scales float32 [SR or ceil(SR/128), SC/128])."""
-    ptr, rows, cols, ld = _src(x)
+    _, rows, cols, _ = _src(x)
     sr, sc = (rows, cols) if axis == ROW else (cols, rows)
     nbytes = int(_lib().snip_paper_scale_bytes(sr, sc, group))
     with _alloc_on(stream):
         codes = torch.empty((sr, sc if fmt == FP8 else sc // 2), dtype=torch.uint8, device=x.device)
         scales = torch.empty((nbytes // 4 // max(1, sc // 128), sc // 128) if sc >= 128 else (0, 0), dtype=torch.float32,
                              device=x.device)
-    _check(_lib().snip_quantize_paper(ptr, rows, cols, ld, fmt, axis, group, codes.data_ptr() if codes.numel() else None,
-                                      scales.data_ptr() if scales.numel() else None, _stream(stream)), "snip_quantize_paper")
+    _check(_nat().quantize_paper(x, fmt, axis, group, codes, scales, _handle_of(stream)), "snip_quantize_paper")
     return codes, scales
 
 
@@ -295,8 +304,8 @@ def snip_quant_error_stats_both(x: torch.Tensor, rule: int = NO_OVERFLOW, out_ro
                                 out_col: Optional[torch.Tensor] = None, workspace: Optional[torch.Tensor] = None,
                                 stream=None):
     """Statistics for both block directions from one read; returns (out_row, out_col)."""
-    ptr, rows, cols, ld = _src(x)
     if out_row is None or out_col is None or workspace is None:
+        _, rows, cols, _ = _src(x)
         with _alloc_on(stream):
             if out_row is None:
                 out_row = alloc_stats(x.device)
@@ -304,27 +313,19 @@ def snip_quant_error_stats_both(x: torch.Tensor, rule: int = NO_OVERFLOW, out_ro
                 out_col = alloc_stats(x.device)
             if workspace is None:
                 workspace = alloc_workspace(rows, cols, x.device)
-    _check(_lib().snip_quant_error_stats_both(ptr, rows, cols, ld, rule, out_row.data_ptr(), out_col.data_ptr(),
-                                              workspace.data_ptr(), workspace.numel(), _stream(stream)),
-           "snip_quant_error_stats_both")
+    _check(_nat().stats_both(x, rule, out_row, out_col, workspace, _handle_of(stream)), "snip_quant_error_stats_both")
     return out_row, out_col
 
 
 def snip_gemm_paper(a_codes, a_scales, a_fmt, a_group, b_codes, b_scales, b_fmt, b_group, out=None,
                     out_dtype=OUT_BF16, stream=None) -> torch.Tensor:
     """C = dequant(A) dequant(B)^T for operands from snip_quantize_paper (stored orientation, uint8 codes)."""
-    def pt(codes, scales, fmt, group):
-        rows = codes.shape[0]
-        cols = codes.shape[1] if fmt == FP8 else codes.shape[1] * 2
-        return _PTensorC(codes.data_ptr() if codes.numel() else None, scales.data_ptr() if scales.numel() else None,
-                         rows, cols, fmt, group)
-    pa, pb = pt(a_codes, a_scales, a_fmt, a_group), pt(b_codes, b_scales, b_fmt, b_group)
     if out is None:
         with _alloc_on(stream):
-            out = torch.empty((pa.rows, pb.rows), dtype=torch.bfloat16 if out_dtype == OUT_BF16 else torch.float32,
+            out = torch.empty((a_codes.shape[0], b_codes.shape[0]), dtype=torch.bfloat16 if out_dtype == OUT_BF16 else torch.float32,
                               device=a_codes.device)
-    _check(_lib().snip_gemm_paper(ctypes.byref(pa), ctypes.byref(pb), out.data_ptr(), out.stride(0), out_dtype,
-                                  _stream(stream)), "snip_gemm_paper")
+    _check(_nat().gemm_paper(a_codes, a_scales, a_fmt, a_group, b_codes, b_scales, b_fmt, b_group, out, out_dtype,
+                             _handle_of(stream)), "snip_gemm_paper")
     return out
 
 
@@ -355,13 +356,8 @@ def snip_adamw_sensitivity(m: torch.Tensor, v: torch.Tensor, g: torch.Tensor, be
                 out = torch.empty(1, dtype=torch.float64, device=m.device)
             if workspace is None:
                 workspace = alloc_workspace(0, 0, m.device)
-    n = m.numel()
-    _check(_lib().snip_adamw_sensitivity(m.data_ptr() if n else None, v.data_ptr() if n else None,
-                                         g.data_ptr() if n else None,
-                                         OUT_BF16 if g.dtype == torch.bfloat16 else OUT_FP32, n,
-                                         float(beta1), float(beta2), float(eps), out.data_ptr(),
-                                         workspace.data_ptr(), workspace.numel(), _stream(stream)),
-           "snip_adamw_sensitivity")
+    _check(_nat().adamw(m, v, g, OUT_BF16 if g.dtype == torch.bfloat16 else OUT_FP32, m.numel(), float(beta1), float(beta2),
+                        float(eps), out, workspace, _handle_of(stream)), "snip_adamw_sensitivity")
     return out
 
 
@@ -371,16 +367,19 @@ def snip_weight_divergence(alpha: float, beta1: float, beta2: float, t: int, sen
                                                float(err_g_sq), n, k))
 
 
-def _gemm(fn_name: str, plan, a: QTensor, b: QTensor, out, out_dtype, stream):
+_GEMM_NAMES = ("snip_gemm_fwd", "snip_gemm_dgrad", "snip_gemm_wgrad")
+
+
+def _gemm(which: int, plan, a: QTensor, b: QTensor, out, out_dtype, stream):
     if not isinstance(plan, _PlanC):
         plan = make_plan(plan)
     if out is None:
         with _alloc_on(stream):
             out = torch.empty((a.rows, b.rows), dtype=torch.bfloat16 if out_dtype == OUT_BF16 else torch.float32,
                               device=a.codes.device)
-    qa, qb = a.c_struct(), b.c_struct()
-    _check(getattr(_lib(), fn_name)(ctypes.byref(plan), ctypes.byref(qa), ctypes.byref(qb), out.data_ptr(),
-                                    out.stride(0), out_dtype, None, 0, _stream(stream)), fn_name)
+    status = _nat().gemm(which, plan, a, b, out, out_dtype, _handle_of(stream))
+    if status:
+        raise SnipError(status, _GEMM_NAMES[which])
     return out
 
 
@@ -388,39 +387,38 @@ def gemm_workspace_bytes(out_rows: int, out_cols: int) -> int:
     return int(_lib().snip_gemm_workspace_bytes(out_rows, out_cols))
 
 
-def _gemm_norm(fn_name, plan, a: QTensor, b: QTensor, out, out_dtype, sum_sq, workspace, stream):
+def _gemm_norm(which: int, plan, a: QTensor, b: QTensor, out, out_dtype, sum_sq, workspace, stream):
     if not isinstance(plan, _PlanC):
         plan = make_plan(plan)
-    dt = torch.bfloat16 if out_dtype == OUT_BF16 else torch.float32
     if out is None or sum_sq is None or workspace is None:
         with _alloc_on(stream):
             if out is None:
-                out = torch.empty((a.rows, b.rows), dtype=dt, device=a.codes.device)
+                out = torch.empty((a.rows, b.rows), dtype=torch.bfloat16 if out_dtype == OUT_BF16 else torch.float32,
+                                  device=a.codes.device)
             if sum_sq is None:
                 sum_sq = torch.empty(1, dtype=torch.float64, device=a.codes.device)
             if workspace is None:
                 workspace = torch.empty(gemm_workspace_bytes(a.rows, b.rows), dtype=torch.uint8, device=a.codes.device)
-    qa, qb = a.c_struct(), b.c_struct()
-    _check(getattr(_lib(), fn_name)(ctypes.byref(plan), ctypes.byref(qa), ctypes.byref(qb),
-                                    out.data_ptr(), out.stride(0), out_dtype, sum_sq.data_ptr(), workspace.data_ptr(),
-                                    workspace.numel(), _stream(stream)), fn_name)
+    status = _nat().gemm_norm(which, plan, a, b, out, out_dtype, sum_sq, workspace, _handle_of(stream))
+    if status:
+        raise SnipError(status, _GEMM_NAMES[which] + "_norm")
     return out, sum_sq
 
 
 def snip_gemm_fwd_norm(plan, xq_row: QTensor, wq_row: QTensor, out=None, out_dtype=OUT_BF16, sum_sq=None,
                        workspace=None, stream=None):
     """snip_gemm_fwd plus the squared Frobenius norm of Y as stored; returns (Y, sum_sq float64[1])."""
-    return _gemm_norm("snip_gemm_fwd_norm", plan, xq_row, wq_row, out, out_dtype, sum_sq, workspace, stream)
+    return _gemm_norm(0, plan, xq_row, wq_row, out, out_dtype, sum_sq, workspace, stream)
 
 
 def snip_gemm_dgrad_norm(plan, dyq_row: QTensor, wq_col: QTensor, out=None, out_dtype=OUT_BF16, sum_sq=None,
                          workspace=None, stream=None):
-    return _gemm_norm("snip_gemm_dgrad_norm", plan, dyq_row, wq_col, out, out_dtype, sum_sq, workspace, stream)
+    return _gemm_norm(1, plan, dyq_row, wq_col, out, out_dtype, sum_sq, workspace, stream)
 
 
 def snip_gemm_wgrad_norm(plan, dyq_col: QTensor, xq_col: QTensor, out=None, out_dtype=OUT_BF16, sum_sq=None,
                          workspace=None, stream=None):
-    return _gemm_norm("snip_gemm_wgrad_norm", plan, dyq_col, xq_col, out, out_dtype, sum_sq, workspace, stream)
+    return _gemm_norm(2, plan, dyq_col, xq_col, out, out_dtype, sum_sq, workspace, stream)
 
 
 def snip_loss_divergence(grad_x_sq: float, err_x_sq: float, m: int, grad_w_sq: float, err_w_sq: float,
@@ -431,33 +429,30 @@ def snip_loss_divergence(grad_x_sq: float, err_x_sq: float, m: int, grad_w_sq: f
 
 def snip_gemm_fwd(plan, xq_row: QTensor, wq_row: QTensor, out=None, out_dtype=OUT_BF16, stream=None):
     """Y[M,N] from quantize(X, ROW) and quantize(W, ROW)."""
-    return _gemm("snip_gemm_fwd", plan, xq_row, wq_row, out, out_dtype, stream)
+    return _gemm(0, plan, xq_row, wq_row, out, out_dtype, stream)
 
 
 def snip_gemm_dgrad(plan, dyq_row: QTensor, wq_col: QTensor, out=None, out_dtype=OUT_BF16, stream=None):
     """dX[M,K] from quantize(dY, ROW) and quantize(W, COL)."""
-    return _gemm("snip_gemm_dgrad", plan, dyq_row, wq_col, out, out_dtype, stream)
+    return _gemm(1, plan, dyq_row, wq_col, out, out_dtype, stream)
 
 
 def snip_gemm_wgrad(plan, dyq_col: QTensor, xq_col: QTensor, out=None, out_dtype=OUT_BF16, stream=None):
     """dW[N,K] from quantize(dY, COL) and quantize(X, COL)."""
-    return _gemm("snip_gemm_wgrad", plan, dyq_col, xq_col, out, out_dtype, stream)
+    return _gemm(2, plan, dyq_col, xq_col, out, out_dtype, stream)
 
 
 def snip_quant_error_stats(x: torch.Tensor, axis: int = ROW, rule: int = NO_OVERFLOW,
                            out: Optional[torch.Tensor] = None, per_line: Optional[torch.Tensor] = None,
                            workspace: Optional[torch.Tensor] = None, stream=None) -> torch.Tensor:
-    ptr, rows, cols, ld = _src(x)
     if out is None or workspace is None:
+        _, rows, cols, _ = _src(x)
         with _alloc_on(stream):
             if out is None:
                 out = alloc_stats(x.device)
             if workspace is None:
                 workspace = alloc_workspace(rows, cols, x.device)
-    _check(_lib().snip_quant_error_stats(ptr, rows, cols, ld, axis, rule, out.data_ptr(),
-                                         per_line.data_ptr() if per_line is not None else None,
-                                         workspace.data_ptr(), workspace.numel(), _stream(stream)),
-           "snip_quant_error_stats")
+    _check(_nat().stats(x, axis, rule, out, per_line, workspace, _handle_of(stream)), "snip_quant_error_stats")
     return out
 
 
