@@ -330,22 +330,24 @@ int gemm_compute_units()
 }
 
 // Which tile serves a call: the one with the smallest estimate of
-//     start + rounds * stages * stage time + (rounds - 1) * turn,     rounds = tiles over compute units,
-// in microseconds.  `start` is what a launch with one stage takes, `turn` the result stores between two tiles of a
-// compute unit; a stage (256 contraction elements for FP4 x FP4, else 128) takes `alone` on a nearly empty chip (latency
-// of the copy - barrier - read - MFMA chain) and `full` with a tile on every compute unit (operand bytes out of L2, and the
-// clock under load).  All from launches timed back to back in a graph: [64 x 4096 x 4096] ... [64 x 4096 x 11008], [200 x
-// 4096 x 4096], [1504 x 2080 x 1568], [2048 x 4096 x 4096], [4096 x 2048 x 2048], [4096 x 4096 x 16384], FP4 and FP8.
-// Over 60 random shapes (1 ... 8192 rows, 64 ... 8192 columns and contraction elements, all format pairs) the pick was
-// on average 1-2 % slower than the fastest tile.
-struct TileCost { GemmTile tile; int m, n; float start, turn, alone[2], full[2]; };      // [0]: FP4 x FP4, [1]: others
+//     start + full rounds * (stages * full + turn) + stages * last
+// in microseconds.  A round is a tile on every compute unit, `turn` what a compute unit loses between two tiles (result
+// stores; for the one-tile-per-workgroup kernel also the next tile's launch and first fill), `start` what a launch with one
+// stage takes.  A stage (256 contraction elements for FP4 x FP4, else 128) takes `full` with a tile on every compute unit
+// (operand bytes out of L2, and the clock under load) and on a nearly empty chip `alone` (latency of the copy - barrier -
+// read - MFMA chain) or, after full rounds, `tail`; `last` lies between by the share of compute units that have a tile.
+// Fitted to 182 problems timed back to back with every tile: the GEMMs of 1B-, 3B- and 7B-shaped blocks and random ones (64
+// ... 16384 tokens, widths 64 ... 11008, FP4 and FP8).  The pick is on average 0.4 % slower than the fastest tile (12 % at
+// worst).  Counting the last round as a full one, as if the 128 x 128 tile turned as fast as the persistent kernel's, had
+// picked that tile where 1.5 rounds of 256 x 256 are faster: [8192 x 3072 x 8192] FP4 119 -> 102 us, FP8 190 -> 178 us.
+struct TileCost { GemmTile tile; int m, n; float start, turn, alone[2], full[2], tail[2]; };      // [0]: FP4 x FP4, [1]: others
 static const TileCost kTileCosts[] = {
-    {GemmTile::kBig,     256, 256, 7.0f, 3.0f, {0.95f, 0.90f}, {1.70f, 1.45f}},
-    {GemmTile::kWide,    256, 128, 5.5f, 2.0f, {0.63f, 0.55f}, {1.08f, 0.92f}},
-    {GemmTile::k128x128, 128, 128, 6.0f, 1.5f, {0.27f, 0.29f}, {0.51f, 0.44f}},
-    {GemmTile::k64x64,    64,  64, 3.3f, 0.7f, {0.17f, 0.19f}, {0.25f, 0.22f}},
-    {GemmTile::k64x32,    64,  32, 3.1f, 0.6f, {0.17f, 0.18f}, {0.25f, 0.25f}},
-    {GemmTile::k32x32,    32,  32, 2.9f, 0.5f, {0.14f, 0.14f}, {0.25f, 0.20f}},
+    {GemmTile::kBig,     256, 256, 7.5f, 4.5f, {1.51f, 0.80f}, {1.67f, 1.48f}, {0.83f, 0.74f}},
+    {GemmTile::kWide,    256, 128, 5.3f, 2.1f, {0.98f, 0.50f}, {1.04f, 0.91f}, {1.25f, 0.63f}},
+    {GemmTile::k128x128, 128, 128, 4.7f, 3.6f, {0.37f, 0.33f}, {0.54f, 0.46f}, {0.47f, 0.29f}},
+    {GemmTile::k64x64,    64,  64, 3.1f, 1.0f, {0.17f, 0.17f}, {0.20f, 0.19f}, {0.25f, 0.14f}},
+    {GemmTile::k64x32,    64,  32, 3.1f, 1.4f, {0.16f, 0.16f}, {0.19f, 0.18f}, {0.18f, 0.19f}},
+    {GemmTile::k32x32,    32,  32, 2.9f, 1.2f, {0.13f, 0.13f}, {0.15f, 0.14f}, {0.13f, 0.13f}},
 };
 
 static bool tile_usable(const GemmArgs& a, GemmTile t)
@@ -376,10 +378,11 @@ static GemmTile pick_tile(const GemmArgs& a)
     double best_t = 0.0;
     for (const TileCost& c : kTileCosts) {
         if (!tile_usable(a, c.tile)) continue;
-        const int64_t tiles = tile_count(a, c.m, c.n), rounds = (tiles + ncu - 1) / ncu;
-        const double load = tiles < ncu ? (double)tiles / (double)ncu : 1.0;
-        const double stage = c.alone[other] + (c.full[other] - c.alone[other]) * load;
-        const double t = c.start + (double)rounds * (double)stages * stage + (double)(rounds - 1) * c.turn;
+        const int64_t tiles = tile_count(a, c.m, c.n), full_rounds = (tiles - 1) / ncu;
+        const double load = (double)(tiles - full_rounds * ncu) / (double)ncu;
+        const double idle = full_rounds > 0 ? c.tail[other] : c.alone[other];
+        const double last = idle + (c.full[other] - idle) * load;
+        const double t = c.start + (double)full_rounds * ((double)stages * c.full[other] + c.turn) + (double)stages * last;
         if (best == GemmTile::kGeneral || t < best_t) { best = c.tile; best_t = t; }
     }
     return best;
