@@ -1,0 +1,50 @@
+"""GPU parity of snip_gemm_paper where its kernel changes what it does: odd and even numbers of 128-element slabs (FP4 x FP4
+takes two per stage), fewer slabs than stage buffers, ragged tiles, more tiles than compute units, every pair of scaling
+groups.  Against the float64 product of the oracle's dequantized operands."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+from paper_2602_01410_amd import workloads as wl
+
+from gpu_util import host, require_gpu, to_dev
+
+pytestmark = pytest.mark.gpu
+
+T, B = oracle.TILE_1x128, oracle.BLOCK_128x128
+
+
+def operand(snip, rng, rows, cols, fmt, group):
+    # rows and slabs of very different size, so that a factor taken from the wrong row or slab shows
+    a = rng.standard_normal((rows, cols)) * 10.0 ** rng.uniform(-2, 2, size=(rows, 1))
+    a *= np.repeat(10.0 ** rng.uniform(-1, 1, size=(1, cols // 128)), 128, axis=1)
+    bits = wl.f32_to_bf16_bits(a.astype(np.float32))
+    codes, scales = snip.snip_quantize_paper(to_dev(bits), fmt, snip.ROW, group)
+    oc, os_ = oracle.quantize_paper(bits, fmt, oracle.ROW, group)
+    return (codes, scales, fmt, group), np.asarray(oracle.dequantize_paper(oc, os_, fmt, group), dtype=np.float64)
+
+
+@pytest.mark.parametrize("groups", [(T, T), (T, B), (B, T), (B, B)])
+@pytest.mark.parametrize("fmts", [(0, 0), (1, 1), (0, 1), (1, 0)])
+@pytest.mark.parametrize("shape", [(1, 1, 128), (128, 128, 256), (130, 72, 384), (257, 391, 640), (96, 300, 1152), (2200, 2050, 384)])
+def test_gemm_paper(shape, fmts, groups):
+    snip = require_gpu()
+    I, J, R = shape
+    rng = np.random.default_rng([I, J, R, *fmts, *groups])
+    (qa, a), (qb, b) = operand(snip, rng, I, R, fmts[0], groups[0]), operand(snip, rng, J, R, fmts[1], groups[1])
+    want = a @ b.T
+    # The matrix core adds the 64 products of an instruction with a shared alignment: bits more than 13 places below the
+    # largest product are dropped (an element of four products, 44.2, 9.0, 4.0 and 0.06, came out off by 0.0054), so the
+    # error of an element is bounded by 2^-12 of the sum of its products' magnitudes (measured over these inputs: up to
+    # 1.04e-4 of it, the same bits from every kernel with this instruction) and by 2^-8 of itself once rounded to bf16.
+    # A factor taken from a wrong row, column or slab is off by a multiple of the magnitudes.
+    mags = np.abs(a) @ np.abs(b).T
+    ld = (J + 7) // 8 * 8
+    for dtype, tdtype, own in ((snip.OUT_FP32, torch.float32, 0.0), (snip.OUT_BF16, torch.bfloat16, 2.0 ** -8)):
+        buf = torch.full((I, ld), 7.0, dtype=tdtype, device="cuda")
+        snip.snip_gemm_paper(*qa, *qb, out=buf[:, :J], out_dtype=dtype)
+        torch.cuda.synchronize()
+        got = host(buf[:, :J].to(torch.float64))
+        assert (np.abs(got - want) <= 2.0 ** -12 * mags + own * np.abs(want)).all()
+        assert bool((buf[:, J:] == 7.0).all())
