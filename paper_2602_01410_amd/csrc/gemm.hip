@@ -289,22 +289,25 @@ hipError_t launch_t(const GemmArgs& a, hipStream_t s)
 
 }  // namespace
 
-// Sum of n workgroup partials in index order, in double: one workgroup, thread t adds t, t + 1024, ...,
-// then a shared-memory tree.
-constexpr int kNormThreads = 1024;
+// Sum of n workgroup partials in double, in a fixed order: one workgroup, thread t adds t, t + 512, ..., then lanes, then waves.
+constexpr int kNormThreads = 512;
 __global__ __launch_bounds__(kNormThreads) void reduce_norm_kernel(const float* __restrict__ partials, int64_t n,
                                                                    double* __restrict__ out)
 {
-    __shared__ double sh[kNormThreads];
+    __shared__ double sh[kNormThreads / 64];
     double a = 0.0;
+#pragma unroll 8
     for (int64_t i = threadIdx.x; i < n; i += kNormThreads) a += (double)partials[i];
-    sh[threadIdx.x] = a;
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) a += __shfl_xor(a, off, 64);
+    if ((threadIdx.x & 63) == 0) sh[threadIdx.x >> 6] = a;
     __syncthreads();
-    for (int st = kNormThreads / 2; st > 0; st >>= 1) {
-        if ((int)threadIdx.x < st) sh[threadIdx.x] += sh[threadIdx.x + st];
-        __syncthreads();
+    if (threadIdx.x == 0) {
+        double t = 0.0;
+#pragma unroll
+        for (int w = 0; w < kNormThreads / 64; ++w) t += sh[w];
+        out[0] = t;
     }
-    if (threadIdx.x == 0) out[0] = sh[0];
 }
 
 hipError_t launch_sum_partials(const float* partials, int64_t n, double* out, hipStream_t s)

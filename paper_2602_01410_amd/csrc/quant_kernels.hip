@@ -596,6 +596,22 @@ __global__ __launch_bounds__(256) void quant_col_kernel(const uint16_t* __restri
     }
 }
 
+// The six sums of a workgroup's waves, added in wave order in double, to partials[workgroup][6].
+template <int WPB>
+__device__ __forceinline__ void store_wave_sums(const float (&sums)[6], int wib, int lane, float* __restrict__ partials)
+{
+    __shared__ float wave_sums[WPB][6];
+    if (lane == 0)
+#pragma unroll
+        for (int j = 0; j < 6; ++j) wave_sums[wib][j] = sums[j];
+    __syncthreads();
+    if (threadIdx.x < 6) {
+        double t = 0.0;
+        for (int w = 0; w < WPB; ++w) t += (double)wave_sums[w][threadIdx.x];
+        partials[(size_t)blockIdx.x * 6 + threadIdx.x] = (float)t;
+    }
+}
+
 // Both orientations of one tensor from one pass over HBM (Sec. 2.2: X feeds the forward GEMM with blocks along
 // its rows and the weight-gradient GEMM with blocks down its columns; W and dY likewise).  A wave owns the same
 // units as in quant_col_kernel.  For each 32-row x 128-column tile it runs the column-block path above and then
@@ -617,43 +633,51 @@ __device__ __forceinline__ void other_format_error(const unsigned* w, unsigned a
     }
 }
 
-// COOP: the four waves of a workgroup share one unit (wave w takes its tiles w, w + 4, ...) and one staging area,
-// for tensors with too few units to give every SIMD a wave: a unit's tiles are then worked on side by side instead
-// of one after the other.  Same bytes out.
-template <int FMT_R, int FMT_C, int RULE, int STATS, bool COOP = false>      // STATS: 0 none, 1 the chosen formats' errors, 2 both formats' errors
-__global__ __launch_bounds__(256) void quant_both_kernel(const uint16_t* __restrict__ x, int rows, int cols, int64_t ld,
+// NW != 0: the NW waves of a workgroup share a unit of RBU tiles (wave w takes tiles w, w + NW, ...) and one staging area.
+// NW == 0 (with statistics): a wave per unit, four of them in a workgroup.  Same bytes out.
+template <int FMT_R, int FMT_C, int RULE, int STATS, int NW, int RBU>      // STATS: 0 none, 1 the chosen formats' errors, 2 both formats' errors
+__global__ __launch_bounds__(NW ? NW * 64 : 256) void quant_both_kernel(const uint16_t* __restrict__ x, int rows, int cols, int64_t ld,
                                                          uint8_t* __restrict__ codes_r, uint8_t* __restrict__ scales_r,
                                                          uint8_t* __restrict__ g4_r, int64_t kpitch_r,
                                                          uint8_t* __restrict__ codes_c, uint8_t* __restrict__ scales_c,
                                                          uint8_t* __restrict__ g4_c, int64_t kpitch_c,
-                                                         float* __restrict__ partials)
+                                                         float* __restrict__ partials, int runs)
 {
-    constexpr int RBU = FMT_C == kFP8 ? 4 : 8;
+    constexpr bool COOP = NW != 0;
+    constexpr int WPB = COOP ? NW : kWavesPerBlock;
     constexpr int ROWB = RBU * (FMT_C == kFP8 ? 32 : 16);
     constexpr int CPR = ROWB / 16;
-    // Without the statistics the loads of the next tile are issued before the current one is worked on (two sets
-    // of 64 registers); with them the wave is bound by its arithmetic and the plain loop is faster.
-    constexpr bool PREFETCH = STATS == 0;
     __shared__ __attribute__((aligned(16))) uint8_t stage[COOP ? 1 : kWavesPerBlock][kColsPerWave * ROWB];
     __shared__ __attribute__((aligned(4))) uint8_t scale_stage[COOP ? RBU * kColsPerWave : 4];   // COOP: scale byte of (tile, column)
     const int lane = threadIdx.x & 63;
     const int wib = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     uint8_t* const reg = stage[COOP ? 0 : wib];
-    const int wave = __builtin_amdgcn_readfirstlane(blockIdx.x * kWavesPerBlock + wib);
+    const int wave = __builtin_amdgcn_readfirstlane(blockIdx.x * WPB + wib);
     const int nwaves = gridDim.x * kWavesPerBlock;
     const int ncg = (cols + kColsPerWave - 1) / kColsPerWave;
     const int nrb = rows / kBlock;
     const int nru = (nrb + RBU - 1) / RBU;
     const int units = ncg * nru;
     const int nblk = cols / kBlock;                       // blocks per row of the row-direction output
-    constexpr int KSTEP = COOP ? kWavesPerBlock : 1;      // distance between the tiles one wave takes
-    const int k_first = COOP ? wib : 0;
     const int64_t out_row_bytes = FMT_C == kFP8 ? rows : rows / 2;
     const uint2 no_seed = make_uint2(0, 0);
     float s0 = 0.f, se_c = 0.f, se_r = 0.f;
     float so_c = 0.f, so_r = 0.f;                         // STATS == 2: error sums of the format not chosen
-    for (int u = COOP ? (int)blockIdx.x : wave; u < units; u += COOP ? (int)gridDim.x : nwaves) {
-        const int ru = u / ncg, cg = u - ru * ncg;
+    // COOP: units go to the XCDs (workgroup id mod 8) in contiguous runs, and a run walks pairs of row units column group by
+    // column group, so that the two halves of a 128-byte line (FP4 codes of a row: 64 bytes per unit; FP4 codes of a column,
+    // likewise) and the scale bytes of neighbouring units meet in one L2.  (the grid is a multiple of 8 workgroups)
+    const int run = (units + 7) / 8, run0 = (int)(blockIdx.x % 8) * run, run1 = min(run0 + run, units);
+    for (int u = COOP ? run0 + (int)(blockIdx.x / 8) : wave; u < (COOP ? run1 : units); u += COOP ? (int)(gridDim.x / 8) : nwaves) {
+        int ru, cg;
+        if (COOP && runs) {
+            const int pair = u / (2 * ncg), rem = u - pair * 2 * ncg;
+            const bool single = 2 * pair + 1 == nru;                  // the last pair may be one row unit
+            ru = 2 * pair + (single ? 0 : rem & 1);
+            cg = single ? rem : rem >> 1;
+        } else {
+            ru = u / ncg;
+            cg = u - ru * ncg;
+        }
         const int c = cg * kColsPerWave + lane * 2;
         const bool act = c < cols;
         const int rcol = cg * kColsPerWave + (lane & 15) * 8;       // row direction: this lane's 8 columns
@@ -765,29 +789,15 @@ __global__ __launch_bounds__(256) void quant_both_kernel(const uint16_t* __restr
                     scales_r[(int64_t)row * nblk + (rcol >> 5)] = (uint8_t)byte;
             }
         };
-        if (PREFETCH) {
-            unsigned cv0[32], cv1[32];
-            uint4 rv0[8], rv1[8];
-            if (k_first < nb) fetch(k_first, cv0, rv0);
-            for (int k = k_first; k < nb; k += 2 * KSTEP) {
-                if (k + KSTEP < nb) fetch(k + KSTEP, cv1, rv1);
-                work(k, cv0, rv0);
-                if (k + KSTEP < nb) {
-                    if (k + 2 * KSTEP < nb) fetch(k + 2 * KSTEP, cv0, rv0);
-                    work(k + KSTEP, cv1, rv1);
-                }
-            }
-        } else {
-            for (int k = k_first; k < nb; k += KSTEP) {
-                unsigned cv[32];
-                uint4 rv[8];
-                fetch(k, cv, rv);
-                work(k, cv, rv);
-            }
+        for (int k = COOP ? wib : 0; k < nb; k += COOP ? NW : 1) {
+            unsigned cv[32];
+            uint4 rv[8];
+            fetch(k, cv, rv);
+            work(k, cv, rv);
         }
         if (COOP) {
             __syncthreads();                                   // all tiles of the unit are staged
-            for (int g = wib; 4 * g < nb; g += kWavesPerBlock) {
+            for (int g = wib; 4 * g < nb; g += WPB) {
                 const int last = min(3, nb - 1 - 4 * g);
                 unsigned lo = 0, hi = 0;
                 for (int i = 0; i <= last; ++i) {
@@ -799,7 +809,7 @@ __global__ __launch_bounds__(256) void quant_both_kernel(const uint16_t* __restr
             }
         }
 #pragma unroll
-        for (int it = k_first; it < kColsPerWave * CPR / 64; it += KSTEP) {
+        for (int it = COOP ? wib : 0; it < kColsPerWave * CPR / 64; it += COOP ? WPB : 1) {
             const int idx = it * 64 + lane;
             const int row = idx / CPR, chunk = idx % CPR;
             const uint4 q = *reinterpret_cast<const uint4*>(reg + row * ROWB + ((chunk ^ ((row >> 1) & (CPR - 1))) * 16));
@@ -815,11 +825,9 @@ __global__ __launch_bounds__(256) void quant_both_kernel(const uint16_t* __restr
         se_r = wave_sum(se_r);
         se_c = wave_sum(se_c);
         if (STATS == 2) { so_r = wave_sum(so_r); so_c = wave_sum(so_c); }
-        if (lane == 0) {
-            float* p = partials + wave * 6;
-            p[0] = s0; p[1] = FMT_R == kFP4 ? se_r : so_r; p[2] = FMT_R == kFP8 ? se_r : so_r;
-            p[3] = s0; p[4] = FMT_C == kFP4 ? se_c : so_c; p[5] = FMT_C == kFP8 ? se_c : so_c;
-        }
+        const float sums[6] = {s0, FMT_R == kFP4 ? se_r : so_r, FMT_R == kFP8 ? se_r : so_r,
+                               s0, FMT_C == kFP4 ? se_c : so_c, FMT_C == kFP8 ? se_c : so_c};
+        store_wave_sums<WPB>(sums, wib, lane, partials);
     }
 }
 
@@ -983,67 +991,70 @@ __global__ __launch_bounds__(256) void stats_both_kernel(const uint16_t* __restr
     }
 }
 
-// Second stage for stats_both_kernel: sums of n partials [n][6] in double, fixed order; out_row and out_col
-// receive three doubles each.
-__global__ __launch_bounds__(1024) void reduce_both_kernel(const float* __restrict__ partials, int n,
+// Second stages: one workgroup adds n partials in double, in a fixed order: thread t takes partials t, t + 512, ..., wave j
+// then adds component j over the threads.
+constexpr int kReduceThreads = 512;
+template <int N>
+__device__ __forceinline__ double reduce_workgroup(const double (&a)[N], double (*sh)[kReduceThreads])      // sh[N]; sum of component j in every lane of wave j
+{
+#pragma unroll
+    for (int j = 0; j < N; ++j) sh[j][threadIdx.x] = a[j];
+    __syncthreads();
+    const int j = threadIdx.x >> 6, lane = threadIdx.x & 63;
+    double t = 0.0;
+    if (j < N) {
+#pragma unroll
+        for (int k = 0; k < kReduceThreads / 64; ++k) t += sh[j][k * 64 + lane];
+#pragma unroll
+        for (int off = 32; off > 0; off >>= 1) t += __shfl_xor(t, off, 64);
+    }
+    return t;
+}
+
+// Partials [n][6] of both block directions; out_row and out_col receive three doubles each.
+__global__ __launch_bounds__(kReduceThreads) void reduce_both_kernel(const float* __restrict__ partials, int n,
                                                            double* __restrict__ out_row, double* __restrict__ out_col,
                                                            int mode_row, int mode_col)
 {
-    __shared__ double sh[6][1024];
+    __shared__ double sh[6][kReduceThreads];
     double a[6] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
-    for (int i = threadIdx.x; i < n; i += 1024)
-        for (int j = 0; j < 6; ++j) a[j] += (double)partials[(size_t)i * 6 + j];
-    for (int j = 0; j < 6; ++j) sh[j][threadIdx.x] = a[j];
-    __syncthreads();
-    for (int st = 512; st > 0; st >>= 1) {
-        if ((int)threadIdx.x < st)
-            for (int j = 0; j < 6; ++j) sh[j][threadIdx.x] += sh[j][threadIdx.x + st];
-        __syncthreads();
+#pragma unroll 4
+    for (int i = threadIdx.x; i < n; i += kReduceThreads) {
+        const float2* p = reinterpret_cast<const float2*>(partials + (size_t)i * 6);
+        const float2 v0 = p[0], v1 = p[1], v2 = p[2];
+        a[0] += (double)v0.x; a[1] += (double)v0.y; a[2] += (double)v1.x;
+        a[3] += (double)v1.y; a[4] += (double)v2.x; a[5] += (double)v2.y;
     }
+    const double t = reduce_workgroup<6>(a, sh);
     // mode 0: all three sums; mode 1 (fused FP4): the FP8 field is NaN; mode 2 (fused FP8): the FP4 field is NaN
-    if (threadIdx.x < 6) {
-        const int f = threadIdx.x % 3;
-        const int mode = threadIdx.x < 3 ? mode_row : mode_col;
-        double* out = threadIdx.x < 3 ? out_row : out_col;
+    const int j = threadIdx.x >> 6;
+    if (j < 6 && (threadIdx.x & 63) == 0) {
+        const int f = j % 3;
+        const int mode = j < 3 ? mode_row : mode_col;
+        double* out = j < 3 ? out_row : out_col;
         const bool absent = (mode == 1 && f == 2) || (mode == 2 && f == 1);
-        if (out) out[f] = absent ? __builtin_nan("") : sh[threadIdx.x][0];
+        if (out) out[f] = absent ? __builtin_nan("") : t;
     }
 }
 
-// Second stage: sum n per-wave partials [n][3] in double, fixed order, one block of 1024 threads.
-// Thread t owns partials 8t .. 8t+7 (and the same window every 8192 partials), read as six float4.
+// Partials [n][3] of one block direction.
 // mode 0: out = {p0, p1, p2}; mode 1 (fused FP4): out = {p0, p1, NaN}; mode 2 (fused FP8): {p0, NaN, p1}.
-constexpr int kReduceThreads = 1024;
 __global__ __launch_bounds__(kReduceThreads) void reduce_partials_kernel(const float* __restrict__ partials, int n,
                                                                          int mode, double* __restrict__ out)
 {
     __shared__ double sh[3][kReduceThreads];
     double a[3] = {0.0, 0.0, 0.0};
-    for (int base = threadIdx.x * 8; base < n; base += kReduceThreads * 8) {
-        if (base + 8 <= n) {
-            const float4* p = reinterpret_cast<const float4*>(partials + (size_t)base * 3);
-            float v[24];
-#pragma unroll
-            for (int k = 0; k < 6; ++k) { const float4 q = p[k]; v[4 * k] = q.x; v[4 * k + 1] = q.y; v[4 * k + 2] = q.z; v[4 * k + 3] = q.w; }
-#pragma unroll
-            for (int k = 0; k < 24; ++k) a[k % 3] += (double)v[k];
-        } else {
-            for (int i = base; i < n; ++i)
-                for (int j = 0; j < 3; ++j) a[j] += (double)partials[(size_t)i * 3 + j];
-        }
+#pragma unroll 8
+    for (int i = threadIdx.x; i < n; i += kReduceThreads) {
+        const float* p = partials + (size_t)i * 3;
+        a[0] += (double)p[0]; a[1] += (double)p[1]; a[2] += (double)p[2];
     }
-    for (int j = 0; j < 3; ++j) sh[j][threadIdx.x] = a[j];
-    __syncthreads();
-    for (int s = kReduceThreads / 2; s > 0; s >>= 1) {
-        if ((int)threadIdx.x < s)
-            for (int j = 0; j < 3; ++j) sh[j][threadIdx.x] += sh[j][threadIdx.x + s];
-        __syncthreads();
-    }
-    if (threadIdx.x == 0) {
-        const double nan = __builtin_nan("");
-        if (mode == 0)      { out[0] = sh[0][0]; out[1] = sh[1][0]; out[2] = sh[2][0]; }
-        else if (mode == 1) { out[0] = sh[0][0]; out[1] = sh[1][0]; out[2] = nan; }
-        else                { out[0] = sh[0][0]; out[1] = nan;      out[2] = sh[1][0]; }
+    const double t = reduce_workgroup<3>(a, sh);
+    const int j = threadIdx.x >> 6;
+    if (j < 3 && (threadIdx.x & 63) == 0) {
+        // the fused statistics deliver two sums: p1 is the error of the format that was written
+        if (mode == 0 || j == 0) out[j] = t;
+        else if (j == 1) { out[mode] = t; out[3 - mode] = __builtin_nan(""); }
     }
 }
 
@@ -1166,21 +1177,64 @@ hipError_t launch_quantize(const QuantArgs& a, hipStream_t s)
     return e;
 }
 
-// With the statistics of both formats: up to this many units of four tiles (half as many again of eight) a tensor is
-// quantized with one workgroup per unit (COOP), see launch_quantize_both.
-constexpr int kCoopMaxUnits = 1024;
+// Work distribution of quant_both_kernel: waves of a workgroup x tiles of the unit they share, or a wave per unit.
+enum class QbForm { k4x4, k4x8, k8x8, kWave };
+
+template <int FMT_R, int FMT_C, int RULE, int STATS, int NW, int RBU>
+static int launch_qb_form(const QuantBothArgs& a, float* partials, hipStream_t s)
+{
+    const int64_t nrb = a.rows / kBlock;
+    const int64_t units = ((a.cols + kColsPerWave - 1) / kColsPerWave) * ((nrb + RBU - 1) / RBU);
+    // A workgroup per unit.  With statistics it also needs a partial-sum slot, and its waves' sums cost as much as a sixth
+    // of a tile: at most kStreamBlocks workgroups with equal shares of the units then.
+    const int64_t most = STATS ? kStreamBlocks / 8 : (int64_t)1 << 24, run = (units + 7) / 8, share = (run + most - 1) / most;
+    const int blocks = NW ? (int)(8 * ((run + share - 1) / share)) : balanced_blocks(units);
+    // FP8 codes of columns, more than 96 MB of source: three workgroups per compute unit (as LDS admits), four and more
+    // only add streams that the memory has to serve at once: [28672 x 8192] 236 -> 209 us, [8192 x 28672] 233 -> 216,
+    // [16384 x 4096] within the noise
+    const unsigned pad = NW && STATS == 0 && FMT_C == kFP8 && a.rows * a.cols > ((int64_t)48 << 20) ? 36000 : 0;
+    hipLaunchKernelGGL((quant_both_kernel<FMT_R, FMT_C, RULE, STATS, NW, RBU>), dim3(blocks), dim3(NW ? NW * 64 : 256), pad, s,
+                       a.x, (int)a.rows, (int)a.cols, a.ld, a.codes_r, a.scales_r, a.g4_r, g4_pitch(a.rows),
+                       a.codes_c, a.scales_c, a.g4_c, g4_pitch(a.cols), partials, STATS != 2);
+    return blocks;
+}
 
 template <int FMT_R, int FMT_C, int RULE, int STATS>
-static void launch_qb(const QuantBothArgs& a, float* partials, int blocks, bool coop, hipStream_t s)
+static int launch_qb(const QuantBothArgs& a, float* partials, QbForm form, hipStream_t s)
 {
-    if (coop)
-        hipLaunchKernelGGL((quant_both_kernel<FMT_R, FMT_C, RULE, STATS, true>), dim3(blocks), dim3(256), 0, s,
-                           a.x, (int)a.rows, (int)a.cols, a.ld, a.codes_r, a.scales_r, a.g4_r, g4_pitch(a.rows),
-                           a.codes_c, a.scales_c, a.g4_c, g4_pitch(a.cols), partials);
-    else
-        hipLaunchKernelGGL((quant_both_kernel<FMT_R, FMT_C, RULE, STATS, false>), dim3(blocks), dim3(256), 0, s,
-                           a.x, (int)a.rows, (int)a.cols, a.ld, a.codes_r, a.scales_r, a.g4_r, g4_pitch(a.rows),
-                           a.codes_c, a.scales_c, a.g4_c, g4_pitch(a.cols), partials);
+    if constexpr (STATS != 0)
+        if (form == QbForm::kWave) return launch_qb_form<FMT_R, FMT_C, RULE, STATS, 0, FMT_C == kFP8 ? 4 : 8>(a, partials, s);
+    if constexpr (FMT_C == kFP4 && STATS == 2)
+        if (form == QbForm::k4x8) return launch_qb_form<FMT_R, FMT_C, RULE, STATS, 4, 8>(a, partials, s);
+    if constexpr (FMT_C == kFP4 && STATS == 0)
+        if (form == QbForm::k8x8) return launch_qb_form<FMT_R, FMT_C, RULE, STATS, 8, 8>(a, partials, s);
+    return launch_qb_form<FMT_R, FMT_C, RULE, STATS, 4, 4>(a, partials, s);
+}
+
+// Which distribution serves a call (measured, us per call back to back in a graph):
+//   - four waves with a tile each wherever nothing else is said: the loads of a tile are a wave's whole chain, and 114-122
+//     registers leave room for four waves per SIMD.  Against four waves with two tiles each (FP4 codes of columns): [2048 x
+//     2048] 9.0 -> 6.4, [4096 x 4096] 15.5 -> 12.8, [8192 x 4096] 27.2 -> 21.9, [16384 x 4096] 48 -> 38.
+//   - eight waves with a tile each for FP4 codes of columns when the source exceeds the memory-side cache (256 MB): a unit
+//     then fills 128-byte lines of the column codes, where halves of them would reach memory one by one: [16384 x 11008]
+//     152 (4 x 4) -> 144, [8192 x 28672] 193 -> 177.
+//   - the complete statistics fill the registers (two waves per SIMD in any form), and a workgroup's barrier and sums cost
+//     8-20 %: a wave per unit as soon as that gives every SIMD work, from 28 M elements (48 M with FP4 codes of columns: eight
+//     tiles per unit): [3072 x 8192] FP8 41.2 (wave) against 38.8 (4 x 4), [8192 x 4096] 41.9 against 47.2; FP4 between
+//     12 M and 48 M elements four waves with two tiles each: [4096 x 4096] 26.0 against 28.6 (4 x 4) and 42.7 (wave).
+//   - statistics of the written formats beyond the memory-side cache: a wave per unit, [8192 x 28672] FP4 216 -> 199.
+static QbForm pick_qb_form(const QuantBothArgs& a, int stats)
+{
+    // SNIP_QUANT_BOTH_UNIT=wave|workgroup in the environment, read at every call, fixes the choice for calls with
+    // statistics, for tests and measurements
+    const char* e = getenv("SNIP_QUANT_BOTH_UNIT");
+    const bool wave = e && e[0] == 'w' && e[1] == 'a', group = e && e[0] == 'w' && e[1] == 'o';
+    const int64_t elems = a.rows * a.cols;
+    const bool large = elems > ((int64_t)128 << 20);
+    if (stats == 0) return large && a.fmt_c == kFP4 ? QbForm::k8x8 : QbForm::k4x4;
+    if (stats == 1) return (large || wave) && !group ? QbForm::kWave : QbForm::k4x4;
+    if ((elems > ((int64_t)(a.fmt_c == kFP8 ? 28 : 48) << 20) || wave) && !group) return QbForm::kWave;
+    return a.fmt_c == kFP4 && elems > ((int64_t)12 << 20) ? QbForm::k4x8 : QbForm::k4x4;
 }
 
 hipError_t launch_quantize_both(const QuantBothArgs& a, hipStream_t s)
@@ -1190,31 +1244,18 @@ hipError_t launch_quantize_both(const QuantBothArgs& a, hipStream_t s)
     // second stage: which field of each triple is "not computed" (NaN); none when both formats are wanted
     const int mode_r = a.both_formats ? 0 : (a.fmt_r == kFP4 ? 1 : 2), mode_c = a.both_formats ? 0 : (a.fmt_c == kFP4 ? 1 : 2);
     if (a.rows == 0 || a.cols == 0) {
-        if (st) hipLaunchKernelGGL(reduce_both_kernel, dim3(1), dim3(1024), 0, s, (const float*)partials, 0, a.stats_r, a.stats_c, mode_r, mode_c);
+        if (st) hipLaunchKernelGGL(reduce_both_kernel, dim3(1), dim3(kReduceThreads), 0, s, (const float*)partials, 0, a.stats_r, a.stats_c, mode_r, mode_c);
         return hipGetLastError();
     }
-    const int64_t nrb = a.rows / kBlock;
-    const int rbu = a.fmt_c == kFP8 ? kRowBlocksPerUnit : 2 * kRowBlocksPerUnit;           // as in quant_both_kernel
-    const int64_t units = ((a.cols + kColsPerWave - 1) / kColsPerWave) * ((nrb + rbu - 1) / rbu);
-    // Work distribution.  One workgroup per unit (its four waves share the unit's tiles, 17 KB of LDS per workgroup,
-    // so more waves are resident) is the faster form except with the statistics of both formats, which fill the
-    // registers: there it pays only while a wave per unit would leave SIMDs without work (measured break-even: 1024
-    // units of four tiles, 1536 of eight).  SNIP_QUANT_BOTH_UNIT=wave|workgroup in the environment, read at every
-    // call, fixes the choice for tests and measurements.
     const int mode = !st ? 0 : (a.both_formats ? 2 : 1);
-    bool coop = mode != 2 || units <= (a.fmt_c == kFP8 ? kCoopMaxUnits : kCoopMaxUnits + kCoopMaxUnits / 2);
-    if (const char* e = getenv("SNIP_QUANT_BOTH_UNIT")) {
-        if (e[0] == 'w' && e[1] == 'a') coop = false;
-        if (e[0] == 'w' && e[1] == 'o') coop = true;
-    }
-    // (a workgroup walks units blockIdx.x, blockIdx.x + gridDim.x, ...; the grid stays within the partial-sum slots)
-    const int blocks = coop ? (int)(units < kStreamBlocks ? units : kStreamBlocks) : balanced_blocks(units);
+    const QbForm form = pick_qb_form(a, mode);
+    int blocks = 0;
     const int key = (a.fmt_r << 4) | (a.fmt_c << 3) | (a.rule << 2) | mode;
     switch (key) {
 #define SNIP_QB_CASE(FR, FC, RU) \
-        case ((FR) << 4) | ((FC) << 3) | ((RU) << 2) | 0: launch_qb<FR, FC, RU, 0>(a, partials, blocks, coop, s); break; \
-        case ((FR) << 4) | ((FC) << 3) | ((RU) << 2) | 1: launch_qb<FR, FC, RU, 1>(a, partials, blocks, coop, s); break; \
-        case ((FR) << 4) | ((FC) << 3) | ((RU) << 2) | 2: launch_qb<FR, FC, RU, 2>(a, partials, blocks, coop, s); break;
+        case ((FR) << 4) | ((FC) << 3) | ((RU) << 2) | 0: blocks = launch_qb<FR, FC, RU, 0>(a, partials, form, s); break; \
+        case ((FR) << 4) | ((FC) << 3) | ((RU) << 2) | 1: blocks = launch_qb<FR, FC, RU, 1>(a, partials, form, s); break; \
+        case ((FR) << 4) | ((FC) << 3) | ((RU) << 2) | 2: blocks = launch_qb<FR, FC, RU, 2>(a, partials, form, s); break;
         SNIP_QB_CASE(0, 0, 0) SNIP_QB_CASE(0, 0, 1) SNIP_QB_CASE(0, 1, 0) SNIP_QB_CASE(0, 1, 1)
         SNIP_QB_CASE(1, 0, 0) SNIP_QB_CASE(1, 0, 1) SNIP_QB_CASE(1, 1, 0) SNIP_QB_CASE(1, 1, 1)
 #undef SNIP_QB_CASE
@@ -1223,7 +1264,7 @@ hipError_t launch_quantize_both(const QuantBothArgs& a, hipStream_t s)
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     if (st) {
-        hipLaunchKernelGGL(reduce_both_kernel, dim3(1), dim3(1024), 0, s, (const float*)partials, blocks * kWavesPerBlock,
+        hipLaunchKernelGGL(reduce_both_kernel, dim3(1), dim3(kReduceThreads), 0, s, (const float*)partials, blocks,
                            a.stats_r, a.stats_c, mode_r, mode_c);
         e = hipGetLastError();
     }
@@ -1234,7 +1275,7 @@ hipError_t launch_stats_both(const StatsArgs& a, double* out_col, hipStream_t s)
 {
     float* partials = (float*)a.workspace;
     if (a.rows == 0 || a.cols == 0) {
-        hipLaunchKernelGGL(reduce_both_kernel, dim3(1), dim3(1024), 0, s, (const float*)partials, 0, a.stats, out_col, 0, 0);
+        hipLaunchKernelGGL(reduce_both_kernel, dim3(1), dim3(kReduceThreads), 0, s, (const float*)partials, 0, a.stats, out_col, 0, 0);
         return hipGetLastError();
     }
     int gx;
@@ -1245,7 +1286,7 @@ hipError_t launch_stats_both(const StatsArgs& a, double* out_col, hipStream_t s)
         hipLaunchKernelGGL((stats_both_kernel<1>), dim3(gx, nsplit), dim3(256), 0, s, a.x, (int)a.rows, (int)a.cols, a.ld, nsplit, partials);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(reduce_both_kernel, dim3(1), dim3(1024), 0, s, (const float*)partials, gx * kWavesPerBlock * nsplit,
+    hipLaunchKernelGGL(reduce_both_kernel, dim3(1), dim3(kReduceThreads), 0, s, (const float*)partials, gx * kWavesPerBlock * nsplit,
                        a.stats, out_col, 0, 0);
     return hipGetLastError();
 }

@@ -105,7 +105,7 @@ hipError_t launch_paper(const PaperArgs& a, hipStream_t s);
 
 size_t workspace_bytes(int64_t rows, int64_t cols);
 hipError_t launch_adamw_sensitivity(const AdamwArgs& a, hipStream_t s);
-// out[0] = sum of partials[0..n) in index order, in double (one workgroup); n may be 0
+// out[0] = sum of partials[0..n) in a fixed order, in double (one workgroup); n may be 0
 hipError_t launch_sum_partials(const float* partials, int64_t n, double* out, hipStream_t s);
 hipError_t launch_quantize(const QuantArgs& a, hipStream_t s);
 hipError_t launch_quantize_both(const QuantBothArgs& a, hipStream_t s);
