@@ -425,21 +425,39 @@ __device__ __forceinline__ void pair_col_block(const unsigned (&v)[32], ColBlock
     }
 }
 
-__device__ __forceinline__ void load_col_block(const uint16_t* __restrict__ p, int64_t ld, bool act, ColBlock& b)
+// Two adjacent columns (c0 + 2 * lane) of 32 rows from `row` on, streaming; zeros past the last column.  `row` is
+// wave-uniform and stepped in scalar registers, out of the compiler's sight: left alone it computes the 32 row addresses
+// ahead, runs out of scalar registers and keeps them in lanes of vector registers, which cost the statistics kernel 118
+// vector instructions per tile of 1360.  One condition around all loads and only where the tile is not whole: a branch
+// around each would keep them from being in flight together.
+__device__ __forceinline__ void load_col_tile(const uint16_t* __restrict__ row, int c0, int lane, int cols, int64_t ld, unsigned (&v)[32])
+{
+    typedef const __attribute__((address_space(1))) uint8_t* gbyte;
+    if (c0 + kColsPerWave <= cols) {
+        gbyte p = (gbyte)(uintptr_t)(row + c0);
+        const unsigned off = (unsigned)lane * 4;
+#pragma unroll
+        for (int i = 0; i < 32; ++i) {
+            v[i] = __builtin_nontemporal_load((const __attribute__((address_space(1))) unsigned*)(p + off));
+            p += ld * 2;
+            asm volatile("" : "+s"(p));
+        }
+    } else {
+#pragma unroll
+        for (int i = 0; i < 32; ++i) v[i] = 0u;
+        if (c0 + 2 * lane < cols) {
+            const uint16_t* p = row + c0 + 2 * lane;
+#pragma unroll
+            for (int i = 0; i < 32; ++i, p += ld) v[i] = ld4(p);
+        }
+    }
+}
+
+__device__ __forceinline__ void load_col_block(const uint16_t* __restrict__ row, int c0, int lane, int cols, int64_t ld, ColBlock& b)
 {
     unsigned v[32];
-#pragma unroll
-    for (int i = 0; i < 32; ++i) v[i] = act ? ld4(p + (int64_t)i * ld) : 0u;
-    unsigned m = 0;
-#pragma unroll
-    for (int i = 0; i < 32; ++i) m = pk_max_u16(m, v[i] & 0x7FFF7FFFu);
-    b.am_lo = m & 0xFFFFu;
-    b.am_hi = m >> 16;
-#pragma unroll
-    for (int k = 0; k < 16; ++k) {
-        b.lo[k] = __builtin_amdgcn_perm(v[2 * k + 1], v[2 * k], 0x05040100u);
-        b.hi[k] = __builtin_amdgcn_perm(v[2 * k + 1], v[2 * k], 0x07060302u);
-    }
+    load_col_tile(row, c0, lane, cols, ld, v);
+    pair_col_block(v, b);
 }
 
 // Codes of one column's block (32 rows) -> the wave's LDS staging area; returns the scale byte.
@@ -523,7 +541,7 @@ __global__ __launch_bounds__(256) void quant_col_kernel(const uint16_t* __restri
         // row block kk of the unit: codes into the staging area, returns the two columns' scale bytes
         auto one_block = [&](int kk, unsigned& y0, unsigned& y1) {
             ColBlock b;
-            load_col_block(x + (int64_t)(rb0 + kk) * kBlock * ld + c, ld, act, b);
+            load_col_block(x + (int64_t)(rb0 + kk) * kBlock * ld, cg * kColsPerWave, lane, cols, ld, b);
             const int64_t e0 = (int64_t)c * rows + (int64_t)(rb0 + kk) * kBlock;       // stored row = source column
             y0 = quant_one_column<FMT, RULE, STATS, SR>(b.lo, b.am_lo, reg + (2 * lane) * ROWB, kk, swz_lo, s0, se, e0, seed);
             y1 = quant_one_column<FMT, RULE, STATS, SR>(b.hi, b.am_hi, reg + (2 * lane + 1) * ROWB, kk, swz_lo, s0, se, e0 + rows, seed);
@@ -852,8 +870,12 @@ __global__ __launch_bounds__(256) void stats_col_kernel(const uint16_t* __restri
         const bool act = c < cols;
         float a0[2] = {0.f, 0.f}, a4[2] = {0.f, 0.f}, a8[2] = {0.f, 0.f};
         for (int rb = rb0; rb < rb1; ++rb) {
+            unsigned v[32];
+            const uint16_t* const p = x + (int64_t)rb * kBlock * ld + c;
+#pragma unroll
+            for (int i = 0; i < 32; ++i) v[i] = act ? ld4(p + (int64_t)i * ld) : 0u;     // (with load_col_tile: 192 registers, 10 % slower)
             ColBlock b;
-            load_col_block(x + (int64_t)rb * kBlock * ld + c, ld, act, b);
+            pair_col_block(v, b);
 #pragma unroll
             for (int h = 0; h < 2; ++h) {
                 const unsigned* w = h ? b.hi : b.lo;
@@ -888,27 +910,29 @@ __global__ __launch_bounds__(256) void stats_col_kernel(const uint16_t* __restri
 
 // Statistics for BOTH block directions from one read of the matrix (the complete Step-1 record of a tensor:
 // its forward operands are blocked along rows, its backward ones down columns, Sec. 2.2).
-// Grid and ownership as in stats_col_kernel: a wave owns 128 columns and a range of 32-row blocks; a lane
+// A wave takes 32 x 128 tiles w, w + waves, ... (row-major), so that the chip reads one band of rows at a time; a lane
 // reads two adjacent columns of every row.  The column-direction errors come straight from those registers
-// (a column's block never leaves the lane).  For the row direction the raw 32 x 128 tile goes through the
+// (a column's block never leaves the lane).  For the row direction the raw tile goes through the
 // wave's 8 KB of LDS and comes back as eight 16-byte pieces per lane: two whole 32-element row blocks, so that
-// the row direction, too, forms a block's maximum and scales inside one lane.  LDS operations
-// of one wave execute in order, so no barrier is needed between the writes and the reads.
-// partials: [waves][6] = {sum x^2, row err4, row err8, sum x^2, col err4, col err8}.
+// the row direction, too, forms a block's maximum and scales inside one lane.  LDS operations of one wave execute in order,
+// so no barrier is needed between the writes and the reads.
+// Bound by vector arithmetic: 20 instructions per element, 4 of them conversions at a third of the rate.  Against waves that
+// own a column group and a range of rows, a branch around every load (us per call): [16384 x 4096] 57.6 -> 45.5, [11008 x
+// 4096] 43.8 -> 35.4, [16384 x 11008] 130 -> 118, [16384 x 96] 32 -> 7.7.  Loading the next tile during the row phase needs
+// 142 registers and is slower (50.8, 37.5, 120).
+// partials: [workgroups][6] = {sum x^2, row err4, row err8, sum x^2, col err4, col err8}.
 template <int RULE>
 __global__ __launch_bounds__(256) void stats_both_kernel(const uint16_t* __restrict__ x, int rows,
-                                                         int cols, int64_t ld, int nsplit,
+                                                         int cols, int64_t ld,
                                                          float* __restrict__ partials)
 {
     __shared__ __attribute__((aligned(16))) unsigned tile[kWavesPerBlock][kBlock * 64];
     const int lane = threadIdx.x & 63;
-    unsigned* const raw = tile[threadIdx.x >> 6];
-    const int wave_x = __builtin_amdgcn_readfirstlane(blockIdx.x * kWavesPerBlock + (threadIdx.x >> 6));
-    const int nwaves_x = gridDim.x * kWavesPerBlock;
-    const int split = blockIdx.y;
+    const int wib = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    unsigned* const raw = tile[wib];
+    const int nwaves = gridDim.x * kWavesPerBlock;
     const int ncg = (cols + kColsPerWave - 1) / kColsPerWave;
-    const int nrb = rows / kBlock;
-    const int rb0 = (int)((int64_t)nrb * split / nsplit), rb1 = (int)((int64_t)nrb * (split + 1) / nsplit);
+    const int ntiles = rows / kBlock * ncg;
     float t0 = 0.f, r4 = 0.f, r8 = 0.f, c4 = 0.f, c8 = 0.f;
     bool bad = false;
     // LDS image of the raw tile: row i holds its sixteen 16-byte pieces at positions piece ^ (i % 4), so that the
@@ -919,14 +943,10 @@ __global__ __launch_bounds__(256) void stats_both_kernel(const uint16_t* __restr
         wpos[t] = (((lane >> 2) ^ t) << 2) | (lane & 3);                                   // dword lane of a row with i % 4 == t
         rpos[t] = (lane >> 2) * 64 + ((((lane & 3) * 4 + t) ^ ((lane >> 2) & 3)) << 2);    // piece t of block lane % 4, row lane / 4
     }
-    for (int cg = wave_x; cg < ncg; cg += nwaves_x) {
-        const int c = cg * kColsPerWave + lane * 2;
-        const bool act = c < cols;
-        for (int rb = rb0; rb < rb1; ++rb) {
-            const uint16_t* p = x + (int64_t)rb * kBlock * ld + c;
+    for (int t = blockIdx.x * kWavesPerBlock + wib; t < ntiles; t += nwaves) {
+            const int rb = t / ncg, c0 = (t - rb * ncg) * kColsPerWave;
             unsigned v[32];
-#pragma unroll
-            for (int i = 0; i < 32; ++i) v[i] = act ? ld4(p + (int64_t)i * ld) : 0u;
+            load_col_tile(x + (int64_t)rb * kBlock * ld, c0, lane, cols, ld, v);
 #pragma unroll
             for (int i = 0; i < 32; ++i) raw[i * 64 + wpos[i & 3]] = v[i];
             // ---- column direction ----
@@ -936,7 +956,7 @@ __global__ __launch_bounds__(256) void stats_both_kernel(const uint16_t* __restr
             unsigned w[16];
 #pragma unroll
             for (int h = 0; h < 2; ++h) {
-#pragma unroll
+    #pragma unroll
                 for (int k = 0; k < 16; ++k)
                     w[k] = __builtin_amdgcn_perm(v[2 * k + 1], v[2 * k], h ? 0x07060302u : 0x05040100u);
                 const unsigned am = h ? m >> 16 : m & 0xFFFFu;
@@ -981,14 +1001,11 @@ __global__ __launch_bounds__(256) void stats_both_kernel(const uint16_t* __restr
                 }
                 bad |= b8 == 0xFFu;
             }
-        }
     }
     if (bad) { r4 = c4 = r8 = c8 = __builtin_nanf(""); }     // a non-finite element poisons every error sum of the wave
     t0 = wave_sum(t0); r4 = wave_sum(r4); r8 = wave_sum(r8); c4 = wave_sum(c4); c8 = wave_sum(c8);
-    if (lane == 0) {
-        float* pp = partials + ((int64_t)split * nwaves_x + wave_x) * 6;
-        pp[0] = t0; pp[1] = r4; pp[2] = r8; pp[3] = t0; pp[4] = c4; pp[5] = c8;
-    }
+    const float sums[6] = {t0, r4, r8, t0, c4, c8};
+    store_wave_sums<kWavesPerBlock>(sums, wib, lane, partials);
 }
 
 // Second stages: one workgroup adds n partials in double, in a fixed order: thread t takes partials t, t + 512, ..., wave j
@@ -1278,15 +1295,17 @@ hipError_t launch_stats_both(const StatsArgs& a, double* out_col, hipStream_t s)
         hipLaunchKernelGGL(reduce_both_kernel, dim3(1), dim3(kReduceThreads), 0, s, (const float*)partials, 0, a.stats, out_col, 0, 0);
         return hipGetLastError();
     }
-    int gx;
-    const int nsplit = col_splits(a.rows, a.cols, &gx);
+    // every wave the same number of tiles or one less
+    const int64_t tiles = (a.rows / kBlock) * ((a.cols + kColsPerWave - 1) / kColsPerWave), most = kStreamWaves;
+    const int64_t share = (tiles + most - 1) / most, waves = (tiles + share - 1) / share;
+    const int blocks = (int)((waves + kWavesPerBlock - 1) / kWavesPerBlock);
     if (a.rule == 0)
-        hipLaunchKernelGGL((stats_both_kernel<0>), dim3(gx, nsplit), dim3(256), 0, s, a.x, (int)a.rows, (int)a.cols, a.ld, nsplit, partials);
+        hipLaunchKernelGGL((stats_both_kernel<0>), dim3(blocks), dim3(256), 0, s, a.x, (int)a.rows, (int)a.cols, a.ld, partials);
     else
-        hipLaunchKernelGGL((stats_both_kernel<1>), dim3(gx, nsplit), dim3(256), 0, s, a.x, (int)a.rows, (int)a.cols, a.ld, nsplit, partials);
+        hipLaunchKernelGGL((stats_both_kernel<1>), dim3(blocks), dim3(256), 0, s, a.x, (int)a.rows, (int)a.cols, a.ld, partials);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(reduce_both_kernel, dim3(1), dim3(kReduceThreads), 0, s, (const float*)partials, gx * kWavesPerBlock * nsplit,
+    hipLaunchKernelGGL(reduce_both_kernel, dim3(1), dim3(kReduceThreads), 0, s, (const float*)partials, blocks,
                        a.stats, out_col, 0, 0);
     return hipGetLastError();
 }
