@@ -339,23 +339,37 @@ int gemm_compute_units()
 // stage takes.  A stage (256 contraction elements for FP4 x FP4, else 128) takes `full` with a tile on every compute unit
 // (operand bytes out of L2, and the clock under load) and on a nearly empty chip `alone` (latency of the copy - barrier -
 // read - MFMA chain) or, after full rounds, `tail`; `last` lies between by the share of compute units that have a tile.
-// Fitted to 182 problems timed back to back with every tile: the GEMMs of 1B-, 3B- and 7B-shaped blocks and random ones (64
-// ... 16384 tokens, widths 64 ... 11008, FP4 and FP8).  The pick is on average 0.4 % slower than the fastest tile (12 % at
-// worst).  Counting the last round as a full one, as if the 128 x 128 tile turned as fast as the persistent kernel's, had
-// picked that tile where 1.5 rounds of 256 x 256 are faster: [8192 x 3072 x 8192] FP4 119 -> 102 us, FP8 190 -> 178 us.
+// Two tables: operands found in a cache (the same call timed over and over) and operands that come from memory (each call on
+// other operands, 800 MB of them), as they do in a training step: it touches a tensor once or twice among some dozens, so a
+// GEMM finds its operands in the 256 MB memory-side cache only while they are a small part of it.  kColdBytes of operands
+// and output is where the second table takes over.
+// Fitted to 182 and 107 problems timed with every tile: the GEMMs of 1B-, 3B- and 7B-shaped blocks and random ones (64 ...
+// 16384 tokens, widths 64 ... 11008, FP4 and FP8).  The pick is on average 0.4 and 0.2 % slower than the fastest tile (12
+// and 7 % at worst).  From memory the 256 x 128 tile that runs ahead beats 256 x 256 more often: [8192 x 3072 x 3072] FP8
+// 87 -> 79 us, [4032 x 5056 x 1952] FP8 73 -> 64.
 struct TileCost { GemmTile tile; int m, n; float start, turn, alone[2], full[2], tail[2]; };      // [0]: FP4 x FP4, [1]: others
-static const TileCost kTileCosts[] = {
-    {GemmTile::kBig,     256, 256, 7.5f, 4.5f, {1.51f, 0.80f}, {1.67f, 1.48f}, {0.83f, 0.74f}},
-    {GemmTile::kWide,    256, 128, 5.3f, 2.1f, {0.98f, 0.50f}, {1.04f, 0.91f}, {1.25f, 0.63f}},
-    {GemmTile::k128x128, 128, 128, 4.7f, 3.6f, {0.37f, 0.33f}, {0.54f, 0.46f}, {0.47f, 0.29f}},
-    {GemmTile::k64x64,    64,  64, 3.1f, 1.0f, {0.17f, 0.17f}, {0.20f, 0.19f}, {0.25f, 0.14f}},
-    {GemmTile::k64x32,    64,  32, 3.1f, 1.4f, {0.16f, 0.16f}, {0.19f, 0.18f}, {0.18f, 0.19f}},
-    {GemmTile::k32x32,    32,  32, 2.9f, 1.2f, {0.13f, 0.13f}, {0.15f, 0.14f}, {0.13f, 0.13f}},
-};
+static const TileCost kTileCosts[2][6] = {{
+    {GemmTile::kBig,       256, 256, 7.5f, 4.5f, {1.51f, 0.80f}, {1.67f, 1.48f}, {0.83f, 0.74f}},
+    {GemmTile::kWide,      256, 128, 5.3f, 2.1f, {0.98f, 0.50f}, {1.04f, 0.91f}, {1.25f, 0.63f}},
+    {GemmTile::k128x128,   128, 128, 4.7f, 3.6f, {0.37f, 0.33f}, {0.54f, 0.46f}, {0.47f, 0.29f}},
+    {GemmTile::k64x64,      64,  64, 3.1f, 1.0f, {0.17f, 0.17f}, {0.20f, 0.19f}, {0.25f, 0.14f}},
+    {GemmTile::k64x32,      64,  32, 3.1f, 1.4f, {0.16f, 0.16f}, {0.19f, 0.18f}, {0.18f, 0.19f}},
+    {GemmTile::k32x32,      32,  32, 2.9f, 1.2f, {0.13f, 0.13f}, {0.15f, 0.14f}, {0.13f, 0.13f}},
+}, {
+    {GemmTile::kBig,       256, 256, 9.5f, 5.4f, {1.23f, 1.24f}, {1.74f, 1.57f}, {0.95f, 1.01f}},
+    {GemmTile::kWideAhead, 256, 128, 7.5f, 2.6f, {1.45f, 1.33f}, {1.09f, 0.93f}, {0.83f, 0.81f}},
+    {GemmTile::k128x128,   128, 128, 6.4f, 3.2f, {0.68f, 0.54f}, {0.59f, 0.53f}, {0.56f, 0.54f}},
+    {GemmTile::k64x64,      64,  64, 4.4f, 1.0f, {0.30f, 0.30f}, {0.22f, 0.23f}, {0.45f, 0.34f}},
+    {GemmTile::k64x32,      64,  32, 3.6f, 1.1f, {0.17f, 0.17f}, {0.28f, 0.23f}, {0.20f, 0.20f}},
+    {GemmTile::k32x32,      32,  32, 3.2f, 1.2f, {0.13f, 0.13f}, {0.18f, 0.18f}, {0.14f, 0.12f}},
+}};
+constexpr double kColdBytes = 16e6;
+
+static bool fast_tile(GemmTile t) { return t == GemmTile::kBig || t == GemmTile::kWide || t == GemmTile::kWideAhead; }
 
 static bool tile_usable(const GemmArgs& a, GemmTile t)
 {
-    if (t == GemmTile::kBig || t == GemmTile::kWide) return gemm_fast_eligible(a);
+    if (fast_tile(t)) return gemm_fast_eligible(a);
     if (t == GemmTile::kGeneral) return true;
     // an output norm has room for one partial per 128 x 128 tile
     return gemm_small_eligible(a) && (!a.norm_out || t == GemmTile::k128x128);
@@ -369,7 +383,7 @@ static GemmTile pick_tile(const GemmArgs& a)
     // cover every tile on every shape); anything else leaves the choice to the estimate
     if (const char* e = getenv("SNIP_GEMM_TILE")) {
         static const struct { const char* name; GemmTile tile; } kNames[] = {
-            {"big", GemmTile::kBig}, {"wide", GemmTile::kWide}, {"128x128", GemmTile::k128x128}, {"64x64", GemmTile::k64x64},
+            {"big", GemmTile::kBig}, {"wide", GemmTile::kWide}, {"ahead", GemmTile::kWideAhead}, {"128x128", GemmTile::k128x128}, {"64x64", GemmTile::k64x64},
             {"64x32", GemmTile::k64x32}, {"32x32", GemmTile::k32x32}, {"general", GemmTile::kGeneral}};
         for (const auto& n : kNames)
             if (!strcmp(e, n.name) && tile_usable(a, n.tile)) return n.tile;
@@ -379,7 +393,9 @@ static GemmTile pick_tile(const GemmArgs& a)
     const int64_t ncu = gemm_compute_units(), stages = (a.R + ke - 1) / ke;
     GemmTile best = GemmTile::kGeneral;
     double best_t = 0.0;
-    for (const TileCost& c : kTileCosts) {
+    const double bytes = (double)a.I * a.R * (a.fmt_a == kFP8 ? 1.0 : 0.5) + (double)a.J * a.R * (a.fmt_b == kFP8 ? 1.0 : 0.5) +
+                         (double)a.I * a.J * (a.out_fp32 ? 4.0 : 2.0);
+    for (const TileCost& c : kTileCosts[bytes > kColdBytes]) {
         if (!tile_usable(a, c.tile)) continue;
         const int64_t tiles = tile_count(a, c.m, c.n), full_rounds = (tiles - 1) / ncu;
         const double load = (double)(tiles - full_rounds * ncu) / (double)ncu;
@@ -404,8 +420,8 @@ hipError_t launch_gemm(const GemmArgs& a, hipStream_t s)
     int64_t partials = 0;
     if (a.I != 0 && a.J != 0) {
         const GemmTile tile = pick_tile(a);
-        const bool fast = tile == GemmTile::kBig || tile == GemmTile::kWide;
-        const hipError_t e = fast ? launch_gemm_fast(a, tile == GemmTile::kWide, s)
+        const bool fast = fast_tile(tile);
+        const hipError_t e = fast ? launch_gemm_fast(a, tile, s)
                                   : tile == GemmTile::kGeneral ? launch_general(a, s) : launch_gemm_small(a, tile, s);
         if (e != hipSuccess) return e;
         partials = tile_count(a, fast ? 256 : 128, tile == GemmTile::kBig ? 256 : 128);

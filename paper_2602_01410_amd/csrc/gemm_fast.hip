@@ -44,13 +44,15 @@ namespace snip {
 namespace {
 
 constexpr int NWAVE = 8, NT = NWAVE * 64;
+constexpr int kAhead = 4;               // stages between a touched line and the copy that group 0 issues at the same time, plus one
 constexpr int TNP = 256;                // rows of the B tile's scale area (a 128-row B tile leaves half of it unused)
 
 // Workgroup tile TM (A rows) x TN (B rows), split over the eight waves as (TM / WTM) x (TN / WTN) wave tiles.
-template <int TM_, int TN_, int WTM_, int WTN_> struct TileCfg {
+template <int TM_, int TN_, int WTM_, int WTN_, bool TOUCH_ = false> struct TileCfg {
     static constexpr int TM = TM_, TN = TN_, WTM = WTM_, WTN = WTN_;
     static constexpr int WGN = TN / WTN;                   // waves along the B rows
     static constexpr int MB = WTM / 32, NB = WTN / 32;     // 32 x 32 MFMA blocks of a wave tile
+    static constexpr bool TOUCH = TOUCH_;                  // pull operand lines into L2 ahead of the copies (see `touch`)
     static_assert(TM == 256 && (TN == 256 || TN == 128), "copy shares and scale areas are laid out for these tiles");
     static_assert((TM / WTM) * (TN / WTN) == NWAVE, "eight waves");
 };
@@ -58,6 +60,11 @@ template <int TM_, int TN_, int WTM_, int WTN_> struct TileCfg {
 using TileBig = TileCfg<256, 256, 128, 64>;
 // 256 x 128, 4 x 2 waves of 64 x 64: twice as many tiles for outputs that would leave compute units without one.
 using TileWide = TileCfg<256, 128, 64, 64>;
+// The same for operands that come from memory.  Back to back with each call on other operands (us, without / with): [4096 x
+// 2048 x 8192] FP8 83 / 71, FP4 48 / 44, [2048 x 4096 x 4096] FP8 46 / 39, [8192 x 1024 x 3072] FP8 38 / 32; with the same
+// operands over and over, which stay in L2 and the memory-side cache, 63 / 69, 39 / 43, 36 / 38, 28 / 30.  (In the 256 x 256 tile it
+// spills registers and loses more than it gains: a stage there takes longer and hides more.)
+using TileWideAhead = TileCfg<256, 128, 64, 64, true>;
 
 template <int FA, int FB, class T> struct FCfg {
     static constexpr int TM = T::TM, TN = T::TN;
@@ -75,6 +82,7 @@ template <int FA, int FB, class T> struct FCfg {
     // the first or the last EPI_BYTES of the array, i.e. it covers the buffer of the tile's last stage (plus the
     // unused middle) and never reaches into the other buffer, which already receives the next tile.
     static constexpr int LDS_BYTES = 159 * 1024;
+    static constexpr int TOUCH = LDS_BYTES;                     // 256 bytes behind the buffers: where touched lines' dwords land, unread
     static constexpr int SLOT1 = LDS_BYTES - SLOT;
     static constexpr int EPI_BYTES = 64 * 1024;
     static constexpr int LA = A_BYTES / 1024 / NWAVE;            // 16-byte copy instructions per wave per stage
@@ -83,7 +91,7 @@ template <int FA, int FB, class T> struct FCfg {
     static constexpr int L = LA + LB + LS;
     static_assert(SLOT1 % 1024 == 0 && SLOT <= SLOT1, "stage buffers must not overlap");
     static_assert(EPI_BYTES <= LDS_BYTES - SLOT, "the result staging area must stay clear of the other stage buffer");
-    static_assert(LDS_BYTES + 64 <= 160 * 1024, "LDS budget");
+    static_assert(LDS_BYTES + 256 + 64 <= 160 * 1024, "LDS budget");
 };
 
 // TAIL: the contraction extent does not end with a stage.  Copies then go through buffer descriptors, which deliver zeros
@@ -101,7 +109,7 @@ __global__ __launch_bounds__(NT) void gemm_fast_kernel(const uint8_t* __restrict
 {
     using C = FCfg<FA, FB, T>;
     constexpr int TM = T::TM, TN = T::TN, WTM = T::WTM, WTN = T::WTN, WGN = T::WGN, MB = T::MB, NB = T::NB;
-    __shared__ __attribute__((aligned(1024))) uint8_t lds[C::LDS_BYTES];
+    __shared__ __attribute__((aligned(1024))) uint8_t lds[C::LDS_BYTES + 256];
     // stage buffer layout: [A codes][B codes][A scale dwords: group-major, 256 rows][B scale dwords]
 
     const int nblk = tiles_i * tiles_j;
@@ -207,6 +215,50 @@ __global__ __launch_bounds__(NT) void gemm_fast_kernel(const uint8_t* __restrict
         for (int j = 0; j < C::L; ++j) issue_one(j, stage, slot);
     };
 
+    // ---- operand lines are pulled into L2 before their copies ask for them.  In a training step a GEMM's operands come from
+    //      memory, and two stage buffers are one stage of lookahead, less than memory takes under load.  Waves 0-3 each touch
+    //      lines (a dword per lane, into LDS that nobody reads) of a stage kAhead - 1 stages after the one they copy: waves 0
+    //      and 1 code rows (the 4 x 8 tiles an XCD works on at a time share their slabs: each tile takes the share of its
+    //      position), waves 2 and 3 the scale groups.
+    const uint8_t* tcur = nullptr;
+    unsigned tstep = 0, ts1 = 0, ts2 = 0;       // lane's line: (lane % lines) * ts1 + (lane / 8 % NG) * ts2
+    int tleft = 0, tu = 0;
+    auto set_touch_tile = [&](int v) {
+        int ti, tj;
+        tile_of(v, nblk, tiles_i, tiles_j, ti, tj);
+        const int i0 = ti * TM, j0 = tj * TN;
+        tu = v;
+        tleft = nstage;
+        if (wave < 2) {
+            // (in a tile that is not whole, one row stands for all)
+            const bool whole = wave == 0 ? i0 + TM <= I : j0 + TN <= J;
+            const int64_t row_bytes = wave == 0 ? a_row_bytes : b_row_bytes;
+            const int row = wave == 0 ? i0 + (whole ? (tj & 7) * (TM / 8) : 0) : j0 + (whole ? (ti & 3) * (TN / 4) : 0);
+            tcur = (wave == 0 ? a_codes : b_codes) + (int64_t)row * row_bytes;
+            ts1 = whole ? (unsigned)row_bytes : 0;
+            tstep = wave == 0 ? C::SBA : C::SBB;
+        } else {
+            const int64_t pitch4 = (wave == 2 ? a_pitch : b_pitch) * 4;
+            tcur = wave == 2 ? a_g4 + (int64_t)i0 * 4 : b_g4 + (int64_t)j0 * 4;
+            ts1 = 128;
+            ts2 = C::NG == 2 && ngrp % 2 == 0 ? (unsigned)pitch4 : 0;
+            tstep = (unsigned)(pitch4 * C::NG);
+        }
+    };
+    auto touch = [&]() {
+        unsigned l = __builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, 0u));
+        asm volatile("" : "+v"(l));                                   // (recomputed here: no register is free to keep it)
+        const unsigned lines = wave == 0 ? TM / 8 : wave == 1 ? TN / 4 : wave == 2 ? TM / 32 : TN / 32;
+        unsigned off = (l & (lines - 1)) * ts1;
+        if (C::NG == 2) off += ((l >> 3) & 1) * ts2;
+        glds4(tcur, off, lds0 + C::TOUCH);
+        tcur += tstep;
+        if (--tleft == 0) {
+            if (tu + (int)gridDim.x < nblk) set_touch_tile(tu + (int)gridDim.x);
+            else { tcur -= tstep; tstep = 0; }                        // nothing more to come: the last stage again
+        }
+    };
+
     // ---- per-lane LDS read offsets ----
     constexpr int NCA = FA == kFP8 ? 2 * C::KS : C::KS, NCB = FB == kFP8 ? 2 * C::KS : C::KS;
     int offa[NCA], offb[NCB];
@@ -268,7 +320,7 @@ __global__ __launch_bounds__(NT) void gemm_fast_kernel(const uint8_t* __restrict
     // buffer `nslot` are spread evenly between the phase's NM MFMAs (the sched_barriers keep them there).
     constexpr int NM = KP * MB * NB;
     auto MM = [&](auto copy_tag, int p, int nxt, int nslot) {
-        constexpr bool COPY = decltype(copy_tag)::value;
+        constexpr bool COPY = decltype(copy_tag)::value != 0, TOUCH = T::TOUCH && decltype(copy_tag)::value == 2;
         constexpr int ca = FB == kFP8 ? 0 : 4, cb = FA == kFP8 ? 0 : 4;
         __builtin_amdgcn_s_setprio(1);
         int idx = 0;
@@ -288,6 +340,7 @@ __global__ __launch_bounds__(NT) void gemm_fast_kernel(const uint8_t* __restrict
 #pragma unroll
                         for (int j = 0; j < C::L; ++j)
                             if (j * NM / C::L == idx) issue_one(j, nxt, nslot);
+                        if (TOUCH && idx == NM - 1) touch();          // after the copies: waits leave it in flight
                         __builtin_amdgcn_sched_barrier(0);
                     }
                     ++idx;
@@ -295,8 +348,9 @@ __global__ __launch_bounds__(NT) void gemm_fast_kernel(const uint8_t* __restrict
         }
         __builtin_amdgcn_s_setprio(0);
     };
-    const std::true_type with_copy{};
-    const std::false_type no_copy{};
+    const std::integral_constant<int, 0> no_copy{};
+    const std::integral_constant<int, 1> with_copy{};
+    const std::integral_constant<int, 2> copy_and_touch{};
 
     // ---- result of tile u: optional sum of squares, then every wave transposes its 128 x 64 block through its
     //      own 8 KB of the staging area at byte `ebase` of the LDS array ----
@@ -441,6 +495,13 @@ __global__ __launch_bounds__(NT) void gemm_fast_kernel(const uint8_t* __restrict
     bool first = true;
     set_copy_tile(u);
     issue(0, 0);
+    if (T::TOUCH && wave < NWAVE / 2) {
+        set_touch_tile(u);
+        const int skip = nstage - 1 < 2 ? nstage - 1 : 2;            // stages 0 and 1 are copied now
+        tcur += (int64_t)skip * tstep;
+        tleft -= skip;
+        for (int k = 2; k <= kAhead; ++k) touch();
+    }
     for (;;) {
         const int un = u + (int)gridDim.x;
         const bool has_next = un < nblk;
@@ -458,7 +519,9 @@ __global__ __launch_bounds__(NT) void gemm_fast_kernel(const uint8_t* __restrict
                 const int slot = (s + par) & 1;
                 // stage 0 of a later tile was waited for before the previous tile's result was stored; waiting
                 // here again would wait for those stores
-                if (s > 0 || first) SNIP_WAIT_VM(0);
+                if (!T::TOUCH) { if (s > 0 || first) SNIP_WAIT_VM(0); }
+                else if (s > 0) SNIP_WAIT_VM(1);                    // (the touch behind the copies stays in flight)
+                else if (first) SNIP_WAIT_VM(kAhead - 1);
                 SNIP_BAR();                                         // b(4s)
                 RD(slot, 0, s); SNIP_BAR();      // b(4s+1)
                 MM(copy_tag, 0, cstage, slot ^ 1); SNIP_BAR();      // b(4s+2)
@@ -472,10 +535,11 @@ __global__ __launch_bounds__(NT) void gemm_fast_kernel(const uint8_t* __restrict
                 const bool last = s == nstage - 1;
                 if (last && has_next) set_copy_tile(un);
                 cut_tail(last ? 0 : s + 1);
-                stage0(with_copy, s, last ? 0 : s + 1);
+                stage0(copy_and_touch, s, last ? 0 : s + 1);
             }
             SNIP_BAR();                                             // b(4S)
-            SNIP_WAIT_VM(0);                                        // own share of the next tile's stage 0
+            if (T::TOUCH && has_next) SNIP_WAIT_VM(1);              // own share of the next tile's stage 0
+            else SNIP_WAIT_VM(0);                                   // nothing may land in LDS after the workgroup's end
         } else {
             // group 1 issues its copies of stage s+2 during M1(s), between b(4s+4) and b(4s+5) (during M1(S-2)
             // those of the next tile's stage 0, during M1(S-1) none); those of stage 1 while it idles through the
@@ -559,9 +623,10 @@ bool gemm_fast_eligible(const GemmArgs& a)
     return a.a_scales_g4 && a.b_scales_g4 && a.R > ke && a.I > 128 && a.J > 128;      // at least two stages
 }
 
-hipError_t launch_gemm_fast(const GemmArgs& a, bool wide, hipStream_t s)
+hipError_t launch_gemm_fast(const GemmArgs& a, GemmTile tile, hipStream_t s)
 {
-    return wide ? launch_fast_tile<TileWide>(a, s) : launch_fast_tile<TileBig>(a, s);
+    if (tile == GemmTile::kBig) return launch_fast_tile<TileBig>(a, s);
+    return tile == GemmTile::kWide ? launch_fast_tile<TileWide>(a, s) : launch_fast_tile<TileWideAhead>(a, s);
 }
 
 }  // namespace snip
