@@ -342,7 +342,8 @@ int gemm_compute_units()
 // Two tables: operands found in a cache (the same call timed over and over) and operands that come from memory (each call on
 // other operands, 800 MB of them), as they do in a training step: it touches a tensor once or twice among some dozens, so a
 // GEMM finds its operands in the 256 MB memory-side cache only while they are a small part of it.  kColdBytes of operands
-// and output is where the second table takes over.
+// is where the second table takes over (a 1B-shaped step, whose smallest operands are 6 MB: 855.7 us, with every call on
+// the second table 857.6).
 // Fitted to 182 and 107 problems timed with every tile: the GEMMs of 1B-, 3B- and 7B-shaped blocks and random ones (64 ...
 // 16384 tokens, widths 64 ... 11008, FP4 and FP8).  The pick is on average 0.4 and 0.2 % slower than the fastest tile (12
 // and 7 % at worst).  From memory the 256 x 128 tile that runs ahead beats 256 x 256 more often: [8192 x 3072 x 3072] FP8
@@ -363,7 +364,7 @@ static const TileCost kTileCosts[2][6] = {{
     {GemmTile::k64x32,      64,  32, 3.6f, 1.1f, {0.17f, 0.17f}, {0.28f, 0.23f}, {0.20f, 0.20f}},
     {GemmTile::k32x32,      32,  32, 3.2f, 1.2f, {0.13f, 0.13f}, {0.18f, 0.18f}, {0.14f, 0.12f}},
 }};
-constexpr double kColdBytes = 16e6;
+constexpr double kColdBytes = 10e6;
 
 static bool fast_tile(GemmTile t) { return t == GemmTile::kBig || t == GemmTile::kWide || t == GemmTile::kWideAhead; }
 
@@ -393,8 +394,7 @@ static GemmTile pick_tile(const GemmArgs& a)
     const int64_t ncu = gemm_compute_units(), stages = (a.R + ke - 1) / ke;
     GemmTile best = GemmTile::kGeneral;
     double best_t = 0.0;
-    const double bytes = (double)a.I * a.R * (a.fmt_a == kFP8 ? 1.0 : 0.5) + (double)a.J * a.R * (a.fmt_b == kFP8 ? 1.0 : 0.5) +
-                         (double)a.I * a.J * (a.out_fp32 ? 4.0 : 2.0);
+    const double bytes = (double)a.I * a.R * (a.fmt_a == kFP8 ? 1.0 : 0.5) + (double)a.J * a.R * (a.fmt_b == kFP8 ? 1.0 : 0.5);
     for (const TileCost& c : kTileCosts[bytes > kColdBytes]) {
         if (!tile_usable(a, c.tile)) continue;
         const int64_t tiles = tile_count(a, c.m, c.n), full_rounds = (tiles - 1) / ncu;
