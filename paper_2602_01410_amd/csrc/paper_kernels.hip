@@ -10,8 +10,7 @@
 // +-448 first: the product can exceed 448 by one rounding).
 //
 // Kernels: quantize along rows (tile maxima by a 16-lane DPP reduction inside the pass), quantize down
-// columns (a lane owns two columns, so tile maxima never leave the lane; the unit is read twice, the
-// second time from cache), a block-maximum pre-pass for the 128x128 groups, and the matching statistics
+// columns (a lane owns two columns; the four waves of a workgroup exchange their maxima), a block-maximum pre-pass for the 128x128 groups, and the matching statistics
 // kernels (both formats from one read).  All are streaming kernels bound by HBM bandwidth or VALU rate.
 #include "snip_internal.h"
 
@@ -257,11 +256,13 @@ __global__ __launch_bounds__(256) void paper_row_kernel(const uint16_t* __restri
 }
 
 // ------------------------------------------------------------------------------------------
-// Blocks down columns, result stored transposed.  A wave owns 128 columns x 128 rows (one tile per
-// column); a lane owns two adjacent columns.  First pass: column maxima (never leave the lane).
-// Second pass (the same 32 KB again, from cache): scale, round, and stage the codes in LDS as a
+// Blocks down columns, result stored transposed.  A workgroup owns 128 columns x 128 rows (one tile per column), its four
+// waves 32 rows each; a lane owns two adjacent columns.  The rows stay in registers: one read serves the column maxima,
+// which the waves exchange through LDS, and the encoding.  The codes are staged in LDS as a
 // [128 stored rows][ROWB] image (ROWB = 128 bytes FP8, 64 bytes FP4) whose 16-byte chunks are XOR-swizzled,
-// then store it with 16 bytes per lane so that whole 128- / 64-byte runs are written.
+// then stored with 16 bytes per lane so that whole 128- / 64-byte runs are written.
+// A wave per unit, which held its 128 rows in 128 registers, left half of the SIMDs without a wave on a [4096 x 2048] tensor:
+// 11.7 -> 8.1 us; [8192 x 2048] in blocks 15.2 -> 11.8, [4096 x 8192] 27.4 -> 23.1 (FP8, kernel trace).
 // ------------------------------------------------------------------------------------------
 template <int FMT>
 __device__ __forceinline__ void encode_column(const unsigned* v, int half, float s, uint8_t* __restrict__ lds_row,
@@ -342,48 +343,45 @@ __global__ __launch_bounds__(256) void paper_col_kernel(const uint16_t* __restri
 {
     constexpr int ROWB = FMT == kFP8 ? 128 : 64;
     constexpr int CPR = ROWB / 16;
-    __shared__ __attribute__((aligned(16))) uint8_t stage[MODE == 0 ? kWavesPerBlock : 1][MODE == 0 ? kColsPerWave * ROWB : 16];
+    __shared__ __attribute__((aligned(16))) uint8_t reg[MODE == 0 ? kColsPerWave * ROWB : 16];
+    __shared__ unsigned maxima[kWavesPerBlock][64];
     const int lane = threadIdx.x & 63;
-    uint8_t* const reg = stage[MODE == 0 ? (threadIdx.x >> 6) : 0];
-    const int wave = __builtin_amdgcn_readfirstlane(blockIdx.x * kWavesPerBlock + (threadIdx.x >> 6));
-    const int nwaves = gridDim.x * kWavesPerBlock;
+    const int k = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);      // this wave's rows: 32 k ... 32 k + 31 of the unit
+    const int wave = blockIdx.x * kWavesPerBlock + k;
     const int ncg = (cols + kColsPerWave - 1) / kColsPerWave;
     const int nru = rows / kGroup;                       // rows is a multiple of 128
     const int units = ncg * nru;
     const int64_t out_row_bytes = FMT == kFP8 ? rows : rows / 2;
     float s0 = 0.f, e4 = 0.f, e8 = 0.f;
-    for (int u = wave; u < units; u += nwaves) {
+    for (int u = blockIdx.x; u < units; u += gridDim.x) {
         const int ru = u / ncg, cg = u - ru * ncg;
         const int c = cg * kColsPerWave + lane * 2;
         const bool act = c < cols;
-        // The unit's 128 rows of this lane's two columns stay in registers: one read serves the group maximum
-        // and the encoding, and all 128 loads are in flight together.  They carry no condition (a lane past the
-        // last column reads column 0 of the same rows and is zeroed under a wave-uniform test).
-        const uint16_t* const base = x + (int64_t)ru * kGroup * ld + (act ? c : 0);
-        unsigned v[4][32];
+        // The loads carry no condition (a lane past the last column reads column 0 of the same rows and is zeroed under
+        // a wave-uniform test), so that all of them are in flight together.
+        const uint16_t* const base = x + ((int64_t)ru * kGroup + k * 32) * ld + (act ? c : 0);
+        unsigned v[32];
 #pragma unroll
-        for (int k = 0; k < 4; ++k)
-#pragma unroll
-            for (int i = 0; i < 32; ++i) v[k][i] = ld4_stream(base + (int64_t)(k * 32 + i) * ld);
+        for (int i = 0; i < 32; ++i) v[i] = ld4_stream(base + (int64_t)i * ld);
         if ((cg + 1) * kColsPerWave > cols) {
 #pragma unroll
-            for (int k = 0; k < 4; ++k)
-#pragma unroll
-                for (int i = 0; i < 32; ++i) v[k][i] = act ? v[k][i] : 0u;
+            for (int i = 0; i < 32; ++i) v[i] = act ? v[i] : 0u;
         }
-        float s8[2] = {1.f, 1.f}, s4[2] = {1.f, 1.f};
         unsigned m = 0;
 #pragma unroll
-        for (int k = 0; k < 4; ++k)
+        for (int i = 0; i < 32; ++i) m = pk_max_u16(m, v[i] & 0x7FFF7FFFu);
+        maxima[k][lane] = m;
+        __syncthreads();                                 // (the staging area is free again, too)
 #pragma unroll
-            for (int i = 0; i < 32; ++i) m = pk_max_u16(m, v[k][i] & 0x7FFF7FFFu);
+        for (int w = 0; w < kWavesPerBlock; ++w) m = pk_max_u16(m, maxima[w][lane]);
+        float s8[2] = {1.f, 1.f}, s4[2] = {1.f, 1.f};
         if (BLOCKS) {
-            // the unit is one 128 x 128 block: its maximum is the maximum over the wave
+            // the unit is one 128 x 128 block: its maximum is the maximum over the lanes
             unsigned bm = umax(m & 0xFFFFu, m >> 16);
             for (int off = 32; off > 0; off >>= 1) bm = umax(bm, (unsigned)__shfl_xor((int)bm, off, 64));
             if (MODE == 1 || FMT == kFP8) s8[0] = s8[1] = group_scale<kFP8>(bm);
             if (MODE == 1 || FMT == kFP4) s4[0] = s4[1] = group_scale<kFP4>(bm);
-            if (MODE == 0 && lane == 0) scales[cg * nru + ru] = FMT == kFP8 ? s8[0] : s4[0];   // stored orientation: [column group][row group]
+            if (MODE == 0 && threadIdx.x == 0) scales[cg * nru + ru] = FMT == kFP8 ? s8[0] : s4[0];   // stored orientation: [column group][row group]
         } else {
             const unsigned am[2] = {m & 0xFFFFu, m >> 16};
 #pragma unroll
@@ -391,34 +389,27 @@ __global__ __launch_bounds__(256) void paper_col_kernel(const uint16_t* __restri
                 if (MODE == 1 || FMT == kFP8) s8[h] = group_scale<kFP8>(am[h]);
                 if (MODE == 1 || FMT == kFP4) s4[h] = group_scale<kFP4>(am[h]);
             }
-            if (MODE == 0 && act) {
+            if (MODE == 0 && act && k == 0) {
                 scales[(int64_t)c * nru + ru] = FMT == kFP8 ? s8[0] : s4[0];
                 scales[(int64_t)(c + 1) * nru + ru] = FMT == kFP8 ? s8[1] : s4[1];
             }
         }
         const int swz = lane & (CPR - 1);
-        float inv8[2], inv4[2];
-        if (MODE == 1) {
+        if (MODE == 0) {
+            encode_column<FMT>(v, 0, FMT == kFP8 ? s8[0] : s4[0], reg + (2 * lane) * ROWB, k, swz);
+            encode_column<FMT>(v, 1, FMT == kFP8 ? s8[1] : s4[1], reg + (2 * lane + 1) * ROWB, k, swz);
+        } else if (act) {
+            float dummy = 0.f;
 #pragma unroll
-            for (int h = 0; h < 2; ++h) { inv8[h] = __fdiv_rn(1.f, s8[h]); inv4[h] = __fdiv_rn(1.f, s4[h]); }
-        }
-#pragma unroll
-        for (int k = 0; k < 4; ++k) {
-            if (MODE == 0) {
-                encode_column<FMT>(v[k], 0, FMT == kFP8 ? s8[0] : s4[0], reg + (2 * lane) * ROWB, k, swz);
-                encode_column<FMT>(v[k], 1, FMT == kFP8 ? s8[1] : s4[1], reg + (2 * lane + 1) * ROWB, k, swz);
-            } else if (act) {
-                float dummy = 0.f;
-#pragma unroll
-                for (int h = 0; h < 2; ++h) {
-                    err_column<kFP8>(v[k], h, s8[h], inv8[h], s0, e8, true);
-                    err_column<kFP4>(v[k], h, s4[h], inv4[h], dummy, e4, false);
-                }
+            for (int h = 0; h < 2; ++h) {
+                err_column<kFP8>(v, h, s8[h], __fdiv_rn(1.f, s8[h]), s0, e8, true);
+                err_column<kFP4>(v, h, s4[h], __fdiv_rn(1.f, s4[h]), dummy, e4, false);
             }
         }
+        __syncthreads();                                 // the codes are staged; everyone has read the maxima
         if (MODE == 0) {
 #pragma unroll
-            for (int it = 0; it < kColsPerWave * CPR / 64; ++it) {
+            for (int it = k; it < kColsPerWave * CPR / 64; it += kWavesPerBlock) {
                 const int idx = it * 64 + lane;
                 const int row = idx / CPR, chunk = idx % CPR;
                 const uint4 val = *reinterpret_cast<const uint4*>(reg + row * ROWB + ((chunk ^ ((row >> 1) & (CPR - 1))) * 16));
@@ -451,7 +442,10 @@ int launch_one(const PaperArgs& a, const float* bs8, const float* bs4, float* pa
         hipLaunchKernelGGL((paper_row_kernel<FMT, BLOCKS, MODE>), dim3(blocks), dim3(256), 0, s,
                            a.x, (int)a.rows, (int)a.cols, a.ld, a.codes, a.scales, bs8, bs4, partials);
     } else {
-        blocks = blocks_for(((a.cols + kColsPerWave - 1) / kColsPerWave) * (a.rows / kGroup));
+        // a workgroup per unit; with statistics it needs four partial-sum slots
+        const int64_t units = ((a.cols + kColsPerWave - 1) / kColsPerWave) * (a.rows / kGroup);
+        const int64_t share = MODE == 1 ? (units + kStreamBlocks - 1) / kStreamBlocks : 1;
+        blocks = (int)((units + share - 1) / share);
         hipLaunchKernelGGL((paper_col_kernel<FMT, BLOCKS, MODE>), dim3(blocks), dim3(256), 0, s,
                            a.x, (int)a.rows, (int)a.cols, a.ld, a.codes, a.scales, bs8, bs4, partials);
     }
