@@ -220,9 +220,7 @@ __global__ __launch_bounds__(NT) void gemm_paper_kernel(const uint8_t* __restric
     // Products of the block worked on last, not yet folded, and its factors: B_BLOCK one value, else A's value and the 16
     // of B's columns (lane (r32, g) holds C[row r32][column 8q + 4g + t] in register 4q + t of a 32 x 32 block).
     v16f pend;
-    float pend_a = 0.f, dbn[16];
-#pragma unroll
-    for (int k = 0; k < 16; ++k) { pend[k] = 0.f; dbn[k] = 0.f; }
+    float pend_a, dbn[16];
     auto fold = [&](v16f& c, int k0, int k1) {
 #pragma unroll
         for (int k = k0; k < k1; ++k)
@@ -336,8 +334,9 @@ __global__ __launch_bounds__(NT) void gemm_paper_kernel(const uint8_t* __restric
     int slot = 0, fslot = 0;
     for (int u = blockIdx.x; u < ntile; u += gridDim.x) {
         clear();
+        // nothing is pending: the tile's first fold adds 0 * 0.  (The factors too: the last tile's may be NaN.)
 #pragma unroll
-        for (int k = 0; k < 16; ++k) pend[k] = 0.f;
+        for (int k = 0; k < 16; ++k) { pend[k] = 0.f; dbn[k] = 0.f; }
         pend_a = 0.f;
         for (int s = 0; s < nstage; ++s) {
             const int slot1 = slot == NST - 1 ? 0 : slot + 1;

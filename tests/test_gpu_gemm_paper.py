@@ -48,3 +48,29 @@ def test_gemm_paper(shape, fmts, groups):
         got = host(buf[:, :J].to(torch.float64))
         assert (np.abs(got - want) <= 2.0 ** -12 * mags + own * np.abs(want)).all()
         assert bool((buf[:, J:] == 7.0).all())
+
+
+@pytest.mark.parametrize("group_a", [T, B])
+@pytest.mark.parametrize("fmts", [(0, 0), (1, 1), (0, 1), (1, 0)])
+def test_non_finite_group_stays_in_its_column(fmts, group_a):
+    # More tiles than compute units: a workgroup's second tile must not see the factors of its first one's last slab.  One
+    # infinity per 128 rows of B, in the last slab, always at another offset (two tiles with the same one would hide it).
+    snip = require_gpu()
+    n, R = 17 * 128, 256
+    if (n // 128) ** 2 <= torch.cuda.get_device_properties(0).multi_processor_count:
+        pytest.fail("the shape needs more tiles")
+    gen = torch.Generator(device="cuda").manual_seed(5)
+    a, b = (torch.randn((n, R), generator=gen, device="cuda").bfloat16() for _ in range(2))
+    qa = (*snip.snip_quantize_paper(a, fmts[0], snip.ROW, group_a), fmts[0], group_a)
+    bad = torch.tensor([t * 128 + 64 * (t % 2) + 32 + t for t in range(n // 128)], device="cuda")
+    runs = []
+    for poison in (False, True):
+        if poison:
+            b[bad, R - 1] = float("inf")
+        qb = (*snip.snip_quantize_paper(b, fmts[1], snip.ROW, T), fmts[1], T)
+        runs.append(snip.snip_gemm_paper(*qa, *qb, out_dtype=snip.OUT_FP32))
+    clean, got = runs
+    others = torch.ones(n, dtype=torch.bool, device="cuda")
+    others[bad] = False
+    assert bool(torch.isnan(got[:, bad]).all())
+    assert torch.equal(got[:, others], clean[:, others])
