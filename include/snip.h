@@ -106,8 +106,8 @@ typedef struct {
 /* Squared Frobenius norms (Sec. 3.1 Step 1): of the tensor, and of q(x) - x for both candidate
  * formats.  A fused quantize call fills sum_sq and the chosen format's field and writes NaN
  * into the other.
- * Range: differences are exact and squares are formed and added per lane in fp32 (wave and
- * workgroup partials in fp32, everything above in double), so the stated 1e-5 relative accuracy
+ * Range: differences are exact and squares are formed and added per lane in fp32 (wave sums in
+ * fp32, everything above in double), so the stated 1e-5 relative accuracy
  * holds for tensors whose nonzero magnitudes lie within [2^-56, 2^48]: below, the squares of
  * the errors (about 2^-5 |x| for FP8) leave the fp32 normal range and count as less than they
  * are; above, sums of squares overflow to infinity.  A lane adds at most rows / 64 (column

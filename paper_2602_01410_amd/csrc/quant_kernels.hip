@@ -616,7 +616,7 @@ __global__ __launch_bounds__(256) void quant_col_kernel(const uint16_t* __restri
 
 // The six sums of a workgroup's waves, added in wave order in double, to partials[workgroup][6].
 template <int WPB>
-__device__ __forceinline__ void store_wave_sums(const float (&sums)[6], int wib, int lane, float* __restrict__ partials)
+__device__ __forceinline__ void store_wave_sums(const float (&sums)[6], int wib, int lane, double* __restrict__ partials)
 {
     __shared__ float wave_sums[WPB][6];
     if (lane == 0)
@@ -626,7 +626,7 @@ __device__ __forceinline__ void store_wave_sums(const float (&sums)[6], int wib,
     if (threadIdx.x < 6) {
         double t = 0.0;
         for (int w = 0; w < WPB; ++w) t += (double)wave_sums[w][threadIdx.x];
-        partials[(size_t)blockIdx.x * 6 + threadIdx.x] = (float)t;
+        partials[(size_t)blockIdx.x * 6 + threadIdx.x] = t;
     }
 }
 
@@ -659,7 +659,7 @@ __global__ __launch_bounds__(NW ? NW * 64 : 256) void quant_both_kernel(const ui
                                                          uint8_t* __restrict__ g4_r, int64_t kpitch_r,
                                                          uint8_t* __restrict__ codes_c, uint8_t* __restrict__ scales_c,
                                                          uint8_t* __restrict__ g4_c, int64_t kpitch_c,
-                                                         float* __restrict__ partials, int runs)
+                                                         double* __restrict__ partials, int runs)
 {
     constexpr bool COOP = NW != 0;
     constexpr int WPB = COOP ? NW : kWavesPerBlock;
@@ -924,7 +924,7 @@ __global__ __launch_bounds__(256) void stats_col_kernel(const uint16_t* __restri
 template <int RULE>
 __global__ __launch_bounds__(256) void stats_both_kernel(const uint16_t* __restrict__ x, int rows,
                                                          int cols, int64_t ld,
-                                                         float* __restrict__ partials)
+                                                         double* __restrict__ partials)
 {
     __shared__ __attribute__((aligned(16))) unsigned tile[kWavesPerBlock][kBlock * 64];
     const int lane = threadIdx.x & 63;
@@ -1029,7 +1029,7 @@ __device__ __forceinline__ double reduce_workgroup(const double (&a)[N], double 
 }
 
 // Partials [n][6] of both block directions; out_row and out_col receive three doubles each.
-__global__ __launch_bounds__(kReduceThreads) void reduce_both_kernel(const float* __restrict__ partials, int n,
+__global__ __launch_bounds__(kReduceThreads) void reduce_both_kernel(const double* __restrict__ partials, int n,
                                                            double* __restrict__ out_row, double* __restrict__ out_col,
                                                            int mode_row, int mode_col)
 {
@@ -1037,10 +1037,10 @@ __global__ __launch_bounds__(kReduceThreads) void reduce_both_kernel(const float
     double a[6] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
 #pragma unroll 4
     for (int i = threadIdx.x; i < n; i += kReduceThreads) {
-        const float2* p = reinterpret_cast<const float2*>(partials + (size_t)i * 6);
-        const float2 v0 = p[0], v1 = p[1], v2 = p[2];
-        a[0] += (double)v0.x; a[1] += (double)v0.y; a[2] += (double)v1.x;
-        a[3] += (double)v1.y; a[4] += (double)v2.x; a[5] += (double)v2.y;
+        const double2* p = reinterpret_cast<const double2*>(partials + (size_t)i * 6);
+        const double2 v0 = p[0], v1 = p[1], v2 = p[2];
+        a[0] += v0.x; a[1] += v0.y; a[2] += v1.x;
+        a[3] += v1.y; a[4] += v2.x; a[5] += v2.y;
     }
     const double t = reduce_workgroup<6>(a, sh);
     // mode 0: all three sums; mode 1 (fused FP4): the FP8 field is NaN; mode 2 (fused FP8): the FP4 field is NaN
@@ -1198,7 +1198,7 @@ hipError_t launch_quantize(const QuantArgs& a, hipStream_t s)
 enum class QbForm { k4x4, k4x8, k8x8, kWave };
 
 template <int FMT_R, int FMT_C, int RULE, int STATS, int NW, int RBU>
-static int launch_qb_form(const QuantBothArgs& a, float* partials, hipStream_t s)
+static int launch_qb_form(const QuantBothArgs& a, double* partials, hipStream_t s)
 {
     const int64_t nrb = a.rows / kBlock;
     const int64_t units = ((a.cols + kColsPerWave - 1) / kColsPerWave) * ((nrb + RBU - 1) / RBU);
@@ -1217,7 +1217,7 @@ static int launch_qb_form(const QuantBothArgs& a, float* partials, hipStream_t s
 }
 
 template <int FMT_R, int FMT_C, int RULE, int STATS>
-static int launch_qb(const QuantBothArgs& a, float* partials, QbForm form, hipStream_t s)
+static int launch_qb(const QuantBothArgs& a, double* partials, QbForm form, hipStream_t s)
 {
     if constexpr (STATS != 0)
         if (form == QbForm::kWave) return launch_qb_form<FMT_R, FMT_C, RULE, STATS, 0, FMT_C == kFP8 ? 4 : 8>(a, partials, s);
@@ -1256,12 +1256,12 @@ static QbForm pick_qb_form(const QuantBothArgs& a, int stats)
 
 hipError_t launch_quantize_both(const QuantBothArgs& a, hipStream_t s)
 {
-    float* partials = (float*)a.workspace;
+    double* partials = (double*)a.workspace;
     const bool st = a.stats_r != nullptr;
     // second stage: which field of each triple is "not computed" (NaN); none when both formats are wanted
     const int mode_r = a.both_formats ? 0 : (a.fmt_r == kFP4 ? 1 : 2), mode_c = a.both_formats ? 0 : (a.fmt_c == kFP4 ? 1 : 2);
     if (a.rows == 0 || a.cols == 0) {
-        if (st) hipLaunchKernelGGL(reduce_both_kernel, dim3(1), dim3(kReduceThreads), 0, s, (const float*)partials, 0, a.stats_r, a.stats_c, mode_r, mode_c);
+        if (st) hipLaunchKernelGGL(reduce_both_kernel, dim3(1), dim3(kReduceThreads), 0, s, (const double*)partials, 0, a.stats_r, a.stats_c, mode_r, mode_c);
         return hipGetLastError();
     }
     const int mode = !st ? 0 : (a.both_formats ? 2 : 1);
@@ -1281,7 +1281,7 @@ hipError_t launch_quantize_both(const QuantBothArgs& a, hipStream_t s)
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     if (st) {
-        hipLaunchKernelGGL(reduce_both_kernel, dim3(1), dim3(kReduceThreads), 0, s, (const float*)partials, blocks,
+        hipLaunchKernelGGL(reduce_both_kernel, dim3(1), dim3(kReduceThreads), 0, s, (const double*)partials, blocks,
                            a.stats_r, a.stats_c, mode_r, mode_c);
         e = hipGetLastError();
     }
@@ -1290,9 +1290,9 @@ hipError_t launch_quantize_both(const QuantBothArgs& a, hipStream_t s)
 
 hipError_t launch_stats_both(const StatsArgs& a, double* out_col, hipStream_t s)
 {
-    float* partials = (float*)a.workspace;
+    double* partials = (double*)a.workspace;
     if (a.rows == 0 || a.cols == 0) {
-        hipLaunchKernelGGL(reduce_both_kernel, dim3(1), dim3(kReduceThreads), 0, s, (const float*)partials, 0, a.stats, out_col, 0, 0);
+        hipLaunchKernelGGL(reduce_both_kernel, dim3(1), dim3(kReduceThreads), 0, s, (const double*)partials, 0, a.stats, out_col, 0, 0);
         return hipGetLastError();
     }
     // every wave the same number of tiles or one less
@@ -1305,7 +1305,7 @@ hipError_t launch_stats_both(const StatsArgs& a, double* out_col, hipStream_t s)
         hipLaunchKernelGGL((stats_both_kernel<1>), dim3(blocks), dim3(256), 0, s, a.x, (int)a.rows, (int)a.cols, a.ld, partials);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(reduce_both_kernel, dim3(1), dim3(kReduceThreads), 0, s, (const float*)partials, blocks,
+    hipLaunchKernelGGL(reduce_both_kernel, dim3(1), dim3(kReduceThreads), 0, s, (const double*)partials, blocks,
                        a.stats, out_col, 0, 0);
     return hipGetLastError();
 }
