@@ -24,25 +24,28 @@ __device__ __forceinline__ unsigned lds_addr(const void* p)
     return (unsigned)(uintptr_t)(const __attribute__((address_space(3))) void*)p;
 }
 // The source address is a wave-uniform 64-bit base (SGPR pair) plus a 32-bit per-lane byte offset.
+// A memory instruction may read a scalar register five wait states after a vector instruction wrote it.  The compiler does
+// not keep that distance in front of inline assembly, and where it runs out of scalar registers (gemm_fast.hip) it fetches
+// an address with v_readlane right there: s_mov and s_nop 3 are the five (tests/test_wait_states.py reads the built code).
 __device__ __forceinline__ void glds16(const uint8_t* base, unsigned lane_off, unsigned lds)
 {
-    asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1" : : "v"(lane_off), "s"(base), "s"(lds) : "memory", "m0");
+    asm volatile("s_mov_b32 m0, %2\n\ts_nop 3\n\tglobal_load_lds_dwordx4 %0, %1" : : "v"(lane_off), "s"(base), "s"(lds) : "memory", "m0");
 }
 __device__ __forceinline__ void glds4(const uint8_t* base, unsigned lane_off, unsigned lds)
 {
-    asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dword %0, %1" : : "v"(lane_off), "s"(base), "s"(lds) : "memory", "m0");
+    asm volatile("s_mov_b32 m0, %2\n\ts_nop 3\n\tglobal_load_lds_dword %0, %1" : : "v"(lane_off), "s"(base), "s"(lds) : "memory", "m0");
 }
 // The same with a buffer descriptor as source: per-lane an offset: per-lane `lane_off` + wave-uniform `soff`; a lane whose offset lies at or
 // past the descriptor's size delivers zeros (kNoSource is past every size used here).
 constexpr unsigned kNoSource = 0x80000000u;
 __device__ __forceinline__ void blds16(v4i rsrc, unsigned lane_off, unsigned soff, unsigned lds)
 {
-    asm volatile("s_mov_b32 m0, %3\n\ts_nop 0\n\tbuffer_load_dwordx4 %0, %1, %2 offen lds"
+    asm volatile("s_mov_b32 m0, %3\n\ts_nop 3\n\tbuffer_load_dwordx4 %0, %1, %2 offen lds"
                  : : "v"(lane_off), "s"(rsrc), "s"(soff), "s"(lds) : "memory", "m0");
 }
 __device__ __forceinline__ void blds4(v4i rsrc, unsigned lane_off, unsigned soff, unsigned lds)
 {
-    asm volatile("s_mov_b32 m0, %3\n\ts_nop 0\n\tbuffer_load_dword %0, %1, %2 offen lds"
+    asm volatile("s_mov_b32 m0, %3\n\ts_nop 3\n\tbuffer_load_dword %0, %1, %2 offen lds"
                  : : "v"(lane_off), "s"(rsrc), "s"(soff), "s"(lds) : "memory", "m0");
 }
 // Raw buffer descriptor (stride 0, 32-bit data format) of `bytes` < 2^31 bytes at `p`; both wave-uniform.
