@@ -3,6 +3,7 @@
 // which tiles are dealt to the chip.  Register layout of the instruction: see gemm.hip.
 #pragma once
 #include "snip_internal.h"
+#include "copy_ranges.h"
 
 namespace snip {
 namespace {
@@ -35,8 +36,8 @@ __device__ __forceinline__ void glds4(const uint8_t* base, unsigned lane_off, un
 {
     asm volatile("s_mov_b32 m0, %2\n\ts_nop 3\n\tglobal_load_lds_dword %0, %1" : : "v"(lane_off), "s"(base), "s"(lds) : "memory", "m0");
 }
-// The same with a buffer descriptor as source: per-lane an offset: per-lane `lane_off` + wave-uniform `soff`; a lane whose offset lies at or
-// past the descriptor's size delivers zeros (kNoSource is past every size used here).
+// The same with a buffer descriptor as source, per-lane offset `lane_off` + wave-uniform `soff`: a lane whose offset lies at
+// or past the descriptor's size - soff delivers zeros (kNoSource is past every size used here; soff: see copy_ranges.h).
 constexpr unsigned kNoSource = 0x80000000u;
 __device__ __forceinline__ void blds16(v4i rsrc, unsigned lane_off, unsigned soff, unsigned lds)
 {

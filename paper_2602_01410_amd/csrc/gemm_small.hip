@@ -68,8 +68,9 @@ __global__ __launch_bounds__(T::NT) void gemm_small_kernel(const uint8_t* __rest
         // ---- a copy wave.  Copy instruction q of an operand fills 1 KB of its LDS tile.
         const int p = wave - T::NC;
         const int a_row_bytes = FA == kFP8 ? R : R / 2, b_row_bytes = FB == kFP8 ? R : R / 2;
-        v4i ra = buffer_desc(a_codes + (int64_t)i0 * a_row_bytes, (unsigned)(min(BM, I - i0) * a_row_bytes));
-        v4i rb = buffer_desc(b_codes + (int64_t)j0 * b_row_bytes, (unsigned)(min(BN, J - j0) * b_row_bytes));
+        const unsigned a_bytes = min(BM, I - i0) * a_row_bytes, b_bytes = min(BN, J - j0) * b_row_bytes;
+        v4i ra = buffer_desc(a_codes + (int64_t)i0 * a_row_bytes, a_bytes);
+        v4i rb = buffer_desc(b_codes + (int64_t)j0 * b_row_bytes, b_bytes);
         auto qa = [&](int j) { return (p + NP * j) % C::NA; };
         auto qb = [&](int j) { return (p + NP * j) % C::NBC; };
         auto row_a = [&](int j) { return qa(j) * (1024 / C::SBA) + lane / (C::SBA / 16); };
@@ -85,24 +86,24 @@ __global__ __launch_bounds__(T::NT) void gemm_small_kernel(const uint8_t* __rest
         // the padded pitch, groups past the last one past the end of the descriptor.
         const unsigned pa = (unsigned)g4_pitch(I) * 4, pb = (unsigned)g4_pitch(J) * 4;       // bytes per scale group
         v4i rs[C::LS];
-        unsigned sstep[C::LS], sdst[C::LS];
+        unsigned spitch[C::LS], srow0[C::LS], sdst[C::LS];
 #pragma unroll
         for (int j = 0; j < C::LS; ++j) {
             const int q = (p + NP * j) % (C::NSA + C::NSB);
             const bool isa = q < C::NSA;
             const int f = (isa ? q : q - C::NSA) * 64 + lane;
             const int grp = isa ? f / BM : f / BN, row = isa ? f % BM : f % BN;
-            const unsigned pitch = isa ? pa : pb, row0 = (unsigned)(isa ? i0 : j0) * 4;
-            os[j] = grp < C::NG ? grp * pitch + row * 4 : kNoSource;
-            rs[j] = buffer_desc((isa ? a_g4 : b_g4) + row0, ngrp * pitch - row0);
-            sstep[j] = C::NG * pitch;
+            spitch[j] = isa ? pa : pb;
+            srow0[j] = (unsigned)(isa ? i0 : j0) * 4;
+            os[j] = grp < C::NG ? scale_lane(grp, row, spitch[j]) : kNoSource;
+            rs[j] = buffer_desc((isa ? a_g4 : b_g4) + srow0[j], scale_range(0, nstage, ngrp, C::NG, spitch[j], srow0[j]).size);
             sdst[j] = C::OFF_SA + q * 256;
         }
         const unsigned lds0 = lds_addr(lds);
         const int tail_stage = R % C::KE != 0 ? nstage - 1 : -1;
         // This wave's share of stage st into stage buffer `slot`.  Every stage issues the same number of copies, so that
         // the waits count in stages.  In a last stage that is not whole, lanes whose chunk lies past the end of the row
-        // lose their source for good; past the last stage the descriptors are empty (no memory is read).
+        // lose their source for good; past the last stage the descriptors are empty and the offsets zero (no memory is read).
         auto issue = [&](int st, int slot) {
             if (st == tail_stage) {
 #pragma unroll
@@ -110,18 +111,20 @@ __global__ __launch_bounds__(T::NT) void gemm_small_kernel(const uint8_t* __rest
 #pragma unroll
                 for (int j = 0; j < C::LB; ++j) ob[j] = chunk_b(j) * 16 < b_row_bytes - st * C::SBB ? ob[j] : kNoSource;
             }
-            if (st == nstage) {
-                ra[2] = rb[2] = 0;
-#pragma unroll
-                for (int j = 0; j < C::LS; ++j) rs[j][2] = 0;
-            }
             const unsigned base = lds0 + slot * C::SLOT;
+            const CopyRange ca = code_range(st, nstage, a_bytes, C::SBA), cb = code_range(st, nstage, b_bytes, C::SBB);
+            ra[2] = ca.size;
+            rb[2] = cb.size;
 #pragma unroll
-            for (int j = 0; j < C::LA; ++j) blds16(ra, oa[j], st * C::SBA, base + qa(j) * 1024);
+            for (int j = 0; j < C::LA; ++j) blds16(ra, oa[j], ca.uniform, base + qa(j) * 1024);
 #pragma unroll
-            for (int j = 0; j < C::LB; ++j) blds16(rb, ob[j], st * C::SBB, base + C::OFF_B + qb(j) * 1024);
+            for (int j = 0; j < C::LB; ++j) blds16(rb, ob[j], cb.uniform, base + C::OFF_B + qb(j) * 1024);
 #pragma unroll
-            for (int j = 0; j < C::LS; ++j) blds4(rs[j], os[j], st * sstep[j], base + sdst[j]);
+            for (int j = 0; j < C::LS; ++j) {
+                const CopyRange cs = scale_range(st, nstage, ngrp, C::NG, spitch[j], srow0[j]);
+                rs[j][2] = cs.size;
+                blds4(rs[j], os[j], cs.uniform, base + sdst[j]);
+            }
         };
 #pragma unroll
         for (int st = 0; st < NST; ++st) issue(st, st);
