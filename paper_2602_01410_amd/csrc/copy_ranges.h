@@ -16,6 +16,10 @@ namespace snip {
 
 struct CopyRange { unsigned size, uniform; };
 
+// Sizes stay below 2^31, so that kNoSource (gemm_common.h) is past every one of them and a group past the last one still has
+// a 32-bit offset.
+constexpr bool descriptor_covers(long long bytes) { return bytes < 1ll << 31; }
+
 // Codes of stage `st`: `bytes` of a tile's rows, `step` bytes of a row per stage.  Past the last stage nothing is in range.
 SNIP_HD constexpr CopyRange code_range(int st, int nstage, unsigned bytes, unsigned step)
 {
@@ -25,9 +29,11 @@ SNIP_HD constexpr CopyRange code_range(int st, int nstage, unsigned bytes, unsig
 // Grouped scales of stage `st` (`ng` groups of 128 contraction elements) for the rows from byte `row0` of a group on: `ngrp`
 // groups, `pitch` bytes apart.  A lane's offset is scale_lane(group inside the stage, row); for the group that an odd `ngrp`
 // leaves out of a last stage it lies at or past size - uniform.
+SNIP_HD constexpr unsigned scale_size(int ngrp, unsigned pitch, unsigned row0) { return (unsigned)ngrp * pitch - row0; }
+SNIP_HD constexpr unsigned scale_uniform(int st, int ng, unsigned pitch) { return (unsigned)(st * ng) * pitch; }
 SNIP_HD constexpr CopyRange scale_range(int st, int nstage, int ngrp, int ng, unsigned pitch, unsigned row0)
 {
-    return st < nstage ? CopyRange{(unsigned)ngrp * pitch - row0, (unsigned)(st * ng) * pitch} : CopyRange{0u, 0u};
+    return st < nstage ? CopyRange{scale_size(ngrp, pitch, row0), scale_uniform(st, ng, pitch)} : CopyRange{0u, 0u};
 }
 SNIP_HD constexpr unsigned scale_lane(int group, int row, unsigned pitch) { return (unsigned)group * pitch + (unsigned)row * 4u; }
 

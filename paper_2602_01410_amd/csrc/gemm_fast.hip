@@ -128,7 +128,6 @@ __global__ __launch_bounds__(NT) void gemm_fast_kernel(const uint8_t* __restrict
     //      to, which runs ahead of the tile being multiplied): wave-uniform base + per-lane 32-bit offset.
     //      Rows past the end of an operand re-read its last row (their products are never stored). ----
     unsigned oa[C::LA], ob[C::LB];
-    const unsigned os = lane * 4;
     const uint8_t* sbase[C::LS];
     int64_t sstep[C::LS];
     const uint8_t* abase;
@@ -139,7 +138,7 @@ __global__ __launch_bounds__(NT) void gemm_fast_kernel(const uint8_t* __restrict
     const int sq = wave * C::LS;
     const bool sop = sq >= 4 * C::NG;
     const unsigned spitch = (unsigned)(sop ? b_pitch : a_pitch) * 4;
-    const unsigned soff0 = sq % (4 * C::NG) / 4 * spitch + (sop && sq % 4 * 64 >= TN ? sq % 4 - TN / 64 : sq % 4) * 256;
+    const unsigned os = TAIL ? scale_lane(sq % (4 * C::NG) / 4, (sop && sq % 4 * 64 >= TN ? sq % 4 - TN / 64 : sq % 4) * 64 + lane, spitch) : lane * 4;
     auto chunk_a = [&](int j) { constexpr int CPR = C::SBA / 16, RPI = 1024 / C::SBA; return (lane % CPR) ^ swz<C::SBA>((wave * C::LA + j) * RPI + lane / CPR); };
     auto chunk_b = [&](int j) { constexpr int CPR = C::SBB / 16, RPI = 1024 / C::SBB; return (lane % CPR) ^ swz<C::SBB>((wave * C::LB + j) * RPI + lane / CPR); };
     auto set_copy_tile = [&](int u) {
@@ -162,7 +161,7 @@ __global__ __launch_bounds__(NT) void gemm_fast_kernel(const uint8_t* __restrict
             const unsigned row4 = (unsigned)(sop ? j0 : i0) * 4;
             ra = buffer_desc(a_codes + (int64_t)i0 * a_row_bytes, (unsigned)(min(TM, I - i0) * a_row_bytes));
             rb = buffer_desc(b_codes + (int64_t)j0 * b_row_bytes, (unsigned)(min(TN, J - j0) * b_row_bytes));
-            rs = buffer_desc((sop ? b_g4 : a_g4) + row4, (unsigned)ngrp * spitch - row4);
+            rs = buffer_desc((sop ? b_g4 : a_g4) + row4, scale_size(ngrp, spitch, row4));
             return;
         }
         // scale copy q of a stage: operand, scale group inside the stage, quarter of the 256 tile rows (the
@@ -206,7 +205,7 @@ __global__ __launch_bounds__(NT) void gemm_fast_kernel(const uint8_t* __restrict
         } else {
             const int k = j - C::LA - C::LB;
             const unsigned dst = base + C::A_BYTES + C::B_BYTES + (wave * C::LS + k) * 256;
-            if constexpr (TAIL) blds4(rs, os, soff0 + stage * (C::NG * spitch) + k * 256, dst);
+            if constexpr (TAIL) blds4(rs, os, scale_uniform(stage, C::NG, spitch) + k * 256, dst);
             else glds4(sbase[k] + stage * sstep[k], os, dst);
         }
     };
@@ -615,11 +614,10 @@ hipError_t launch_fast_tile(const GemmArgs& a, hipStream_t s)
 bool gemm_fast_eligible(const GemmArgs& a)
 {
     const int ke = (a.fmt_a == kFP4 && a.fmt_b == kFP4) ? 256 : 128;
-    // 32-bit source offsets: 256 rows of codes below 2^31 bytes and, where the last stage is not whole, a grouped scale
-    // copy below 2^32
+    // 32-bit source offsets: 256 rows of codes and, where the last stage is not whole, a grouped scale copy within a descriptor
     if (a.R > (1 << 22)) return false;
     const int64_t groups = (a.R + 127) / 128, most = std::max(g4_pitch(a.I), g4_pitch(a.J)) * 4 * groups;
-    if (a.R % ke != 0 && most >= ((int64_t)1 << 32)) return false;
+    if (a.R % ke != 0 && !descriptor_covers(most)) return false;
     return a.a_scales_g4 && a.b_scales_g4 && a.R > ke && a.I > 128 && a.J > 128;      // at least two stages
 }
 

@@ -96,7 +96,7 @@ __global__ __launch_bounds__(T::NT) void gemm_small_kernel(const uint8_t* __rest
             spitch[j] = isa ? pa : pb;
             srow0[j] = (unsigned)(isa ? i0 : j0) * 4;
             os[j] = grp < C::NG ? scale_lane(grp, row, spitch[j]) : kNoSource;
-            rs[j] = buffer_desc((isa ? a_g4 : b_g4) + srow0[j], scale_range(0, nstage, ngrp, C::NG, spitch[j], srow0[j]).size);
+            rs[j] = buffer_desc((isa ? a_g4 : b_g4) + srow0[j], scale_size(ngrp, spitch[j], srow0[j]));
             sdst[j] = C::OFF_SA + q * 256;
         }
         const unsigned lds0 = lds_addr(lds);
@@ -346,10 +346,10 @@ hipError_t launch_small_tile(const GemmArgs& a, hipStream_t s)
 
 bool gemm_small_eligible(const GemmArgs& a)
 {
-    // 32-bit source offsets inside the buffer descriptors: 128 rows of codes and a whole grouped scale copy below 2^31 bytes
+    // 32-bit source offsets inside the buffer descriptors: 128 rows of codes and a whole grouped scale copy
     const int64_t groups = (a.R + 127) / 128;
-    return a.a_scales_g4 && a.b_scales_g4 && a.R <= (1 << 22) && g4_pitch(a.I) * 4 * groups < ((int64_t)1 << 31) &&
-           g4_pitch(a.J) * 4 * groups < ((int64_t)1 << 31) && (a.I + 31) / 32 * ((a.J + 31) / 32) < ((int64_t)1 << 31);
+    return a.a_scales_g4 && a.b_scales_g4 && a.R <= (1 << 22) && descriptor_covers(g4_pitch(a.I) * 4 * groups) &&
+           descriptor_covers(g4_pitch(a.J) * 4 * groups) && (a.I + 31) / 32 * ((a.J + 31) / 32) < ((int64_t)1 << 31);
 }
 
 hipError_t launch_gemm_small(const GemmArgs& a, GemmTile tile, hipStream_t s)

@@ -37,12 +37,30 @@ int main()
             }
             const CopyRange s = scale_range(st, nstage, ngrp, ng, pitch, i0 * 4);
             CHECK(s.uniform <= s.size);
+            // a wave's second copy of a stage (64 rows on, tiles of 128 and 256 rows) in the uniform offset: there up to the last stage
+            if (tile >= 128 && st < nstage) {
+                const CopyRange t{s.size, s.uniform + 256};
+                CHECK(t.uniform <= t.size);
+                for (int g = 0; g < ng; ++g) for (int row = 0; row < tile - 64; ++row)
+                    CHECK(in_range(t, scale_lane(g, row, pitch)) == (st * ng + g < ngrp));
+            }
             for (int g = 0; g < ng; ++g) for (int row = 0; row < tile; ++row) {
                 const unsigned lane = scale_lane(g, row, pitch);
                 CHECK(in_range(s, lane) == (st * ng + g < ngrp && st < nstage));
                 CHECK(!in_range(s, lane) || i0 * 4 + s.uniform + lane == (unsigned)(st * ng + g) * pitch + (i0 + row) * 4);
             }
             CHECK(!in_range(c, 0x80000000u) && !in_range(s, 0x80000000u));
+        }
+    }
+    // the largest grouped scale copies: nothing wraps in 32 bits
+    for (long long pitch = 1024; pitch <= 1ll << 30; pitch *= 4) {
+        const int ngrp = (int)(((1ll << 31) - 1) / pitch), rows = (int)(pitch / 4), r = ngrp * 128;
+        for (int ng = 1; ng < 3; ++ng) for (int st = 0, n = (ngrp + ng - 1) / ng; st < n; st += st < n - 2 && n > 1000 ? n / 1000 : 1) {
+            const unsigned row0 = (unsigned)pitch - 1024;
+            CHECK(descriptor_covers(ngrp * pitch) && !descriptor_covers((ngrp + 1) * pitch));
+            const CopyRange s = scale_range(st, n, ngrp, ng, (unsigned)pitch, row0);
+            CHECK(s.size == ngrp * pitch - row0 && s.uniform == (long long)st * ng * pitch && s.uniform <= s.size);
+            for (int g = 0; g < ng; ++g) CHECK(in_range(s, scale_lane(g, 255, (unsigned)pitch)) == (st * ng + g < ngrp));
         }
     }
     std::printf("%ld\n", checks);

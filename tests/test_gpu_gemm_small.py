@@ -66,3 +66,24 @@ def test_norm_with_ragged_contraction(fmt, monkeypatch):
         torch.cuda.synchronize()
         # fp32 sums of squares per lane, wave and workgroup (bound of test_gpu_gemm.py)
         assert float(nrm[0]) == pytest.approx(float(y.double().square().sum()), rel=5e-6), tile
+
+
+@pytest.mark.parametrize("tile", TILES + ("ahead",))
+def test_no_scale_behind_the_last_group_is_read(tile, monkeypatch):
+    """FP4 with an odd number of scale groups, several tiles each way: the last stage's second group does not exist.  Behind
+    the grouped copies lie bytes that mean "not a number"."""
+    snip = require_gpu()
+    i, j, r = 520, 648, 1152
+    gen = torch.Generator(device="cuda").manual_seed(7)
+    qs = []
+    for rows in (i, j):
+        q = snip.alloc_qtensor(rows, r, snip.FP4)
+        n = q.scales_g4.numel()
+        q.scales_g4 = torch.full((n + 64 * 1024,), 0xFF, dtype=torch.uint8, device="cuda")[:n].view(q.scales_g4.shape)
+        snip.snip_quantize(torch.randn((rows, r), generator=gen, device="cuda").bfloat16(), snip.FP4, snip.ROW, out=q)
+        qs.append(q)
+    outs = []
+    for t in ("general", tile):
+        monkeypatch.setenv("SNIP_GEMM_TILE", t)
+        outs.append(snip.snip_gemm_fwd((snip.FP4,) * 6, *qs, out_dtype=snip.OUT_FP32))
+    assert bool(torch.isfinite(outs[0]).all()) and torch.equal(*outs)
