@@ -43,8 +43,9 @@ def build_library(verbose: bool = False) -> str:
         if verbose or res.returncode != 0:
             print(res.stdout)
             print(res.stderr)
-    if any(r.returncode != 0 for r in results):
-        raise RuntimeError("hipcc failed building libsnip_hip.so")
+    failed = sorted({os.path.basename(r.args[r.args.index("-o") + 1]) for r in results if r.returncode != 0})
+    if failed:
+        raise RuntimeError("compiling failed: " + ", ".join(failed))
     # device microbenchmarks (measured roofline denominators), run by `bench.py --microbench`
     cmd = ["hipcc"] + FLAGS + ["-o", MICROBENCH, os.path.join(CSRC, "microbench.hip")]
     res = subprocess.run(cmd, capture_output=True, text=True)

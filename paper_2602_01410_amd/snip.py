@@ -60,14 +60,19 @@ _native = None          # csrc/binding.cpp, bound to the library of _handle
 
 
 def _nat():
-    """The native half of this binding: the same calls with tensors and QTensors as arguments."""
-    if _native is None or _handle is None:
+    """The native half of this binding: the same calls with tensors and QTensors as arguments.  It is compiled against the
+    installed torch; what goes through _lib() alone does without it."""
+    global _native
+    if _native is None:
         _lib()
+        from . import _snip_binding
+        _snip_binding.bind(LIB_PATH)
+        _native = _snip_binding
     return _native
 
 
 def _lib():
-    global _handle, _native
+    global _handle
     if _handle is None:
         if not os.path.exists(LIB_PATH):
             raise RuntimeError(
@@ -129,16 +134,13 @@ def _lib():
         lib.snip_quant_error_stats_noalloc.argtypes = [vp, i64, i64, i64, ci, ci, vp, vp, vp]
         lib.snip_status_string.restype = ctypes.c_char_p
         lib.snip_status_string.argtypes = [ci]
-        from . import _snip_binding
-        _snip_binding.bind(LIB_PATH)
-        _native = _snip_binding
         _handle = lib
     return _handle
 
 
 def _stream(stream) -> int:
     if stream is None:
-        return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
+        stream = torch.cuda.current_stream()
     return stream.cuda_stream if hasattr(stream, "cuda_stream") else int(stream)
 
 

@@ -1,5 +1,8 @@
 """The native half of the Python binding on the CPU: what is not a CUDA tensor, a QTensor or a plan is refused with a
 Python exception, before anything reaches the library."""
+import subprocess
+import sys
+
 import pytest
 import torch
 
@@ -28,3 +31,20 @@ def test_library_status_becomes_an_exception():
     with pytest.raises(snip.SnipError) as e:                 # operand format differs from the plan
         snip.snip_gemm_wgrad((0, 0, 0, 0, 1, 1), q, q, out=torch.zeros((32, 32), dtype=torch.bfloat16), stream=0)
     assert e.value.status == 3
+
+
+def test_library_without_the_native_half():
+    """Sizes, host functions and operands need the library alone: the native half is tied to one torch."""
+    code = """
+import sys
+sys.modules["paper_2602_01410_amd._snip_binding"] = None          # importing it raises
+from paper_2602_01410_amd import snip
+assert snip.workspace_bytes(32, 64) > 0 and snip.alloc_qtensor(32, 64, snip.FP8, device="cpu").codes.shape == (32, 64)
+assert snip.snip_loss_divergence(1.0, 1.0, 1, 1.0, 1.0, 1, 1) > 0
+try:
+    snip._nat()
+except ImportError:
+    print("refused")
+"""
+    res = subprocess.run([sys.executable, "-c", code], capture_output=True, text=True, timeout=300)
+    assert res.returncode == 0 and res.stdout.strip() == "refused", res.stderr
