@@ -340,10 +340,15 @@ int gemm_compute_units()
 // (operand bytes out of L2, and the clock under load) and on a nearly empty chip `alone` (latency of the copy - barrier -
 // read - MFMA chain) or, after full rounds, `tail`; `last` lies between by the share of compute units that have a tile.
 // Two tables: operands found in a cache (the same call timed over and over) and operands that come from memory (each call on
-// other operands, 800 MB of them), as they do in a training step: it touches a tensor once or twice among some dozens, so a
-// GEMM finds its operands in the 256 MB memory-side cache only while they are a small part of it.  kColdBytes of operands
-// is where the second table takes over (a 1B-shaped step, whose smallest operands are 6 MB: 855.7 us, with every call on
-// the second table 857.6).
+// other operands, 800 MB of them).  Which holds depends on the bytes touched since the operands were written or last used,
+// which a call cannot see: up to 128 MB they are in the 256 MB memory-side cache, at 256 MB the tables come out even, from
+// 512 MB on they are in memory.  A training step touches 9-15 times a GEMM's operands for one linear, 60-100 times for a
+// block of seven, so in a block operands of a few MB already come from memory; but below 8 MB the tile that runs ahead gains
+// too little there.  kColdBytes of operands is where the second table takes over.  Over 84 problems of 3 ... 100 MB at six
+// distances, the pick's mean loss against the fastest tile in % (cached / from memory), by threshold: 4 MB 3.9 / 0.8, 8 MB
+// 2.8 / 0.9, 10 MB 2.6 / 1.0, 12 MB 2.4 / 1.1, 16 MB 1.8 / 2.0, 50 MB 0.8 / 3.8.  The price: a caller that uses the same 10
+// ... 100 MB again at once gets calls 4-12 % slower where the picks differ (SNIP_GEMM_TILE can undo that); from memory the
+// same problems gain 11-17 %.
 // Fitted to 182 and 107 problems timed with every tile: the GEMMs of 1B-, 3B- and 7B-shaped blocks and random ones (64 ...
 // 16384 tokens, widths 64 ... 11008, FP4 and FP8).  The pick is on average 0.4 and 0.2 % slower than the fastest tile (12
 // and 7 % at worst).  From memory the 256 x 128 tile that runs ahead beats 256 x 256 more often: [8192 x 3072 x 3072] FP8

@@ -44,7 +44,7 @@ namespace snip {
 namespace {
 
 constexpr int NWAVE = 8, NT = NWAVE * 64;
-constexpr int kAhead = 4;               // stages between a touched line and the copy that group 0 issues at the same time, plus one
+constexpr int kAhead = 4;               // a touched line belongs to the stage that many after the one group 0 copies at the same time
 constexpr int TNP = 256;                // rows of the B tile's scale area (a 128-row B tile leaves half of it unused)
 
 // Workgroup tile TM (A rows) x TN (B rows), split over the eight waves as (TM / WTM) x (TN / WTN) wave tiles.
@@ -216,7 +216,7 @@ __global__ __launch_bounds__(NT) void gemm_fast_kernel(const uint8_t* __restrict
 
     // ---- operand lines are pulled into L2 before their copies ask for them.  In a training step a GEMM's operands come from
     //      memory, and two stage buffers are one stage of lookahead, less than memory takes under load.  Waves 0-3 each touch
-    //      lines (a dword per lane, into LDS that nobody reads) of a stage kAhead - 1 stages after the one they copy: waves 0
+    //      lines (a dword per lane, into LDS that nobody reads) of the stage kAhead stages after the one they copy: waves 0
     //      and 1 code rows (the 4 x 8 tiles an XCD works on at a time share their slabs: each tile takes the share of its
     //      position), waves 2 and 3 the scale groups.
     const uint8_t* tcur = nullptr;
