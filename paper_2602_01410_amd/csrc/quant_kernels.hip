@@ -16,6 +16,7 @@
 //             per-wave partials are summed in double by a single-block kernel in fixed order.
 #include "snip_internal.h"
 #include <cstdlib>
+#include <cstring>
 
 namespace snip {
 namespace {
@@ -1242,15 +1243,22 @@ static int launch_qb(const QuantBothArgs& a, double* partials, QbForm form, hipS
 //   - statistics of the written formats beyond the memory-side cache: a wave per unit, [8192 x 28672] FP4 216 -> 199.
 static QbForm pick_qb_form(const QuantBothArgs& a, int stats)
 {
-    // SNIP_QUANT_BOTH_UNIT=wave|workgroup in the environment, read at every call, fixes the choice for calls with
-    // statistics, for tests and measurements
-    const char* e = getenv("SNIP_QUANT_BOTH_UNIT");
-    const bool wave = e && e[0] == 'w' && e[1] == 'a', group = e && e[0] == 'w' && e[1] == 'o';
+    // SNIP_QUANT_BOTH_UNIT=4x4|4x8|8x8|wave in the environment, read at every call, fixes the form where it exists for the
+    // call, =workgroup keeps to a workgroup per unit; for tests and measurements
+    bool group = false;
+    if (const char* e = getenv("SNIP_QUANT_BOTH_UNIT")) {
+        const bool fp4 = a.fmt_c == kFP4;
+        const struct { const char* name; QbForm form; bool exists; } kForms[] = {
+            {"4x4", QbForm::k4x4, true}, {"4x8", QbForm::k4x8, fp4 && stats == 2}, {"8x8", QbForm::k8x8, fp4 && stats == 0}, {"wave", QbForm::kWave, stats != 0}};
+        for (const auto& f : kForms)
+            if (!strcmp(e, f.name) && f.exists) return f.form;
+        group = !strcmp(e, "workgroup");
+    }
     const int64_t elems = a.rows * a.cols;
     const bool large = elems > ((int64_t)128 << 20);
     if (stats == 0) return large && a.fmt_c == kFP4 ? QbForm::k8x8 : QbForm::k4x4;
-    if (stats == 1) return (large || wave) && !group ? QbForm::kWave : QbForm::k4x4;
-    if ((elems > ((int64_t)(a.fmt_c == kFP8 ? 28 : 48) << 20) || wave) && !group) return QbForm::kWave;
+    if (stats == 1) return large && !group ? QbForm::kWave : QbForm::k4x4;
+    if (elems > ((int64_t)(a.fmt_c == kFP8 ? 28 : 48) << 20) && !group) return QbForm::kWave;
     return a.fmt_c == kFP4 && elems > ((int64_t)12 << 20) ? QbForm::k4x8 : QbForm::k4x4;
 }
 

@@ -44,13 +44,14 @@ def check(rows, cols, fr, fc, rule, stats):
 @pytest.mark.parametrize("shape", [(32, 32), (160, 96), (416, 1056), (1120, 352)])
 @pytest.mark.parametrize("fmts", [(0, 0), (1, 1), (0, 1), (1, 0)])
 @pytest.mark.parametrize("stats", [0, 1, 2])
-def test_small(shape, fmts, stats):
+def test_small(shape, fmts, stats, quant_both_unit):
     check(*shape, *fmts, 0, stats)
 
 
-# four waves with two tiles each (12 M ... 48 M elements, FP4 columns), a wave per unit (beyond), eight waves with a tile each and
-# the limited occupancy of FP8 columns (beyond the memory-side cache)
-@pytest.mark.parametrize("shape,fmts,stats", [((3232, 4128), (1, 1), 2), ((3232, 4128), (0, 1), 2), ((8224, 6112), (1, 1), 2),
+# the library's own choice: four waves with two tiles each (12 M ... 48 M elements, FP4 columns; 48 M = 50331648: just below and
+# just above), a wave per unit (beyond, FP8 columns from 28 M), eight waves with a tile each and the limited occupancy of FP8
+# columns (beyond the memory-side cache)
+@pytest.mark.parametrize("shape,fmts,stats", [((3232, 4128), (1, 1), 2), ((3232, 4128), (0, 1), 2), ((8224, 6112), (1, 1), 2), ((8224, 6176), (1, 1), 2),
                                               ((8224, 4128), (0, 0), 2), ((8224, 6176), (1, 0), 0), ((16672, 8096), (1, 1), 0),
                                               ((16672, 8096), (0, 1), 0), ((16672, 8096), (0, 0), 0), ((16672, 8096), (1, 1), 1)])
 def test_large(shape, fmts, stats):

@@ -10,8 +10,8 @@ pytestmark = pytest.mark.gpu
 
 # the four waves of a workgroup: tiles below each other (one unit) or side by side (a unit each)
 @pytest.mark.parametrize("call,unit,shape", [("stats_both", None, (128, 128)), ("stats_both", None, (32, 512)),
-                                             ("chosen", "workgroup", (128, 128)), ("chosen", "wave", (32, 512)),
-                                             ("both_formats", "workgroup", (128, 128)), ("both_formats", "wave", (32, 512))])
+                                             ("chosen", "4x4", (128, 128)), ("chosen", "wave", (32, 512)), ("both_formats", "4x4", (128, 128)),
+                                             ("both_formats", "4x8", (128, 128)), ("both_formats", "wave", (32, 512))])
 def test_workgroup_sums_are_not_rounded(call, unit, shape, monkeypatch):
     snip = require_gpu()
     if unit:
