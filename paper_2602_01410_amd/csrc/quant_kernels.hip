@@ -945,63 +945,63 @@ __global__ __launch_bounds__(256) void stats_both_kernel(const uint16_t* __restr
         rpos[t] = (lane >> 2) * 64 + ((((lane & 3) * 4 + t) ^ ((lane >> 2) & 3)) << 2);    // piece t of block lane % 4, row lane / 4
     }
     for (int t = blockIdx.x * kWavesPerBlock + wib; t < ntiles; t += nwaves) {
-            const int rb = t / ncg, c0 = (t - rb * ncg) * kColsPerWave;
-            unsigned v[32];
-            load_col_tile(x + (int64_t)rb * kBlock * ld, c0, lane, cols, ld, v);
+        const int rb = t / ncg, c0 = (t - rb * ncg) * kColsPerWave;
+        unsigned v[32];
+        load_col_tile(x + (int64_t)rb * kBlock * ld, c0, lane, cols, ld, v);
 #pragma unroll
-            for (int i = 0; i < 32; ++i) raw[i * 64 + wpos[i & 3]] = v[i];
-            // ---- column direction ----
+        for (int i = 0; i < 32; ++i) raw[i * 64 + wpos[i & 3]] = v[i];
+        // ---- column direction ----
+        unsigned m = 0;
+#pragma unroll
+        for (int i = 0; i < 32; ++i) m = pk_max_u16(m, v[i] & 0x7FFF7FFFu);
+        unsigned w[16];
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+#pragma unroll
+            for (int k = 0; k < 16; ++k)
+                w[k] = __builtin_amdgcn_perm(v[2 * k + 1], v[2 * k], h ? 0x07060302u : 0x05040100u);
+            const unsigned am = h ? m >> 16 : m & 0xFFFFu;
+            const unsigned b8 = scale_byte<kFP8, RULE>(am), b4 = scale_byte<kFP4, RULE>(am);
+            const float sc8 = scale_operand(b8), sc4 = scale_operand(b4);
+            float dummy = 0.f;
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+                const unsigned e0 = enc8<RULE>(w[4 * k], w[4 * k + 1], sc8, b8);
+                const unsigned e1 = enc8<RULE>(w[4 * k + 2], w[4 * k + 3], sc8, b8);
+                err8(w + 4 * k, e0, e1, sc8, t0, c8, true);
+                const unsigned e4 = enc4(w[4 * k], w[4 * k + 1], w[4 * k + 2], w[4 * k + 3], sc4);
+                err4(w + 4 * k, e4, sc4, dummy, c4, false);
+            }
+            bad |= b8 == 0xFFu;
+        }
+        // ---- row direction: the lane takes two whole blocks, block lane % 4 of tile rows lane / 4 and
+        //      16 + lane / 4, as four 16-byte pieces each, so that a block's maximum and its two scales are
+        //      formed once per 32 elements, inside the lane ----
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+            uint4 q[4];
+#pragma unroll
+            for (int k = 0; k < 4; ++k) q[k] = *reinterpret_cast<const uint4*>(raw + h * 16 * 64 + rpos[k]);
             unsigned m = 0;
 #pragma unroll
-            for (int i = 0; i < 32; ++i) m = pk_max_u16(m, v[i] & 0x7FFF7FFFu);
-            unsigned w[16];
+            for (int k = 0; k < 4; ++k)
+                m = pk_max_u16(m, pk_max_u16(pk_max_u16(q[k].x & 0x7FFF7FFFu, q[k].y & 0x7FFF7FFFu),
+                                             pk_max_u16(q[k].z & 0x7FFF7FFFu, q[k].w & 0x7FFF7FFFu)));
+            const unsigned lo = m & 0xFFFFu, hi = m >> 16;
+            const unsigned am = lo > hi ? lo : hi;
+            const unsigned b8 = scale_byte<kFP8, RULE>(am), b4 = scale_byte<kFP4, RULE>(am);
+            const float sc8 = scale_operand(b8), sc4 = scale_operand(b4);
+            float dummy = 0.f;
 #pragma unroll
-            for (int h = 0; h < 2; ++h) {
-    #pragma unroll
-                for (int k = 0; k < 16; ++k)
-                    w[k] = __builtin_amdgcn_perm(v[2 * k + 1], v[2 * k], h ? 0x07060302u : 0x05040100u);
-                const unsigned am = h ? m >> 16 : m & 0xFFFFu;
-                const unsigned b8 = scale_byte<kFP8, RULE>(am), b4 = scale_byte<kFP4, RULE>(am);
-                const float sc8 = scale_operand(b8), sc4 = scale_operand(b4);
-                float dummy = 0.f;
-#pragma unroll
-                for (int k = 0; k < 4; ++k) {
-                    const unsigned e0 = enc8<RULE>(w[4 * k], w[4 * k + 1], sc8, b8);
-                    const unsigned e1 = enc8<RULE>(w[4 * k + 2], w[4 * k + 3], sc8, b8);
-                    err8(w + 4 * k, e0, e1, sc8, t0, c8, true);
-                    const unsigned e4 = enc4(w[4 * k], w[4 * k + 1], w[4 * k + 2], w[4 * k + 3], sc4);
-                    err4(w + 4 * k, e4, sc4, dummy, c4, false);
-                }
-                bad |= b8 == 0xFFu;
+            for (int k = 0; k < 4; ++k) {
+                const unsigned ww[4] = {q[k].x, q[k].y, q[k].z, q[k].w};
+                const unsigned e0 = enc8<RULE>(ww[0], ww[1], sc8, b8), e1 = enc8<RULE>(ww[2], ww[3], sc8, b8);
+                const unsigned e4 = enc4(ww[0], ww[1], ww[2], ww[3], sc4);
+                err8(ww, e0, e1, sc8, dummy, r8, false);
+                err4(ww, e4, sc4, dummy, r4, false);
             }
-            // ---- row direction: the lane takes two whole blocks, block lane % 4 of tile rows lane / 4 and
-            //      16 + lane / 4, as four 16-byte pieces each, so that a block's maximum and its two scales are
-            //      formed once per 32 elements, inside the lane ----
-#pragma unroll
-            for (int h = 0; h < 2; ++h) {
-                uint4 q[4];
-#pragma unroll
-                for (int k = 0; k < 4; ++k) q[k] = *reinterpret_cast<const uint4*>(raw + h * 16 * 64 + rpos[k]);
-                unsigned m = 0;
-#pragma unroll
-                for (int k = 0; k < 4; ++k)
-                    m = pk_max_u16(m, pk_max_u16(pk_max_u16(q[k].x & 0x7FFF7FFFu, q[k].y & 0x7FFF7FFFu),
-                                                 pk_max_u16(q[k].z & 0x7FFF7FFFu, q[k].w & 0x7FFF7FFFu)));
-                const unsigned lo = m & 0xFFFFu, hi = m >> 16;
-                const unsigned am = lo > hi ? lo : hi;
-                const unsigned b8 = scale_byte<kFP8, RULE>(am), b4 = scale_byte<kFP4, RULE>(am);
-                const float sc8 = scale_operand(b8), sc4 = scale_operand(b4);
-                float dummy = 0.f;
-#pragma unroll
-                for (int k = 0; k < 4; ++k) {
-                    const unsigned ww[4] = {q[k].x, q[k].y, q[k].z, q[k].w};
-                    const unsigned e0 = enc8<RULE>(ww[0], ww[1], sc8, b8), e1 = enc8<RULE>(ww[2], ww[3], sc8, b8);
-                    const unsigned e4 = enc4(ww[0], ww[1], ww[2], ww[3], sc4);
-                    err8(ww, e0, e1, sc8, dummy, r8, false);
-                    err4(ww, e4, sc4, dummy, r4, false);
-                }
-                bad |= b8 == 0xFFu;
-            }
+            bad |= b8 == 0xFFu;
+        }
     }
     if (bad) { r4 = c4 = r8 = c8 = __builtin_nanf(""); }     // a non-finite element poisons every error sum of the wave
     t0 = wave_sum(t0); r4 = wave_sum(r4); r8 = wave_sum(r8); c4 = wave_sum(c4); c8 = wave_sum(c8);
