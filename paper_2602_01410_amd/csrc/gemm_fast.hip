@@ -35,6 +35,10 @@
 // 4096: all workgroups finish a tile together, 32 MB per round, and the next tile's copies queue behind them in
 // the wave's memory counter.
 //
+// Registers: 256 vector registers (256 x 256), 195-219 (256 x 128).  Scalar registers run out and spill to lanes of vector
+// registers: 21-27 for bf16 outputs and 67-74 for fp32 (256 x 256; 256 x 128 15-22 and 62-74), 43-67 and 88-125 in the form
+// that runs ahead, 43-88 and 86-142 with TAIL.
+//
 // See gemm.hip for the register layout of v_mfma_scale_f32_32x32x64_f8f6f4.
 #include "gemm_common.h"
 #include <algorithm>
