@@ -1207,13 +1207,14 @@ static int launch_qb_form(const QuantBothArgs& a, double* partials, hipStream_t 
     // of a tile: at most kStreamBlocks workgroups with equal shares of the units then.
     const int64_t most = STATS ? kStreamBlocks / 8 : (int64_t)1 << 24, run = (units + 7) / 8, share = (run + most - 1) / most;
     const int blocks = NW ? (int)(8 * ((run + share - 1) / share)) : balanced_blocks(units);
-    // FP8 codes of columns, more than 96 MB of source: three workgroups per compute unit (as LDS admits), four and more
-    // only add streams that the memory has to serve at once: [28672 x 8192] 236 -> 209 us, [8192 x 28672] 233 -> 216,
-    // [16384 x 4096] within the noise
-    const unsigned pad = NW && STATS == 0 && FMT_C == kFP8 && a.rows * a.cols > ((int64_t)48 << 20) ? 36000 : 0;
+    // FP4 codes of rows and FP8 codes of columns, more than 96 MB of source: three workgroups per compute unit (as LDS admits),
+    // four and more only add streams that the memory has to serve at once: [12288 x 4096] 47.0 -> 45.9 us, [24576 x 4096] 87.0
+    // -> 84.0, [28672 x 8192] 185.6 -> 180.6, [16384 x 4096] 63.1 -> 63.5.  With FP8 codes of rows it is no gain: 48.8 -> 48.5,
+    // 88.6 -> 88.4, 191 -> 192, and [16384 x 4096] 65.3 -> 67.4, [16384 x 8192] 117 -> 121.
+    const unsigned pad = NW && STATS == 0 && FMT_R == kFP4 && FMT_C == kFP8 && a.rows * a.cols > ((int64_t)48 << 20) ? 36000 : 0;
     hipLaunchKernelGGL((quant_both_kernel<FMT_R, FMT_C, RULE, STATS, NW, RBU>), dim3(blocks), dim3(NW ? NW * 64 : 256), pad, s,
                        a.x, (int)a.rows, (int)a.cols, a.ld, a.codes_r, a.scales_r, a.g4_r, g4_pitch(a.rows),
-                       a.codes_c, a.scales_c, a.g4_c, g4_pitch(a.cols), partials, STATS != 2);
+                       a.codes_c, a.scales_c, a.g4_c, g4_pitch(a.cols), partials, STATS != 2 && NW == RBU);
     return blocks;
 }
 
@@ -1222,7 +1223,7 @@ static int launch_qb(const QuantBothArgs& a, double* partials, QbForm form, hipS
 {
     if constexpr (STATS != 0)
         if (form == QbForm::kWave) return launch_qb_form<FMT_R, FMT_C, RULE, STATS, 0, FMT_C == kFP8 ? 4 : 8>(a, partials, s);
-    if constexpr (FMT_C == kFP4 && STATS == 2)
+    if constexpr (FMT_C == kFP4 && (STATS == 2 || (STATS == 1 && FMT_R == kFP8)))
         if (form == QbForm::k4x8) return launch_qb_form<FMT_R, FMT_C, RULE, STATS, 4, 8>(a, partials, s);
     if constexpr (FMT_C == kFP4 && STATS == 0)
         if (form == QbForm::k8x8) return launch_qb_form<FMT_R, FMT_C, RULE, STATS, 8, 8>(a, partials, s);
@@ -1240,7 +1241,12 @@ static int launch_qb(const QuantBothArgs& a, double* partials, QbForm form, hipS
 //     8-20 %: a wave per unit as soon as that gives every SIMD work, from 28 M elements (48 M with FP4 codes of columns: eight
 //     tiles per unit): [3072 x 8192] FP8 41.2 (wave) against 38.8 (4 x 4), [8192 x 4096] 41.9 against 47.2; FP4 between
 //     12 M and 48 M elements four waves with two tiles each: [4096 x 4096] 26.0 against 28.6 (4 x 4) and 42.7 (wave).
-//   - statistics of the written formats beyond the memory-side cache: a wave per unit, [8192 x 28672] FP4 216 -> 199.
+//   - statistics of the written formats: a wave per unit from 56 M elements on ([16384 x 4096] FP4 66.8 -> 62.6, FP8 77.0 -> 72.2,
+//     [16384 x 8192] 125 -> 110 and 139 -> 128; [12288 x 4096] 51.1 against 58.9 and 57.7 against 59.2), if at two waves per
+//     SIMD its last round is not too empty ([24576 x 4096] FP4, 0.75 of whole rounds, 94.1 -> 88.5; [16384 x 5120], 0.62, 82.3
+//     against 87.9).  Otherwise with FP8 rows and FP4 columns four waves with two tiles each from 20 M elements on: [10240 x 4096]
+//     47.5 (4 x 4) -> 46.3, [16384 x 5120] 90.5 -> 84.3; with FP4 rows they gain less (44.5 -> 43.7, 82.3 -> 80.2) and stay out.
+constexpr int64_t kTwoWavesPerSimd = 2048;
 static QbForm pick_qb_form(const QuantBothArgs& a, int stats)
 {
     // SNIP_QUANT_BOTH_UNIT=4x4|4x8|8x8|wave in the environment, read at every call, fixes the form where it exists for the
@@ -1249,7 +1255,7 @@ static QbForm pick_qb_form(const QuantBothArgs& a, int stats)
     if (const char* e = getenv("SNIP_QUANT_BOTH_UNIT")) {
         const bool fp4 = a.fmt_c == kFP4;
         const struct { const char* name; QbForm form; bool exists; } kForms[] = {
-            {"4x4", QbForm::k4x4, true}, {"4x8", QbForm::k4x8, fp4 && stats == 2}, {"8x8", QbForm::k8x8, fp4 && stats == 0}, {"wave", QbForm::kWave, stats != 0}};
+            {"4x4", QbForm::k4x4, true}, {"4x8", QbForm::k4x8, fp4 && (stats == 2 || (stats == 1 && a.fmt_r == kFP8))}, {"8x8", QbForm::k8x8, fp4 && stats == 0}, {"wave", QbForm::kWave, stats != 0}};
         for (const auto& f : kForms)
             if (!strcmp(e, f.name) && f.exists) return f.form;
         group = !strcmp(e, "workgroup");
@@ -1257,7 +1263,12 @@ static QbForm pick_qb_form(const QuantBothArgs& a, int stats)
     const int64_t elems = a.rows * a.cols;
     const bool large = elems > ((int64_t)128 << 20);
     if (stats == 0) return large && a.fmt_c == kFP4 ? QbForm::k8x8 : QbForm::k4x4;
-    if (stats == 1) return large && !group ? QbForm::kWave : QbForm::k4x4;
+    if (stats == 1) {
+        const int64_t tiles = a.fmt_c == kFP8 ? 4 : 8, waves = ((a.cols + kColsPerWave - 1) / kColsPerWave) * ((a.rows / kBlock + tiles - 1) / tiles);
+        const int64_t rounds = (waves + kTwoWavesPerSimd - 1) / kTwoWavesPerSimd;
+        if (elems > ((int64_t)56 << 20) && 10 * waves >= 7 * rounds * kTwoWavesPerSimd && !group) return QbForm::kWave;
+        return a.fmt_r == kFP8 && a.fmt_c == kFP4 && elems > ((int64_t)20 << 20) ? QbForm::k4x8 : QbForm::k4x4;
+    }
     if (elems > ((int64_t)(a.fmt_c == kFP8 ? 28 : 48) << 20) && !group) return QbForm::kWave;
     return a.fmt_c == kFP4 && elems > ((int64_t)12 << 20) ? QbForm::k4x8 : QbForm::k4x4;
 }

@@ -49,10 +49,12 @@ def test_small(shape, fmts, stats, quant_both_unit):
 
 
 # the library's own choice: four waves with two tiles each (12 M ... 48 M elements, FP4 columns; 48 M = 50331648: just below and
-# just above), a wave per unit (beyond, FP8 columns from 28 M), eight waves with a tile each and the limited occupancy of FP8
-# columns (beyond the memory-side cache)
+# just above), a wave per unit (beyond, FP8 columns from 28 M), eight waves with a tile each (beyond the memory-side cache) and
+# the limited occupancy of FP8 columns beside FP4 rows; with the written formats' statistics a wave per unit from 56 M on, where
+# it fills its rounds, or four waves with two tiles each
 @pytest.mark.parametrize("shape,fmts,stats", [((3232, 4128), (1, 1), 2), ((3232, 4128), (0, 1), 2), ((8224, 6112), (1, 1), 2), ((8224, 6176), (1, 1), 2),
                                               ((8224, 4128), (0, 0), 2), ((8224, 6176), (1, 0), 0), ((16672, 8096), (1, 1), 0),
-                                              ((16672, 8096), (0, 1), 0), ((16672, 8096), (0, 0), 0), ((16672, 8096), (1, 1), 1)])
+                                              ((16672, 8096), (0, 1), 0), ((16672, 8096), (0, 0), 0), ((16672, 8096), (1, 1), 1),
+                                              ((8192, 7392), (1, 1), 1), ((8192, 7392), (0, 0), 1), ((8224, 8224), (0, 1), 1), ((3232, 6624), (0, 1), 1)])
 def test_large(shape, fmts, stats):
     check(*shape, *fmts, 1 if stats == 0 else 0, stats)
