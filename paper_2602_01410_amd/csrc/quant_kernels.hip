@@ -682,13 +682,17 @@ __global__ __launch_bounds__(NW ? NW * 64 : 256) void quant_both_kernel(const ui
     const uint2 no_seed = make_uint2(0, 0);
     float s0 = 0.f, se_c = 0.f, se_r = 0.f;
     float so_c = 0.f, so_r = 0.f;                         // STATS == 2: error sums of the format not chosen
-    // COOP: units go to the XCDs (workgroup id mod 8) in contiguous runs, and a run walks pairs of row units column group by
-    // column group, so that the two halves of a 128-byte line (FP4 codes of a row: 64 bytes per unit; FP4 codes of a column,
-    // likewise) and the scale bytes of neighbouring units meet in one L2.  (the grid is a multiple of 8 workgroups)
-    const int run = (units + 7) / 8, run0 = (int)(blockIdx.x % 8) * run, run1 = min(run0 + run, units);
-    for (int u = COOP ? run0 + (int)(blockIdx.x / 8) : wave; u < (COOP ? run1 : units); u += COOP ? (int)(gridDim.x / 8) : nwaves) {
+    // COOP, `runs`: units go to the XCDs (workgroup id mod 8) in contiguous runs, and a run walks pairs of row units column
+    // group by column group, so that the two halves of a 128-byte line (FP4 codes of a row: 64 bytes per unit; FP4 codes of a
+    // column, likewise) and the scale bytes of neighbouring units meet in one L2 (the grid is a multiple of 8 workgroups).
+    // Otherwise units are dealt in order and the chip reads one band of rows at a time.  Which one: launch_qb_form.
+    const int run = (units + 7) / 8, run0 = (int)(blockIdx.x % 8) * run;
+    const bool in_runs = COOP && runs;
+    const int u_first = in_runs ? run0 + (int)(blockIdx.x / 8) : COOP ? (int)blockIdx.x : wave, u_end = in_runs ? min(run0 + run, units) : units;
+    const int u_step = in_runs ? (int)(gridDim.x / 8) : COOP ? (int)gridDim.x : nwaves;
+    for (int u = u_first; u < u_end; u += u_step) {
         int ru, cg;
-        if (COOP && runs) {
+        if (in_runs) {
             const int pair = u / (2 * ncg), rem = u - pair * 2 * ncg;
             const bool single = 2 * pair + 1 == nru;                  // the last pair may be one row unit
             ru = 2 * pair + (single ? 0 : rem & 1);
@@ -1212,9 +1216,15 @@ static int launch_qb_form(const QuantBothArgs& a, double* partials, hipStream_t 
     // -> 84.0, [28672 x 8192] 185.6 -> 180.6, [16384 x 4096] 63.1 -> 63.5.  With FP8 codes of rows it is no gain: 48.8 -> 48.5,
     // 88.6 -> 88.4, 191 -> 192, and [16384 x 4096] 65.3 -> 67.4, [16384 x 8192] 117 -> 121.
     const unsigned pad = NW && STATS == 0 && FMT_R == kFP4 && FMT_C == kFP8 && a.rows * a.cols > ((int64_t)48 << 20) ? 36000 : 0;
+    // Order of the units (see quant_both_kernel): runs below 8 M elements, where the tensor fits the L2s ([1504 x 2080] 12.0
+    // against 12.4 us dealt), and without statistics from 8192 rows on, if rows start on whole lines of 256 bytes ([8192 x 3072]
+    // FP8 29.0 (dealt) -> 27.9, [12288 x 4096] FP4 46.1 -> 44.3, [8192 x 28672] 204 -> 184).  Elsewhere the eight runs, far
+    // apart, meet in few memory channels: [8224 x 8224] FP4 83.7 (runs) -> 73.9, [8160 x 8160] 88.6 -> 68.5, [4096 x 11008] FP8
+    // 47.3 -> 44.9, with statistics [8192 x 4096] FP4 50.4 -> 48.8.
+    const bool runs = a.rows * a.cols < ((int64_t)8 << 20) || (STATS == 0 && a.rows >= 8192 && a.ld % 128 == 0);
     hipLaunchKernelGGL((quant_both_kernel<FMT_R, FMT_C, RULE, STATS, NW, RBU>), dim3(blocks), dim3(NW ? NW * 64 : 256), pad, s,
                        a.x, (int)a.rows, (int)a.cols, a.ld, a.codes_r, a.scales_r, a.g4_r, g4_pitch(a.rows),
-                       a.codes_c, a.scales_c, a.g4_c, g4_pitch(a.cols), partials, STATS != 2 && NW == RBU);
+                       a.codes_c, a.scales_c, a.g4_c, g4_pitch(a.cols), partials, runs);
     return blocks;
 }
 
@@ -1223,7 +1233,7 @@ static int launch_qb(const QuantBothArgs& a, double* partials, QbForm form, hipS
 {
     if constexpr (STATS != 0)
         if (form == QbForm::kWave) return launch_qb_form<FMT_R, FMT_C, RULE, STATS, 0, FMT_C == kFP8 ? 4 : 8>(a, partials, s);
-    if constexpr (FMT_C == kFP4 && (STATS == 2 || (STATS == 1 && FMT_R == kFP8)))
+    if constexpr (FMT_C == kFP4 && STATS != 0)
         if (form == QbForm::k4x8) return launch_qb_form<FMT_R, FMT_C, RULE, STATS, 4, 8>(a, partials, s);
     if constexpr (FMT_C == kFP4 && STATS == 0)
         if (form == QbForm::k8x8) return launch_qb_form<FMT_R, FMT_C, RULE, STATS, 8, 8>(a, partials, s);
@@ -1241,11 +1251,12 @@ static int launch_qb(const QuantBothArgs& a, double* partials, QbForm form, hipS
 //     8-20 %: a wave per unit as soon as that gives every SIMD work, from 28 M elements (48 M with FP4 codes of columns: eight
 //     tiles per unit): [3072 x 8192] FP8 41.2 (wave) against 38.8 (4 x 4), [8192 x 4096] 41.9 against 47.2; FP4 between
 //     12 M and 48 M elements four waves with two tiles each: [4096 x 4096] 26.0 against 28.6 (4 x 4) and 42.7 (wave).
-//   - statistics of the written formats: a wave per unit from 56 M elements on ([16384 x 4096] FP4 66.8 -> 62.6, FP8 77.0 -> 72.2,
-//     [16384 x 8192] 125 -> 110 and 139 -> 128; [12288 x 4096] 51.1 against 58.9 and 57.7 against 59.2), if at two waves per
-//     SIMD its last round is not too empty ([24576 x 4096] FP4, 0.75 of whole rounds, 94.1 -> 88.5; [16384 x 5120], 0.62, 82.3
-//     against 87.9).  Otherwise with FP8 rows and FP4 columns four waves with two tiles each from 20 M elements on: [10240 x 4096]
-//     47.5 (4 x 4) -> 46.3, [16384 x 5120] 90.5 -> 84.3; with FP4 rows they gain less (44.5 -> 43.7, 82.3 -> 80.2) and stay out.
+//   - statistics of the written formats: a wave per unit from 56 M elements on ([16384 x 4096] FP4 62.9 (4 x 4) -> 61.7, FP8 71.2
+//     -> 71.1, [16384 x 8192] 122 -> 109 and 141 -> 128; [12288 x 4096] 50.8 against 59.0 and 56.6 against 57.9), if at two
+//     waves per SIMD the last round is not too empty ([24576 x 4096] FP4, 0.75 of whole rounds, 95.2 -> 88.8; [16384 x 5120],
+//     0.62, 82.6 against 88.0) and, for FP4 columns, rows start on whole lines ([12320 x 8224] 118 against 116, 4 x 8 112).
+//     FP4 columns that a wave per unit does not serve take four waves with two tiles each from there on ([8224 x 8224] 81.3 (4 x
+//     4) -> 76.6, [16384 x 5120] 82.6 -> 79.8), beside FP8 rows from 20 M on ([12288 x 4096] 52.9 -> 51.8).
 constexpr int64_t kTwoWavesPerSimd = 2048;
 static QbForm pick_qb_form(const QuantBothArgs& a, int stats)
 {
@@ -1255,7 +1266,7 @@ static QbForm pick_qb_form(const QuantBothArgs& a, int stats)
     if (const char* e = getenv("SNIP_QUANT_BOTH_UNIT")) {
         const bool fp4 = a.fmt_c == kFP4;
         const struct { const char* name; QbForm form; bool exists; } kForms[] = {
-            {"4x4", QbForm::k4x4, true}, {"4x8", QbForm::k4x8, fp4 && (stats == 2 || (stats == 1 && a.fmt_r == kFP8))}, {"8x8", QbForm::k8x8, fp4 && stats == 0}, {"wave", QbForm::kWave, stats != 0}};
+            {"4x4", QbForm::k4x4, true}, {"4x8", QbForm::k4x8, fp4 && stats != 0}, {"8x8", QbForm::k8x8, fp4 && stats == 0}, {"wave", QbForm::kWave, stats != 0}};
         for (const auto& f : kForms)
             if (!strcmp(e, f.name) && f.exists) return f.form;
         group = !strcmp(e, "workgroup");
@@ -1266,8 +1277,9 @@ static QbForm pick_qb_form(const QuantBothArgs& a, int stats)
     if (stats == 1) {
         const int64_t tiles = a.fmt_c == kFP8 ? 4 : 8, waves = ((a.cols + kColsPerWave - 1) / kColsPerWave) * ((a.rows / kBlock + tiles - 1) / tiles);
         const int64_t rounds = (waves + kTwoWavesPerSimd - 1) / kTwoWavesPerSimd;
-        if (elems > ((int64_t)56 << 20) && 10 * waves >= 7 * rounds * kTwoWavesPerSimd && !group) return QbForm::kWave;
-        return a.fmt_r == kFP8 && a.fmt_c == kFP4 && elems > ((int64_t)20 << 20) ? QbForm::k4x8 : QbForm::k4x4;
+        const bool many = elems > ((int64_t)56 << 20), full = 100 * waves >= 65 * rounds * kTwoWavesPerSimd;
+        if (many && full && (a.fmt_c == kFP8 || a.ld % 128 == 0) && !group) return QbForm::kWave;
+        return a.fmt_c == kFP4 && (many || (a.fmt_r == kFP8 && elems > ((int64_t)20 << 20))) ? QbForm::k4x8 : QbForm::k4x4;
     }
     if (elems > ((int64_t)(a.fmt_c == kFP8 ? 28 : 48) << 20) && !group) return QbForm::kWave;
     return a.fmt_c == kFP4 && elems > ((int64_t)12 << 20) ? QbForm::k4x8 : QbForm::k4x4;
