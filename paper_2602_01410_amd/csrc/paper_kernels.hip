@@ -262,7 +262,11 @@ __global__ __launch_bounds__(256) void paper_row_kernel(const uint16_t* __restri
 // [128 stored rows][ROWB] image (ROWB = 128 bytes FP8, 64 bytes FP4) whose 16-byte chunks are XOR-swizzled,
 // then stored with 16 bytes per lane so that whole 128- / 64-byte runs are written.
 // A wave per unit, which held its 128 rows in 128 registers, left half of the SIMDs without a wave on a [4096 x 2048] tensor:
-// 11.7 -> 8.1 us; [8192 x 2048] in blocks 15.2 -> 11.8, [4096 x 8192] 27.4 -> 23.1 (FP8, kernel trace).
+// 11.7 -> 8.1 us; [8192 x 2048] in blocks 15.2 -> 11.8, [4096 x 8192] 27.4 -> 23.1 (FP8, kernel trace).  Four column groups in a
+// row go to one XCD, 1 KB of a source row: dealt one by one (the same calls, us: a wave per unit / one by one / four) [16384 x
+// 4096] FP4 32.8 / 35.6 / 32.9, [4096 x 28672] FP4 55.7 / 60.5 / 57.6, [12288 x 8192] FP8 63.8 / 56.8 / 54.9.  A wave per unit
+// is still the faster one with FP4 codes of very large tensors of some pitches ([24576 x 4096] 48.3 against 51.9, [8192 x 28672]
+// 117 against 137; not so [16384 x 11008], 101 against 93).
 // ------------------------------------------------------------------------------------------
 template <int FMT>
 __device__ __forceinline__ void encode_column(const unsigned* v, int half, float s, uint8_t* __restrict__ lds_row,
@@ -334,6 +338,7 @@ __device__ __forceinline__ void err_column(const unsigned* v, int half, float s,
     }
 }
 
+constexpr int kAdjacent = 4;
 template <int FMT, bool BLOCKS, int MODE>
 __global__ __launch_bounds__(256) void paper_col_kernel(const uint16_t* __restrict__ x, int rows, int cols, int64_t ld,
                                                         uint8_t* __restrict__ codes, float* __restrict__ scales,
@@ -353,7 +358,10 @@ __global__ __launch_bounds__(256) void paper_col_kernel(const uint16_t* __restri
     const int units = ncg * nru;
     const int64_t out_row_bytes = FMT == kFP8 ? rows : rows / 2;
     float s0 = 0.f, e4 = 0.f, e8 = 0.f;
-    for (int u = blockIdx.x; u < units; u += gridDim.x) {
+    for (int b = blockIdx.x; b < units; b += gridDim.x) {
+        // workgroups b, b + 8, ... run on one XCD: of every 8 * kAdjacent units each XCD takes kAdjacent in a row
+        const int b0 = b / (8 * kAdjacent) * (8 * kAdjacent);
+        const int u = b0 + 8 * kAdjacent <= units ? b0 + (b & 7) * kAdjacent + ((b - b0) >> 3) : b;
         const int ru = u / ncg, cg = u - ru * ncg;
         const int c = cg * kColsPerWave + lane * 2;
         const bool act = c < cols;

@@ -159,3 +159,17 @@ def test_gemm_paper_ragged_outputs_and_exact_case():
     a64 = wl.bf16_bits_to_f32(A).astype(np.float64)
     b64 = wl.bf16_bits_to_f32(B).astype(np.float64)
     assert np.array_equal(host(c).astype(np.float64), a64 @ b64.T)
+
+
+@pytest.mark.parametrize("group", [oracle.TILE_1x128, oracle.BLOCK_128x128])
+@pytest.mark.parametrize("fmt", [0, 1])
+@pytest.mark.parametrize("shape", [(128, 3970), (384, 1344), (512, 1026), (256, 4224)])
+def test_column_units_in_any_number(shape, fmt, group):
+    """Units of 128 x 128 that fill whole rounds of the order they are taken in, and that leave 0, 1 and 4 over; the last
+    column group ragged: the same codes and scales as the transposed source along its rows."""
+    snip = require_gpu()
+    rows, cols = shape
+    gen = torch.Generator(device="cuda").manual_seed(rows + cols)
+    x = torch.randn((rows, (cols + 7) // 8 * 8), generator=gen, device="cuda").bfloat16()[:, :cols]
+    got, want = snip.snip_quantize_paper(x, fmt, snip.COL, group), snip.snip_quantize_paper(x.t().contiguous(), fmt, snip.ROW, group)
+    assert torch.equal(got[0], want[0]) and torch.equal(got[1], want[1])
