@@ -77,10 +77,10 @@ __device__ __forceinline__ float wave_sum(float v)
 template <int FMT, int RULE>
 __device__ __forceinline__ unsigned scale_byte(unsigned amax_bits)
 {
-    int b = (int)(amax_bits >> 7) - Fmt<FMT>::emax;
-    if (RULE == 0 && (amax_bits & 0x7Fu) > Fmt<FMT>::mmax) b += 1;
+    // (rule 0: adding 0x7F - mmax carries into the exponent where the mantissa exceeds mmax)
+    int b = (int)amax_bits + ((RULE == 0 ? 0x7F - (int)Fmt<FMT>::mmax : 0) - (Fmt<FMT>::emax << 7));
     b = b < 0 ? 0 : b;
-    return amax_bits >= 0x7F80u ? 0xFFu : (unsigned)b;
+    return amax_bits >= 0x7F80u ? 0xFFu : (unsigned)b >> 7;
 }
 
 // The conversion instructions read only the exponent field of their scale operand; the
@@ -477,8 +477,10 @@ __device__ __forceinline__ unsigned quant_one_column(const unsigned* w, unsigned
 #pragma unroll
         for (int k = 0; k < 8; ++k) {
             c[k] = enc8<RULE>(w[2 * k], w[2 * k + 1], sc, byte);
-            if (bad) c[k] = 0;
         }
+        if (__builtin_amdgcn_ballot_w64(bad) != 0)                       // wave-uniform
+#pragma unroll
+            for (int k = 0; k < 8; ++k) c[k] = bad ? 0u : c[k];
         *reinterpret_cast<uint4*>(lds_row + (((rb_local * 2 + 0) ^ swz) * 16)) = make_uint4(c[0], c[1], c[2], c[3]);
         *reinterpret_cast<uint4*>(lds_row + (((rb_local * 2 + 1) ^ swz) * 16)) = make_uint4(c[4], c[5], c[6], c[7]);
         if (STATS) {
@@ -491,8 +493,10 @@ __device__ __forceinline__ unsigned quant_one_column(const unsigned* w, unsigned
         for (int k = 0; k < 4; ++k) {
             c[k] = SR ? enc4_sr_at(w + 4 * k, sc, e0 + 8 * k, seed)
                       : enc4(w[4 * k], w[4 * k + 1], w[4 * k + 2], w[4 * k + 3], sc);
-            if (bad) c[k] = 0;
         }
+        if (__builtin_amdgcn_ballot_w64(bad) != 0)                       // wave-uniform
+#pragma unroll
+            for (int k = 0; k < 4; ++k) c[k] = bad ? 0u : c[k];
         *reinterpret_cast<uint4*>(lds_row + ((rb_local ^ swz) * 16)) = make_uint4(c[0], c[1], c[2], c[3]);
         if (STATS) {
 #pragma unroll
@@ -652,18 +656,47 @@ __device__ __forceinline__ void other_format_error(const unsigned* w, unsigned a
     }
 }
 
+// Memory access of quant_both_kernel: buffer descriptors with a wave-uniform base per tile, a lane offset that is the same for
+// every row of the tile and the row's offset in a scalar register, so that a load or store costs no vector instruction for its
+// address; a lane that has nothing to load or store takes an offset past the descriptor's end (loads deliver zeros, stores
+// are dropped) instead of a branch.
+typedef __amdgpu_buffer_rsrc_t rsrc_t;
+typedef unsigned v2u_t __attribute__((ext_vector_type(2)));
+// A 16-byte store takes its whole offset in the lane: with a scalar register for the offset the hardware was seen to store the
+// first dword of a vector register that the next instruction overwrote, and the compiler puts no wait state there (it does
+// where the scalar offset is a constant); stores of 4 and 8 bytes do not read late.
+constexpr int kPast = (int)0x80000000u;                // past the end of every descriptor
+__device__ __forceinline__ rsrc_t tile_rsrc(const void* p) { return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(p), 0, 0x7FFFFFFF, 0x00020000); }
+__device__ __forceinline__ void step(int& soff, int by)
+{
+    soff += by;
+    asm volatile("" : "+s"(soff));                      // stepped, not computed ahead: 32 offsets at once would not fit the scalar registers
+}
+
 // NW != 0: the NW waves of a workgroup share a unit of RBU tiles (wave w takes tiles w, w + NW, ...) and one staging area.
+// Without statistics NW more waves take the rows of the tiles (SPLIT), and the first NW the columns: 60-67 registers instead
+// of 96 put seven waves on a SIMD instead of four or five, and the two chains of a tile run side by side.  With statistics
+// a workgroup would wait for its column waves, whose work is the longer: [8192 x 4096] FP4 54 us against 41.
 // NW == 0 (with statistics): a wave per unit, four of them in a workgroup.  Same bytes out.
+// Without statistics bound by memory (and by launch and one tile's chain below 4 M elements), with them by vector arithmetic.
+// Vector instructions per tile of 4096 elements, FP4: 765 -> 464 without statistics, 1800 -> 1480 with all of them, when
+// addresses and conditions moved into descriptors and scalar registers.  Both changes, us per call on sources in memory,
+// before -> now: [256 x 512] FP8 5.2 -> 4.0, [2048 x 2048] FP4 7.7 -> 6.2, [4096 x 8192] FP4 34.8 -> 29.9, FP8 39.1 -> 34.0, [16384 x
+// 11008] FP4 141 -> 133, FP8 177 -> 165; with all statistics [4096 x 4096] FP4 27.0 -> 24.8, [16384 x 4096] 77 -> 68, FP8 81.5 -> 76,
+// [16384 x 11008] FP4 195 -> 174, FP8 214 -> 197.
+// Offsets inside a tile are 32-bit: launch_quantize_both keeps to tensors whose rows are short enough (qb_offsets_fit).
+constexpr int qb_threads(int nw, int stats) { return nw ? nw * (stats ? 64 : 128) : 256; }
 template <int FMT_R, int FMT_C, int RULE, int STATS, int NW, int RBU>      // STATS: 0 none, 1 the chosen formats' errors, 2 both formats' errors
-__global__ __launch_bounds__(NW ? NW * 64 : 256) void quant_both_kernel(const uint16_t* __restrict__ x, int rows, int cols, int64_t ld,
+__global__ __launch_bounds__(qb_threads(NW, STATS)) void quant_both_kernel(const uint16_t* __restrict__ x, int rows, int cols, int64_t ld,
                                                          uint8_t* __restrict__ codes_r, uint8_t* __restrict__ scales_r,
                                                          uint8_t* __restrict__ g4_r, int64_t kpitch_r,
                                                          uint8_t* __restrict__ codes_c, uint8_t* __restrict__ scales_c,
                                                          uint8_t* __restrict__ g4_c, int64_t kpitch_c,
                                                          double* __restrict__ partials, int runs)
 {
-    constexpr bool COOP = NW != 0;
-    constexpr int WPB = COOP ? NW : kWavesPerBlock;
+    constexpr bool COOP = NW != 0, SPLIT = STATS == 0;
+    static_assert(COOP || !SPLIT, "a wave per unit is for the statistics");
+    constexpr int WPB = qb_threads(NW, STATS) / 64;
     constexpr int ROWB = RBU * (FMT_C == kFP8 ? 32 : 16);
     constexpr int CPR = ROWB / 16;
     __shared__ __attribute__((aligned(16))) uint8_t stage[COOP ? 1 : kWavesPerBlock][kColsPerWave * ROWB];
@@ -678,7 +711,8 @@ __global__ __launch_bounds__(NW ? NW * 64 : 256) void quant_both_kernel(const ui
     const int nru = (nrb + RBU - 1) / RBU;
     const int units = ncg * nru;
     const int nblk = cols / kBlock;                       // blocks per row of the row-direction output
-    const int64_t out_row_bytes = FMT_C == kFP8 ? rows : rows / 2;
+    const int pitch_x = (int)ld * 2;
+    const int pitch_r = FMT_R == kFP8 ? cols : cols / 2, pitch_c = FMT_C == kFP8 ? rows : rows / 2;      // bytes of a stored row
     const uint2 no_seed = make_uint2(0, 0);
     float s0 = 0.f, se_c = 0.f, se_r = 0.f;
     float so_c = 0.f, so_r = 0.f;                         // STATS == 2: error sums of the format not chosen
@@ -701,51 +735,52 @@ __global__ __launch_bounds__(NW ? NW * 64 : 256) void quant_both_kernel(const ui
             ru = u / ncg;
             cg = u - ru * ncg;
         }
-        const int c = cg * kColsPerWave + lane * 2;
-        const bool act = c < cols;
-        const int rcol = cg * kColsPerWave + (lane & 15) * 8;       // row direction: this lane's 8 columns
-        const bool ract = rcol < cols;
+        const int c0 = cg * kColsPerWave;
+        const bool act = c0 + lane * 2 < cols;                        // column direction: this lane's 2 columns
+        const bool ract = c0 + (lane & 15) * 8 < cols;                // row direction: this lane's 8 columns
         const int rb0 = ru * RBU;
         const int nb = min(nrb - rb0, RBU);
         const int swz_lo = lane & (CPR - 1);
-        // Tiles of the unit, top to bottom.
         unsigned g4_lo = 0, g4_hi = 0;
-        // Loads carry no condition (a lane past the last column reads column 0 of the same rows instead and is
-        // zeroed afterwards, under a wave-uniform test), so that all 40 of a tile stay in flight together.
-        const bool ragged = (cg + 1) * kColsPerWave > cols;
+        auto tile_x = [&](int k) { return tile_rsrc(x + (int64_t)(rb0 + k) * kBlock * ld + c0); };
         // Four row blocks done (the last group of a tensor may hold fewer: blocks 0 .. last): their scale bytes of a
         // column are one dword of the row-major array (when the row length allows it) and exactly one dword of the
         // grouped copy.
         auto store_col_scales = [&](int rbh, int last, unsigned lo, unsigned hi) {
-            if (act) {
-                uint8_t* s_lo = scales_c + (int64_t)c * nrb + rbh;
-                if ((nrb & 3) == 0) {
-                    *reinterpret_cast<unsigned*>(s_lo) = lo;
-                    *reinterpret_cast<unsigned*>(s_lo + nrb) = hi;
-                } else {
-                    for (int i = 0; i <= last; ++i) { s_lo[i] = (uint8_t)(lo >> (8 * i)); s_lo[nrb + i] = (uint8_t)(hi >> (8 * i)); }
+            const rsrc_t ss = tile_rsrc(scales_c + (int64_t)c0 * nrb + rbh);
+            const int voff = act ? 2 * lane * nrb : kPast;
+            if ((nrb & 3) == 0) {
+                __builtin_amdgcn_raw_buffer_store_b32(lo, ss, voff, 0, 0);
+                __builtin_amdgcn_raw_buffer_store_b32(hi, ss, voff, nrb, 0);
+            } else {
+                for (int i = 0; i <= last; ++i) {
+                    __builtin_amdgcn_raw_buffer_store_b8((uint8_t)(lo >> (8 * i)), ss, voff, i, 0);
+                    __builtin_amdgcn_raw_buffer_store_b8((uint8_t)(hi >> (8 * i)), ss, voff, nrb + i, 0);
                 }
-                if (g4_c)
-                    *reinterpret_cast<uint2*>(g4_c + ((int64_t)(rbh / kRowBlocksPerUnit) * kpitch_c + c) * 4) = make_uint2(lo, hi);
             }
+            if (g4_c)
+                __builtin_amdgcn_raw_buffer_store_b64(v2u_t{lo, hi}, tile_rsrc(g4_c + ((int64_t)(rbh / kRowBlocksPerUnit) * kpitch_c + c0) * 4),
+                                                      act ? lane * 8 : kPast, 0, 0);
+        };
+        auto fetch_col = [&](int k, unsigned (&cv)[32]) {
+            const rsrc_t sx = tile_x(k);
+            const int voff = act ? lane * 4 : kPast;
+            int soff = 0;
+#pragma unroll
+            for (int i = 0; i < 32; ++i) { cv[i] = __builtin_amdgcn_raw_buffer_load_b32(sx, voff, soff, 0); step(soff, pitch_x); }
         };
         auto fetch_row = [&](int k, uint4 (&rv)[8]) {
-            const uint16_t* pr = x + (int64_t)((rb0 + k) * kBlock + (lane >> 4)) * ld + (ract ? rcol : 0);
+            const rsrc_t sx = tile_x(k);
+            const int voff = ract ? (lane >> 4) * pitch_x + (lane & 15) * 16 : kPast;
+            int soff = 0;
 #pragma unroll
-            for (int j = 0; j < 8; ++j) rv[j] = *reinterpret_cast<const uint4*>(pr + (int64_t)(4 * j) * ld);
-        };
-        auto fetch = [&](int k, unsigned (&cv)[32], uint4 (&rv)[8]) {
-            load_col_raw(x + (int64_t)(rb0 + k) * kBlock * ld + (act ? c : 0), ld, cv);
-            fetch_row(k, rv);
-        };
-        auto work = [&](int k, unsigned (&cv)[32], uint4 (&rv)[8]) {
-            if (ragged) {
-#pragma unroll
-                for (int i = 0; i < 32; ++i) cv[i] = act ? cv[i] : 0u;
-#pragma unroll
-                for (int j = 0; j < 8; ++j) rv[j] = ract ? rv[j] : make_uint4(0, 0, 0, 0);
+            for (int j = 0; j < 8; ++j) {
+                const v4u_t v = __builtin_amdgcn_raw_buffer_load_b128(sx, voff, soff, 0);
+                rv[j] = make_uint4(v[0], v[1], v[2], v[3]);
+                step(soff, 4 * pitch_x);
             }
-            // ---- column direction
+        };
+        auto work_col = [&](int k, unsigned (&cv)[32]) {
             ColBlock b;
             pair_col_block(cv, b);
             const unsigned y0 = quant_one_column<FMT_C, RULE, STATS != 0, false>(b.lo, b.am_lo, reg + (2 * lane) * ROWB, k, swz_lo, s0, se_c, 0, no_seed);
@@ -765,58 +800,90 @@ __global__ __launch_bounds__(NW ? NW * 64 : 256) void quant_both_kernel(const ui
                     g4_lo = 0; g4_hi = 0;
                 }
             }
-            // ---- row direction
-            const int row0 = (rb0 + k) * kBlock + (lane >> 4);
+        };
+        auto work_row = [&](int k, uint4 (&rv)[8]) {
+            const int row0 = (rb0 + k) * kBlock;
+            const rsrc_t sc_codes = tile_rsrc(codes_r + (int64_t)row0 * pitch_r + (FMT_R == kFP8 ? c0 : c0 / 2));
+            const int voff = ract ? (lane >> 4) * pitch_r + (lane & 15) * (FMT_R == kFP8 ? 8 : 4) : kPast;
+            int soff = 0;
+            int d_lo = 0, d_hi = 0;
 #pragma unroll
             for (int j = 0; j < 8; ++j) {
-                const int row = row0 + 4 * j;
                 const unsigned am = quad_max(amax8(rv[j]));
                 const unsigned byte = scale_byte<FMT_R, RULE>(am);
                 const float sc = scale_operand(byte);
                 const bool bad = byte == 0xFFu;
                 const unsigned w[4] = {rv[j].x, rv[j].y, rv[j].z, rv[j].w};
-                const int64_t e0 = (int64_t)row * cols + rcol;
                 float unused = 0.f;
                 if (FMT_R == kFP8) {
-                    unsigned c0 = enc8<RULE>(w[0], w[1], sc, byte), c1 = enc8<RULE>(w[2], w[3], sc, byte);
-                    if (bad) { c0 = 0; c1 = 0; }
-                    if (ract) *reinterpret_cast<uint2*>(codes_r + e0) = make_uint2(c0, c1);
-                    if (STATS) err8(w, c0, c1, sc, unused, se_r, false);
+                    unsigned e0 = enc8<RULE>(w[0], w[1], sc, byte), e1 = enc8<RULE>(w[2], w[3], sc, byte);
+                    if (bad) { e0 = 0; e1 = 0; }
+                    __builtin_amdgcn_raw_buffer_store_b64(v2u_t{e0, e1}, sc_codes, voff, soff, 0);
+                    if (STATS) err8(w, e0, e1, sc, unused, se_r, false);
                     if (STATS == 2) {
                         const unsigned bo = scale_byte<kFP4, RULE>(am);
                         const float sco = scale_operand(bo);
                         err4(w, enc4(w[0], w[1], w[2], w[3], sco), sco, unused, so_r, false);
                     }
                 } else {
-                    unsigned c4 = enc4(w[0], w[1], w[2], w[3], sc);
-                    if (bad) c4 = 0;
-                    if (ract) *reinterpret_cast<unsigned*>(codes_r + (e0 >> 1)) = c4;
-                    if (STATS) err4(w, c4, sc, unused, se_r, false);
+                    unsigned e4 = enc4(w[0], w[1], w[2], w[3], sc);
+                    if (bad) e4 = 0;
+                    __builtin_amdgcn_raw_buffer_store_b32(e4, sc_codes, voff, soff, 0);
+                    if (STATS) err4(w, e4, sc, unused, se_r, false);
                     if (STATS == 2) {
                         const unsigned bo = scale_byte<kFP8, RULE>(am);
                         const float sco = scale_operand(bo);
                         err8(w, enc8<RULE>(w[0], w[1], sco, bo), enc8<RULE>(w[2], w[3], sco, bo), sco, unused, so_r, false);
                     }
                 }
-                // the four block bytes of this row's 128-column group: one dword of the grouped copy and,
-                // when rows hold a whole number of groups, of the row-major array too
-                const unsigned p1 = (unsigned)__builtin_amdgcn_update_dpp(0, (int)byte, 0x104, 0xF, 0xF, true);   // lane + 4
-                const unsigned p2 = (unsigned)__builtin_amdgcn_update_dpp(0, (int)byte, 0x108, 0xF, 0xF, true);   // lane + 8
-                const unsigned p3 = (unsigned)__builtin_amdgcn_update_dpp(0, (int)byte, 0x10C, 0xF, 0xF, true);   // lane + 12
-                const unsigned d = byte | (p1 << 8) | (p2 << 16) | (p3 << 24);
-                if (ract && (lane & 15) == 0) {
-                    if ((nblk & 3) == 0) *reinterpret_cast<unsigned*>(scales_r + (int64_t)row * nblk + cg * 4) = d;
-                    if (g4_r) *reinterpret_cast<unsigned*>(g4_r + ((int64_t)cg * kpitch_r + row) * 4) = d;
-                }
-                if ((nblk & 3) != 0 && ract && (lane & 3) == 0)
-                    scales_r[(int64_t)row * nblk + (rcol >> 5)] = (uint8_t)byte;
+                step(soff, 4 * pitch_r);
+                // the four block bytes of this row's 128 columns as a dword, in all 16 lanes of the row; quad j % 4 keeps it
+                int d = (int)(byte << (8 * ((lane >> 2) & 3)));
+                d |= __builtin_amdgcn_update_dpp(0, d, 0x124, 0xF, 0xF, true);                  // row_ror:4
+                d |= __builtin_amdgcn_update_dpp(0, d, 0x128, 0xF, 0xF, true);                  // row_ror:8
+                int& keep = j < 4 ? d_lo : d_hi;
+                if ((j & 3) == 0) keep = __builtin_amdgcn_update_dpp(keep, d, 0xE4, 0xF, 1, false);
+                if ((j & 3) == 1) keep = __builtin_amdgcn_update_dpp(keep, d, 0xE4, 0xF, 2, false);
+                if ((j & 3) == 2) keep = __builtin_amdgcn_update_dpp(keep, d, 0xE4, 0xF, 4, false);
+                if ((j & 3) == 3) keep = __builtin_amdgcn_update_dpp(keep, d, 0xE4, 0xF, 8, false);
             }
+            // the tile's 32 dwords at once: one of the grouped copy and, when rows hold a whole number of groups, of the
+            // row-major array per row
+            const int row = 16 * (lane & 1) + 4 * ((lane >> 2) & 3) + (lane >> 4);
+            const int d = lane & 1 ? d_hi : d_lo;
+            const bool mine = (lane & 2) == 0;
+            const rsrc_t ss = tile_rsrc(scales_r + (int64_t)row0 * nblk + cg * 4);
+            const int soff_r = mine ? row * nblk : kPast;
+            if ((nblk & 3) == 0) {
+                __builtin_amdgcn_raw_buffer_store_b32(d, ss, soff_r, 0, 0);
+            } else {
+                for (int i = 0; i < min(4, nblk - cg * 4); ++i) __builtin_amdgcn_raw_buffer_store_b8((uint8_t)((unsigned)d >> (8 * i)), ss, soff_r, i, 0);
+            }
+            if (g4_r) __builtin_amdgcn_raw_buffer_store_b32(d, tile_rsrc(g4_r + ((int64_t)cg * kpitch_r + row0) * 4), mine ? row * 4 : kPast, 0, 0);
         };
-        for (int k = COOP ? wib : 0; k < nb; k += COOP ? NW : 1) {
-            unsigned cv[32];
-            uint4 rv[8];
-            fetch(k, cv, rv);
-            work(k, cv, rv);
+        if (SPLIT) {
+            if (wib < NW) {
+                for (int k = wib; k < nb; k += NW) {
+                    unsigned cv[32];
+                    fetch_col(k, cv);
+                    work_col(k, cv);
+                }
+            } else {
+                for (int k = wib - NW; k < nb; k += NW) {
+                    uint4 rv[8];
+                    fetch_row(k, rv);
+                    work_row(k, rv);
+                }
+            }
+        } else {
+            for (int k = COOP ? wib : 0; k < nb; k += COOP ? NW : 1) {
+                unsigned cv[32];
+                uint4 rv[8];
+                fetch_col(k, cv);
+                fetch_row(k, rv);
+                work_col(k, cv);
+                work_row(k, rv);
+            }
         }
         if (COOP) {
             __syncthreads();                                   // all tiles of the unit are staged
@@ -831,15 +898,15 @@ __global__ __launch_bounds__(NW ? NW * 64 : 256) void quant_both_kernel(const ui
                 store_col_scales(rb0 + 4 * g, last, lo, hi);
             }
         }
+        const rsrc_t sc_codes = tile_rsrc(codes_c + (int64_t)c0 * pitch_c + (int64_t)ru * ROWB);
+        const int chunk = lane % CPR, blk = FMT_C == kFP8 ? chunk >> 1 : chunk;
+        const int lane_off = (lane / CPR) * pitch_c + chunk * 16;
 #pragma unroll
         for (int it = COOP ? wib : 0; it < kColsPerWave * CPR / 64; it += COOP ? WPB : 1) {
-            const int idx = it * 64 + lane;
-            const int row = idx / CPR, chunk = idx % CPR;
-            const uint4 q = *reinterpret_cast<const uint4*>(reg + row * ROWB + ((chunk ^ ((row >> 1) & (CPR - 1))) * 16));
-            const int cc = cg * kColsPerWave + row;
-            const int blk = FMT_C == kFP8 ? chunk >> 1 : chunk;
-            if (cc < cols && blk < nb)
-                *reinterpret_cast<uint4*>(codes_c + (int64_t)cc * out_row_bytes + (int64_t)ru * ROWB + chunk * 16) = q;
+            const int row = it * (64 / CPR) + lane / CPR;
+            const v4u_t q = *reinterpret_cast<const v4u_t*>(reg + row * ROWB + ((chunk ^ ((row >> 1) & (CPR - 1))) * 16));
+            // (no scalar offset in a 16-byte store: see tile_rsrc)
+            __builtin_amdgcn_raw_buffer_store_b128(q, sc_codes, c0 + row < cols && blk < nb ? lane_off + it * (64 / CPR) * pitch_c : kPast, 0, 0);
         }
         if (COOP) __syncthreads();                             // the staging areas go to the next unit
     }
@@ -1211,18 +1278,14 @@ static int launch_qb_form(const QuantBothArgs& a, double* partials, hipStream_t 
     // of a tile: at most kStreamBlocks workgroups with equal shares of the units then.
     const int64_t most = STATS ? kStreamBlocks / 8 : (int64_t)1 << 24, run = (units + 7) / 8, share = (run + most - 1) / most;
     const int blocks = NW ? (int)(8 * ((run + share - 1) / share)) : balanced_blocks(units);
-    // FP4 codes of rows and FP8 codes of columns, more than 96 MB of source: three workgroups per compute unit (as LDS admits),
-    // four and more only add streams that the memory has to serve at once: [12288 x 4096] 47.0 -> 45.9 us, [24576 x 4096] 87.0
-    // -> 84.0, [28672 x 8192] 185.6 -> 180.6, [16384 x 4096] 63.1 -> 63.5.  With FP8 codes of rows it is no gain: 48.8 -> 48.5,
-    // 88.6 -> 88.4, 191 -> 192, and [16384 x 4096] 65.3 -> 67.4, [16384 x 8192] 117 -> 121.
-    const unsigned pad = NW && STATS == 0 && FMT_R == kFP4 && FMT_C == kFP8 && a.rows * a.cols > ((int64_t)48 << 20) ? 36000 : 0;
-    // Order of the units (see quant_both_kernel): runs below 8 M elements, where the tensor fits the L2s ([1504 x 2080] 12.0
-    // against 12.4 us dealt), and without statistics from 8192 rows on, if rows start on whole lines of 256 bytes ([8192 x 3072]
-    // FP8 29.0 (dealt) -> 27.9, [12288 x 4096] FP4 46.1 -> 44.3, [8192 x 28672] 204 -> 184).  Elsewhere the eight runs, far
-    // apart, meet in few memory channels: [8224 x 8224] FP4 83.7 (runs) -> 73.9, [8160 x 8160] 88.6 -> 68.5, [4096 x 11008] FP8
-    // 47.3 -> 44.9, with statistics [8192 x 4096] FP4 50.4 -> 48.8.
-    const bool runs = a.rows * a.cols < ((int64_t)8 << 20) || (STATS == 0 && a.rows >= 8192 && a.ld % 128 == 0);
-    hipLaunchKernelGGL((quant_both_kernel<FMT_R, FMT_C, RULE, STATS, NW, RBU>), dim3(blocks), dim3(NW ? NW * 64 : 256), pad, s,
+    // Order of the units (see quant_both_kernel): runs below 8 M elements, where the tensor fits the L2s ([1504 x 2080] FP4 6.1
+    // against 6.7 us dealt), and without statistics for rows of more than 12288 columns, if they start on whole lines of 256 bytes
+    // ([8192 x 16384] FP4 103.9 (dealt) -> 96.1, FP8 127.7 -> 123.1, [4096 x 28672] 91.8 -> 86.6 and 120 -> 110, [16384 x 14336] 182
+    // -> 170 and 223 -> 212; FP8 rows beside FP4 columns 98.7 -> 96.5 on [4096 x 28672], 109.0 -> 111.5 on [8192 x 16384]).
+    // Elsewhere the eight runs, far apart, meet in few memory channels: [8160 x 8160] FP4 81.5 (runs) -> 68.4, [16384 x 8192] 105.8
+    // -> 98.1, [8192 x 11008] 74.9 -> 70.4, FP8 88.4 -> 85.2, [8192 x 4096] 34.7 -> 33.3.
+    const bool runs = a.rows * a.cols < ((int64_t)8 << 20) || (STATS == 0 && a.cols > 12288 && a.ld % 128 == 0);
+    hipLaunchKernelGGL((quant_both_kernel<FMT_R, FMT_C, RULE, STATS, NW, RBU>), dim3(blocks), dim3(qb_threads(NW, STATS)), 0, s,
                        a.x, (int)a.rows, (int)a.cols, a.ld, a.codes_r, a.scales_r, a.g4_r, g4_pitch(a.rows),
                        a.codes_c, a.scales_c, a.g4_c, g4_pitch(a.cols), partials, runs);
     return blocks;
@@ -1241,12 +1304,13 @@ static int launch_qb(const QuantBothArgs& a, double* partials, QbForm form, hipS
 }
 
 // Which distribution serves a call (measured, us per call back to back in a graph):
-//   - four waves with a tile each wherever nothing else is said: the loads of a tile are a wave's whole chain, and 114-122
-//     registers leave room for four waves per SIMD.  Against four waves with two tiles each (FP4 codes of columns): [2048 x
-//     2048] 9.0 -> 6.4, [4096 x 4096] 15.5 -> 12.8, [8192 x 4096] 27.2 -> 21.9, [16384 x 4096] 48 -> 38.
-//   - eight waves with a tile each for FP4 codes of columns when the source exceeds the memory-side cache (256 MB): a unit
-//     then fills 128-byte lines of the column codes, where halves of them would reach memory one by one: [16384 x 11008]
-//     152 (4 x 4) -> 144, [8192 x 28672] 193 -> 177.
+//   - four waves with a tile each (for either direction, without statistics) wherever nothing else is said: the loads of a
+//     tile are a wave's whole chain.  Against four waves with two tiles each (FP4 codes of columns): [2048 x 2048] 9.0 -> 6.4,
+//     [4096 x 4096] 15.5 -> 12.8, [8192 x 4096] 27.2 -> 21.9.
+//   - without statistics eight and eight waves for FP4 codes of columns from 56 M elements on: a unit then fills 128-byte lines
+//     of the column codes, where halves of them would reach memory one by one: [8192 x 8192] 55.9 (4 x 4) -> 52.9, [16384 x
+//     11008] 143 -> 133, [8192 x 28672] 191 -> 166, [8160 x 8160] 81.5 -> 68.4; [12288 x 4096] 41.7 against 41.3, beside FP8 rows 43.6
+//     against 44.5, [4096 x 4096] 16.5 against 17.4.
 //   - the complete statistics fill the registers (two waves per SIMD in any form), and a workgroup's barrier and sums cost
 //     8-20 %: a wave per unit as soon as that gives every SIMD work, from 28 M elements (48 M with FP4 codes of columns: eight
 //     tiles per unit): [3072 x 8192] FP8 41.2 (wave) against 38.8 (4 x 4), [8192 x 4096] 41.9 against 47.2; FP4 between
@@ -1272,8 +1336,7 @@ static QbForm pick_qb_form(const QuantBothArgs& a, int stats)
         group = !strcmp(e, "workgroup");
     }
     const int64_t elems = a.rows * a.cols;
-    const bool large = elems > ((int64_t)128 << 20);
-    if (stats == 0) return large && a.fmt_c == kFP4 ? QbForm::k8x8 : QbForm::k4x4;
+    if (stats == 0) return a.fmt_c == kFP4 && elems > ((int64_t)56 << 20) ? QbForm::k8x8 : QbForm::k4x4;
     if (stats == 1) {
         const int64_t tiles = a.fmt_c == kFP8 ? 4 : 8, waves = ((a.cols + kColsPerWave - 1) / kColsPerWave) * ((a.rows / kBlock + tiles - 1) / tiles);
         const int64_t rounds = (waves + kTwoWavesPerSimd - 1) / kTwoWavesPerSimd;
@@ -1285,8 +1348,37 @@ static QbForm pick_qb_form(const QuantBothArgs& a, int stats)
     return a.fmt_c == kFP4 && elems > ((int64_t)12 << 20) ? QbForm::k4x8 : QbForm::k4x4;
 }
 
+// quant_both_kernel addresses a tile, and the column codes of a unit, with 32-bit offsets.
+static bool qb_offsets_fit(const QuantBothArgs& a)
+{
+    const int64_t most = (int64_t)1 << 31;
+    return a.ld * 2 * kBlock + 256 < most && a.cols * kBlock + 256 < most && a.rows * kColsPerWave + 256 < most;
+}
+
+// Rows longer than that (32 M elements of a source row, 16 M rows): one orientation at a time, and the complete record from
+// the statistics kernel.  Codes and scales are the same bytes.
+static hipError_t launch_quantize_each(const QuantBothArgs& a, hipStream_t s)
+{
+    for (int axis = 0; axis < 2; ++axis) {
+        QuantArgs q;
+        q.x = a.x; q.rows = a.rows; q.cols = a.cols; q.ld = a.ld;
+        q.fmt = axis ? a.fmt_c : a.fmt_r; q.axis = axis; q.rule = a.rule;
+        q.codes = axis ? a.codes_c : a.codes_r; q.scales = axis ? a.scales_c : a.scales_r; q.scales_g4 = axis ? a.g4_c : a.g4_r;
+        q.stats = a.both_formats ? nullptr : axis ? a.stats_c : a.stats_r;
+        q.workspace = a.workspace;
+        const hipError_t e = launch_quantize(q, s);
+        if (e != hipSuccess) return e;
+    }
+    if (!a.stats_r || !a.both_formats) return hipSuccess;
+    StatsArgs t;
+    t.x = a.x; t.rows = a.rows; t.cols = a.cols; t.ld = a.ld;
+    t.axis = 0; t.rule = a.rule; t.stats = a.stats_r; t.per_line = nullptr; t.workspace = a.workspace;
+    return launch_stats_both(t, a.stats_c, s);
+}
+
 hipError_t launch_quantize_both(const QuantBothArgs& a, hipStream_t s)
 {
+    if (a.rows > 0 && a.cols > 0 && !qb_offsets_fit(a)) return launch_quantize_each(a, s);
     double* partials = (double*)a.workspace;
     const bool st = a.stats_r != nullptr;
     // second stage: which field of each triple is "not computed" (NaN); none when both formats are wanted
