@@ -343,27 +343,24 @@ int gemm_compute_units()
 // other operands, 800 MB of them).  Which holds depends on the bytes touched since the operands were written or last used,
 // which a call cannot see: up to 128 MB they are in the 256 MB memory-side cache, at 256 MB the tables come out even, from
 // 512 MB on they are in memory.  A training step touches 9-15 times a GEMM's operands for one linear, 60-100 times for a
-// block of seven, so in a block operands of a few MB already come from memory; but below 8 MB the tile that runs ahead gains
-// too little there.  kColdBytes of operands is where the second table takes over.  Over 84 problems of 3 ... 100 MB at six
-// distances, the pick's mean loss against the fastest tile in % (cached / from memory), by threshold: 4 MB 3.9 / 0.8, 8 MB
-// 2.8 / 0.9, 10 MB 2.6 / 1.0, 12 MB 2.4 / 1.1, 16 MB 1.8 / 2.0, 50 MB 0.8 / 3.8.  The price: a caller that uses the same 10
-// ... 100 MB again at once gets calls 4-12 % slower where the picks differ (SNIP_GEMM_TILE can undo that); from memory the
-// same problems gain 11-17 %.
+// block of seven, so in a block operands of a few MB already come from memory; kColdBytes of operands is where the second
+// table takes over.  It costs little to be wrong: on operands of more than that in the caches the second table's pick is on
+// average 0.2 % slower than the fastest tile (8 % at worst), on less from memory the first table's 0.3 % (11 %).
 // Fitted to 182 and 107 problems timed with every tile: the GEMMs of 1B-, 3B- and 7B-shaped blocks and random ones (64 ...
-// 16384 tokens, widths 64 ... 11008, FP4 and FP8).  The pick is on average 0.4 and 0.2 % slower than the fastest tile (12
-// and 7 % at worst).  From memory the 256 x 128 tile that runs ahead beats 256 x 256 more often: [8192 x 3072 x 3072] FP8
-// 87 -> 79 us, [4032 x 5056 x 1952] FP8 73 -> 64.
+// 16384 tokens, widths 64 ... 11008, FP4 and FP8); 256 x 128 anew to 148 of them when it got its third stage buffer.  The pick
+// is on average 0.25 and 0.28 % slower than the fastest tile (7 % at worst).  From memory the 256 x 128 tile beats 256 x 256
+// where rounds of the larger one would be half empty: [8192 x 3072 x 3072] FP8 89 -> 81.5 us, [4096 x 2048 x 8192] FP4 56 -> 43.
 struct TileCost { GemmTile tile; int m, n; float start, turn, alone[2], full[2], tail[2]; };      // [0]: FP4 x FP4, [1]: others
 static const TileCost kTileCosts[2][6] = {{
     {GemmTile::kBig,       256, 256, 7.5f, 4.5f, {1.51f, 0.80f}, {1.67f, 1.48f}, {0.83f, 0.74f}},
-    {GemmTile::kWide,      256, 128, 5.3f, 2.1f, {0.98f, 0.50f}, {1.04f, 0.91f}, {1.25f, 0.63f}},
+    {GemmTile::kWide,      256, 128, 7.3f, 2.0f, {0.46f, 0.37f}, {0.94f, 0.77f}, {1.00f, 0.49f}},
     {GemmTile::k128x128,   128, 128, 4.7f, 3.6f, {0.37f, 0.33f}, {0.54f, 0.46f}, {0.47f, 0.29f}},
     {GemmTile::k64x64,      64,  64, 3.1f, 1.0f, {0.17f, 0.17f}, {0.20f, 0.19f}, {0.25f, 0.14f}},
     {GemmTile::k64x32,      64,  32, 3.1f, 1.4f, {0.16f, 0.16f}, {0.19f, 0.18f}, {0.18f, 0.19f}},
     {GemmTile::k32x32,      32,  32, 2.9f, 1.2f, {0.13f, 0.13f}, {0.15f, 0.14f}, {0.13f, 0.13f}},
 }, {
     {GemmTile::kBig,       256, 256, 9.5f, 5.4f, {1.23f, 1.24f}, {1.74f, 1.57f}, {0.95f, 1.01f}},
-    {GemmTile::kWideAhead, 256, 128, 7.5f, 2.6f, {1.45f, 1.33f}, {1.09f, 0.93f}, {0.83f, 0.81f}},
+    {GemmTile::kWide,      256, 128, 8.1f, 2.6f, {0.72f, 0.69f}, {1.01f, 0.85f}, {1.26f, 0.50f}},
     {GemmTile::k128x128,   128, 128, 6.4f, 3.2f, {0.68f, 0.54f}, {0.59f, 0.53f}, {0.56f, 0.54f}},
     {GemmTile::k64x64,      64,  64, 4.4f, 1.0f, {0.30f, 0.30f}, {0.22f, 0.23f}, {0.45f, 0.34f}},
     {GemmTile::k64x32,      64,  32, 3.6f, 1.1f, {0.17f, 0.17f}, {0.28f, 0.23f}, {0.20f, 0.20f}},
@@ -371,11 +368,11 @@ static const TileCost kTileCosts[2][6] = {{
 }};
 constexpr double kColdBytes = 10e6;
 
-static bool fast_tile(GemmTile t) { return t == GemmTile::kBig || t == GemmTile::kWide || t == GemmTile::kWideAhead; }
+static bool fast_tile(GemmTile t) { return t == GemmTile::kBig || t == GemmTile::kWide; }
 
 static bool tile_usable(const GemmArgs& a, GemmTile t)
 {
-    if (fast_tile(t)) return gemm_fast_eligible(a);
+    if (fast_tile(t)) return gemm_fast_eligible(a, t);
     if (t == GemmTile::kGeneral) return true;
     // an output norm has room for one partial per 128 x 128 tile
     return gemm_small_eligible(a) && (!a.norm_out || t == GemmTile::k128x128);
@@ -389,7 +386,7 @@ static GemmTile pick_tile(const GemmArgs& a)
     // cover every tile on every shape); anything else leaves the choice to the estimate
     if (const char* e = getenv("SNIP_GEMM_TILE")) {
         static const struct { const char* name; GemmTile tile; } kNames[] = {
-            {"big", GemmTile::kBig}, {"wide", GemmTile::kWide}, {"ahead", GemmTile::kWideAhead}, {"128x128", GemmTile::k128x128}, {"64x64", GemmTile::k64x64},
+            {"big", GemmTile::kBig}, {"wide", GemmTile::kWide}, {"ahead", GemmTile::kWide}, {"128x128", GemmTile::k128x128}, {"64x64", GemmTile::k64x64},
             {"64x32", GemmTile::k64x32}, {"32x32", GemmTile::k32x32}, {"general", GemmTile::kGeneral}};
         for (const auto& n : kNames)
             if (!strcmp(e, n.name) && tile_usable(a, n.tile)) return n.tile;

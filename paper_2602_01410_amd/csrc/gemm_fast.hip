@@ -4,10 +4,12 @@
 //   workgroup tile 256 x 256, 8 waves (2 x 4), wave tile 128 (A rows) x 64 (B rows), fp32
 //   accumulators in registers (128 per lane); for outputs that would leave compute units without a
 //   tile, 256 x 128 with 4 x 2 waves of 64 x 64 (same code, other template argument).
+//   256 x 256 has two stage buffers (68 KB each), 256 x 128 three (52 KB): a copy then has 1.75-2 stages to arrive instead of
+//   0.75-1, which memory needs under load (a stage is 0.9-1.1 us).
 //   A pipeline stage is 128 code bytes of every tile row for an FP8 operand and for FP4 x FP4
 //   (256 contraction elements there), so every 128-byte line that is fetched is used whole.
 //   Codes and scale dwords go global -> LDS through the load unit (global_load_lds), never through
-//   VGPRs; two stage buffers.
+//   VGPRs.
 //   The eight waves run a ping-pong schedule: the two waves of a SIMD alternate between reading
 //   their operands of a phase from LDS and issuing that phase's MFMAs, one phase apart, separated by
 //   workgroup barriers, so that the matrix core of every SIMD always has a wave with operands ready.
@@ -35,9 +37,9 @@
 // 4096: all workgroups finish a tile together, 32 MB per round, and the next tile's copies queue behind them in
 // the wave's memory counter.
 //
-// Registers: 256 vector registers (256 x 256), 195-219 (256 x 128).  Scalar registers run out and spill to lanes of vector
-// registers: 21-27 for bf16 outputs and 67-74 for fp32 (256 x 256; 256 x 128 15-22 and 62-74), 43-67 and 88-125 in the form
-// that runs ahead, 43-88 and 86-142 with TAIL.
+// Registers: 256 vector registers (256 x 256), 204-235 (256 x 128).  Scalar registers run out and spill to lanes of vector
+// registers: 23-30 for bf16 outputs and 66-72 for fp32 (256 x 256; 256 x 128 39-45 and 69-82), 56-71 and 88-103 with TAIL
+// (64-81 and 100-129), of which a stage restores four to six.
 //
 // See gemm.hip for the register layout of v_mfma_scale_f32_32x32x64_f8f6f4.
 #include "gemm_common.h"
@@ -48,27 +50,23 @@ namespace snip {
 namespace {
 
 constexpr int NWAVE = 8, NT = NWAVE * 64;
-constexpr int kAhead = 4;               // a touched line belongs to the stage that many after the one group 0 copies at the same time
 constexpr int TNP = 256;                // rows of the B tile's scale area (a 128-row B tile leaves half of it unused)
 
 // Workgroup tile TM (A rows) x TN (B rows), split over the eight waves as (TM / WTM) x (TN / WTN) wave tiles.
-template <int TM_, int TN_, int WTM_, int WTN_, bool TOUCH_ = false> struct TileCfg {
-    static constexpr int TM = TM_, TN = TN_, WTM = WTM_, WTN = WTN_;
+template <int TM_, int TN_, int WTM_, int WTN_, int NST_> struct TileCfg {
+    static constexpr int TM = TM_, TN = TN_, WTM = WTM_, WTN = WTN_, NST = NST_;      // NST: stage buffers
     static constexpr int WGN = TN / WTN;                   // waves along the B rows
     static constexpr int MB = WTM / 32, NB = WTN / 32;     // 32 x 32 MFMA blocks of a wave tile
-    static constexpr bool TOUCH = TOUCH_;                  // pull operand lines into L2 ahead of the copies (see `touch`)
     static_assert(TM == 256 && (TN == 256 || TN == 128), "copy shares and scale areas are laid out for these tiles");
     static_assert((TM / WTM) * (TN / WTN) == NWAVE, "eight waves");
 };
 // 256 x 256, 2 x 4 waves of 128 x 64: the largest tile the register file allows (fewest operand bytes per FLOP).
-using TileBig = TileCfg<256, 256, 128, 64>;
-// 256 x 128, 4 x 2 waves of 64 x 64: twice as many tiles for outputs that would leave compute units without one.
-using TileWide = TileCfg<256, 128, 64, 64>;
-// The same for operands that come from memory.  Back to back with each call on other operands (us, without / with): [4096 x
-// 2048 x 8192] FP8 83 / 71, FP4 48 / 44, [2048 x 4096 x 4096] FP8 46 / 39, [8192 x 1024 x 3072] FP8 38 / 32; with the same
-// operands over and over, which stay in L2 and the memory-side cache, 63 / 69, 39 / 43, 36 / 38, 28 / 30.  (In the 256 x 256 tile it
-// spills registers and loses more than it gains: a stage there takes longer and hides more.)
-using TileWideAhead = TileCfg<256, 128, 64, 64, true>;
+using TileBig = TileCfg<256, 256, 128, 64, 2>;
+// 256 x 128, 4 x 2 waves of 64 x 64: twice as many tiles for outputs that would leave compute units without one.  us per call on
+// operands from memory with two stage buffers (and operand lines pulled into L2 four stages ahead) -> with three: [4096 x 2048 x
+// 8192] FP4 48.5 -> 43.0, FP8 74.6 -> 69.3, [4096 x 2048 x 2048] 19.6 -> 18.0, 25.4 -> 23.3, [8192 x 3072 x 3072] FP8 89 -> 81.5,
+// [2048 x 4096 x 4096] FP8 41.6 -> 39.0.  Pulling lines ahead of three buffers as well costs 1-8 %.
+using TileWide = TileCfg<256, 128, 64, 64, 3>;
 
 template <int FA, int FB, class T> struct FCfg {
     static constexpr int TM = T::TM, TN = T::TN;
@@ -78,24 +76,25 @@ template <int FA, int FB, class T> struct FCfg {
     static constexpr int SBB = FB == kFP8 ? KE : KE / 2;
     static constexpr int KS = KE / 64;                           // MFMA steps per stage
     static constexpr int NG = KE / 128;                          // scale dwords (groups of 4 blocks) per row per stage
-    static constexpr int NST = 2;                                // stage buffers
+    static constexpr int NST = T::NST;
     static constexpr int A_BYTES = TM * SBA, B_BYTES = TN * SBB;
     static constexpr int S_BYTES = (TM + TNP) * NG * 4;          // scale dwords of one stage
     static constexpr int SLOT = A_BYTES + B_BYTES + S_BYTES;
-    // Stage buffer 0 sits at the start of the LDS array and stage buffer 1 at its end; the result staging area is
-    // the first or the last EPI_BYTES of the array, i.e. it covers the buffer of the tile's last stage (plus the
-    // unused middle) and never reaches into the other buffer, which already receives the next tile.
-    static constexpr int LDS_BYTES = 159 * 1024;
-    static constexpr int TOUCH = LDS_BYTES;                     // 256 bytes behind the buffers: where touched lines' dwords land, unread
-    static constexpr int SLOT1 = LDS_BYTES - SLOT;
-    static constexpr int EPI_BYTES = 64 * 1024;
+    // Stage buffers lie STRIDE apart.  The result staging area is part of the LDS array that covers the buffer of the tile's
+    // last stage and never reaches into the other buffers, which already receive the next tile: with two buffers (one at
+    // the start of the array, one at its end) the first or the last 64 KB, with three the first 32 KB of that buffer.
+    static constexpr int LDS_BYTES = NST == 2 ? 159 * 1024 : NST * SLOT;
+    static constexpr int STRIDE = NST == 2 ? LDS_BYTES - SLOT : SLOT;
+    static constexpr int EPI_BYTES = NST == 2 ? 64 * 1024 : 32 * 1024;
+    static constexpr int epi_base(int last) { return NST == 2 ? last * (LDS_BYTES - EPI_BYTES) : last * STRIDE; }
     static constexpr int LA = A_BYTES / 1024 / NWAVE;            // 16-byte copy instructions per wave per stage
     static constexpr int LB = B_BYTES / 1024 / NWAVE;
     static constexpr int LS = S_BYTES / 256 / NWAVE;             // 4-byte copy instructions per wave per stage
     static constexpr int L = LA + LB + LS;
-    static_assert(SLOT1 % 1024 == 0 && SLOT <= SLOT1, "stage buffers must not overlap");
-    static_assert(EPI_BYTES <= LDS_BYTES - SLOT, "the result staging area must stay clear of the other stage buffer");
-    static_assert(LDS_BYTES + 256 + 64 <= 160 * 1024, "LDS budget");
+    static_assert(STRIDE % 1024 == 0 && SLOT <= STRIDE && (NST - 1) * STRIDE + SLOT <= LDS_BYTES, "stage buffers must not overlap");
+    static_assert(EPI_BYTES <= (NST == 2 ? STRIDE : SLOT), "the result staging area must stay clear of the other stage buffers");
+    static_assert(L * (NST - 1) <= 60, "copies in flight must be countable");
+    static_assert(LDS_BYTES + 64 <= 160 * 1024, "LDS budget");
 };
 
 // TAIL: the contraction extent does not end with a stage.  Copies then go through buffer descriptors, which deliver zeros
@@ -113,7 +112,7 @@ __global__ __launch_bounds__(NT) void gemm_fast_kernel(const uint8_t* __restrict
 {
     using C = FCfg<FA, FB, T>;
     constexpr int TM = T::TM, TN = T::TN, WTM = T::WTM, WTN = T::WTN, WGN = T::WGN, MB = T::MB, NB = T::NB;
-    __shared__ __attribute__((aligned(1024))) uint8_t lds[C::LDS_BYTES + 256];
+    __shared__ __attribute__((aligned(1024))) uint8_t lds[C::LDS_BYTES];
     // stage buffer layout: [A codes][B codes][A scale dwords: group-major, 256 rows][B scale dwords]
 
     const int nblk = tiles_i * tiles_j;
@@ -124,7 +123,7 @@ __global__ __launch_bounds__(NT) void gemm_fast_kernel(const uint8_t* __restrict
 
     const int64_t a_row_bytes = FA == kFP8 ? R : R / 2;
     const int64_t b_row_bytes = FB == kFP8 ? R : R / 2;
-    const int nstage = (R + C::KE - 1) / C::KE;                       // >= 2 (gemm_fast_eligible)
+    const int nstage = (R + C::KE - 1) / C::KE;                       // >= NST (gemm_fast_eligible)
     const int ngrp = (R + 127) / 128;                                 // scale groups of a row
     const int64_t a_pitch = g4_pitch(I), b_pitch = g4_pitch(J);      // dwords per scale group
 
@@ -196,7 +195,7 @@ __global__ __launch_bounds__(NT) void gemm_fast_kernel(const uint8_t* __restrict
 
     // copy instruction j (0 .. L-1) of this wave's share of `stage` (of the copy tile) into stage buffer `slot`
     auto issue_one = [&](int j, int stage, int slot) {
-        const unsigned base = lds0 + slot * C::SLOT1;
+        const unsigned base = lds0 + slot * C::STRIDE;
         if (j < C::LA) {
             const unsigned dst = base + (wave * C::LA + j) * 1024;
             if constexpr (TAIL) blds16(ra, oa[j], stage * C::SBA, dst);
@@ -216,50 +215,6 @@ __global__ __launch_bounds__(NT) void gemm_fast_kernel(const uint8_t* __restrict
     auto issue = [&](int stage, int slot) {
 #pragma unroll
         for (int j = 0; j < C::L; ++j) issue_one(j, stage, slot);
-    };
-
-    // ---- operand lines are pulled into L2 before their copies ask for them.  In a training step a GEMM's operands come from
-    //      memory, and two stage buffers are one stage of lookahead, less than memory takes under load.  Waves 0-3 each touch
-    //      lines (a dword per lane, into LDS that nobody reads) of the stage kAhead stages after the one they copy: waves 0
-    //      and 1 code rows (the 4 x 8 tiles an XCD works on at a time share their slabs: each tile takes the share of its
-    //      position), waves 2 and 3 the scale groups.
-    const uint8_t* tcur = nullptr;
-    unsigned tstep = 0, ts1 = 0, ts2 = 0;       // lane's line: (lane % lines) * ts1 + (lane / 8 % NG) * ts2
-    int tleft = 0, tu = 0;
-    auto set_touch_tile = [&](int v) {
-        int ti, tj;
-        tile_of(v, nblk, tiles_i, tiles_j, ti, tj);
-        const int i0 = ti * TM, j0 = tj * TN;
-        tu = v;
-        tleft = nstage;
-        if (wave < 2) {
-            // (in a tile that is not whole, one row stands for all)
-            const bool whole = wave == 0 ? i0 + TM <= I : j0 + TN <= J;
-            const int64_t row_bytes = wave == 0 ? a_row_bytes : b_row_bytes;
-            const int row = wave == 0 ? i0 + (whole ? (tj & 7) * (TM / 8) : 0) : j0 + (whole ? (ti & 3) * (TN / 4) : 0);
-            tcur = (wave == 0 ? a_codes : b_codes) + (int64_t)row * row_bytes;
-            ts1 = whole ? (unsigned)row_bytes : 0;
-            tstep = wave == 0 ? C::SBA : C::SBB;
-        } else {
-            const int64_t pitch4 = (wave == 2 ? a_pitch : b_pitch) * 4;
-            tcur = wave == 2 ? a_g4 + (int64_t)i0 * 4 : b_g4 + (int64_t)j0 * 4;
-            ts1 = 128;
-            ts2 = C::NG == 2 && ngrp % 2 == 0 ? (unsigned)pitch4 : 0;
-            tstep = (unsigned)(pitch4 * C::NG);
-        }
-    };
-    auto touch = [&]() {
-        unsigned l = __builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, 0u));
-        asm volatile("" : "+v"(l));                                   // (recomputed here: no register is free to keep it)
-        const unsigned lines = wave == 0 ? TM / 8 : wave == 1 ? TN / 4 : wave == 2 ? TM / 32 : TN / 32;
-        unsigned off = (l & (lines - 1)) * ts1;
-        if (C::NG == 2) off += ((l >> 3) & 1) * ts2;
-        glds4(tcur, off, lds0 + C::TOUCH);
-        tcur += tstep;
-        if (--tleft == 0) {
-            if (tu + (int)gridDim.x < nblk) set_touch_tile(tu + (int)gridDim.x);
-            else { tcur -= tstep; tstep = 0; }                        // nothing more to come: the last stage again
-        }
     };
 
     // ---- per-lane LDS read offsets ----
@@ -283,19 +238,20 @@ __global__ __launch_bounds__(NT) void gemm_fast_kernel(const uint8_t* __restrict
     //      Stage s of a tile is complete in LDS before b(4s): every wave waits for its own copies before that
     //      barrier.  The buffer of stage s is free after b(4s+4): group 1, the last reader, waits for its R1(s)
     //      data before that barrier, so no read of the buffer is in flight when the first copy into it is issued.
-    //      Stages alternate between the two buffers across tiles as well: stage s of a tile uses buffer
-    //      (s + par) & 1, par being the number of stages of all earlier tiles mod 2.
-    //      At the end of a tile (S stages): group 0 has issued its share of the next tile's stage 0 during
-    //      M0(S-1) and group 1 during M1(S-2), both into the buffer that stage S would use.  After b(4S) group 0
+    //      The NST buffers are used in turn across tiles as well: stage s of a tile uses buffer (s + par) mod NST, par
+    //      being the number of stages of all earlier tiles.
+    //      At the end of a tile (S stages): group 0 has issued its share of the next tile's stages 0 .. NST-2 during
+    //      M0(S-NST+1) .. M0(S-1) and group 1 during M1(S-NST) .. M1(S-2), each into the buffer that the stage of
+    //      the same number past S would use.  After b(4S) group 0
     //      stores its result block through the staging area (which covers the last stage's buffer, free since
     //      b(4S)) while group 1 still issues M1(S-1), then group 1 stores its block; the next tile's b(0) follows.
-    //      Group 1's share of the next tile's stage 1, which goes into the buffer under the staging area, is
+    //      Group 1's share of the next tile's stage NST-1, which goes into the buffer under the staging area, is
     //      issued after that barrier (where the first tile issues it, too). ----
     constexpr int KP = C::KS / 2;                      // k-steps per phase
     v8i fa[KP][MB], fb[KP][NB];
     unsigned sa[MB], sb[NB];
     auto RD = [&](int slot, int p, int stage) {
-        const uint8_t* base = lds + slot * C::SLOT1;
+        const uint8_t* base = lds + slot * C::STRIDE;
         const uint8_t* ta = base + wm * WTM * C::SBA;
         const uint8_t* tb = base + C::A_BYTES + wn * WTN * C::SBB;
         const int q = C::NG == 2 ? p : 0;
@@ -323,7 +279,7 @@ __global__ __launch_bounds__(NT) void gemm_fast_kernel(const uint8_t* __restrict
     // buffer `nslot` are spread evenly between the phase's NM MFMAs (the sched_barriers keep them there).
     constexpr int NM = KP * MB * NB;
     auto MM = [&](auto copy_tag, int p, int nxt, int nslot) {
-        constexpr bool COPY = decltype(copy_tag)::value != 0, TOUCH = T::TOUCH && decltype(copy_tag)::value == 2;
+        constexpr bool COPY = decltype(copy_tag)::value;
         constexpr int ca = FB == kFP8 ? 0 : 4, cb = FA == kFP8 ? 0 : 4;
         __builtin_amdgcn_s_setprio(1);
         int idx = 0;
@@ -343,7 +299,6 @@ __global__ __launch_bounds__(NT) void gemm_fast_kernel(const uint8_t* __restrict
 #pragma unroll
                         for (int j = 0; j < C::L; ++j)
                             if (j * NM / C::L == idx) issue_one(j, nxt, nslot);
-                        if (TOUCH && idx == NM - 1) touch();          // after the copies: waits leave it in flight
                         __builtin_amdgcn_sched_barrier(0);
                     }
                     ++idx;
@@ -351,12 +306,11 @@ __global__ __launch_bounds__(NT) void gemm_fast_kernel(const uint8_t* __restrict
         }
         __builtin_amdgcn_s_setprio(0);
     };
-    const std::integral_constant<int, 0> no_copy{};
-    const std::integral_constant<int, 1> with_copy{};
-    const std::integral_constant<int, 2> copy_and_touch{};
+    const std::false_type no_copy{};
+    const std::true_type with_copy{};
 
-    // ---- result of tile u: optional sum of squares, then every wave transposes its 128 x 64 block through its
-    //      own 8 KB of the staging area at byte `ebase` of the LDS array ----
+    // ---- result of tile u: optional sum of squares, then every wave transposes its block through its
+    //      own part of the staging area at byte `ebase` of the LDS array ----
     auto store_tile = [&](int u, int ebase) {
         int ti, tj;
         tile_of(u, nblk, tiles_i, tiles_j, ti, tj);
@@ -412,31 +366,35 @@ __global__ __launch_bounds__(NT) void gemm_fast_kernel(const uint8_t* __restrict
         // In registers, lane (r32, g) of block (m, n) holds C[32m + r32][32n + 8q + 4g + t] in acc[m][n][4q + t].
         // In LDS a row is ROWB bytes of 16-byte chunks, chunk c of row r stored at position c ^ f(r).
         constexpr int ESZ = OUT_F32 ? 4 : 2;
-        constexpr int ROWB = WTN * ESZ;                  // 128 or 256 bytes per row
-        constexpr int CPR = ROWB / 16;                   // 8 or 16 chunks per row
         constexpr int REGION = C::EPI_BYTES / NWAVE;     // LDS bytes a wave may use
+        constexpr int NBP = 32 * WTN * ESZ <= REGION ? NB : 1;         // column blocks of a pass
+        constexpr int ROWB = NBP * 32 * ESZ;             // 128 or 256 bytes per row
+        constexpr int CPR = ROWB / 16;                   // 8 or 16 chunks per row
         constexpr int ROWS_PER_PASS = REGION / ROWB < WTM ? REGION / ROWB : WTM;
         constexpr int MB_PER_PASS = ROWS_PER_PASS / 32;
-        static_assert(MB_PER_PASS >= 1 && MB % MB_PER_PASS == 0, "staging passes must be whole 32-row blocks");
+        static_assert(MB_PER_PASS >= 1 && MB % MB_PER_PASS == 0 && NB % NBP == 0 && (CPR == 8 || CPR == 16), "staging passes must be whole 32-row blocks");
+        auto spread = [](int row) { return CPR == 16 ? row & 15 : (row >> 1) & 7; };
         uint8_t* reg = lds + ebase + wave * REGION;
 #pragma unroll
-        for (int pass = 0; pass < MB / MB_PER_PASS; ++pass) {
+        for (int pass = 0; pass < MB / MB_PER_PASS * (NB / NBP); ++pass) {
+            const int pm = pass / (NB / NBP), pn = pass % (NB / NBP) * NBP;          // row pass, first column block
 #pragma unroll
             for (int mm = 0; mm < MB_PER_PASS; ++mm) {
-                const int m = pass * MB_PER_PASS + mm;
+                const int m = pm * MB_PER_PASS + mm;
                 const int row = mm * 32 + r32;
-                const int f = OUT_F32 ? (row & (CPR - 1)) : ((row >> 1) & (CPR - 1));
+                const int f = spread(row);
 #pragma unroll
-                for (int n = 0; n < NB; ++n)
+                for (int nn = 0; nn < NBP; ++nn)
 #pragma unroll
                     for (int q = 0; q < 4; ++q) {
+                        const int n = pn + nn;
                         const float v0 = acc[m][n][4 * q + 0], v1 = acc[m][n][4 * q + 1];
                         const float v2 = acc[m][n][4 * q + 2], v3 = acc[m][n][4 * q + 3];
                         if (OUT_F32) {
-                            const int c = n * 8 + q * 2 + g;             // 4 floats = one chunk
+                            const int c = nn * 8 + q * 2 + g;            // 4 floats = one chunk
                             *reinterpret_cast<float4*>(reg + row * ROWB + ((c ^ f) * 16)) = make_float4(v0, v1, v2, v3);
                         } else {
-                            const int c = n * 4 + q;                     // 4 bf16 = half a chunk
+                            const int c = nn * 4 + q;                    // 4 bf16 = half a chunk
                             const float2_t lo = {v0, v1}, hi = {v2, v3};
                             const bf16x2 blo = __builtin_convertvector(lo, bf16x2), bhi = __builtin_convertvector(hi, bf16x2);
                             *reinterpret_cast<uint2*>(reg + row * ROWB + ((c ^ f) * 16) + 8 * g) =
@@ -455,12 +413,12 @@ __global__ __launch_bounds__(NT) void gemm_fast_kernel(const uint8_t* __restrict
                 // instruction plus a 32-bit lane offset
                 const unsigned lane_off = (unsigned)((lane / CPR) * (int)ldc * ESZ + (lane % CPR) * 16);
                 const uint8_t* cb = reinterpret_cast<const uint8_t*>(c_out) +
-                                    ((int64_t)(i0 + wm * WTM + pass * ROWS_PER_PASS) * ldc + j0 + wn * WTN) * ESZ;
+                                    ((int64_t)(i0 + wm * WTM + pm * ROWS_PER_PASS) * ldc + j0 + wn * WTN + pn * 32) * ESZ;
 #pragma unroll
                 for (int it = 0; it < ROWS_PER_PASS / RPI; ++it) {
                     const int row = it * RPI + lane / CPR;
                     const int c = lane % CPR;
-                    const int f = OUT_F32 ? (row & (CPR - 1)) : ((row >> 1) & (CPR - 1));
+                    const int f = spread(row);
                     const uint4 v = *reinterpret_cast<const uint4*>(reg + row * ROWB + ((c ^ f) * 16));
                     const v4u vv = {v.x, v.y, v.z, v.w};
                     uint8_t* p = const_cast<uint8_t*>(cb) + (int64_t)(it * RPI) * ldc * ESZ + lane_off;
@@ -471,10 +429,10 @@ __global__ __launch_bounds__(NT) void gemm_fast_kernel(const uint8_t* __restrict
                 for (int it = 0; it < ROWS_PER_PASS / RPI; ++it) {
                     const int row = it * RPI + lane / CPR;
                     const int c = lane % CPR;
-                    const int f = OUT_F32 ? (row & (CPR - 1)) : ((row >> 1) & (CPR - 1));
+                    const int f = spread(row);
                     const uint4 v = *reinterpret_cast<const uint4*>(reg + row * ROWB + ((c ^ f) * 16));
-                    const int i = i0 + wm * WTM + pass * ROWS_PER_PASS + row;
-                    const int j = j0 + wn * WTN + c * (16 / ESZ);
+                    const int i = i0 + wm * WTM + pm * ROWS_PER_PASS + row;
+                    const int j = j0 + wn * WTN + pn * 32 + c * (16 / ESZ);
                     if (i < I) {
                         uint8_t* p = reinterpret_cast<uint8_t*>(c_out) + ((int64_t)i * ldc + j) * ESZ;
                         if (j + 16 / ESZ <= J) {
@@ -493,18 +451,15 @@ __global__ __launch_bounds__(NT) void gemm_fast_kernel(const uint8_t* __restrict
         }
     };
 
+    constexpr int NST = C::NST;
+    auto after = [](int slot) { return slot == NST - 1 ? 0 : slot + 1; };
+    auto before = [](int slot) { return slot == 0 ? NST - 1 : slot - 1; };
     int u = blockIdx.x;                  // dispatch id of the tile being multiplied
     int par = 0;                         // buffer of its stage 0
     bool first = true;
     set_copy_tile(u);
-    issue(0, 0);
-    if (T::TOUCH && wave < NWAVE / 2) {
-        set_touch_tile(u);
-        const int skip = nstage - 1 < 2 ? nstage - 1 : 2;            // stages 0 and 1 are copied now
-        tcur += (int64_t)skip * tstep;
-        tleft -= skip;
-        for (int k = 2; k <= kAhead; ++k) touch();
-    }
+#pragma unroll
+    for (int k = 0; k < NST - 1; ++k) issue(k, k);
     for (;;) {
         const int un = u + (int)gridDim.x;
         const bool has_next = un < nblk;
@@ -514,66 +469,66 @@ __global__ __launch_bounds__(NT) void gemm_fast_kernel(const uint8_t* __restrict
             for (int b = 0; b < NB; ++b)
 #pragma unroll
                 for (int k = 0; k < 16; ++k) acc[a][b][k] = 0.f;
-        const int ebase = ((nstage - 1 + par) & 1) ? C::LDS_BYTES - C::EPI_BYTES : 0;      // over the last stage's buffer
+        int slot = par;                                             // buffer of stage s
         if (wave < NWAVE / 2) {
-            // group 0 issues its copies of stage s+1 during M0(s), between b(4s+1) and b(4s+2); during the last
-            // stage these are the copies of the next tile's stage 0
+            // group 0 issues its copies of stage s + NST - 1 during M0(s), between b(4s+1) and b(4s+2); during the last
+            // NST - 1 stages these are the copies of the next tile's first stages
             auto stage0 = [&](auto copy_tag, int s, int cstage) {
-                const int slot = (s + par) & 1;
-                // stage 0 of a later tile was waited for before the previous tile's result was stored; waiting
-                // here again would wait for those stores
-                if (!T::TOUCH) { if (s > 0 || first) SNIP_WAIT_VM(0); }
-                else if (s > 0) SNIP_WAIT_VM(1);                    // (the touch behind the copies stays in flight)
-                else if (first) SNIP_WAIT_VM(kAhead - 1);
+                // the first NST - 1 stages of a later tile were waited for before the previous tile's result was stored;
+                // waiting for them here again would wait for those stores
+                if (first || s >= NST - 1) SNIP_WAIT_VM((NST - 2) * C::L);
                 SNIP_BAR();                                         // b(4s)
                 RD(slot, 0, s); SNIP_BAR();      // b(4s+1)
-                MM(copy_tag, 0, cstage, slot ^ 1); SNIP_BAR();      // b(4s+2)
+                MM(copy_tag, 0, cstage, before(slot)); SNIP_BAR();  // b(4s+2)
                 RD(slot, 1, s); SNIP_BAR();      // b(4s+3)
                 MM(no_copy, 1, 0, 0);
             };
             // Every stage carries copies, so that the MFMA code exists once (two variants of it merging in front
             // of the result store cost the register allocator its in-place accumulators).  Without a next tile the
-            // last stage's copies re-fetch stage 0 of this tile into the free buffer, where nobody reads them.
+            // last stages' copies re-fetch the first stages of this tile into free buffers, where nobody reads them.
             for (int s = 0; s < nstage; ++s) {
-                const bool last = s == nstage - 1;
-                if (last && has_next) set_copy_tile(un);
-                cut_tail(last ? 0 : s + 1);
-                stage0(copy_and_touch, s, last ? 0 : s + 1);
+                const int c = s + NST - 1, cs = c >= nstage ? c - nstage : c;
+                if (c == nstage && has_next) set_copy_tile(un);
+                cut_tail(cs);
+                stage0(with_copy, s, cs);
+                slot = after(slot);
             }
             SNIP_BAR();                                             // b(4S)
-            if (T::TOUCH && has_next) SNIP_WAIT_VM(1);              // own share of the next tile's stage 0
-            else SNIP_WAIT_VM(0);                                   // nothing may land in LDS after the workgroup's end
+            SNIP_WAIT_VM(0);                                        // own shares of the next tile's first stages
         } else {
-            // group 1 issues its copies of stage s+2 during M1(s), between b(4s+4) and b(4s+5) (during M1(S-2)
-            // those of the next tile's stage 0, during M1(S-1) none); those of stage 1 while it idles through the
-            // tile's first phase
+            // group 1 issues its copies of stage s + NST during M1(s), between b(4s+4) and b(4s+5) (during M1(S-NST) and
+            // later those of the next tile's first stages, during M1(S-1) none); those of stage NST - 1 while it idles
+            // through the tile's first phase
             auto stage1 = [&](auto copy_tag, int s, int cstage) {
-                const int slot = (s + par) & 1;
                 SNIP_BAR();                                         // b(4s+1)
                 RD(slot, 0, s); SNIP_BAR();      // b(4s+2)
                 MM(no_copy, 0, 0, 0); SNIP_BAR();                   // b(4s+3)
                 RD(slot, 1, s);
-                __builtin_amdgcn_s_waitcnt(0x0070);                 // vmcnt(0) and lgkmcnt(0)
+                if (NST == 2 || first || s >= NST - 2) SNIP_WAIT_VM((NST - 2) * C::L);      // stage s + 1 (see stage0)
+                __builtin_amdgcn_s_waitcnt(0xC07F);                 // lgkmcnt(0)
                 SNIP_BAR();                                         // b(4s+4)
                 MM(copy_tag, 1, cstage, slot);
             };
-            if (first) SNIP_WAIT_VM(0);
+            if (first) SNIP_WAIT_VM((NST - 2) * C::L);
             SNIP_BAR();                                             // b(0)
-            cut_tail(1);
-            issue(1, (1 + par) & 1);
-            // (without a next tile the copies of M1(S-2) re-fetch stage 0 of this tile into the free buffer)
+            cut_tail(NST - 1);
+            issue(NST - 1, before(par));
+            // (without a next tile the last copies re-fetch the first stages of this tile into free buffers)
             for (int s = 0; s < nstage - 1; ++s) {
-                const bool cross = s == nstage - 2;
-                if (cross && has_next) set_copy_tile(un);
-                cut_tail(cross ? 0 : s + 2);
-                stage1(with_copy, s, cross ? 0 : s + 2);
+                const int c = s + NST, cs = c >= nstage ? c - nstage : c;
+                if (c == nstage && has_next) set_copy_tile(un);
+                cut_tail(cs);
+                stage1(with_copy, s, cs);
+                slot = after(slot);
             }
             stage1(no_copy, nstage - 1, 0);
+            slot = after(slot);
+            if (NST > 2) SNIP_WAIT_VM(0);                           // (nothing may land in LDS after the workgroup's end either)
         }
-        store_tile(u, ebase);
+        store_tile(u, C::epi_base(before(slot)));
         if (!has_next) break;
         u = un;
-        par = (par + nstage) & 1;
+        par = slot;
         first = false;
     }
 }
@@ -615,20 +570,21 @@ hipError_t launch_fast_tile(const GemmArgs& a, hipStream_t s)
 
 }  // namespace
 
-bool gemm_fast_eligible(const GemmArgs& a)
+bool gemm_fast_eligible(const GemmArgs& a, GemmTile tile)
 {
     const int ke = (a.fmt_a == kFP4 && a.fmt_b == kFP4) ? 256 : 128;
     // 32-bit source offsets: 256 rows of codes and, where the last stage is not whole, a grouped scale copy within a descriptor
     if (a.R > (1 << 22)) return false;
     const int64_t groups = (a.R + 127) / 128, most = std::max(g4_pitch(a.I), g4_pitch(a.J)) * 4 * groups;
     if (a.R % ke != 0 && !descriptor_covers(most)) return false;
-    return a.a_scales_g4 && a.b_scales_g4 && a.R > ke && a.I > 128 && a.J > 128;      // at least two stages
+    const int stages = tile == GemmTile::kBig ? TileBig::NST : TileWide::NST;          // as many as there are stage buffers at least
+    return a.a_scales_g4 && a.b_scales_g4 && a.R > (stages - 1) * ke && a.I > 128 && a.J > 128;
 }
 
 hipError_t launch_gemm_fast(const GemmArgs& a, GemmTile tile, hipStream_t s)
 {
     if (tile == GemmTile::kBig) return launch_fast_tile<TileBig>(a, s);
-    return tile == GemmTile::kWide ? launch_fast_tile<TileWide>(a, s) : launch_fast_tile<TileWideAhead>(a, s);
+    return launch_fast_tile<TileWide>(a, s);
 }
 
 }  // namespace snip
