@@ -78,3 +78,21 @@ def test_weight_divergence_chain():
     got = snip.snip_weight_divergence(3e-4, B1, B2, 1000, s, err_g_sq, lin.N, lin.K)
     want = oracle.weight_divergence(3e-4, B1, B2, 1000, oracle.adamw_sensitivity_sq(m, v, g, B1, B2, EPS), err_g_sq, lin.N, lin.K)
     assert got == pytest.approx(want, rel=TOL)
+
+
+@pytest.mark.parametrize("low,high,eps", [(1e-44, 1e-39, 1e-8), (1e-30, 1e-27, 1e-8), (2e-29, 1e-26, 1e-8), (2e-29, 1e-26, 1e-20), (2e-29, 1e-26, 0.0),
+                                          (1e-12, 1e-2, 1e-8), (1e-12, 1e-2, 1e-33), (1e26, 5e28, 1e-8), (1e28, 1e32, 1e-8)])
+def test_adamw_ranges_of_v(low, high, eps):
+    """v on both sides of the limits of the approximated root (2^-96 = 1.3e-29 and 2^96 = 7.9e28), zeros among it where eps allows,
+    eps below the limit and zero.  (Below 1e-29 without eps the exact divisor root * d^2 leaves fp32's range: not a case.)"""
+    snip = require_gpu()
+    rng = np.random.default_rng(112)
+    n = 4096 + 3
+    v = np.exp(rng.uniform(np.log(low), np.log(high), n)).astype(np.float32)
+    g = (np.sqrt(v.astype(np.float64)) * rng.standard_normal(n)).astype(np.float32)
+    m = (0.3 * np.sqrt(v.astype(np.float64)) * rng.standard_normal(n)).astype(np.float32)
+    if eps == 1e-8:
+        dead = rng.random(n) < 0.01
+        v[dead] = 0; m[dead] = 0; g[dead] = 0
+    eps = float(np.float32(eps))
+    assert run(snip, m, v, torch.from_numpy(g), eps=eps) == pytest.approx(oracle.adamw_sensitivity_sq(m, v, g, B1, B2, eps), rel=TOL)
