@@ -289,11 +289,13 @@ hipError_t launch_t(const GemmArgs& a, hipStream_t s)
 
 }  // namespace
 
-// Sum of n workgroup partials in double, in a fixed order: one workgroup, thread t adds t, t + 512, ..., then lanes, then waves.
+// Sum of n workgroup partials in double, in a fixed order: thread t adds t, t + 512, ..., then lanes, then waves.  Workgroup b
+// sums the partials from b * stride on to out[b].
 constexpr int kNormThreads = 512;
-__global__ __launch_bounds__(kNormThreads) void reduce_norm_kernel(const float* __restrict__ partials, int64_t n,
+__global__ __launch_bounds__(kNormThreads) void reduce_norm_kernel(const float* __restrict__ partials, int64_t n, int64_t stride,
                                                                    double* __restrict__ out)
 {
+    partials += (int64_t)blockIdx.x * stride;
     __shared__ double sh[kNormThreads / 64];
     double a = 0.0;
 #pragma unroll 8
@@ -306,13 +308,13 @@ __global__ __launch_bounds__(kNormThreads) void reduce_norm_kernel(const float* 
         double t = 0.0;
 #pragma unroll
         for (int w = 0; w < kNormThreads / 64; ++w) t += sh[w];
-        out[0] = t;
+        out[blockIdx.x] = t;
     }
 }
 
-hipError_t launch_sum_partials(const float* partials, int64_t n, double* out, hipStream_t s)
+hipError_t launch_sum_partials(const float* partials, int64_t n, double* out, hipStream_t s, int sums, int64_t stride)
 {
-    hipLaunchKernelGGL(reduce_norm_kernel, dim3(1), dim3(kNormThreads), 0, s, partials, n, out);
+    hipLaunchKernelGGL(reduce_norm_kernel, dim3(sums), dim3(kNormThreads), 0, s, partials, n, stride, out);
     return hipGetLastError();
 }
 

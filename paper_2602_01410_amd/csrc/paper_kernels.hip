@@ -10,8 +10,8 @@
 // +-448 first: the product can exceed 448 by one rounding).
 //
 // Kernels: quantize along rows (tile maxima by a 16-lane DPP reduction inside the pass), quantize down
-// columns (a lane owns two columns; the four waves of a workgroup exchange their maxima), a block-maximum pre-pass for the 128x128 groups, and the matching statistics
-// kernels (both formats from one read).  All are streaming kernels bound by HBM bandwidth or VALU rate.
+// columns (a lane owns two columns; the four waves of a workgroup exchange their maxima), 128x128 blocks along rows (a workgroup
+// owns a block), and the matching statistics kernels (both formats from one read).  All are streaming kernels bound by HBM bandwidth or VALU rate.
 #include "snip_internal.h"
 
 namespace snip {
@@ -141,58 +141,95 @@ __device__ __forceinline__ void err8(const unsigned* w, float s, float inv_s, fl
     }
 }
 
-// ------------------------------------------------------------------------------------------
-// Block maxima for the 128x128 groups.  One wave per 128 x 128 block of the SOURCE; a lane reads
-// two adjacent columns of every row.  Output: the block's scale for FP8 and for FP4 at
-// scales8 / scales4 [index], index in the stored orientation (transposed for the column variant).
-// ------------------------------------------------------------------------------------------
-__global__ __launch_bounds__(256) void block_scale_kernel(const uint16_t* __restrict__ x, int rows, int cols, int64_t ld,
-                                                          int transpose_index, float* __restrict__ scales8,
-                                                          float* __restrict__ scales4)
+// Unit of workgroup b.  Workgroups b, b + 8, ... run on one XCD: of every 8 * kAdjacent units each XCD takes kAdjacent in a row.
+constexpr int kAdjacent = 4;
+__device__ __forceinline__ int unit_of(int b, int units)
 {
+    const int b0 = b / (8 * kAdjacent) * (8 * kAdjacent);
+    return b0 + 8 * kAdjacent <= units ? b0 + (b & 7) * kAdjacent + ((b - b0) >> 3) : b;
+}
+
+// ------------------------------------------------------------------------------------------
+// 128x128 blocks, codes along rows.  A workgroup owns a block, its four waves 32 rows each; 16 lanes hold a row's 128 columns,
+// eight 16-byte loads are in flight.  The block stays in registers while the waves exchange their maxima, so the source is read
+// once.  Against a pass for the maxima and a pass for the codes, us per call on sources in memory: [8192 x 2048] FP8 20.7 -> 11.6,
+// [4096 x 8192] 36 -> 22, FP4 31 -> 19, [16384 x 11008] 173 -> 106 and 145 -> 80; statistics (with one second stage for the three
+// sums instead of three) [8192 x 2048] 29 -> 14.5, [16384 x 11008] 158 -> 98.
+// MODE as below; scales [row / 128][col / 128].
+// ------------------------------------------------------------------------------------------
+template <int FMT, int MODE>
+__global__ __launch_bounds__(256) void paper_block_kernel(const uint16_t* __restrict__ x, int rows, int cols, int64_t ld,
+                                                          uint8_t* __restrict__ codes, float* __restrict__ scales,
+                                                          float* __restrict__ partials)
+{
+    __shared__ unsigned maxima[2][kWavesPerBlock];
     const int lane = threadIdx.x & 63;
-    const int nbr = (rows + kGroup - 1) / kGroup, nbc = (cols + kGroup - 1) / kGroup;
-    const int nblocks = nbr * nbc;
-    const int wave0 = blockIdx.x * kWavesPerBlock + (threadIdx.x >> 6);
-    for (int b = wave0; b < nblocks; b += gridDim.x * kWavesPerBlock) {
-        const int br = b / nbc, bc = b - br * nbc;
-        const int c = bc * kGroup + lane * 2;
-        const int r0 = br * kGroup, r1 = min(r0 + kGroup, rows);
-        // 128 loads in flight, none under a condition: rows past the end repeat the last row (a maximum does not
-        // mind), lanes past the last column read column 0 and are discarded
-        const uint16_t* const base = x + (c < cols ? c : 0);
-        unsigned v[4][32];
+    const int wib = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int ncb = cols / kGroup, units = (rows + kGroup - 1) / kGroup * ncb;
+    float s0 = 0.f, e4 = 0.f, e8 = 0.f;
+    int turn = 0;
+    for (int b = blockIdx.x; b < units; b += gridDim.x, turn ^= 1) {
+        const int u = unit_of(b, units);
+        const int br = u / ncb, bc = u - br * ncb;
+        const int col = bc * kGroup + (lane & 15) * 8, row0 = br * kGroup + wib * 32 + (lane >> 4);
+        // rows past the end re-read the last row: a maximum does not mind, and nothing else comes of them
+        uint4 v[8];
 #pragma unroll
-        for (int k = 0; k < 4; ++k)
-#pragma unroll
-            for (int i = 0; i < 32; ++i) v[k][i] = *reinterpret_cast<const unsigned*>(base + (int64_t)min(r0 + k * 32 + i, r1 - 1) * ld);
+        for (int j = 0; j < 8; ++j) v[j] = ld16_stream(x + (int64_t)min(row0 + 4 * j, rows - 1) * ld + col);
         unsigned m = 0;
 #pragma unroll
-        for (int k = 0; k < 4; ++k)
+        for (int j = 0; j < 8; ++j) m = umax(m, amax8(v[j]));
+        m = row16_max(m);
+        m = umax(m, (unsigned)__shfl_xor((int)m, 16, 64));
+        m = umax(m, (unsigned)__shfl_xor((int)m, 32, 64));
+        if (lane == 0) maxima[turn][wib] = m;
+        __syncthreads();                                 // (two sets: the next block's maxima do not wait for readers of this one's)
 #pragma unroll
-            for (int i = 0; i < 32; ++i) m = pk_max_u16(m, v[k][i] & 0x7FFF7FFFu);
-        if (c >= cols) m = 0;
-        unsigned am = umax(m & 0xFFFFu, m >> 16);
-        for (int off = 32; off > 0; off >>= 1) am = umax(am, (unsigned)__shfl_xor((int)am, off, 64));
-        if (lane == 0) {
-            const int idx = transpose_index ? bc * nbr + br : br * nbc + bc;
-            if (scales8) scales8[idx] = group_scale<kFP8>(am);
-            if (scales4) scales4[idx] = group_scale<kFP4>(am);
+        for (int w = 0; w < kWavesPerBlock; ++w) m = umax(m, maxima[turn][w]);
+        const float s8 = MODE == 1 || FMT == kFP8 ? group_scale<kFP8>(m) : 1.f, s4 = MODE == 1 || FMT == kFP4 ? group_scale<kFP4>(m) : 1.f;
+        if (MODE == 0) {
+            const float s = FMT == kFP8 ? s8 : s4;
+            const bool bad = s != s;
+            if (threadIdx.x == 0) scales[u] = s;
+#pragma unroll
+            for (int j = 0; j < 8; ++j) {
+                const unsigned w[4] = {v[j].x, v[j].y, v[j].z, v[j].w};
+                unsigned c0, c1;
+                encode8<FMT>(w, s, c0, c1);
+                if (bad) { c0 = 0; c1 = 0; }
+                const int64_t e0 = (int64_t)(row0 + 4 * j) * cols + col;
+                if (row0 + 4 * j < rows) {
+                    if (FMT == kFP8) *reinterpret_cast<uint2*>(codes + e0) = make_uint2(c0, c1);
+                    else             *reinterpret_cast<unsigned*>(codes + (e0 >> 1)) = c0;
+                }
+            }
+        } else {
+            const float i8 = __fdiv_rn(1.f, s8), i4 = __fdiv_rn(1.f, s4);
+#pragma unroll
+            for (int j = 0; j < 8; ++j) {
+                const unsigned w[4] = {v[j].x, v[j].y, v[j].z, v[j].w};
+                float dummy = 0.f;
+                if (row0 + 4 * j < rows) {
+                    err8<kFP8>(w, s8, i8, s0, e8, true);
+                    err8<kFP4>(w, s4, i4, dummy, e4, false);
+                }
+            }
         }
+    }
+    if (MODE == 1) {
+        const int wave = blockIdx.x * kWavesPerBlock + wib;
+        s0 = wave_sum(s0); e4 = wave_sum(e4); e8 = wave_sum(e8);
+        if (lane == 0) { partials[wave] = s0; partials[kStreamWaves + wave] = e4; partials[2 * kStreamWaves + wave] = e8; }
     }
 }
 
 // ------------------------------------------------------------------------------------------
-// Blocks along rows.  A lane owns 8 consecutive elements, 16 lanes own a 128-element tile.
-// BLOCKS: the scale comes from block_scales [row / 128][col / 128]; otherwise it is the tile's own
-// and is written to scales [row][col / 128].
+// 1x128 tiles along rows.  A lane owns 8 consecutive elements, 16 lanes own a tile; its scale goes to scales [row][col / 128].
 // MODE 0: write codes (+ tile scales).  MODE 1: statistics of both formats, nothing written but partials.
 // ------------------------------------------------------------------------------------------
-template <int FMT, bool BLOCKS, int MODE>
+template <int FMT, int MODE>
 __global__ __launch_bounds__(256) void paper_row_kernel(const uint16_t* __restrict__ x, int rows, int cols, int64_t ld,
                                                         uint8_t* __restrict__ codes, float* __restrict__ scales,
-                                                        const float* __restrict__ block_scales8,
-                                                        const float* __restrict__ block_scales4,
                                                         float* __restrict__ partials)
 {
     const int lane = threadIdx.x & 63;
@@ -218,18 +255,11 @@ __global__ __launch_bounds__(256) void paper_row_kernel(const uint16_t* __restri
         for (int j = 0; j < kUnroll; ++j) {
             const int row = rg * kUnroll + j;
             const unsigned w[4] = {v[j].x, v[j].y, v[j].z, v[j].w};
-            const int gidx = BLOCKS ? (row >> 7) * ng + (col >> 7) : row * ng + (col >> 7);
+            const int gidx = row * ng + (col >> 7);
             float s8 = 1.f, s4 = 1.f;
-            if (BLOCKS) {
-                if (act[j]) {
-                    if (MODE == 1 || FMT == kFP8) s8 = block_scales8[gidx];
-                    if (MODE == 1 || FMT == kFP4) s4 = block_scales4[gidx];
-                }
-            } else {
-                const unsigned am = row16_max(amax8(v[j]));
-                if (MODE == 1 || FMT == kFP8) s8 = group_scale<kFP8>(am);
-                if (MODE == 1 || FMT == kFP4) s4 = group_scale<kFP4>(am);
-            }
+            const unsigned am = row16_max(amax8(v[j]));
+            if (MODE == 1 || FMT == kFP8) s8 = group_scale<kFP8>(am);
+            if (MODE == 1 || FMT == kFP4) s4 = group_scale<kFP4>(am);
             if (MODE == 0) {
                 const float s = FMT == kFP8 ? s8 : s4;
                 const bool bad = s != s;
@@ -240,7 +270,7 @@ __global__ __launch_bounds__(256) void paper_row_kernel(const uint16_t* __restri
                 if (act[j]) {
                     if (FMT == kFP8) *reinterpret_cast<uint2*>(codes + e0) = make_uint2(c0, c1);
                     else             *reinterpret_cast<unsigned*>(codes + (e0 >> 1)) = c0;
-                    if (!BLOCKS && (lane & 15) == 0) scales[gidx] = s;
+                    if ((lane & 15) == 0) scales[gidx] = s;
                 }
             } else if (act[j]) {
                 float dummy = 0.f;
@@ -338,12 +368,9 @@ __device__ __forceinline__ void err_column(const unsigned* v, int half, float s,
     }
 }
 
-constexpr int kAdjacent = 4;
 template <int FMT, bool BLOCKS, int MODE>
 __global__ __launch_bounds__(256) void paper_col_kernel(const uint16_t* __restrict__ x, int rows, int cols, int64_t ld,
                                                         uint8_t* __restrict__ codes, float* __restrict__ scales,
-                                                        const float* __restrict__ block_scales8,
-                                                        const float* __restrict__ block_scales4,
                                                         float* __restrict__ partials)
 {
     constexpr int ROWB = FMT == kFP8 ? 128 : 64;
@@ -359,9 +386,7 @@ __global__ __launch_bounds__(256) void paper_col_kernel(const uint16_t* __restri
     const int64_t out_row_bytes = FMT == kFP8 ? rows : rows / 2;
     float s0 = 0.f, e4 = 0.f, e8 = 0.f;
     for (int b = blockIdx.x; b < units; b += gridDim.x) {
-        // workgroups b, b + 8, ... run on one XCD: of every 8 * kAdjacent units each XCD takes kAdjacent in a row
-        const int b0 = b / (8 * kAdjacent) * (8 * kAdjacent);
-        const int u = b0 + 8 * kAdjacent <= units ? b0 + (b & 7) * kAdjacent + ((b - b0) >> 3) : b;
+        const int u = unit_of(b, units);
         const int ru = u / ncg, cg = u - ru * ncg;
         const int c = cg * kColsPerWave + lane * 2;
         const bool act = c < cols;
@@ -433,78 +458,63 @@ __global__ __launch_bounds__(256) void paper_col_kernel(const uint16_t* __restri
     }
 }
 
-int blocks_for(int64_t units)
+// Workgroups for `units` units of a workgroup each: one per unit, as long as a launch takes them.  Statistics need four
+// partial-sum slots per workgroup: equal shares then.
+int blocks_for(int64_t units, bool stats)
 {
-    if (units <= 0) return 1;
-    const int64_t per_wave = (units + kStreamWaves - 1) / kStreamWaves;
-    const int64_t waves = (units + per_wave - 1) / per_wave;
-    return (int)((waves + kWavesPerBlock - 1) / kWavesPerBlock);
+    const int64_t most = stats ? kStreamBlocks : kMostBlocks, share = (units + most - 1) / most;
+    return units <= 0 ? 1 : (int)((units + share - 1) / share);
 }
 
 template <int FMT, bool BLOCKS, int MODE>
-int launch_one(const PaperArgs& a, const float* bs8, const float* bs4, float* partials, hipStream_t s)
+int launch_one(const PaperArgs& a, float* partials, hipStream_t s)
 {
+    const int64_t groups = ((a.rows + kGroup - 1) / kGroup) * ((a.cols + kGroup - 1) / kGroup);
     int blocks;
-    if (a.axis == 0) {
-        blocks = blocks_for(((a.rows + kUnroll - 1) / kUnroll) * ((a.cols + kSeg - 1) / kSeg));
-        hipLaunchKernelGGL((paper_row_kernel<FMT, BLOCKS, MODE>), dim3(blocks), dim3(256), 0, s,
-                           a.x, (int)a.rows, (int)a.cols, a.ld, a.codes, a.scales, bs8, bs4, partials);
-    } else {
-        // a workgroup per unit; with statistics it needs four partial-sum slots
-        const int64_t units = ((a.cols + kColsPerWave - 1) / kColsPerWave) * (a.rows / kGroup);
-        const int64_t share = MODE == 1 ? (units + kStreamBlocks - 1) / kStreamBlocks : 1;
-        blocks = (int)((units + share - 1) / share);
+    if (a.axis != 0) {
+        blocks = blocks_for(groups, MODE == 1);
         hipLaunchKernelGGL((paper_col_kernel<FMT, BLOCKS, MODE>), dim3(blocks), dim3(256), 0, s,
-                           a.x, (int)a.rows, (int)a.cols, a.ld, a.codes, a.scales, bs8, bs4, partials);
+                           a.x, (int)a.rows, (int)a.cols, a.ld, a.codes, a.scales, partials);
+    } else if (BLOCKS) {
+        blocks = blocks_for(groups, MODE == 1);
+        hipLaunchKernelGGL((paper_block_kernel<FMT, MODE>), dim3(blocks), dim3(256), 0, s,
+                           a.x, (int)a.rows, (int)a.cols, a.ld, a.codes, a.scales, partials);
+    } else {
+        const int64_t units = ((a.rows + kUnroll - 1) / kUnroll) * ((a.cols + kSeg - 1) / kSeg);
+        blocks = blocks_for((units + kWavesPerBlock - 1) / kWavesPerBlock, MODE == 1);
+        hipLaunchKernelGGL((paper_row_kernel<FMT, MODE>), dim3(blocks), dim3(256), 0, s,
+                           a.x, (int)a.rows, (int)a.cols, a.ld, a.codes, a.scales, partials);
     }
     return blocks;
 }
 
 }  // namespace
 
+// (room for two scales per group as well: earlier forms of the statistics kept them there, and callers have allocated it)
 size_t paper_workspace_bytes(int64_t rows, int64_t cols)
 {
     const size_t nblocks = (size_t)((rows + kGroup - 1) / kGroup) * (size_t)((cols + kGroup - 1) / kGroup);
     return 3 * (size_t)kStreamWaves * sizeof(float) + 2 * nblocks * sizeof(float);
 }
 
-// Workspace layout: [3][kStreamWaves] float partial sums, then the FP8 and the FP4 block-scale arrays.
+// Workspace layout: [3][kStreamWaves] float partial sums.
 hipError_t launch_paper(const PaperArgs& a, hipStream_t s)
 {
     const bool stats = a.stats != nullptr;
     float* partials = (float*)a.workspace;
-    const bool empty = a.rows == 0 || a.cols == 0;
-    const size_t nblocks = (size_t)((a.rows + kGroup - 1) / kGroup) * (size_t)((a.cols + kGroup - 1) / kGroup);
-    float* bs8 = nullptr;
-    float* bs4 = nullptr;
-    if (a.blocks && !empty && a.axis == 0) {       // the column kernel finds its blocks' maxima itself
-        if (stats) { bs8 = partials + 3 * kStreamWaves; bs4 = bs8 + nblocks; }
-        else       { bs8 = a.fmt == kFP8 ? a.scales : nullptr; bs4 = a.fmt == kFP4 ? a.scales : nullptr; }   // the output array itself
-        hipLaunchKernelGGL(block_scale_kernel, dim3(blocks_for((int64_t)nblocks)), dim3(256), 0, s,
-                           a.x, (int)a.rows, (int)a.cols, a.ld, a.axis == 1 ? 1 : 0, bs8, bs4);
-        const hipError_t e = hipGetLastError();
-        if (e != hipSuccess) return e;
-    }
     int blocks = 0;
-    if (!empty) {
+    if (a.rows != 0 && a.cols != 0) {
         if (stats) {
-            blocks = a.blocks ? launch_one<kFP8, true, 1>(a, bs8, bs4, partials, s) : launch_one<kFP8, false, 1>(a, bs8, bs4, partials, s);
+            blocks = a.blocks ? launch_one<kFP8, true, 1>(a, partials, s) : launch_one<kFP8, false, 1>(a, partials, s);
         } else if (a.fmt == kFP8) {
-            blocks = a.blocks ? launch_one<kFP8, true, 0>(a, bs8, bs4, partials, s) : launch_one<kFP8, false, 0>(a, bs8, bs4, partials, s);
+            blocks = a.blocks ? launch_one<kFP8, true, 0>(a, partials, s) : launch_one<kFP8, false, 0>(a, partials, s);
         } else {
-            blocks = a.blocks ? launch_one<kFP4, true, 0>(a, bs8, bs4, partials, s) : launch_one<kFP4, false, 0>(a, bs8, bs4, partials, s);
+            blocks = a.blocks ? launch_one<kFP4, true, 0>(a, partials, s) : launch_one<kFP4, false, 0>(a, partials, s);
         }
         const hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
     }
-    if (stats) {
-        const int64_t n = (int64_t)blocks * kWavesPerBlock;
-        for (int j = 0; j < 3; ++j) {
-            const hipError_t e = launch_sum_partials(partials + (size_t)j * kStreamWaves, n, a.stats + j, s);
-            if (e != hipSuccess) return e;
-        }
-    }
-    return hipSuccess;
+    return stats ? launch_sum_partials(partials, (int64_t)blocks * kWavesPerBlock, a.stats, s, 3, kStreamWaves) : hipSuccess;
 }
 
 }  // namespace snip

@@ -17,6 +17,7 @@ constexpr int kBlock = 32;  // elements per scale
 constexpr int kStreamBlocks = 2048;
 constexpr int kWavesPerBlock = 4;
 constexpr int kStreamWaves = kStreamBlocks * kWavesPerBlock;
+constexpr int64_t kMostBlocks = (int64_t)1 << 22;    // workgroups of a launch that needs no slot per workgroup (threads are counted in 32 bits)
 constexpr int kMaxColSplits = 64;    // row splits of the column-statistics kernel
 // Workspace of the streaming kernels: partial sums, for one block direction [kStreamWaves][3] fp32 of waves, for both at most
 // [kStreamBlocks][6] fp64 of workgroups; then [kMaxColSplits][cols][3] fp32 per-column partials for the per-line column
@@ -107,8 +108,8 @@ hipError_t launch_paper(const PaperArgs& a, hipStream_t s);
 
 size_t workspace_bytes(int64_t rows, int64_t cols);
 hipError_t launch_adamw_sensitivity(const AdamwArgs& a, hipStream_t s);
-// out[0] = sum of partials[0..n) in a fixed order, in double (one workgroup); n may be 0
-hipError_t launch_sum_partials(const float* partials, int64_t n, double* out, hipStream_t s);
+// out[i] = sum of partials[i * stride ... i * stride + n) in a fixed order, in double, for i < sums; n may be 0
+hipError_t launch_sum_partials(const float* partials, int64_t n, double* out, hipStream_t s, int sums = 1, int64_t stride = 0);
 hipError_t launch_quantize(const QuantArgs& a, hipStream_t s);
 hipError_t launch_quantize_both(const QuantBothArgs& a, hipStream_t s);
 hipError_t launch_stats(const StatsArgs& a, hipStream_t s);
