@@ -350,19 +350,20 @@ int gemm_compute_units()
 // average 0.2 % slower than the fastest tile (8 % at worst), on less from memory the first table's 0.3 % (11 %).
 // Fitted to 182 and 107 problems timed with every tile: the GEMMs of 1B-, 3B- and 7B-shaped blocks and random ones (64 ...
 // 16384 tokens, widths 64 ... 11008, FP4 and FP8); the tiles from 128 x 128 on anew to 154 of them when 256 x 128 got its third
-// stage buffer.  The pick is on average 0.25 and 0.20 % slower than the fastest tile (7 % at worst).  From memory the 256 x 128 tile beats 256 x 256
-// where rounds of the larger one would be half empty: [8192 x 3072 x 3072] FP8 89 -> 81.5 us, [4096 x 2048 x 8192] FP4 56 -> 43.
+// stage buffer, and 256 x 128 by what single-phase stages gained on 36.  The pick is on average 0.25 and 0.13 % slower than the
+// fastest tile (9 % at worst).  From memory the 256 x 128 tile beats 256 x 256
+// where rounds of the larger one would be half empty: [8192 x 3072 x 3072] FP8 87 -> 82 us, [4096 x 2048 x 8192] FP4 57 -> 43.
 struct TileCost { GemmTile tile; int m, n; float start, turn, alone[2], full[2], tail[2]; };      // [0]: FP4 x FP4, [1]: others
 static const TileCost kTileCosts[2][6] = {{
     {GemmTile::kBig,       256, 256, 7.5f, 4.5f, {1.51f, 0.80f}, {1.67f, 1.48f}, {0.83f, 0.74f}},
-    {GemmTile::kWide,      256, 128, 7.3f, 2.0f, {0.46f, 0.37f}, {0.94f, 0.77f}, {1.00f, 0.49f}},
+    {GemmTile::kWide,      256, 128, 7.2f, 2.0f, {0.45f, 0.35f}, {0.92f, 0.73f}, {0.98f, 0.46f}},
     {GemmTile::k128x128,   128, 128, 4.7f, 3.6f, {0.37f, 0.33f}, {0.54f, 0.46f}, {0.47f, 0.29f}},
     {GemmTile::k64x64,      64,  64, 3.1f, 1.0f, {0.17f, 0.17f}, {0.20f, 0.19f}, {0.25f, 0.14f}},
     {GemmTile::k64x32,      64,  32, 3.1f, 1.4f, {0.16f, 0.16f}, {0.19f, 0.18f}, {0.18f, 0.19f}},
     {GemmTile::k32x32,      32,  32, 2.9f, 1.2f, {0.13f, 0.13f}, {0.15f, 0.14f}, {0.13f, 0.13f}},
 }, {
     {GemmTile::kBig,       256, 256, 10.5f, 5.5f, {1.12f, 1.14f}, {1.67f, 1.51f}, {1.05f, 0.97f}},
-    {GemmTile::kWide,      256, 128, 8.4f, 2.7f, {0.74f, 0.71f}, {1.04f, 0.88f}, {1.30f, 0.52f}},
+    {GemmTile::kWide,      256, 128, 8.3f, 2.6f, {0.71f, 0.68f}, {1.00f, 0.85f}, {1.25f, 0.50f}},
     {GemmTile::k128x128,   128, 128, 5.2f, 2.7f, {0.53f, 0.53f}, {0.66f, 0.57f}, {0.05f, 0.05f}},
     {GemmTile::k64x64,      64,  64, 4.4f, 1.0f, {0.30f, 0.30f}, {0.22f, 0.23f}, {0.45f, 0.34f}},
     {GemmTile::k64x32,      64,  32, 3.6f, 1.1f, {0.17f, 0.17f}, {0.28f, 0.23f}, {0.20f, 0.20f}},

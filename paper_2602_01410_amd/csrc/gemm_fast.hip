@@ -53,20 +53,23 @@ constexpr int NWAVE = 8, NT = NWAVE * 64;
 constexpr int TNP = 256;                // rows of the B tile's scale area (a 128-row B tile leaves half of it unused)
 
 // Workgroup tile TM (A rows) x TN (B rows), split over the eight waves as (TM / WTM) x (TN / WTN) wave tiles.
-template <int TM_, int TN_, int WTM_, int WTN_, int NST_> struct TileCfg {
-    static constexpr int TM = TM_, TN = TN_, WTM = WTM_, WTN = WTN_, NST = NST_;      // NST: stage buffers
+template <int TM_, int TN_, int WTM_, int WTN_, int NST_, int PH_> struct TileCfg {
+    static constexpr int TM = TM_, TN = TN_, WTM = WTM_, WTN = WTN_, NST = NST_, PH = PH_;      // stage buffers, phases of a stage
     static constexpr int WGN = TN / WTN;                   // waves along the B rows
     static constexpr int MB = WTM / 32, NB = WTN / 32;     // 32 x 32 MFMA blocks of a wave tile
     static_assert(TM == 256 && (TN == 256 || TN == 128), "copy shares and scale areas are laid out for these tiles");
     static_assert((TM / WTM) * (TN / WTN) == NWAVE, "eight waves");
 };
 // 256 x 256, 2 x 4 waves of 128 x 64: the largest tile the register file allows (fewest operand bytes per FLOP).
-using TileBig = TileCfg<256, 256, 128, 64, 2>;
+using TileBig = TileCfg<256, 256, 128, 64, 2, 2>;
 // 256 x 128, 4 x 2 waves of 64 x 64: twice as many tiles for outputs that would leave compute units without one.  us per call on
 // operands from memory with two stage buffers (and operand lines pulled into L2 four stages ahead) -> with three: [4096 x 2048 x
 // 8192] FP4 48.5 -> 43.0, FP8 74.6 -> 69.3, [4096 x 2048 x 2048] 19.6 -> 18.0, 25.4 -> 23.3, [8192 x 3072 x 3072] FP8 89 -> 81.5,
-// [2048 x 4096 x 4096] FP8 41.6 -> 39.0.  Pulling lines ahead of three buffers as well costs 1-8 %.
-using TileWide = TileCfg<256, 128, 64, 64, 3>;
+// [2048 x 4096 x 4096] FP8 41.6 -> 39.0.  Pulling lines ahead of three buffers as well costs 1-8 %.  A stage is one phase here (its
+// operands take 64 registers), which halves the barriers and the LDS latencies of a stage; two phases -> one: [4096 x 2048 x 2048]
+// FP4 18.5 -> 17.4, FP8 24.4 -> 23.2, [4096 x 2048 x 8192] 44.8 -> 43.0 and 68.6 -> 65.5, [8192 x 3072 x 3072] 59.0 -> 55.8 and 84.8 -> 82.9,
+// [3072 x 8192 x 8192] 118 -> 112 and 186 -> 175; operands in the caches 2-9 %.
+using TileWide = TileCfg<256, 128, 64, 64, 3, 1>;
 
 template <int FA, int FB, class T> struct FCfg {
     static constexpr int TM = T::TM, TN = T::TN;
@@ -228,13 +231,15 @@ __global__ __launch_bounds__(NT) void gemm_fast_kernel(const uint8_t* __restrict
     v16f acc[MB][NB];
 
     // ---- ping-pong schedule.  The two waves that share a SIMD (wave w and w + 4) belong to different
-    //      groups.  A stage is two phases; in every phase a wave either reads its operands of that phase
+    //      groups.  A stage is PH phases (two below); in every phase a wave either reads its operands of that phase
     //      from LDS into registers (R) or issues that phase's MFMAs (M).  Workgroup barriers separate the
     //      phases and group 1 runs one phase behind group 0, so while one wave of a SIMD feeds the matrix
     //      core the other one fetches:
     //          barrier    b0      b1      b2      b3      b4      b5 ...
     //          group 0        R0(0)   M0(0)   R1(0)   M1(0)   R0(1)   M0(1)
     //          group 1        -       R0(0)   M0(0)   R1(0)   M1(0)   R0(1)
+    //      (256 x 128, one phase: R(0) M(0) R(1) ..., b(4s) and b(4s+1) only; M0 and M1 below are the same then, and b(4s+4) is the
+    //      barrier behind b(4s+1).)
     //      Stage s of a tile is complete in LDS before b(4s): every wave waits for its own copies before that
     //      barrier.  The buffer of stage s is free after b(4s+4): group 1, the last reader, waits for its R1(s)
     //      data before that barrier, so no read of the buffer is in flight when the first copy into it is issued.
@@ -247,25 +252,29 @@ __global__ __launch_bounds__(NT) void gemm_fast_kernel(const uint8_t* __restrict
     //      b(4S)) while group 1 still issues M1(S-1), then group 1 stores its block; the next tile's b(0) follows.
     //      Group 1's share of the next tile's stage NST-1, which goes into the buffer under the staging area, is
     //      issued after that barrier (where the first tile issues it, too). ----
-    constexpr int KP = C::KS / 2;                      // k-steps per phase
+    constexpr int PH = T::PH, KP = C::KS / PH;         // phases of a stage, k-steps per phase
+    constexpr int NQ = (KP + 1) / 2;                   // scale dwords per row and phase
     v8i fa[KP][MB], fb[KP][NB];
-    unsigned sa[MB], sb[NB];
+    unsigned sa[NQ][MB], sb[NQ][NB];
     auto RD = [&](int slot, int p, int stage) {
         const uint8_t* base = lds + slot * C::STRIDE;
         const uint8_t* ta = base + wm * WTM * C::SBA;
         const uint8_t* tb = base + C::A_BYTES + wn * WTN * C::SBB;
-        const int q = C::NG == 2 ? p : 0;
 #pragma unroll
-        for (int m = 0; m < MB; ++m) sa[m] = *reinterpret_cast<const unsigned*>(base + sca_off + q * TM * 4 + m * 128) >> (8 * g);
+        for (int i = 0; i < NQ; ++i) {
+            const int q = C::NG == 2 ? p * NQ + i : 0;
 #pragma unroll
-        for (int n = 0; n < NB; ++n) sb[n] = *reinterpret_cast<const unsigned*>(base + scb_off + q * TNP * 4 + n * 128) >> (8 * g);
-        // scale bytes past the last block are unspecified (a group past the last one was delivered as zeros)
-        if (TAIL && (R & 127) != 0 && stage * C::NG + q == ngrp - 1) {
-            const unsigned mask = ((1u << (8 * ((R & 127) / kBlock))) - 1u) >> (8 * g);
+            for (int m = 0; m < MB; ++m) sa[i][m] = *reinterpret_cast<const unsigned*>(base + sca_off + q * TM * 4 + m * 128) >> (8 * g);
 #pragma unroll
-            for (int m = 0; m < MB; ++m) sa[m] &= mask;
+            for (int n = 0; n < NB; ++n) sb[i][n] = *reinterpret_cast<const unsigned*>(base + scb_off + q * TNP * 4 + n * 128) >> (8 * g);
+            // scale bytes past the last block are unspecified (a group past the last one was delivered as zeros)
+            if (TAIL && (R & 127) != 0 && stage * C::NG + q == ngrp - 1) {
+                const unsigned mask = ((1u << (8 * ((R & 127) / kBlock))) - 1u) >> (8 * g);
 #pragma unroll
-            for (int n = 0; n < NB; ++n) sb[n] &= mask;
+                for (int m = 0; m < MB; ++m) sa[i][m] &= mask;
+#pragma unroll
+                for (int n = 0; n < NB; ++n) sb[i][n] &= mask;
+            }
         }
 #pragma unroll
         for (int k = 0; k < KP; ++k) {
@@ -291,9 +300,9 @@ __global__ __launch_bounds__(NT) void gemm_fast_kernel(const uint8_t* __restrict
 #pragma unroll
                 for (int n = 0; n < NB; ++n) {
                     if ((ks & 1) == 0)
-                        acc[m][n] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(fb[k][n], fa[k][m], acc[m][n], ca, cb, 0, (int)sb[n], 0, (int)sa[m]);
+                        acc[m][n] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(fb[k][n], fa[k][m], acc[m][n], ca, cb, 0, (int)sb[k / 2][n], 0, (int)sa[k / 2][m]);
                     else
-                        acc[m][n] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(fb[k][n], fa[k][m], acc[m][n], ca, cb, 2, (int)sb[n], 2, (int)sa[m]);
+                        acc[m][n] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(fb[k][n], fa[k][m], acc[m][n], ca, cb, 2, (int)sb[k / 2][n], 2, (int)sa[k / 2][m]);
                     if (COPY) {
                         __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
@@ -479,9 +488,12 @@ __global__ __launch_bounds__(NT) void gemm_fast_kernel(const uint8_t* __restrict
                 if (first || s >= NST - 1) SNIP_WAIT_VM((NST - 2) * C::L);
                 SNIP_BAR();                                         // b(4s)
                 RD(slot, 0, s); SNIP_BAR();      // b(4s+1)
-                MM(copy_tag, 0, cstage, before(slot)); SNIP_BAR();  // b(4s+2)
-                RD(slot, 1, s); SNIP_BAR();      // b(4s+3)
-                MM(no_copy, 1, 0, 0);
+                MM(copy_tag, 0, cstage, before(slot));
+                if (PH == 2) {
+                    SNIP_BAR();                                     // b(4s+2)
+                    RD(slot, 1, s); SNIP_BAR();  // b(4s+3)
+                    MM(no_copy, 1, 0, 0);
+                }
             };
             // Every stage carries copies, so that the MFMA code exists once (two variants of it merging in front
             // of the result store cost the register allocator its in-place accumulators).  Without a next tile the
@@ -501,13 +513,16 @@ __global__ __launch_bounds__(NT) void gemm_fast_kernel(const uint8_t* __restrict
             // through the tile's first phase
             auto stage1 = [&](auto copy_tag, int s, int cstage) {
                 SNIP_BAR();                                         // b(4s+1)
-                RD(slot, 0, s); SNIP_BAR();      // b(4s+2)
-                MM(no_copy, 0, 0, 0); SNIP_BAR();                   // b(4s+3)
-                RD(slot, 1, s);
+                RD(slot, 0, s);
+                if (PH == 2) {
+                    SNIP_BAR();                  // b(4s+2)
+                    MM(no_copy, 0, 0, 0); SNIP_BAR();               // b(4s+3)
+                    RD(slot, 1, s);
+                }
                 if (NST == 2 || first || s >= NST - 2) SNIP_WAIT_VM((NST - 2) * C::L);      // stage s + 1 (see stage0)
                 __builtin_amdgcn_s_waitcnt(0xC07F);                 // lgkmcnt(0)
                 SNIP_BAR();                                         // b(4s+4)
-                MM(copy_tag, 1, cstage, slot);
+                MM(copy_tag, PH - 1, cstage, slot);
             };
             if (first) SNIP_WAIT_VM((NST - 2) * C::L);
             SNIP_BAR();                                             // b(0)
