@@ -164,50 +164,47 @@ __device__ __forceinline__ void threefry2x32_20(unsigned c0, unsigned c1, unsign
 // to the 22 mantissa bits that FP4 drops (denormalised below 1) and rounds up on a carry, so with a seed
 // R << 24 it rounds up iff floor(256 p) + R >= 256 -- the rule above with R = 255 - rnd.  The second
 // element of a pair takes the seed shifted by one bit, which would tie its random number to the first
-// one's; every element therefore goes through the first slot of its own instruction (second slot 0.0).
-// Bits below the top eight of the seed must be zero, or they could carry into the comparison.
+// one's; every element therefore goes through the first slot of its own instruction, and what the second slot makes
+// of whatever its register holds is masked away (a zero there costs a move per element: 17.8 vector instructions per element along
+// rows and 17.1 along columns then, 16.1 and 15.5 now, which is what bounds these kernels: us per call along rows [8192 x
+// 8192] 43.0 -> 38.7, [4096 x 8192] 24.6 -> 21.8, [2048 x 4096] 8.2 -> 7.5; along columns 44.6 -> 42.1, 23.0 -> 22.8, 9.1 -> 8.6).
+// Bits below the top eight of the seed must be zero, or they could carry into the comparison.  The form that takes
+// packed bf16 would save the unpacking, but it drops bits of p between 1/4 and 1.
 // The instruction is written as inline assembly: it replaces one byte of its destination and keeps the
 // other three, and the compiler's builtin for it does not tie the destination to the previous value.
 typedef float float2_t_sr __attribute__((ext_vector_type(2)));
 #define SNIP_SR_CVT(dst, src, seed, sc, OPSEL) \
-    asm("v_cvt_scalef32_sr_pk_fp4_f32 %0, %1, %2, %3" OPSEL : "+v"(dst) : "v"(src), "v"(seed), "v"(sc))
+    asm("v_cvt_scalef32_sr_pk_fp4_f32 %0, %1, %2, %3" OPSEL : "+v"(dst) : "v"(float2_t_sr{src, __uint_as_float(any_value())}), "v"(seed), "v"(sc))
 
-// Four bf16 pairs (8 consecutive stored elements) -> 8 FP4 nibbles with stochastic rounding; r0 holds
-// the random bytes of elements 0-3, r1 those of elements 4-7; sc is the block scale operand.
-__device__ __forceinline__ unsigned enc4_sr(const unsigned* w, float sc, unsigned r0, unsigned r1)
+// 8 consecutive stored elements -> 8 FP4 nibbles with stochastic rounding; r0 holds the
+// random bytes of elements 0-3, r1 those of elements 4-7; sc is the block scale operand.
+__device__ __forceinline__ unsigned enc4_sr(const float (&e)[8], float sc, unsigned r0, unsigned r1)
 {
-    const unsigned n0 = ~r0, n1 = ~r1;                      // 255 - rnd in every byte
-    unsigned even = 0, odd = 0;                             // byte i: code of element 2i / 2i+1 in its low nibble
-    float2_t_sr xe[4], xo[4];
-    unsigned se[4], so[4];
+    const unsigned n[2] = {~r0, ~r1};                       // 255 - rnd in every byte
+    unsigned even = any_value(), odd = any_value();         // byte i: code of element 2i / 2i+1 in its low nibble
+    unsigned s[8];                                          // byte i % 4 of n moved to the top byte, zeros below
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        const unsigned nn = i < 2 ? n0 : n1;
-        // byte (2i mod 4) resp. (2i+1 mod 4) of nn moved to the top byte, zeros below
-        se[i] = __builtin_amdgcn_perm(nn, 0u, (i & 1) ? 0x060C0C0Cu : 0x040C0C0Cu);
-        so[i] = __builtin_amdgcn_perm(nn, 0u, (i & 1) ? 0x070C0C0Cu : 0x050C0C0Cu);
-        xe[i] = float2_t_sr{__uint_as_float(w[i] << 16), 0.f};
-        xo[i] = float2_t_sr{__uint_as_float(w[i] & 0xFFFF0000u), 0.f};
-    }
-    SNIP_SR_CVT(even, xe[0], se[0], sc, "");
-    SNIP_SR_CVT(even, xe[1], se[1], sc, " op_sel:[0,0,1,0]");
-    SNIP_SR_CVT(even, xe[2], se[2], sc, " op_sel:[0,0,0,1]");
-    SNIP_SR_CVT(even, xe[3], se[3], sc, " op_sel:[0,0,1,1]");
-    SNIP_SR_CVT(odd, xo[0], so[0], sc, "");
-    SNIP_SR_CVT(odd, xo[1], so[1], sc, " op_sel:[0,0,1,0]");
-    SNIP_SR_CVT(odd, xo[2], so[2], sc, " op_sel:[0,0,0,1]");
-    SNIP_SR_CVT(odd, xo[3], so[3], sc, " op_sel:[0,0,1,1]");
-    return even | (odd << 4);
+    for (int i = 0; i < 8; ++i)
+        s[i] = i % 4 == 0 ? n[i / 4] << 24 : i % 4 == 3 ? n[i / 4] & 0xFF000000u
+                          : __builtin_amdgcn_perm(n[i / 4], 0u, i % 4 == 1 ? 0x050C0C0Cu : 0x060C0C0Cu);
+    SNIP_SR_CVT(even, e[0], s[0], sc, "");
+    SNIP_SR_CVT(odd, e[1], s[1], sc, "");
+    SNIP_SR_CVT(even, e[2], s[2], sc, " op_sel:[0,0,1,0]");
+    SNIP_SR_CVT(odd, e[3], s[3], sc, " op_sel:[0,0,1,0]");
+    SNIP_SR_CVT(even, e[4], s[4], sc, " op_sel:[0,0,0,1]");
+    SNIP_SR_CVT(odd, e[5], s[5], sc, " op_sel:[0,0,0,1]");
+    SNIP_SR_CVT(even, e[6], s[6], sc, " op_sel:[0,0,1,1]");
+    SNIP_SR_CVT(odd, e[7], s[7], sc, " op_sel:[0,0,1,1]");
+    return (even & 0x0F0F0F0Fu) | ((odd << 4) & 0xF0F0F0F0u);
 }
 #undef SNIP_SR_CVT
 
-// Codes of the 8 consecutive stored elements that start at stored position e0 (a multiple of 8).
-__device__ __forceinline__ unsigned enc4_sr_at(const unsigned* w, float sc, int64_t e0, uint2 seed)
+// Codes of the 8 consecutive stored elements that start at stored position 8 * grp.
+__device__ __forceinline__ unsigned enc4_sr_at(const float (&e)[8], float sc, uint64_t grp, uint2 seed)
 {
-    const uint64_t grp = (uint64_t)e0 >> 3;
     unsigned r0, r1;
     threefry2x32_20((unsigned)grp, (unsigned)(grp >> 32), seed.x, seed.y, r0, r1);
-    return enc4_sr(w, sc, r0, r1);
+    return enc4_sr(e, sc, r0, r1);
 }
 
 // s0 += x_lo^2 + x_hi^2 for a bf16 pair (one instruction: the products are exact, the sum is rounded once)
@@ -359,45 +356,68 @@ __global__ __launch_bounds__(256) void quant_row_kernel(const uint16_t* __restri
     const int nwaves = gridDim.x * kWavesPerBlock;
     const int spr = (cols + kSeg - 1) / kSeg;
     const int units = ((rows + kUnroll - 1) / kUnroll) * spr;
-    const int nblk = cols / kBlock;
     float s0 = 0.f, se = 0.f;
 
     for (int u = wave; u < units; u += nwaves) {
         const int rg = u / spr;
         const int col = (u - rg * spr) * kSeg + lane * 8;
+        // Loads carry no condition: lanes past the last column read column 0 and rows past the last one that row; with
+        // statistics they count as zeros, otherwise only their scale bytes are cleared (they reach the grouped copy).
+        const bool in = col < cols;
+        const unsigned ucol = in ? (unsigned)col : 0u;
         uint4 v[kUnroll];
-        bool act[kUnroll];
+#pragma unroll
+        for (int j = 0; j < kUnroll; ++j) v[j] = ld16(x + (int64_t)min(rg * kUnroll + j, rows - 1) * ld + ucol);
+        // stored position of the unit's first row / 8, stepped in scalar registers out of the compiler's sight (it would multiply
+        // anew for every address, in 64 bits on the vector unit)
+        const int64_t step = cols >> 3;
+        int64_t at0 = (int64_t)(rg * kUnroll) * step;
+        asm volatile("" : "+s"(at0));
+        int64_t at = at0;
+        unsigned packed = 0, c0[kUnroll], c1[kUnroll];
 #pragma unroll
         for (int j = 0; j < kUnroll; ++j) {
             const int row = rg * kUnroll + j;
-            act[j] = row < rows && col < cols;
-            v[j] = make_uint4(0, 0, 0, 0);
-            if (act[j]) v[j] = ld16(x + (int64_t)row * ld + col);
-        }
-        unsigned packed = 0;
-#pragma unroll
-        for (int j = 0; j < kUnroll; ++j) {
-            const int row = rg * kUnroll + j;
+            const bool act = in && row < rows;
+            if (STATS && !act) v[j] = make_uint4(0, 0, 0, 0);
             const unsigned am = quad_max(amax8(v[j]));
             const unsigned byte = scale_byte<FMT, RULE>(am);
             const float sc = scale_operand(byte);
             const bool bad = byte == 0xFFu;
             const unsigned w[4] = {v[j].x, v[j].y, v[j].z, v[j].w};
-            const int64_t e0 = (int64_t)row * cols + col;
             if (FMT == kFP8) {
-                unsigned c0 = enc8<RULE>(w[0], w[1], sc, byte), c1 = enc8<RULE>(w[2], w[3], sc, byte);
-                if (bad) { c0 = 0; c1 = 0; }
-                if (act[j]) *reinterpret_cast<uint2*>(codes + e0) = make_uint2(c0, c1);
-                if (STATS) err8(w, c0, c1, sc, s0, se, true);
+                c0[j] = enc8<RULE>(w[0], w[1], sc, byte); c1[j] = enc8<RULE>(w[2], w[3], sc, byte);
+                if (bad) { c0[j] = 0; c1[j] = 0; }
+                if (STATS) err8(w, c0[j], c1[j], sc, s0, se, true);
+            } else if (SR) {
+                float e[8];
+#pragma unroll
+                for (int i = 0; i < 4; ++i) unpack2(w[i], e[2 * i], e[2 * i + 1]);
+                c0[j] = enc4_sr_at(e, sc, (uint64_t)at + ucol / 8, seed);
+                at += step;
+                if (bad) c0[j] = 0;
             } else {
-                unsigned c = SR ? enc4_sr_at(w, sc, e0, seed) : enc4(w[0], w[1], w[2], w[3], sc);
-                if (bad) c = 0;
-                if (act[j]) *reinterpret_cast<unsigned*>(codes + (e0 >> 1)) = c;
-                if (STATS) err4(w, c, sc, s0, se, true);
+                c0[j] = enc4(w[0], w[1], w[2], w[3], sc);
+                if (bad) c0[j] = 0;
+                if (STATS) err4(w, c0[j], sc, s0, se, true);
             }
-            if (act[j] && (lane & 3) == 0)
-                scales[(int64_t)row * nblk + (col >> 5)] = (uint8_t)byte;
-            packed |= byte << (8 * j);
+            packed |= (act ? byte : 0u) << (8 * j);
+        }
+        if (in) {
+            at = at0;
+#pragma unroll
+            for (int j = 0; j < kUnroll; ++j, at += step) {
+                if (rg * kUnroll + j >= rows) break;                 // wave-uniform
+                if (FMT == kFP8) *reinterpret_cast<uint2*>(codes + at * 8 + ucol) = make_uint2(c0[j], c1[j]);
+                else             *reinterpret_cast<unsigned*>(codes + at * 4 + ucol / 2) = c0[j];
+            }
+            at = at0;
+            if ((lane & 3) == 0)
+#pragma unroll
+                for (int j = 0; j < kUnroll; ++j, at += step) {
+                    if (rg * kUnroll + j >= rows) break;
+                    scales[(at >> 2) + ucol / kBlock] = (uint8_t)(packed >> (8 * j));
+                }
         }
         // Grouped copy: `packed` holds this block's byte for each of the 4 rows.  Fetch the same
         // word from the next three quads (the next three blocks of the same 128-element group),
@@ -491,11 +511,18 @@ __device__ __forceinline__ void load_col_raw(const uint16_t* __restrict__ p, int
     for (int i = 0; i < 32; ++i) v[i] = ld4<false>(p + (int64_t)i * ld);
 }
 
-__device__ __forceinline__ void pair_col_block(const unsigned (&v)[32], ColBlock& b)
+// Magnitude bits of both columns' maxima, the first column's in the low half.
+__device__ __forceinline__ unsigned col_maxima(const unsigned (&v)[32])
 {
     unsigned m = 0;
 #pragma unroll
     for (int i = 0; i < 32; ++i) m = pk_max_u16(m, v[i] & 0x7FFF7FFFu);
+    return m;
+}
+
+__device__ __forceinline__ void pair_col_block(const unsigned (&v)[32], ColBlock& b)
+{
+    const unsigned m = col_maxima(v);
     b.am_lo = m & 0xFFFFu;
     b.am_hi = m >> 16;
 #pragma unroll
@@ -533,20 +560,12 @@ __device__ __forceinline__ void load_col_tile(const uint16_t* __restrict__ row, 
     }
 }
 
-__device__ __forceinline__ void load_col_block(const uint16_t* __restrict__ row, int c0, int lane, int cols, int64_t ld, ColBlock& b)
-{
-    unsigned v[32];
-    load_col_tile(row, c0, lane, cols, ld, v);
-    pair_col_block(v, b);
-}
-
 // Codes of one column's block (32 rows) -> the wave's LDS staging area; returns the scale byte.
 // In LDS the wave keeps a [128 stored rows][ROWB bytes] image of its unit's output (ROWB = 128: 128 source
 // rows of FP8 codes or 256 of FP4 codes); 16-byte chunk c of row r sits at position c ^ ((r >> 1) & (CPR-1)).
-template <int FMT, int RULE, bool STATS, bool SR>
+template <int FMT, int RULE, bool STATS>
 __device__ __forceinline__ unsigned quant_one_column(const unsigned* w, unsigned am, uint8_t* __restrict__ lds_row,
-                                                     int rb_local, int swz, float& s0, float& se,
-                                                     int64_t e0, uint2 seed)      // e0: stored position of w[0]'s first element
+                                                     int rb_local, int swz, float& s0, float& se)
 {
     const unsigned byte = scale_byte<FMT, RULE>(am);
     const float sc = scale_operand(byte);
@@ -570,8 +589,7 @@ __device__ __forceinline__ unsigned quant_one_column(const unsigned* w, unsigned
         unsigned c[4];
 #pragma unroll
         for (int k = 0; k < 4; ++k) {
-            c[k] = SR ? enc4_sr_at(w + 4 * k, sc, e0 + 8 * k, seed)
-                      : enc4(w[4 * k], w[4 * k + 1], w[4 * k + 2], w[4 * k + 3], sc);
+            c[k] = enc4(w[4 * k], w[4 * k + 1], w[4 * k + 2], w[4 * k + 3], sc);
         }
         if (__builtin_amdgcn_ballot_w64(bad) != 0)                       // wave-uniform
 #pragma unroll
@@ -582,6 +600,30 @@ __device__ __forceinline__ unsigned quant_one_column(const unsigned* w, unsigned
             for (int k = 0; k < 4; ++k) err4(w + 4 * k, c[k], sc, s0, se, true);
         }
     }
+    return byte;
+}
+
+// The same with stochastic rounding, of the column in the low (HI: high) halves of v; grp: stored position of its first
+// element / 8, a multiple of 4.
+template <int RULE, bool HI>
+__device__ __forceinline__ unsigned quant_sr_column(const unsigned (&v)[32], unsigned am, uint8_t* __restrict__ lds_row, int rb_local,
+                                                    int swz, uint64_t grp, uint2 seed)
+{
+    const unsigned byte = scale_byte<kFP4, RULE>(am);
+    const float sc = scale_operand(byte);
+    const bool bad = byte == 0xFFu;
+    unsigned c[4];
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+        float e[8];
+#pragma unroll
+        for (int i = 0; i < 8; ++i) e[i] = __uint_as_float(HI ? v[8 * k + i] & 0xFFFF0000u : v[8 * k + i] << 16);
+        c[k] = enc4_sr_at(e, sc, grp | (unsigned)k, seed);
+    }
+    if (__builtin_amdgcn_ballot_w64(bad) != 0)                           // wave-uniform
+#pragma unroll
+        for (int k = 0; k < 4; ++k) c[k] = bad ? 0u : c[k];
+    *reinterpret_cast<uint4*>(lds_row + ((rb_local ^ swz) * 16)) = make_uint4(c[0], c[1], c[2], c[3]);
     return byte;
 }
 
@@ -624,11 +666,20 @@ __global__ __launch_bounds__(256) void quant_col_kernel(const uint16_t* __restri
         const int swz_lo = lane & (CPR - 1);          // ((2 * lane) >> 1) & (CPR - 1); the odd row shares it
         // row block kk of the unit: codes into the staging area, returns the two columns' scale bytes
         auto one_block = [&](int kk, unsigned& y0, unsigned& y1) {
-            ColBlock b;
-            load_col_block(x + (int64_t)(rb0 + kk) * kBlock * ld, cg * kColsPerWave, lane, cols, ld, b);
-            const int64_t e0 = (int64_t)c * rows + (int64_t)(rb0 + kk) * kBlock;       // stored row = source column
-            y0 = quant_one_column<FMT, RULE, STATS, SR>(b.lo, b.am_lo, reg + (2 * lane) * ROWB, kk, swz_lo, s0, se, e0, seed);
-            y1 = quant_one_column<FMT, RULE, STATS, SR>(b.hi, b.am_hi, reg + (2 * lane + 1) * ROWB, kk, swz_lo, s0, se, e0 + rows, seed);
+            unsigned v[32];
+            load_col_tile(x + (int64_t)(rb0 + kk) * kBlock * ld, cg * kColsPerWave, lane, cols, ld, v);
+            uint8_t* const r0 = reg + (2 * lane) * ROWB;
+            if (SR) {
+                const unsigned m = col_maxima(v);
+                const uint64_t grp = (uint64_t)c * (unsigned)(rows >> 3) + (unsigned)((rb0 + kk) * 4);         // stored row = source column
+                y0 = quant_sr_column<RULE, false>(v, m & 0xFFFFu, r0, kk, swz_lo, grp, seed);
+                y1 = quant_sr_column<RULE, true>(v, m >> 16, r0 + ROWB, kk, swz_lo, grp + (unsigned)(rows >> 3), seed);
+            } else {
+                ColBlock b;
+                pair_col_block(v, b);
+                y0 = quant_one_column<FMT, RULE, STATS>(b.lo, b.am_lo, r0, kk, swz_lo, s0, se);
+                y1 = quant_one_column<FMT, RULE, STATS>(b.hi, b.am_hi, r0 + ROWB, kk, swz_lo, s0, se);
+            }
         };
         // Four row blocks at a time (blocks 0 .. last of the group starting at rbh): their scale bytes of a column
         // form one dword of the row-major array (when the row length allows it) and exactly one dword of the
@@ -820,7 +871,6 @@ __global__ __launch_bounds__(qb_threads(NW, STATS), STATS ? 2 : 1) void quant_bo
     const int nblk = cols / kBlock;                       // blocks per row of the row-direction output
     const int pitch_x = (int)ld * 2;
     const int pitch_r = FMT_R == kFP8 ? cols : cols / 2, pitch_c = FMT_C == kFP8 ? rows : rows / 2;      // bytes of a stored row
-    const uint2 no_seed = make_uint2(0, 0);
     float s0 = 0.f, se_c = 0.f, se_r = 0.f;
     float so_c = 0.f, so_r = 0.f;                         // STATS == 2: error sums of the format not chosen
     // COOP, `runs`: units go to the XCDs (workgroup id mod 8) in contiguous runs, and a run walks pairs of row units column
@@ -892,8 +942,8 @@ __global__ __launch_bounds__(qb_threads(NW, STATS), STATS ? 2 : 1) void quant_bo
             if (STATS == 0) {
                 ColBlock b;
                 pair_col_block(cv, b);
-                y0 = quant_one_column<FMT_C, RULE, false, false>(b.lo, b.am_lo, reg + (2 * lane) * ROWB, k, swz_lo, s0, se_c, 0, no_seed);
-                y1 = quant_one_column<FMT_C, RULE, false, false>(b.hi, b.am_hi, reg + (2 * lane + 1) * ROWB, k, swz_lo, s0, se_c, 0, no_seed);
+                y0 = quant_one_column<FMT_C, RULE, false>(b.lo, b.am_lo, reg + (2 * lane) * ROWB, k, swz_lo, s0, se_c);
+                y1 = quant_one_column<FMT_C, RULE, false>(b.hi, b.am_hi, reg + (2 * lane + 1) * ROWB, k, swz_lo, s0, se_c);
             } else {
                 float xc[32];
 #pragma unroll
