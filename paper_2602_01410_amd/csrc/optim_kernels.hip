@@ -28,17 +28,17 @@ __device__ __forceinline__ float sens_any(float m, float v, float g, float c1, f
 }
 
 // The same where v is 0 or in [kLow, kHigh] (nothing under- or overflows on the way) and so is eps or d; `w` is v, or 1 in
-// place of 0.
+// place of 0.  (0 is told by ==: a NaN in v, which passes the range check of sens4, has to reach the term.)
 constexpr float kLow = 0x1p-96f, kHigh = 0x1p96f;
 __device__ __forceinline__ float sens_normal(float m, float v, float w, float g, float c1, float c2, float eps)
 {
     const float y = __builtin_amdgcn_rsqf(w);
     const float s = w * y;
     // s plus the rest of the root and eps, rounded once (eps is a fixed number of units in the last place of the root)
-    const float d = v > 0.f ? s + fmaf(fmaf(-s, s, w), 0.5f * y, eps) : eps;
+    const float d = v == 0.f ? eps : s + fmaf(fmaf(-s, s, w), 0.5f * y, eps);
     const float r0 = __builtin_amdgcn_rcpf(d);
     const float r = fmaf(r0, fmaf(-d, r0, 1.f), r0);
-    const float second = v > 0.f ? c2 * m * g * y * r * r : 0.f;        // (in this order nothing overflows that the quotient does not)
+    const float second = v == 0.f ? 0.f : c2 * m * g * y * r * r;        // (in this order nothing overflows that the quotient does not)
     const float q = c1 * r, first = fmaf(fmaf(-q, d, c1), r, q);
     return first - second;
 }

@@ -96,3 +96,23 @@ def test_adamw_ranges_of_v(low, high, eps):
         v[dead] = 0; m[dead] = 0; g[dead] = 0
     eps = float(np.float32(eps))
     assert run(snip, m, v, torch.from_numpy(g), eps=eps) == pytest.approx(oracle.adamw_sensitivity_sq(m, v, g, B1, B2, eps), rel=TOL)
+
+
+@pytest.mark.parametrize("lone", [False, True])
+@pytest.mark.parametrize("array,value", [("v", np.nan), ("v", -1e-6), ("v", np.inf), ("m", np.nan), ("m", np.inf), ("g", np.nan), ("g", -np.inf)])
+def test_adamw_not_a_number_reaches_the_sum(array, value, lone):
+    """One NaN, infinity or negative v at each position of a group of four among ordinary elements (n a multiple of 4), and with
+    an element out of the approximated root's range in the same wave: NaN, infinity or a sum as the oracle has it."""
+    snip = require_gpu()
+    rng = np.random.default_rng(113)
+    n = 4096
+    for at in (0, 1, 2, 3, 1022, 4095):
+        g = (1e-3 * rng.standard_normal(n)).astype(np.float32)
+        m = (0.3e-3 * rng.standard_normal(n)).astype(np.float32)
+        v = (1e-6 * (0.5 + rng.random(n))).astype(np.float32)
+        if not lone:
+            other = at // 256 * 256 + 8 + at % 4                     # a wave takes 256 consecutive elements
+            v[other], m[other], g[other] = 1e-30, 0, 0
+        {"m": m, "v": v, "g": g}[array][at] = value
+        want = oracle.adamw_sensitivity_sq(m, v, g, B1, B2, EPS)
+        assert run(snip, m, v, torch.from_numpy(g)) == pytest.approx(want, rel=TOL, nan_ok=True), at
