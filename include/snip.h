@@ -318,7 +318,10 @@ snip_status snip_quant_error_stats_paper(const void* x, int64_t rows, int64_t co
  *          8-byte aligned; e.g. the dW a wgrad call produced).
  *   beta1, beta2 in [0, 1), eps >= 0 (SNIP_ERR_FORMAT otherwise).
  *   sum_sq: device, one double.  workspace: device, required, >= snip_workspace_bytes(0, 0).
- * fp32 arithmetic with correctly rounded division and square root; fixed summation order. */
+ * fp32 arithmetic.  Each of the two parts of an element's term is within 5e-7 of its value: correctly rounded root
+ * and quotients, or, where v is zero or in [2^-96, 2^96] and eps in [2^-96, 1], approximated ones that are as close
+ * (root and eps are rounded together there).  Infinities, NaNs and negative v reach the sum as in the expression.
+ * Fixed summation order. */
 snip_status snip_adamw_sensitivity(const float* m, const float* v, const void* g,
                                    snip_out_dtype g_dtype, int64_t n, float beta1, float beta2,
                                    float eps, double* sum_sq, void* workspace,

@@ -4,10 +4,12 @@
 //     (1 - beta1) / (sqrt(v) + eps)  -  (1 - beta2) m g / (sqrt(v) (sqrt(v) + eps)^2),
 // and Step 1 of the method collects its Frobenius norm.  One streaming pass over m, v (fp32) and
 // g (fp32 or bf16): 12 or 10 bytes per element read, nothing written but one partial per wave: bound by
-// HBM.  fp32 arithmetic: square root and quotient come from the hardware's approximations and a Newton step each, the
-// root and eps are rounded together: the sum is within 2e-9 of 64-bit arithmetic, where a correctly rounded root plus eps
-// was 1.5e-8 off (eps is a constant number of units in the root's last place), and an element takes 27 vector instructions,
-// not 46.  Sums per lane and wave in fp32, across waves in double in a fixed order.
+// HBM.  fp32 arithmetic: square root and quotients come from the hardware's approximations and a Newton step each, the
+// root and eps are rounded together: over 2^20 elements the sum is within 4e-9 of 64-bit arithmetic, where a correctly rounded
+// root plus eps was up to 3e-8 off (eps is a constant number of units in the root's last place).  One element's squared first
+// part is 0.9e-7 off (rms; correctly rounded 0.9-1.0e-7), its second part 1.9e-7 (1.9-2.5e-7); with one approximated root
+// in the second part and no step for it it was 1.9-2.2e-7.  An element takes 29 vector instructions, not 46.  Sums per lane
+// (four, added in double) and wave in fp32, across waves in double in a fixed order.
 #include "snip_internal.h"
 
 namespace snip {
@@ -27,18 +29,18 @@ __device__ __forceinline__ float sens_any(float m, float v, float g, float c1, f
     return first - second;
 }
 
-// The same where v is 0 or in [kLow, kHigh] (nothing under- or overflows on the way) and so is eps or d; `w` is v, or 1 in
-// place of 0.  (0 is told by ==: a NaN in v, which passes the range check of sens4, has to reach the term.)
+// The same where v is 0 or in [kLow, kHigh] and eps in [kLow, 1] (nothing under- or overflows on the way that the result does
+// not); `w` is v, or 1 in place of 0.  A NaN in v reaches the term: it is told from 0 by ==, not by >.
 constexpr float kLow = 0x1p-96f, kHigh = 0x1p96f;
 __device__ __forceinline__ float sens_normal(float m, float v, float w, float g, float c1, float c2, float eps)
 {
     const float y = __builtin_amdgcn_rsqf(w);
-    const float s = w * y;
+    const float s = w * y, h = 0.5f * y;
     // s plus the rest of the root and eps, rounded once (eps is a fixed number of units in the last place of the root)
-    const float d = v == 0.f ? eps : s + fmaf(fmaf(-s, s, w), 0.5f * y, eps);
+    const float d = v == 0.f ? eps : s + fmaf(fmaf(-s, s, w), h, eps);
     const float r0 = __builtin_amdgcn_rcpf(d);
     const float r = fmaf(r0, fmaf(-d, r0, 1.f), r0);
-    const float second = v == 0.f ? 0.f : c2 * m * g * y * r * r;        // (in this order nothing overflows that the quotient does not)
+    const float second = v == 0.f ? 0.f : c2 * m * g * r * r * fmaf(h, fmaf(-s, y, 1.f), y);      // (1 / root last: it may be 2^48)
     const float q = c1 * r, first = fmaf(fmaf(-q, d, c1), r, q);
     return first - second;
 }
@@ -71,7 +73,7 @@ __global__ __launch_bounds__(256) void adamw_sens_kernel(const float* __restrict
     const int64_t nthreads = (int64_t)gridDim.x * 256;
     const int64_t tid = (int64_t)blockIdx.x * 256 + threadIdx.x;
     const int64_t n4 = n / 4;
-    const bool eps_normal = eps >= kLow && eps <= kHigh;
+    const bool eps_normal = eps >= kLow && eps <= 1.f;
     v4f acc4 = {0.f, 0.f, 0.f, 0.f};
     // streaming (non-temporal) loads: nothing is read twice and the three arrays exceed every cache
     auto load = [&](int64_t q, v4f& mm, v4f& vv, v4f& gg) {
@@ -90,7 +92,7 @@ __global__ __launch_bounds__(256) void adamw_sens_kernel(const float* __restrict
         load(q, mm, vv, gg);
         sens4(mm, vv, gg, c1, c2, eps, eps_normal, acc4);
     }
-    float acc = (acc4[0] + acc4[1]) + (acc4[2] + acc4[3]);
+    float acc = (float)(((double)acc4[0] + acc4[1]) + ((double)acc4[2] + acc4[3]));
     // the last n % 4 elements
     const int64_t i = n4 * 4 + tid;
     if (i < n) {
