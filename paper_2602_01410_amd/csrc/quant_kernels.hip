@@ -1122,12 +1122,13 @@ __global__ __launch_bounds__(256) void stats_col_kernel(const uint16_t* __restri
             for (int i = 0; i < 32; ++i) v[i] = act ? ld4(p + (int64_t)i * ld) : 0u;     // (with load_col_tile: 192 registers, 10 % slower)
 #pragma unroll
             for (int h = 0; h < 2; ++h) {
-                float xc[32];
+                float xc[32], sq[4] = {0.f, 0.f, 0.f, 0.f};          // (a block's squares on their own: fewer roundings of the large sum)
 #pragma unroll
                 for (int i = 0; i < 32; ++i) {
                     xc[i] = __uint_as_float(h ? v[i] & 0xFFFF0000u : v[i] << 16);
-                    a0[h] = fmaf(xc[i], xc[i], a0[h]);
+                    sq[i & 3] = fmaf(xc[i], xc[i], sq[i & 3]);
                 }
+                a0[h] += (sq[0] + sq[1]) + (sq[2] + sq[3]);
                 const unsigned am = magnitude_bits(max_abs<32>(xc));
                 both_errors<32, RULE>(xc, am, a4[h], a8[h]);
                 if (am >= 0x7F80u) { a4[h] = __builtin_nanf(""); a8[h] = __builtin_nanf(""); }

@@ -28,3 +28,19 @@ def test_workgroup_sums_are_not_rounded(call, unit, shape, monkeypatch):
         assert row[0].item() == col[0].item() == 2.0 ** 24 + 3
         field = 2 if fmt == snip.FP8 else 1
         assert row[field].item() == col[field].item() == 0.0
+
+
+def test_column_sums_of_squares_are_exact_on_constant_columns():
+    """65536 rows of one value per column, its square an odd number of 16 bits: 32 of them are 21 bits, and 32 such blocks of a
+    lane 26 bits with five zeros at the end.  fp32 holds each of these sums (not each of 1024 squares added one by one), and
+    the lanes' sums are added in double."""
+    snip = require_gpu()
+    rows, cols = 65536, 160
+    values = (torch.arange(cols, device="cuda") % 64 * 2 + 129).double() / 128
+    x = values.bfloat16().expand(rows, cols).contiguous()
+    lines = torch.empty((cols, 3), dtype=torch.float32, device="cuda")
+    total = snip.snip_quant_error_stats(x, snip.COL, per_line=lines)
+    want = rows * values.square()
+    assert torch.equal(lines[:, 0].double(), want)
+    # a wave adds 64 lanes' sums of two columns in fp32: seven roundings
+    assert abs(float(total[0]) / float(want.sum()) - 1) <= 7 * 2.0 ** -24
