@@ -205,14 +205,21 @@ __global__ __launch_bounds__(256) void paper_block_kernel(const uint16_t* __rest
             }
         } else {
             const float i8 = __fdiv_rn(1.f, s8), i4 = __fdiv_rn(1.f, s4);
+            // (at most 16 elements are added one by one before their sums meet those of the rows before: the rounding of a long
+            // chain leans one way)
 #pragma unroll
-            for (int j = 0; j < 8; ++j) {
-                const unsigned w[4] = {v[j].x, v[j].y, v[j].z, v[j].w};
-                float dummy = 0.f;
-                if (row0 + 4 * j < rows) {
-                    err8<kFP8>(w, s8, i8, s0, e8, true);
-                    err8<kFP4>(w, s4, i4, dummy, e4, false);
+            for (int h = 0; h < 4; ++h) {
+                float t0 = 0.f, t4 = 0.f, t8 = 0.f;
+#pragma unroll
+                for (int j = 2 * h; j < 2 * h + 2; ++j) {
+                    const unsigned w[4] = {v[j].x, v[j].y, v[j].z, v[j].w};
+                    float dummy = 0.f;
+                    if (row0 + 4 * j < rows) {
+                        err8<kFP8>(w, s8, i8, t0, t8, true);
+                        err8<kFP4>(w, s4, i4, dummy, t4, false);
+                    }
                 }
+                s0 += t0; e4 += t4; e8 += t8;
             }
         }
     }

@@ -173,3 +173,27 @@ def test_column_units_in_any_number(shape, fmt, group):
     x = torch.randn((rows, (cols + 7) // 8 * 8), generator=gen, device="cuda").bfloat16()[:, :cols]
     got, want = snip.snip_quantize_paper(x, fmt, snip.COL, group), snip.snip_quantize_paper(x.t().contiguous(), fmt, snip.ROW, group)
     assert torch.equal(got[0], want[0]) and torch.equal(got[1], want[1])
+
+
+def test_block_statistics_keep_small_rows_beside_large_ones():
+    """A lane's 64 elements of a block: 16 squares of 2^16 and 48 of 2^-4.  The sums of 16 are exact and so is 2^20 + 3; added one
+    by one the small squares are a half unit of the sum's last place each and vanish."""
+    snip = require_gpu()
+    x = torch.full((256, 384), 0.25, device="cuda", dtype=torch.bfloat16)
+    x[torch.arange(256, device="cuda") % 32 < 8] = 256.0
+    out = snip.snip_quant_error_stats_paper(x, snip.ROW, snip.BLOCK_128x128)
+    assert float(out[0]) == float(x.double().square().sum())
+
+
+def test_block_statistics_of_more_blocks_than_workgroups():
+    """2499 blocks of 128 x 128 along rows, the last band ragged, two per workgroup but for the last: the second one's maxima go to the other
+    set, and a block's magnitude differs from its neighbours', so that a maximum of the block before would show."""
+    snip = require_gpu()
+    rows, cols = 6500, 6272
+    gen = torch.Generator(device="cuda").manual_seed(135)
+    scale = torch.exp2(torch.randint(-8, 9, (51, 49), generator=gen, device="cuda").float())
+    x = torch.randn((rows, cols), generator=gen, device="cuda") * scale.repeat_interleave(128, 0)[:rows].repeat_interleave(128, 1)
+    x = x.bfloat16()
+    out = snip.snip_quant_error_stats_paper(x, snip.ROW, snip.BLOCK_128x128)
+    want = oracle.stats_paper(host(x.view(torch.int16)).view(np.uint16), oracle.ROW, oracle.BLOCK_128x128)
+    np.testing.assert_allclose(host(out), want, rtol=1e-5)
