@@ -89,7 +89,7 @@ template <int FA, int FB, class T> struct FCfg {
     static constexpr int LDS_BYTES = NST == 2 ? 159 * 1024 : NST * SLOT;
     static constexpr int STRIDE = NST == 2 ? LDS_BYTES - SLOT : SLOT;
     static constexpr int EPI_BYTES = NST == 2 ? 64 * 1024 : 32 * 1024;
-    static constexpr int epi_base(int last) { return NST == 2 ? last * (LDS_BYTES - EPI_BYTES) : last * STRIDE; }
+    static constexpr int epi_base(int last) { return NST == 2 ? (last ? LDS_BYTES - EPI_BYTES : 0) : last * STRIDE; }
     static constexpr int LA = A_BYTES / 1024 / NWAVE;            // 16-byte copy instructions per wave per stage
     static constexpr int LB = B_BYTES / 1024 / NWAVE;
     static constexpr int LS = S_BYTES / 256 / NWAVE;             // 4-byte copy instructions per wave per stage
@@ -478,17 +478,23 @@ __global__ __launch_bounds__(NT) void gemm_fast_kernel(const uint8_t* __restrict
             for (int b = 0; b < NB; ++b)
 #pragma unroll
                 for (int k = 0; k < 16; ++k) acc[a][b][k] = 0.f;
-        int slot = par;                                             // buffer of stage s
+        // Buffer of stage s.  With two buffers it follows from s; this and what comes of it below keeps the forms that two buffers
+        // need, without those for more: fewer scalar instructions in a stage.  256 x 256 is 0.6 % faster so from memory (18 shapes,
+        // all formats) and 1.8 % on operands in the caches ([3072 x 3072 x 8192] FP8 75.6 -> 73.0 us).
+        int ring = par;
+        auto slot_of = [&](int s) { return NST == 2 ? (s + par) & 1 : ring; };
+        const int ebase2 = NST == 2 ? C::epi_base((nstage - 1 + par) & 1) : 0;
         if (wave < NWAVE / 2) {
             // group 0 issues its copies of stage s + NST - 1 during M0(s), between b(4s+1) and b(4s+2); during the last
             // NST - 1 stages these are the copies of the next tile's first stages
             auto stage0 = [&](auto copy_tag, int s, int cstage) {
+                const int slot = slot_of(s);
                 // the first NST - 1 stages of a later tile were waited for before the previous tile's result was stored;
                 // waiting for them here again would wait for those stores
                 if (first || s >= NST - 1) SNIP_WAIT_VM((NST - 2) * C::L);
                 SNIP_BAR();                                         // b(4s)
                 RD(slot, 0, s); SNIP_BAR();      // b(4s+1)
-                MM(copy_tag, 0, cstage, before(slot));
+                MM(copy_tag, 0, cstage, NST == 2 ? slot ^ 1 : before(slot));
                 if (PH == 2) {
                     SNIP_BAR();                                     // b(4s+2)
                     RD(slot, 1, s); SNIP_BAR();  // b(4s+3)
@@ -499,11 +505,13 @@ __global__ __launch_bounds__(NT) void gemm_fast_kernel(const uint8_t* __restrict
             // of the result store cost the register allocator its in-place accumulators).  Without a next tile the
             // last stages' copies re-fetch the first stages of this tile into free buffers, where nobody reads them.
             for (int s = 0; s < nstage; ++s) {
-                const int c = s + NST - 1, cs = c >= nstage ? c - nstage : c;
-                if (c == nstage && has_next) set_copy_tile(un);
+                const int c = s + NST - 1;
+                const bool past = NST == 2 ? s == nstage - 1 : c >= nstage;
+                const int cs = past ? (NST == 2 ? 0 : c - nstage) : c;
+                if ((NST == 2 ? past : c == nstage) && has_next) set_copy_tile(un);
                 cut_tail(cs);
                 stage0(with_copy, s, cs);
-                slot = after(slot);
+                if (NST > 2) ring = after(ring);
             }
             SNIP_BAR();                                             // b(4S)
             SNIP_WAIT_VM(0);                                        // own shares of the next tile's first stages
@@ -512,6 +520,7 @@ __global__ __launch_bounds__(NT) void gemm_fast_kernel(const uint8_t* __restrict
             // later those of the next tile's first stages, during M1(S-1) none); those of stage NST - 1 while it idles
             // through the tile's first phase
             auto stage1 = [&](auto copy_tag, int s, int cstage) {
+                const int slot = slot_of(s);
                 SNIP_BAR();                                         // b(4s+1)
                 RD(slot, 0, s);
                 if (PH == 2) {
@@ -519,31 +528,37 @@ __global__ __launch_bounds__(NT) void gemm_fast_kernel(const uint8_t* __restrict
                     MM(no_copy, 0, 0, 0); SNIP_BAR();               // b(4s+3)
                     RD(slot, 1, s);
                 }
-                if (NST == 2 || first || s >= NST - 2) SNIP_WAIT_VM((NST - 2) * C::L);      // stage s + 1 (see stage0)
-                __builtin_amdgcn_s_waitcnt(0xC07F);                 // lgkmcnt(0)
+                if (NST == 2) {
+                    __builtin_amdgcn_s_waitcnt(0x0070);             // vmcnt(0) and lgkmcnt(0)
+                } else {
+                    if (first || s >= NST - 2) SNIP_WAIT_VM((NST - 2) * C::L);              // stage s + 1 (see stage0)
+                    __builtin_amdgcn_s_waitcnt(0xC07F);             // lgkmcnt(0)
+                }
                 SNIP_BAR();                                         // b(4s+4)
                 MM(copy_tag, PH - 1, cstage, slot);
             };
             if (first) SNIP_WAIT_VM((NST - 2) * C::L);
             SNIP_BAR();                                             // b(0)
             cut_tail(NST - 1);
-            issue(NST - 1, before(par));
+            issue(NST - 1, NST == 2 ? (1 + par) & 1 : before(par));
             // (without a next tile the last copies re-fetch the first stages of this tile into free buffers)
             for (int s = 0; s < nstage - 1; ++s) {
-                const int c = s + NST, cs = c >= nstage ? c - nstage : c;
-                if (c == nstage && has_next) set_copy_tile(un);
+                const int c = s + NST;
+                const bool past = NST == 2 ? s == nstage - 2 : c >= nstage;
+                const int cs = past ? (NST == 2 ? 0 : c - nstage) : c;
+                if ((NST == 2 ? past : c == nstage) && has_next) set_copy_tile(un);
                 cut_tail(cs);
                 stage1(with_copy, s, cs);
-                slot = after(slot);
+                if (NST > 2) ring = after(ring);
             }
             stage1(no_copy, nstage - 1, 0);
-            slot = after(slot);
+            if (NST > 2) ring = after(ring);
             if (NST > 2) SNIP_WAIT_VM(0);                           // (nothing may land in LDS after the workgroup's end either)
         }
-        store_tile(u, C::epi_base(before(slot)));
+        store_tile(u, NST == 2 ? ebase2 : C::epi_base(before(ring)));
         if (!has_next) break;
         u = un;
-        par = slot;
+        par = NST == 2 ? (par + nstage) & 1 : ring;
         first = false;
     }
 }
