@@ -375,7 +375,7 @@ static bool fast_tile(GemmTile t) { return t == GemmTile::kBig || t == GemmTile:
 
 static bool tile_usable(const GemmArgs& a, GemmTile t)
 {
-    if (fast_tile(t)) return gemm_fast_eligible(a, t);
+    if (fast_tile(t)) return gemm_fast_eligible(a);
     if (t == GemmTile::kGeneral) return true;
     // an output norm has room for one partial per 128 x 128 tile
     return gemm_small_eligible(a) && (!a.norm_out || t == GemmTile::k128x128);

@@ -120,7 +120,7 @@ hipError_t launch_gemm(const GemmArgs& a, hipStream_t s);
 // Workgroup tiles of the GEMM kernels: the persistent kernel's (gemm_fast.hip), those of one tile per workgroup
 // (gemm_small.hip) and the general kernel's (gemm.hip).
 enum class GemmTile { kBig, kWide, k128x128, k64x64, k64x32, k32x32, kGeneral };
-bool gemm_fast_eligible(const GemmArgs& a, GemmTile tile);
+bool gemm_fast_eligible(const GemmArgs& a);
 bool gemm_small_eligible(const GemmArgs& a);
 hipError_t launch_gemm_fast(const GemmArgs& a, GemmTile tile, hipStream_t s);
 hipError_t launch_gemm_small(const GemmArgs& a, GemmTile tile, hipStream_t s);

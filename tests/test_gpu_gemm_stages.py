@@ -1,7 +1,8 @@
-"""The 256 x 128 GEMM tile (three stage buffers, one phase a stage) against the 256 x 256 one (two and two) and the general
-kernel: all add the products of an output element in the same order, so every byte of the result agrees.  Stage counts: the
-fewest it takes, one and two more (each start of the ring of buffers for a second tile), whole and cut last stages; one
-tile, ragged tiles, more tiles than compute units (the next tile's first stages are copied before the result is stored)."""
+"""The 256 x 128 GEMM tile (three stage buffers and one phase a stage, two and two for contractions of two stages) against the
+256 x 256 one (two and two) and the general kernel: all add the products of an output element in the same order, so every byte
+of the result agrees.  Stage counts: the fewest of either, and up to two more (each start of the ring of buffers for a second
+tile), whole and cut last stages; one tile, tiles that end a row and a few columns after another, ragged tiles, more tiles than
+compute units (the next tile's first stages are copied before the result is stored)."""
 import pytest
 import torch
 
@@ -11,9 +12,9 @@ pytestmark = pytest.mark.gpu
 
 
 @pytest.mark.parametrize("fmts", [(0, 0), (1, 1), (0, 1), (1, 0)])
-@pytest.mark.parametrize("stages", [3, 4, 5])
+@pytest.mark.parametrize("stages", [2, 3, 4, 5])
 @pytest.mark.parametrize("cut", [0, 96])
-@pytest.mark.parametrize("shape", [(256, 128), (300, 200), (4400, 2300)])
+@pytest.mark.parametrize("shape", [(256, 256), (257, 136), (300, 200), (4400, 2300)])
 def test_same_bytes_in_both_tiles(shape, cut, stages, fmts, monkeypatch):
     snip = require_gpu()
     i, j = shape
