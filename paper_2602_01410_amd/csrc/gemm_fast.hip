@@ -70,8 +70,10 @@ using TileBig = TileCfg<256, 256, 128, 64, 2, 2>;
 // FP4 18.5 -> 17.4, FP8 24.4 -> 23.2, [4096 x 2048 x 8192] 44.8 -> 43.0 and 68.6 -> 65.5, [8192 x 3072 x 3072] 59.0 -> 55.8 and 84.8 -> 82.9,
 // [3072 x 8192 x 8192] 118 -> 112 and 186 -> 175; operands in the caches 2-9 %.
 using TileWide = TileCfg<256, 128, 64, 64, 3, 1>;
-// The same tile for contractions of two stages, which three buffers do not take.  Against the best other tile: [15616 x 384 x 512]
-// FP4 11.3 -> 8.3 us, [10304 x 672 x 384] 11.8 -> 9.2, [2048 x 3456 x 512] 10.3 -> 8.1.
+// The same tile for contractions of two stages, which three buffers do not take, and of three whole ones, where the result's two
+// passes cost more than the third buffer gives.  Two stages against the best other tile: [15616 x 384 x 512] FP4 11.3 -> 8.3 us,
+// [10304 x 672 x 384] 11.8 -> 9.2, [2048 x 3456 x 512] 10.3 -> 8.1.  Three against three buffers, 10 outputs in all formats: -3.3 %
+// (cached) and 0 (memory) over several rounds, -1.2 and -2.2 % in one; three stages of which the last is cut +5 ... +7 %, four +3 ... +8 %.
 using TileShort = TileCfg<256, 128, 64, 64, 2, 2>;
 
 template <int FA, int FB, class T> struct FCfg {
@@ -129,7 +131,7 @@ __global__ __launch_bounds__(NT) void gemm_fast_kernel(const uint8_t* __restrict
 
     const int64_t a_row_bytes = FA == kFP8 ? R : R / 2;
     const int64_t b_row_bytes = FB == kFP8 ? R : R / 2;
-    const int nstage = (R + C::KE - 1) / C::KE;                       // >= NST (gemm_fast_eligible)
+    const int nstage = (R + C::KE - 1) / C::KE;                       // >= NST (launch_gemm_fast)
     const int ngrp = (R + 127) / 128;                                 // scale groups of a row
     const int64_t a_pitch = g4_pitch(I), b_pitch = g4_pitch(J);      // dwords per scale group
 
@@ -620,7 +622,8 @@ bool gemm_fast_eligible(const GemmArgs& a)
 hipError_t launch_gemm_fast(const GemmArgs& a, GemmTile tile, hipStream_t s)
 {
     if (tile == GemmTile::kBig) return launch_fast_tile<TileBig>(a, s);
-    return a.R > (TileWide::NST - 1) * stage_extent(a) ? launch_fast_tile<TileWide>(a, s) : launch_fast_tile<TileShort>(a, s);
+    const int64_t ke = stage_extent(a);
+    return a.R > 2 * ke && a.R != 3 * ke ? launch_fast_tile<TileWide>(a, s) : launch_fast_tile<TileShort>(a, s);
 }
 
 }  // namespace snip
