@@ -347,27 +347,28 @@ int gemm_compute_units()
 // 512 MB on they are in memory.  A training step touches 9-15 times a GEMM's operands for one linear, 60-100 times for a
 // block of seven, so in a block operands of a few MB already come from memory; kColdBytes of operands is where the second
 // table takes over.  It costs little to be wrong: on operands of more than that in the caches the second table's pick is on
-// average 0.2 % slower than the fastest tile (8 % at worst), on less from memory the first table's 0.3 % (11 %).
-// Fitted to 182 and 107 problems timed with every tile: the GEMMs of 1B-, 3B- and 7B-shaped blocks and random ones (64 ...
-// 16384 tokens, widths 64 ... 11008, FP4 and FP8); the tiles from 128 x 128 on anew to 154 of them when 256 x 128 got its third
-// stage buffer, and 256 x 128 by what single-phase stages gained on 36.  The pick is on average 0.25 and 0.13 % slower than the
-// fastest tile (9 % at worst).  From memory the 256 x 128 tile beats 256 x 256
-// where rounds of the larger one would be half empty: [8192 x 3072 x 3072] FP8 87 -> 82 us, [4096 x 2048 x 8192] FP4 57 -> 43.
+// average 0.6 % slower than the fastest tile, on less from memory the first table's 0.1 %.
+// Fitted to 2847 problems timed with every tile (the GEMMs of 1B- to 70B-shaped blocks, 1 ... 512 tokens against a block's
+// weights, outputs just past whole rounds with contractions of 1024 ... 16384, random ones of 64 ... 16384 rows; three format
+// pairs), `tail` at least `alone`: a lower one fits some long contractions better and picks tiles whose last round is a
+// quarter full ([2048 x 2304 x 3072] FP8 37 us with 128 x 128 for 26 with 256 x 128).  On 1233 other problems the pick is on
+// average 0.2 % (cached, up to 10 MB) and 0.5 % (from memory, more) slower than the fastest tile, 20 % at worst (rows of few
+// tokens by very wide weights, where the tables are rough).
 struct TileCost { GemmTile tile; int m, n; float start, turn, alone[2], full[2], tail[2]; };      // [0]: FP4 x FP4, [1]: others
 static const TileCost kTileCosts[2][6] = {{
-    {GemmTile::kBig,       256, 256, 7.5f, 4.5f, {1.51f, 0.80f}, {1.67f, 1.48f}, {0.83f, 0.74f}},
-    {GemmTile::kWide,      256, 128, 7.2f, 2.0f, {0.45f, 0.35f}, {0.92f, 0.73f}, {0.98f, 0.46f}},
-    {GemmTile::k128x128,   128, 128, 4.7f, 3.6f, {0.37f, 0.33f}, {0.54f, 0.46f}, {0.47f, 0.29f}},
-    {GemmTile::k64x64,      64,  64, 3.1f, 1.0f, {0.17f, 0.17f}, {0.20f, 0.19f}, {0.25f, 0.14f}},
-    {GemmTile::k64x32,      64,  32, 3.1f, 1.4f, {0.16f, 0.16f}, {0.19f, 0.18f}, {0.18f, 0.19f}},
-    {GemmTile::k32x32,      32,  32, 2.9f, 1.2f, {0.13f, 0.13f}, {0.15f, 0.14f}, {0.13f, 0.13f}},
+    {GemmTile::kBig,      256, 256, 7.7f, 4.5f, {0.61f, 0.62f}, {1.90f, 1.42f}, {0.61f, 0.62f}},
+    {GemmTile::kWide,     256, 128, 6.6f, 2.4f, {0.45f, 0.39f}, {0.94f, 0.70f}, {0.49f, 0.41f}},
+    {GemmTile::k128x128,  128, 128, 4.8f, 2.4f, {0.27f, 0.27f}, {0.59f, 0.45f}, {0.35f, 0.27f}},
+    {GemmTile::k64x64,     64,  64, 3.2f, 0.8f, {0.16f, 0.17f}, {0.22f, 0.17f}, {0.16f, 0.17f}},
+    {GemmTile::k64x32,     64,  32, 3.2f, 0.8f, {0.14f, 0.14f}, {0.18f, 0.13f}, {0.22f, 0.14f}},
+    {GemmTile::k32x32,     32,  32, 3.0f, 0.8f, {0.12f, 0.13f}, {0.15f, 0.11f}, {0.20f, 0.13f}},
 }, {
-    {GemmTile::kBig,       256, 256, 10.5f, 5.5f, {1.12f, 1.14f}, {1.67f, 1.51f}, {1.05f, 0.97f}},
-    {GemmTile::kWide,      256, 128, 8.3f, 2.6f, {0.71f, 0.68f}, {1.00f, 0.85f}, {1.25f, 0.50f}},
-    {GemmTile::k128x128,   128, 128, 5.2f, 2.7f, {0.53f, 0.53f}, {0.66f, 0.57f}, {0.05f, 0.05f}},
-    {GemmTile::k64x64,      64,  64, 4.4f, 1.0f, {0.30f, 0.30f}, {0.22f, 0.23f}, {0.45f, 0.34f}},
-    {GemmTile::k64x32,      64,  32, 3.6f, 1.1f, {0.17f, 0.17f}, {0.28f, 0.23f}, {0.20f, 0.20f}},
-    {GemmTile::k32x32,      32,  32, 3.2f, 1.2f, {0.13f, 0.13f}, {0.18f, 0.18f}, {0.14f, 0.12f}},
+    {GemmTile::kBig,      256, 256, 11.3f, 5.3f, {1.07f, 1.04f}, {1.88f, 1.48f}, {1.07f, 1.04f}},
+    {GemmTile::kWide,     256, 128, 8.2f, 2.8f, {0.68f, 0.58f}, {1.01f, 0.80f}, {0.68f, 0.58f}},
+    {GemmTile::k128x128,  128, 128, 6.9f, 3.0f, {0.56f, 0.50f}, {0.66f, 0.54f}, {0.56f, 0.50f}},
+    {GemmTile::k64x64,     64,  64, 5.5f, 0.3f, {0.20f, 0.28f}, {0.26f, 0.22f}, {0.31f, 0.28f}},
+    {GemmTile::k64x32,     64,  32, 4.0f, 0.9f, {0.14f, 0.14f}, {0.24f, 0.18f}, {0.17f, 0.14f}},
+    {GemmTile::k32x32,     32,  32, 3.8f, 1.4f, {0.12f, 0.13f}, {0.18f, 0.15f}, {0.14f, 0.14f}},
 }};
 constexpr double kColdBytes = 10e6;
 
