@@ -913,7 +913,7 @@ __global__ __launch_bounds__(qb_threads(NW, STATS), STATS ? 2 : 1) void quant_bo
             if ((nrb & 3) == 0) {
                 __builtin_amdgcn_raw_buffer_store_b32(lo, ss, voff, 0, 0);
                 __builtin_amdgcn_raw_buffer_store_b32(hi, ss, voff, nrb, 0);
-            } else {
+            } else if (!COOP) {
                 for (int i = 0; i <= last; ++i) {
                     __builtin_amdgcn_raw_buffer_store_b8((uint8_t)(lo >> (8 * i)), ss, voff, i, 0);
                     __builtin_amdgcn_raw_buffer_store_b8((uint8_t)(hi >> (8 * i)), ss, voff, nrb + i, 0);
@@ -1029,7 +1029,12 @@ __global__ __launch_bounds__(qb_threads(NW, STATS), STATS ? 2 : 1) void quant_bo
             if ((nblk & 3) == 0) {
                 __builtin_amdgcn_raw_buffer_store_b32(d, ss, soff_r, 0, 0);
             } else {
-                for (int i = 0; i < min(4, nblk - cg * 4); ++i) __builtin_amdgcn_raw_buffer_store_b8((uint8_t)((unsigned)d >> (8 * i)), ss, soff_r, i, 0);
+                // (four lanes to a row: all of a quad hold both dwords)
+                int l = lane;
+                asm volatile("" : "+v"(l));                    // (computed here, kept over the units it is registers that other waves need)
+                const int b = l & 3, off = cg * 4 + b < nblk ? (4 * ((l >> 2) & 3) + (l >> 4)) * nblk + b : kPast;
+                __builtin_amdgcn_raw_buffer_store_b8((uint8_t)((unsigned)d_lo >> (8 * b)), ss, off, 0, 0);
+                __builtin_amdgcn_raw_buffer_store_b8((uint8_t)((unsigned)d_hi >> (8 * b)), ss, off, 16 * nblk, 0);
             }
             if (g4_r) __builtin_amdgcn_raw_buffer_store_b32(d, tile_rsrc(g4_r + ((int64_t)cg * kpitch_r + row0) * 4), mine ? row * 4 : kPast, 0, 0);
         };
@@ -1069,6 +1074,16 @@ __global__ __launch_bounds__(qb_threads(NW, STATS), STATS ? 2 : 1) void quant_bo
                 }
                 store_col_scales(rb0 + 4 * g, last, lo, hi);
             }
+            // Rows of no whole number of dwords: bytes, four lanes to a column, the columns dealt to the waves (a lane for two whole
+            // columns, in one wave, is four times the requests).
+            if ((nrb & 3) != 0)
+                for (int p = wib; p < (nb + 3) / 4 * 8; p += WPB) {
+                    int l = lane;
+                    asm volatile("" : "+v"(l));
+                    const int blk = p / 8 * 4 + (l & 3), col = p % 8 * 16 + (l >> 2);
+                    __builtin_amdgcn_raw_buffer_store_b8(scale_stage[blk * kColsPerWave + col], tile_rsrc(scales_c + (int64_t)c0 * nrb + rb0),
+                                                         blk < nb && c0 + col < cols ? col * nrb + blk : kPast, 0, 0);
+                }
         }
         const rsrc_t sc_codes = tile_rsrc(codes_c + (int64_t)c0 * pitch_c + (int64_t)ru * ROWB);
         int l = lane;
