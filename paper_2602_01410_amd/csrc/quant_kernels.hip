@@ -1448,12 +1448,16 @@ static int launch_qb_form(const QuantBothArgs& a, double* partials, hipStream_t 
     const int64_t most = STATS ? kStreamBlocks / 8 : (int64_t)1 << 24, run = (units + 7) / 8, share = (run + most - 1) / most;
     const int blocks = NW ? (int)(8 * ((run + share - 1) / share)) : balanced_blocks(units);
     // Order of the units (see quant_both_kernel): runs below 8 M elements, where the tensor fits the L2s ([1504 x 2080] FP4 6.1
-    // against 6.7 us dealt), and without statistics for rows of more than 12288 columns, if they start on whole lines of 256 bytes
+    // against 6.7 us dealt), below 24 M if rows hold no whole number of four blocks, so that their scale bytes share dwords and lines
+    // with the neighbours' at odd places ([896 x 9408] FP4 11.4 (dealt) -> 9.9, [2432 x 4896] 14.8 -> 12.5, [4096 x 4128] 20.1 -> 15.3,
+    // [3264 x 5952] 20.6 -> 18.7, FP8 23.3 -> 22.4, with statistics [2432 x 4896] 19.2 -> 17.3; whole groups [2080 x 4096] 8.9 -> 11.1),
+    // and without statistics for rows of more than 12288 columns, if they start on whole lines of 256 bytes
     // ([8192 x 16384] FP4 103.9 (dealt) -> 96.1, FP8 127.7 -> 123.1, [4096 x 28672] 91.8 -> 86.6 and 120 -> 110, [16384 x 14336] 182
     // -> 170 and 223 -> 212; FP8 rows beside FP4 columns 98.7 -> 96.5 on [4096 x 28672], 109.0 -> 111.5 on [8192 x 16384]).
     // Elsewhere the eight runs, far apart, meet in few memory channels: [8160 x 8160] FP4 81.5 (runs) -> 68.4, [16384 x 8192] 105.8
     // -> 98.1, [8192 x 11008] 74.9 -> 70.4, FP8 88.4 -> 85.2, [8192 x 4096] 34.7 -> 33.3.
-    const bool runs = a.rows * a.cols < ((int64_t)8 << 20) || (STATS == 0 && a.cols > 12288 && a.ld % 128 == 0);
+    const int64_t near = a.cols % (4 * kBlock) != 0 ? (int64_t)24 << 20 : (int64_t)8 << 20;
+    const bool runs = a.rows * a.cols < near || (STATS == 0 && a.cols > 12288 && a.ld % 128 == 0);
     hipLaunchKernelGGL((quant_both_kernel<FMT_R, FMT_C, RULE, STATS, NW, RBU>), dim3(blocks), dim3(qb_threads(NW, STATS)), 0, s,
                        a.x, (int)a.rows, (int)a.cols, a.ld, a.codes_r, a.scales_r, a.g4_r, g4_pitch(a.rows),
                        a.codes_c, a.scales_c, a.g4_c, g4_pitch(a.cols), partials, runs);
