@@ -694,7 +694,7 @@ __global__ __launch_bounds__(256) void quant_col_kernel(const uint16_t* __restri
                 if ((nrb & 3) == 0) {
                     *reinterpret_cast<unsigned*>(s_lo) = lo;
                     *reinterpret_cast<unsigned*>(s_lo + nrb) = hi;
-                } else {
+                } else if (!COOP) {
                     for (int k = 0; k <= last; ++k) { s_lo[k] = (uint8_t)(lo >> (8 * k)); s_lo[nrb + k] = (uint8_t)(hi >> (8 * k)); }
                 }
                 if (scales_g4)
@@ -718,6 +718,14 @@ __global__ __launch_bounds__(256) void quant_col_kernel(const uint16_t* __restri
                 }
                 store_scales(rb0 + h * kRowBlocksPerUnit, last, lo, hi);
             }
+            // (as in quant_both_kernel)
+            if ((nrb & 3) != 0)
+                for (int p = wib; p < (nb + 3) / 4 * 8; p += kWavesPerBlock) {
+                    int l = lane;
+                    asm volatile("" : "+v"(l));
+                    const int blk = p / 8 * 4 + (l & 3), col = p % 8 * 16 + (l >> 2), to = cg * kColsPerWave + col;
+                    if (blk < nb && to < cols) scales[(int64_t)to * nrb + rb0 + blk] = scale_stage[blk * kColsPerWave + col];
+                }
         } else {
             for (int h = 0; h < RBU / kRowBlocksPerUnit; ++h) {
                 const int nbh = min(nb - h * kRowBlocksPerUnit, kRowBlocksPerUnit);
