@@ -68,7 +68,7 @@ def test_norm_with_ragged_contraction(fmt, monkeypatch):
         assert float(nrm[0]) == pytest.approx(float(y.double().square().sum()), rel=5e-6), tile
 
 
-@pytest.mark.parametrize("tile", TILES + ("ahead",))
+@pytest.mark.parametrize("tile", TILES)
 def test_no_scale_behind_the_last_group_is_read(tile, monkeypatch):
     """FP4 with an odd number of scale groups, several tiles each way: the last stage's second group does not exist.  Behind
     the grouped copies lie bytes that mean "not a number"."""

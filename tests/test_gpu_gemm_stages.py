@@ -19,6 +19,7 @@ def test_same_bytes_in_both_tiles(shape, cut, stages, fmts, monkeypatch):
     snip = require_gpu()
     i, j = shape
     r = stages * (256 if fmts == (1, 1) else 128) - cut
+    assert i > 128 and j > 128                                   # with two stages and more: what the two large tiles take
     gen = torch.Generator(device="cuda").manual_seed(i + j + r)
     a = snip.snip_quantize(torch.randn((i, r), generator=gen, device="cuda").bfloat16(), fmts[0], snip.ROW)
     b = snip.snip_quantize(torch.randn((j, r), generator=gen, device="cuda").bfloat16(), fmts[1], snip.ROW)

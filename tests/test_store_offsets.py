@@ -16,8 +16,15 @@ def with_scalar_offset(lines):
     return [line for line in lines if re.search(r"buffer_store_dwordx[34]\s+\S+\s+\S+\s+s\[\d+:\d+\],\s+s\d+\b", line)]
 
 
+def test_scan_finds_a_store_with_a_scalar_offset():
+    bad = ["\tbuffer_store_dwordx4 v[2:5], v10, s[24:27], s65 offen // x", "\tbuffer_store_dwordx3 v[2:4], v10, s[24:27], s3 offen offset:16",
+           "\tbuffer_store_dwordx4 v[2:5], off, s[24:27], s65"]
+    good = ["\tbuffer_store_dwordx4 v[2:5], v10, s[24:27], 0 offen", "\tbuffer_store_dwordx2 v[2:3], v10, s[24:27], s65 offen",
+            "\tbuffer_store_dwordx4 v[2:5], off, s[24:27], 0 offset:16", "\tglobal_store_dwordx4 v[0:1], v[2:5], off"]
+    assert with_scalar_offset([line for pair in zip(bad + [""], good) for line in pair]) == bad
+
+
 def test_library(tmp_path):
-    assert with_scalar_offset(["\tbuffer_store_dwordx4 v[2:5], v10, s[24:27], s65 offen // x\n", "\tbuffer_store_dwordx4 v[2:5], v10, s[24:27], 0 offen\n"])[1:] == []
     if not os.path.exists(OBJDUMP):
         pytest.skip("no disassembler")
     stores = 0
