@@ -40,11 +40,9 @@ __device__ __forceinline__ uint4 ld16(const uint16_t* p)
     const v4u_t v = __builtin_nontemporal_load(reinterpret_cast<const v4u_t*>(p));
     return make_uint4(v[0], v[1], v[2], v[3]);
 }
-template <bool LAST_USE = true>
 __device__ __forceinline__ unsigned ld4(const uint16_t* p)
 {
-    if (LAST_USE) return __builtin_nontemporal_load(reinterpret_cast<const unsigned*>(p));
-    return *reinterpret_cast<const unsigned*>(p);
+    return __builtin_nontemporal_load(reinterpret_cast<const unsigned*>(p));
 }
 
 __device__ __forceinline__ unsigned pk_max_u16(unsigned a, unsigned b)
@@ -212,31 +210,31 @@ __device__ __forceinline__ void acc_sq(unsigned w, float& s0)
 {
     asm("v_dot2c_f32_bf16 %0, %1, %1" : "+v"(s0) : "v"(w));
 }
-__device__ __forceinline__ void acc_err(float2_t q, unsigned w, float& s0, float& se, bool want_s0)
+__device__ __forceinline__ void acc_err(float2_t q, unsigned w, float& s0, float& se)
 {
     const float xl = __uint_as_float(w << 16), xh = __uint_as_float(w & 0xFFFF0000u);
     const float dl = q[0] - xl, dh = q[1] - xh;
     se = fmaf(dl, dl, se);
     se = fmaf(dh, dh, se);
-    if (want_s0) acc_sq(w, s0);
+    acc_sq(w, s0);
 }
 
 // Error sums of 8 source elements w[0..3] against their FP8 codes c[0..1].
 __device__ __forceinline__ void err8(const unsigned* w, unsigned c0, unsigned c1, float sc,
-                                     float& s0, float& se, bool want_s0)
+                                     float& s0, float& se)
 {
-    acc_err(__builtin_amdgcn_cvt_scalef32_pk_f32_fp8(c0, sc, false), w[0], s0, se, want_s0);
-    acc_err(__builtin_amdgcn_cvt_scalef32_pk_f32_fp8(c0, sc, true),  w[1], s0, se, want_s0);
-    acc_err(__builtin_amdgcn_cvt_scalef32_pk_f32_fp8(c1, sc, false), w[2], s0, se, want_s0);
-    acc_err(__builtin_amdgcn_cvt_scalef32_pk_f32_fp8(c1, sc, true),  w[3], s0, se, want_s0);
+    acc_err(__builtin_amdgcn_cvt_scalef32_pk_f32_fp8(c0, sc, false), w[0], s0, se);
+    acc_err(__builtin_amdgcn_cvt_scalef32_pk_f32_fp8(c0, sc, true),  w[1], s0, se);
+    acc_err(__builtin_amdgcn_cvt_scalef32_pk_f32_fp8(c1, sc, false), w[2], s0, se);
+    acc_err(__builtin_amdgcn_cvt_scalef32_pk_f32_fp8(c1, sc, true),  w[3], s0, se);
 }
 __device__ __forceinline__ void err4(const unsigned* w, unsigned c, float sc,
-                                     float& s0, float& se, bool want_s0)
+                                     float& s0, float& se)
 {
-    acc_err(__builtin_amdgcn_cvt_scalef32_pk_f32_fp4(c, sc, 0), w[0], s0, se, want_s0);
-    acc_err(__builtin_amdgcn_cvt_scalef32_pk_f32_fp4(c, sc, 1), w[1], s0, se, want_s0);
-    acc_err(__builtin_amdgcn_cvt_scalef32_pk_f32_fp4(c, sc, 2), w[2], s0, se, want_s0);
-    acc_err(__builtin_amdgcn_cvt_scalef32_pk_f32_fp4(c, sc, 3), w[3], s0, se, want_s0);
+    acc_err(__builtin_amdgcn_cvt_scalef32_pk_f32_fp4(c, sc, 0), w[0], s0, se);
+    acc_err(__builtin_amdgcn_cvt_scalef32_pk_f32_fp4(c, sc, 1), w[1], s0, se);
+    acc_err(__builtin_amdgcn_cvt_scalef32_pk_f32_fp4(c, sc, 2), w[2], s0, se);
+    acc_err(__builtin_amdgcn_cvt_scalef32_pk_f32_fp4(c, sc, 3), w[3], s0, se);
 }
 
 // The same on elements unpacked to fp32, which is what the statistics work on: unpacked once, an element serves the block's
@@ -388,7 +386,7 @@ __global__ __launch_bounds__(256) void quant_row_kernel(const uint16_t* __restri
             if (FMT == kFP8) {
                 c0[j] = enc8<RULE>(w[0], w[1], sc, byte); c1[j] = enc8<RULE>(w[2], w[3], sc, byte);
                 if (bad) { c0[j] = 0; c1[j] = 0; }
-                if (STATS) err8(w, c0[j], c1[j], sc, s0, se, true);
+                if (STATS) err8(w, c0[j], c1[j], sc, s0, se);
             } else if (SR) {
                 float e[8];
 #pragma unroll
@@ -399,7 +397,7 @@ __global__ __launch_bounds__(256) void quant_row_kernel(const uint16_t* __restri
             } else {
                 c0[j] = enc4(w[0], w[1], w[2], w[3], sc);
                 if (bad) c0[j] = 0;
-                if (STATS) err4(w, c0[j], sc, s0, se, true);
+                if (STATS) err4(w, c0[j], sc, s0, se);
             }
             packed |= (act ? byte : 0u) << (8 * j);
         }
@@ -504,13 +502,6 @@ struct ColBlock {
     unsigned am_lo, am_hi;     // magnitude bits of each column's block maximum
 };
 
-// (the caller reads these lines again)
-__device__ __forceinline__ void load_col_raw(const uint16_t* __restrict__ p, int64_t ld, unsigned (&v)[32])
-{
-#pragma unroll
-    for (int i = 0; i < 32; ++i) v[i] = ld4<false>(p + (int64_t)i * ld);
-}
-
 // Magnitude bits of both columns' maxima, the first column's in the low half.
 __device__ __forceinline__ unsigned col_maxima(const unsigned (&v)[32])
 {
@@ -587,7 +578,7 @@ __device__ __forceinline__ unsigned quant_one_column(const unsigned* w, unsigned
         *reinterpret_cast<uint4*>(lds_row + (((rb_local * 2 + 1) ^ swz) * 16)) = make_uint4(c[4], c[5], c[6], c[7]);
         if (STATS) {
 #pragma unroll
-            for (int k = 0; k < 4; ++k) err8(w + 4 * k, c[2 * k], c[2 * k + 1], sc, s0, se, true);
+            for (int k = 0; k < 4; ++k) err8(w + 4 * k, c[2 * k], c[2 * k + 1], sc, s0, se);
         }
     } else {
         unsigned c[4];
@@ -601,7 +592,7 @@ __device__ __forceinline__ unsigned quant_one_column(const unsigned* w, unsigned
         *reinterpret_cast<uint4*>(lds_row + ((rb_local ^ swz) * 16)) = make_uint4(c[0], c[1], c[2], c[3]);
         if (STATS) {
 #pragma unroll
-            for (int k = 0; k < 4; ++k) err4(w + 4 * k, c[k], sc, s0, se, true);
+            for (int k = 0; k < 4; ++k) err4(w + 4 * k, c[k], sc, s0, se);
         }
     }
     return byte;
