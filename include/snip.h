@@ -210,7 +210,7 @@ snip_status snip_quantize_sr_fp4(const void* x, int64_t rows, int64_t cols, int6
  * the launcher picks for the shape.  The matrix-core kernels have tiles from 256 x 256 down to
  * 32 x 32 outputs per workgroup; the environment variable
  * SNIP_GEMM_TILE=big|wide|ahead|128x128|64x64|64x32|32x32|general (big = 256 x 256, wide = 256 x 128,
- * ahead = the same for operands that come from memory), read at every call, fixes the tile where it can
+ * ahead is another name of wide), read at every call, fixes the tile where it can
  * serve the call, for measurements and tests, and never changes a result. */
 snip_status snip_gemm_fwd(const snip_layer_plan* plan, const snip_qtensor* xq_row,
                           const snip_qtensor* wq_row, void* y, int64_t ld_out,

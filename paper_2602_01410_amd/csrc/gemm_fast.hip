@@ -4,7 +4,7 @@
 //   workgroup tile 256 x 256, 8 waves (2 x 4), wave tile 128 (A rows) x 64 (B rows), fp32
 //   accumulators in registers (128 per lane); for outputs that would leave compute units without a
 //   tile, 256 x 128 with 4 x 2 waves of 64 x 64 (same code, other template argument).
-//   256 x 256 has two stage buffers (68 KB each), 256 x 128 three (52 KB): a copy then has 1.75-2 stages to arrive instead of
+//   256 x 256 has two stage buffers (68 KB each), 256 x 128 three (52 KB; two for few stages): a copy then has 1.75-2 stages to arrive instead of
 //   0.75-1, which memory needs under load (a stage is 0.9-1.1 us).
 //   A pipeline stage is 128 code bytes of every tile row for an FP8 operand and for FP4 x FP4
 //   (256 contraction elements there), so every 128-byte line that is fetched is used whole.
@@ -37,9 +37,9 @@
 // 4096: all workgroups finish a tile together, 32 MB per round, and the next tile's copies queue behind them in
 // the wave's memory counter.
 //
-// Registers: 256 vector registers (256 x 256), 204-235 (256 x 128).  Scalar registers run out and spill to lanes of vector
-// registers: 23-30 for bf16 outputs and 66-72 for fp32 (256 x 256; 256 x 128 39-45 and 69-82), 56-71 and 88-103 with TAIL
-// (64-81 and 100-129), of which a stage restores four to six.
+// Registers: 256 vector registers (256 x 256), 200-247 (256 x 128; 195-215 with two buffers).  Scalar registers run out and spill to
+// lanes of vector registers: 23-30 for bf16 outputs and 69-77 for fp32 (256 x 256; 256 x 128 39-46 and 69-82, with two buffers 17-25
+// and 64-69), 58-74 and 89-103 with TAIL (64-80 and 103-129, 46-61 and 87-104), of which a stage restores four to six.
 //
 // See gemm.hip for the register layout of v_mfma_scale_f32_32x32x64_f8f6f4.
 #include "gemm_common.h"
