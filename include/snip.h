@@ -111,7 +111,9 @@ typedef struct {
  * holds for tensors whose nonzero magnitudes lie within [2^-56, 2^48]: below, the squares of
  * the errors (about 2^-5 |x| for FP8) leave the fp32 normal range and count as less than they
  * are; above, sums of squares overflow to infinity.  A lane adds at most rows / 64 (column
- * blocks) or cols / 8 (row blocks) groups of 8 squares before its sum moves to the next level,
+ * blocks) or cols / 8 (row blocks) groups of 8 elements before its sum moves to the next level
+ * (squared differences one by one, the elements' own squares in pairs, or 32 of a column's block
+ * first where columns are only summed and not quantized),
  * which keeps the rounding of a sum of n equal terms below 1e-5 up to about 2^22 rows. */
 typedef struct { double sum_sq, err_sq_fp4, err_sq_fp8; } snip_stats;
 
