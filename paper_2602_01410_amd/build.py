@@ -14,7 +14,7 @@ MICROBENCH = os.path.join(_HERE, "snip_microbench")
 OBJDIR = os.path.join(_HERE, "_build")          # object files (not tracked)
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
          "-Wno-unused-command-line-argument"]
-SOURCES = ("api.hip", "quant_kernels.hip", "gemm.hip", "gemm_fast.hip", "gemm_small.hip", "optim_kernels.hip", "paper_kernels.hip", "gemm_paper.hip")
+SOURCES = ("api.hip", "quant_kernels.hip", "gemm.hip", "gemm_fast.hip", "gemm_small.hip", "optim_kernels.hip", "paper_kernels.hip", "gemm_paper.hip", "gemm_paper_wide.hip")
 
 
 def binding_command():

@@ -103,6 +103,8 @@ struct GemmPaperArgs {
     void* c; int64_t ldc; int out_fp32;
 };
 hipError_t launch_gemm_paper(const GemmPaperArgs& a, hipStream_t s);
+bool gemm_paper_wide_eligible(const GemmPaperArgs& a);
+hipError_t launch_gemm_paper_wide(const GemmPaperArgs& a, hipStream_t s);
 size_t paper_workspace_bytes(int64_t rows, int64_t cols);
 hipError_t launch_paper(const PaperArgs& a, hipStream_t s);
 
