@@ -353,15 +353,16 @@ int gemm_compute_units()
 // pairs), `tail` at least `alone`: a lower one fits some long contractions better and picks tiles whose last round is a
 // quarter full ([2048 x 2304 x 3072] FP8 37 us with 128 x 128 for 26 with 256 x 128).  On 1233 other problems the pick is on
 // average 0.2 % (cached, up to 10 MB) and 0.5 % (from memory, more) slower than the fastest tile, 20 % at worst (rows of few
-// tokens by very wide weights, where the tables are rough).
+// tokens by very wide weights, where the tables are rough).  (The cached stages of 64 x 32 and 32 x 32 follow what two stages per
+// barrier took off them since.)
 struct TileCost { GemmTile tile; int m, n; float start, turn, alone[2], full[2], tail[2]; };      // [0]: FP4 x FP4, [1]: others
 static const TileCost kTileCosts[2][6] = {{
     {GemmTile::kBig,      256, 256, 7.7f, 4.5f, {0.61f, 0.62f}, {1.90f, 1.42f}, {0.61f, 0.62f}},
     {GemmTile::kWide,     256, 128, 6.6f, 2.4f, {0.45f, 0.39f}, {0.94f, 0.70f}, {0.49f, 0.41f}},
     {GemmTile::k128x128,  128, 128, 4.8f, 2.4f, {0.27f, 0.27f}, {0.59f, 0.45f}, {0.35f, 0.27f}},
     {GemmTile::k64x64,     64,  64, 3.2f, 0.8f, {0.16f, 0.17f}, {0.22f, 0.17f}, {0.16f, 0.17f}},
-    {GemmTile::k64x32,     64,  32, 3.2f, 0.8f, {0.14f, 0.14f}, {0.18f, 0.13f}, {0.22f, 0.14f}},
-    {GemmTile::k32x32,     32,  32, 3.0f, 0.8f, {0.12f, 0.13f}, {0.15f, 0.11f}, {0.20f, 0.13f}},
+    {GemmTile::k64x32,     64,  32, 3.2f, 0.8f, {0.12f, 0.12f}, {0.16f, 0.12f}, {0.20f, 0.13f}},
+    {GemmTile::k32x32,     32,  32, 3.0f, 0.8f, {0.10f, 0.11f}, {0.14f, 0.10f}, {0.18f, 0.12f}},
 }, {
     {GemmTile::kBig,      256, 256, 11.3f, 5.3f, {1.07f, 1.04f}, {1.88f, 1.48f}, {1.07f, 1.04f}},
     {GemmTile::kWide,     256, 128, 8.2f, 2.8f, {0.68f, 0.58f}, {1.01f, 0.80f}, {0.68f, 0.58f}},
@@ -370,7 +371,6 @@ static const TileCost kTileCosts[2][6] = {{
     {GemmTile::k64x32,     64,  32, 4.0f, 0.9f, {0.14f, 0.14f}, {0.24f, 0.18f}, {0.17f, 0.14f}},
     {GemmTile::k32x32,     32,  32, 3.8f, 1.4f, {0.12f, 0.13f}, {0.18f, 0.15f}, {0.14f, 0.14f}},
 }};
-constexpr double kColdBytes = 10e6;
 
 static bool fast_tile(GemmTile t) { return t == GemmTile::kBig || t == GemmTile::kWide; }
 
@@ -400,8 +400,7 @@ static GemmTile pick_tile(const GemmArgs& a)
     const int64_t ncu = gemm_compute_units(), stages = (a.R + ke - 1) / ke;
     GemmTile best = GemmTile::kGeneral;
     double best_t = 0.0;
-    const double bytes = (double)a.I * a.R * (a.fmt_a == kFP8 ? 1.0 : 0.5) + (double)a.J * a.R * (a.fmt_b == kFP8 ? 1.0 : 0.5);
-    for (const TileCost& c : kTileCosts[bytes > kColdBytes]) {
+    for (const TileCost& c : kTileCosts[gemm_operand_bytes(a) > kColdBytes]) {
         if (!tile_usable(a, c.tile)) continue;
         const int64_t tiles = tile_count(a, c.m, c.n), full_rounds = (tiles - 1) / ncu;
         const double load = (double)(tiles - full_rounds * ncu) / (double)ncu;

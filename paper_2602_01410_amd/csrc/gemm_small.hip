@@ -11,8 +11,13 @@
 //   whose operands were read a stage earlier, are issued; the buffer of stage s is refilled with stage s + NST.
 //   Measured (us per call, back to back in a graph; before: the general kernel): [64 x 4096 x 4096] FP4 23.6 -> 5.2, FP8
 //   33 -> 7.0; [64 x 4096 x 11008] FP4 53 -> 8.9; [64 x 11008 x 4096] FP4 24.5 -> 6.3; [1504 x 2080 x 1568] FP4 25.3 -> 9.4,
-//   FP8 31.5 -> 11.9; [256 x 512 x 512] FP8 6.5 (256 x 128 tile) -> 3.45.  What is left is the chain of a stage (barrier,
-//   LDS latency, dependent MFMAs: about 0.14 us for 256 FP4 elements) and 3 us of launch, first fill and result.
+//   FP8 31.5 -> 11.9; [256 x 512 x 512] FP8 6.5 (256 x 128 tile) -> 3.45.
+//   Waves with one 32 x 32 block have one chain of dependent MFMAs, 160 cycles of a stage's 300; the rest was the LDS latency behind the
+//   last of them and the barrier.  The tiles of one or two such waves therefore take two stages per barrier (G) on operands of up to 10 MB and ask
+//   for the next two during the first five of eight MFMAs: operands in the caches [64 x 4096 x 11008] FP4 9.27 -> 8.33, FP8 16.0 -> 14.1,
+//   [64 x 4096 x 4096] 5.33 -> 4.96 and 7.66 -> 6.79, [1 x 2048 x 2048] FP8 5.03 -> 4.60; from memory the same (18.4 -> 18.3).  With four
+//   stages, or a ring of 12 or 16, slower (the rings' fill and LDS cost more than they hide), the 64 x 64 tile too (12.3 -> 16.7 on [1504 x
+//   2080 x 1568]: one workgroup per compute unit instead of two).  What is left is the chain and 3 us of launch, first fill and result.
 //   Copies go through buffer descriptors: rows past the end of an operand and chunks past the end of a row deliver
 //   zeros, and the scale bytes past the last block are masked, so any contraction extent that is a multiple of 32 runs.
 #include "gemm_common.h"
@@ -20,9 +25,10 @@
 namespace snip {
 namespace {
 
-// BM x BN tile, one compute wave per WTM x WTN part, NP copy waves, NST stage buffers.
-template <int BM_, int BN_, int WTM_, int WTN_, int NST_, int NP_> struct SmallTile {
-    static constexpr int BM = BM_, BN = BN_, WTM = WTM_, WTN = WTN_, NST = NST_, NP = NP_;
+// BM x BN tile, one compute wave per WTM x WTN part, NP copy waves, NST stage buffers, a barrier every G stages.
+template <int BM_, int BN_, int WTM_, int WTN_, int NST_, int NP_, int G_> struct SmallTile {
+    static constexpr int BM = BM_, BN = BN_, WTM = WTM_, WTN = WTN_, NST = NST_, NP = NP_, G = G_;
+    static_assert(NST % G == 0 && NST >= 2 * G, "the ring holds whole groups of stages");
     static constexpr int NC = (BM / WTM) * (BN / WTN), NT = (NC + NP) * 64;
     static constexpr int WGN = BN / WTN;
     static constexpr int MB = WTM / 32, NB = WTN / 32;
@@ -53,7 +59,7 @@ __global__ __launch_bounds__(T::NT) void gemm_small_kernel(const uint8_t* __rest
                                                            int tiles_i, int tiles_j, float* __restrict__ norm_partials)
 {
     using C = SmallCfg<FA, FB, T>;
-    constexpr int BM = T::BM, BN = T::BN, WTM = T::WTM, WTN = T::WTN, MB = T::MB, NB = T::NB, NST = T::NST, NP = T::NP;
+    constexpr int BM = T::BM, BN = T::BN, WTM = T::WTM, WTN = T::WTN, MB = T::MB, NB = T::NB, NST = T::NST, NP = T::NP, G = T::G;
     __shared__ __attribute__((aligned(1024))) uint8_t lds[C::LDS_BYTES];
 
     int ti, tj;
@@ -128,14 +134,15 @@ __global__ __launch_bounds__(T::NT) void gemm_small_kernel(const uint8_t* __rest
         };
 #pragma unroll
         for (int st = 0; st < NST; ++st) issue(st, st);
-        SNIP_WAIT_VM(C::L * (NST - 1));                          // stage 0
+        SNIP_WAIT_VM(C::L * (NST - G));                          // the first G stages
         SNIP_BAR();
         int slot = 0;
-        for (int s = 0; s < nstage; ++s) {
-            SNIP_WAIT_VM(C::L * (NST - 2));                      // stage s + 1 has landed
-            SNIP_BAR();                                          // the compute waves have read stage s
-            issue(s + NST, slot);
-            slot = slot == NST - 1 ? 0 : slot + 1;
+        for (int s = 0; s < nstage; s += G) {
+            SNIP_WAIT_VM(C::L * (NST - 2 * G));                  // stages s + G ... s + 2 G - 1 have landed
+            SNIP_BAR();                                          // the compute waves have read stages s ... s + G - 1
+#pragma unroll
+            for (int j = 0; j < G; ++j) issue(s + NST + j, slot + j);
+            slot = slot == NST - G ? 0 : slot + G;
         }
         SNIP_WAIT_VM(0);                                         // the empty copies past the last stage write zeros
         SNIP_BAR();
@@ -161,35 +168,36 @@ __global__ __launch_bounds__(T::NT) void gemm_small_kernel(const uint8_t* __rest
 #pragma unroll
             for (int k = 0; k < 16; ++k) acc[a][b][k] = 0.f;
 
-    // Operands of one stage: codes of its KS MFMA steps and scale dwords.
-    struct Operands { v8i fa[C::KS][MB], fb[C::KS][NB]; unsigned sa[C::NG][MB], sb[C::NG][NB]; } op0, op1;
+    // Operands of G stages: codes of their KS MFMA steps and scale dwords.
+    constexpr int KG = G * C::KS, QG = G * C::NG;
+    struct Operands { v8i fa[KG][MB], fb[KG][NB]; unsigned sa[QG][MB], sb[QG][NB]; } op0, op1;
     auto read_scales = [&](Operands& o, int slot) {
-        const uint8_t* base = lds + slot * C::SLOT;
 #pragma unroll
-        for (int q = 0; q < C::NG; ++q) {
+        for (int q = 0; q < QG; ++q) {
+            const uint8_t* base = lds + (slot + q / C::NG) * C::SLOT;
 #pragma unroll
-            for (int m = 0; m < MB; ++m) o.sa[q][m] = *reinterpret_cast<const unsigned*>(base + sca_off + q * BM * 4 + m * 128);
+            for (int m = 0; m < MB; ++m) o.sa[q][m] = *reinterpret_cast<const unsigned*>(base + sca_off + q % C::NG * BM * 4 + m * 128);
 #pragma unroll
-            for (int n = 0; n < NB; ++n) o.sb[q][n] = *reinterpret_cast<const unsigned*>(base + scb_off + q * BN * 4 + n * 128);
+            for (int n = 0; n < NB; ++n) o.sb[q][n] = *reinterpret_cast<const unsigned*>(base + scb_off + q % C::NG * BN * 4 + n * 128);
         }
     };
-    constexpr int NR = C::KS * (MB + NB);                        // operand blocks of a stage
+    constexpr int NR = KG * (MB + NB);                           // operand blocks of G stages
     auto read_block = [&](Operands& o, int slot, int r) {
-        const uint8_t* base = lds + slot * C::SLOT;
-        const int ks = r / (MB + NB), i = r % (MB + NB);
-        if (i < MB) o.fa[ks][i] = read_frag<FA>(base + wm * WTM * C::SBA, i * 32 * C::SBA, offa, ks);
-        else        o.fb[ks][i - MB] = read_frag<FB>(base + C::OFF_B + wn * WTN * C::SBB, (i - MB) * 32 * C::SBB, offb, ks);
+        const int k = r / (MB + NB), i = r % (MB + NB), ks = k % C::KS;
+        const uint8_t* base = lds + (slot + k / C::KS) * C::SLOT;
+        if (i < MB) o.fa[k][i] = read_frag<FA>(base + wm * WTM * C::SBA, i * 32 * C::SBA, offa, ks);
+        else        o.fb[k][i - MB] = read_frag<FB>(base + C::OFF_B + wn * WTN * C::SBB, (i - MB) * 32 * C::SBB, offb, ks);
     };
     constexpr int ca = FB == kFP8 ? 0 : 4, cb = FA == kFP8 ? 0 : 4;              // first operand = B tile
-    // Stage s: its operands are in `cur`; those of stage s + 1 are read meanwhile.
+    // Stages s ... s + G - 1: their operands are in `cur`; those of the next G are read meanwhile.
     auto step = [&](Operands& cur, Operands& nxt, int s, int slot1) {
-        SNIP_BAR();                                              // stage s + 1 is complete
+        SNIP_BAR();                                              // the next G stages are complete
         read_scales(nxt, slot1);
         __builtin_amdgcn_sched_barrier(0);
         // scale bytes past the last block are unspecified: masked (whole groups past the end were delivered as zeros)
-        if ((nkb & 3) != 0 && s == nstage - 1) {
+        if ((nkb & 3) != 0 && s + G >= nstage) {
 #pragma unroll
-            for (int q = 0; q < C::NG; ++q) {
+            for (int q = 0; q < QG; ++q) {
                 const unsigned mask = s * C::NG + q == ngrp - 1 ? (1u << (8 * (nkb & 3))) - 1u : 0xFFFFFFFFu;
 #pragma unroll
                 for (int m = 0; m < MB; ++m) cur.sa[q][m] &= mask;
@@ -199,49 +207,49 @@ __global__ __launch_bounds__(T::NT) void gemm_small_kernel(const uint8_t* __rest
         }
         // lane group g looks at bytes g and 2 + g of its rows' dwords
 #pragma unroll
-        for (int q = 0; q < C::NG; ++q) {
+        for (int q = 0; q < QG; ++q) {
 #pragma unroll
             for (int m = 0; m < MB; ++m) cur.sa[q][m] >>= 8 * g;
 #pragma unroll
             for (int n = 0; n < NB; ++n) cur.sb[q][n] >>= 8 * g;
         }
-        // the next stage's operands are requested between the MFMAs: all at once they would fill the LDS queue and hold
-        // the MFMAs back for the time of all waves' reads
-        constexpr int NM = C::KS * MB * NB;
+        // the next stages' operands are requested between the MFMAs: all at once they would fill the LDS queue and hold
+        // the MFMAs back for the time of all waves' reads.  (A stage past the last one multiplies the zeros it was filled with.)
+        constexpr int NM = KG * MB * NB, NI = G == 1 ? NM : NM * 5 / 8;      // (G > 1: the last ones arrive while the chain goes on)
         int idx = 0;
 #pragma unroll
-        for (int ks = 0; ks < C::KS; ++ks)
+        for (int k = 0; k < KG; ++k)
 #pragma unroll
             for (int m = 0; m < MB; ++m)
 #pragma unroll
                 for (int n = 0; n < NB; ++n) {
-                    if ((ks & 1) == 0)
-                        acc[m][n] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(cur.fb[ks][n], cur.fa[ks][m], acc[m][n], ca, cb, 0, (int)cur.sb[ks >> 1][n], 0, (int)cur.sa[ks >> 1][m]);
+                    if ((k & 1) == 0)
+                        acc[m][n] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(cur.fb[k][n], cur.fa[k][m], acc[m][n], ca, cb, 0, (int)cur.sb[k >> 1][n], 0, (int)cur.sa[k >> 1][m]);
                     else
-                        acc[m][n] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(cur.fb[ks][n], cur.fa[ks][m], acc[m][n], ca, cb, 2, (int)cur.sb[ks >> 1][n], 2, (int)cur.sa[ks >> 1][m]);
+                        acc[m][n] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(cur.fb[k][n], cur.fa[k][m], acc[m][n], ca, cb, 2, (int)cur.sb[k >> 1][n], 2, (int)cur.sa[k >> 1][m]);
                     __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
                     for (int r = 0; r < NR; ++r)
-                        if (r * NM / NR == idx) read_block(nxt, slot1, r);
+                        if (r * NI / NR == idx) read_block(nxt, slot1, r);
                     __builtin_amdgcn_sched_barrier(0);
                     ++idx;
                 }
         __builtin_amdgcn_sched_barrier(0);
-        __builtin_amdgcn_s_waitcnt(0xC07F);                      // lgkmcnt(0): stage s + 1 is read before the next barrier
+        __builtin_amdgcn_s_waitcnt(0xC07F);                      // lgkmcnt(0): they are read before the next barrier
     };
-    SNIP_BAR();                                                  // stage 0 is complete
+    SNIP_BAR();                                                  // the first G stages are complete
     read_scales(op0, 0);
 #pragma unroll
     for (int r = 0; r < NR; ++r) read_block(op0, 0, r);
     __builtin_amdgcn_s_waitcnt(0xC07F);
-    int slot1 = NST == 1 ? 0 : 1;
+    int slot1 = G;
     for (int s = 0;;) {
         step(op0, op1, s, slot1);
-        slot1 = slot1 == NST - 1 ? 0 : slot1 + 1;
-        if (++s == nstage) break;
+        slot1 = slot1 == NST - G ? 0 : slot1 + G;
+        if ((s += G) >= nstage) break;
         step(op1, op0, s, slot1);
-        slot1 = slot1 == NST - 1 ? 0 : slot1 + 1;
-        if (++s == nstage) break;
+        slot1 = slot1 == NST - G ? 0 : slot1 + G;
+        if ((s += G) >= nstage) break;
     }
     SNIP_BAR();                                                  // nothing writes to the stage buffers any more
 
@@ -354,11 +362,16 @@ bool gemm_small_eligible(const GemmArgs& a)
 
 hipError_t launch_gemm_small(const GemmArgs& a, GemmTile tile, hipStream_t s)
 {
+    const bool cached = gemm_operand_bytes(a) <= kColdBytes;
     switch (tile) {
-        case GemmTile::k128x128: return launch_small_tile<SmallTile<128, 128, 64, 64, 4, 4>>(a, s);
-        case GemmTile::k64x64:   return launch_small_tile<SmallTile<64, 64, 32, 32, 4, 4>>(a, s);
-        case GemmTile::k64x32:   return launch_small_tile<SmallTile<64, 32, 32, 32, 6, 4>>(a, s);
-        default:                 return launch_small_tile<SmallTile<32, 32, 32, 32, 8, 4>>(a, s);
+        case GemmTile::k128x128: return launch_small_tile<SmallTile<128, 128, 64, 64, 4, 4, 1>>(a, s);
+        case GemmTile::k64x64:   return launch_small_tile<SmallTile<64, 64, 32, 32, 4, 4, 1>>(a, s);
+        // Two stages per barrier where operands are likely cached.  From memory their larger steps cost 64 x 32 2-4 %, and 16 % with more
+        // tiles than compute units ([9 x 21120 x 7936] FP8 42.4 -> 49.2), 32 x 32 up to 1 %.
+        case GemmTile::k64x32:
+            return cached ? launch_small_tile<SmallTile<64, 32, 32, 32, 6, 4, 2>>(a, s) : launch_small_tile<SmallTile<64, 32, 32, 32, 6, 4, 1>>(a, s);
+        default:
+            return cached ? launch_small_tile<SmallTile<32, 32, 32, 32, 8, 4, 2>>(a, s) : launch_small_tile<SmallTile<32, 32, 32, 32, 8, 4, 1>>(a, s);
     }
 }
 
