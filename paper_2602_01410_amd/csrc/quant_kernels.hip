@@ -853,7 +853,7 @@ __global__ __launch_bounds__(qb_threads(NW, STATS), STATS ? 2 : 1) void quant_bo
                                                          uint8_t* __restrict__ g4_r, int64_t kpitch_r,
                                                          uint8_t* __restrict__ codes_c, uint8_t* __restrict__ scales_c,
                                                          uint8_t* __restrict__ g4_c, int64_t kpitch_c,
-                                                         double* __restrict__ partials, int runs)
+                                                         double* __restrict__ partials, int turn)
 {
     constexpr bool COOP = NW != 0, SPLIT = STATS == 0;
     static_assert(COOP || !SPLIT, "a wave per unit is for the statistics");
@@ -876,17 +876,17 @@ __global__ __launch_bounds__(qb_threads(NW, STATS), STATS ? 2 : 1) void quant_bo
     const int pitch_r = FMT_R == kFP8 ? cols : cols / 2, pitch_c = FMT_C == kFP8 ? rows : rows / 2;      // bytes of a stored row
     float s0 = 0.f, se_c = 0.f, se_r = 0.f;
     float so_c = 0.f, so_r = 0.f;                         // STATS == 2: error sums of the format not chosen
-    // COOP, `runs`: units go to the XCDs (workgroup id mod 8) in contiguous runs, and a run walks pairs of row units column
-    // group by column group, so that the two halves of a 128-byte line (FP4 codes of a row: 64 bytes per unit; FP4 codes of a
-    // column, likewise) and the scale bytes of neighbouring units meet in one L2 (the grid is a multiple of 8 workgroups).
-    // Otherwise units are dealt in order and the chip reads one band of rows at a time.  Which one: launch_qb_form.
-    const int run = (units + 7) / 8, run0 = (int)(blockIdx.x % 8) * run;
-    const bool in_runs = COOP && runs;
-    const int u_first = in_runs ? run0 + (int)(blockIdx.x / 8) : COOP ? (int)blockIdx.x : wave, u_end = in_runs ? min(run0 + run, units) : units;
-    const int u_step = in_runs ? (int)(gridDim.x / 8) : COOP ? (int)gridDim.x : nwaves;
-    for (int u = u_first; u < u_end; u += u_step) {
-        int ru, cg;
-        if (in_runs) {
+    // COOP: units go to the XCDs (workgroup id mod 8) in turns of `turn` consecutive ones, in an order that walks pairs of row
+    // units column group by column group, so that the two halves of a 128-byte line (FP4 codes of a row: 64 bytes per unit; FP4
+    // codes of a column, likewise) and the scale bytes of neighbouring units meet in one L2 (the grid is a multiple of 8
+    // workgroups).  How many: launch_qb_form.
+    const int v_end = COOP ? (units + 8 * turn - 1) / (8 * turn) * (8 * turn) : units;
+    for (int v = COOP ? (int)blockIdx.x : wave; v < v_end; v += COOP ? (int)gridDim.x : nwaves) {
+        int ru, cg, u = v;
+        if (COOP) {
+            const int i = v >> 3, c = i / turn;
+            u = (c * 8 + (v & 7)) * turn + (i - c * turn);
+            if (u >= units) continue;
             const int pair = u / (2 * ncg), rem = u - pair * 2 * ncg;
             const bool single = 2 * pair + 1 == nru;                  // the last pair may be one row unit
             ru = 2 * pair + (single ? 0 : rem & 1);
@@ -1442,24 +1442,25 @@ static int launch_qb_form(const QuantBothArgs& a, double* partials, hipStream_t 
 {
     const int64_t nrb = a.rows / kBlock;
     const int64_t units = ((a.cols + kColsPerWave - 1) / kColsPerWave) * ((nrb + RBU - 1) / RBU);
+    // Order of the units (see quant_both_kernel): in turns of eight (two row units by four column groups) from 8 M elements on, 24 M
+    // if rows hold no whole number of four blocks; an eighth of the tensor each below, where it fits the L2s ([1504 x 2080] FP4 5.7
+    // against 7.8 us), and without statistics for rows of more than 16384 columns that start on whole lines of 256 bytes
+    // ([8192 x 28672] FP4 169 against 175, FP8 214 against 212; [4096 x 16384] 53.5 against 51.8).  Dealt one by one, half lines of
+    // codes and dwords of scales reach memory from two L2s: 37 % more bytes written than there are for [16384 x 11008] FP4.  us per call,
+    // dealt -> turns of eight: that 139 -> 132, FP8 164 -> 160, [8192 x 4096] 30.2 -> 27.6, 33.7 -> 32.0, [32768 x 4096] 101 -> 94, 120 -> 112,
+    // [16384 x 8192] 105 -> 93.5, 125 -> 119, [8160 x 8160] 66 -> 67, 91 -> 82; [4096 x 4096] 16.6 -> 16.3; with all statistics [11008 x
+    // 4096] FP4 55.0 -> 50.8, [3072 x 8192] 33.2 -> 31.6; inside the step of a 70B-shaped block FP4 817 -> 783, FP8 191 -> 184.  Eighths of large tensors, far apart, meet in few memory channels: [16384 x
+    // 8192] FP4 105, [32768 x 4096] FP8 135.
+    const int64_t near = a.cols % (4 * kBlock) != 0 ? (int64_t)24 << 20 : (int64_t)8 << 20;
+    const bool eighths = a.rows * a.cols < near || (STATS == 0 && a.cols > 16384 && a.ld % 128 == 0);
+    const int64_t turn = eighths ? (units + 7) / 8 : 8;
     // A workgroup per unit.  With statistics it also needs a partial-sum slot, and its waves' sums cost as much as a sixth
     // of a tile: at most kStreamBlocks workgroups with equal shares of the units then.
-    const int64_t most = STATS ? kStreamBlocks / 8 : (int64_t)1 << 24, run = (units + 7) / 8, share = (run + most - 1) / most;
+    const int64_t most = STATS ? kStreamBlocks / 8 : (int64_t)1 << 24, run = (units + 8 * turn - 1) / (8 * turn) * turn, share = (run + most - 1) / most;
     const int blocks = NW ? (int)(8 * ((run + share - 1) / share)) : balanced_blocks(units);
-    // Order of the units (see quant_both_kernel): runs below 8 M elements, where the tensor fits the L2s ([1504 x 2080] FP4 6.1
-    // against 6.7 us dealt), below 24 M if rows hold no whole number of four blocks, so that their scale bytes share dwords and lines
-    // with the neighbours' at odd places ([896 x 9408] FP4 11.4 (dealt) -> 9.9, [2432 x 4896] 14.8 -> 12.5, [4096 x 4128] 20.1 -> 15.3,
-    // [3264 x 5952] 20.6 -> 18.7, FP8 23.3 -> 22.4, with statistics [2432 x 4896] 19.2 -> 17.3; whole groups [2080 x 4096] 8.9 -> 11.1),
-    // and without statistics for rows of more than 12288 columns, if they start on whole lines of 256 bytes
-    // ([8192 x 16384] FP4 103.9 (dealt) -> 96.1, FP8 127.7 -> 123.1, [4096 x 28672] 91.8 -> 86.6 and 120 -> 110, [16384 x 14336] 182
-    // -> 170 and 223 -> 212; FP8 rows beside FP4 columns 98.7 -> 96.5 on [4096 x 28672], 109.0 -> 111.5 on [8192 x 16384]).
-    // Elsewhere the eight runs, far apart, meet in few memory channels: [8160 x 8160] FP4 81.5 (runs) -> 68.4, [16384 x 8192] 105.8
-    // -> 98.1, [8192 x 11008] 74.9 -> 70.4, FP8 88.4 -> 85.2, [8192 x 4096] 34.7 -> 33.3.
-    const int64_t near = a.cols % (4 * kBlock) != 0 ? (int64_t)24 << 20 : (int64_t)8 << 20;
-    const bool runs = a.rows * a.cols < near || (STATS == 0 && a.cols > 12288 && a.ld % 128 == 0);
     hipLaunchKernelGGL((quant_both_kernel<FMT_R, FMT_C, RULE, STATS, NW, RBU>), dim3(blocks), dim3(qb_threads(NW, STATS)), 0, s,
                        a.x, (int)a.rows, (int)a.cols, a.ld, a.codes_r, a.scales_r, a.g4_r, g4_pitch(a.rows),
-                       a.codes_c, a.scales_c, a.g4_c, g4_pitch(a.cols), partials, runs);
+                       a.codes_c, a.scales_c, a.g4_c, g4_pitch(a.cols), partials, (int)turn);
     return blocks;
 }
 
