@@ -50,7 +50,6 @@ namespace snip {
 namespace {
 
 constexpr int NWAVE = 8, NT = NWAVE * 64;
-constexpr int TNP = 256;                // rows of the B tile's scale area (a 128-row B tile leaves half of it unused)
 
 // Workgroup tile TM (A rows) x TN (B rows), split over the eight waves as (TM / WTM) x (TN / WTN) wave tiles.
 template <int TM_, int TN_, int WTM_, int WTN_, int NST_, int PH_> struct TileCfg {
@@ -86,8 +85,10 @@ template <int FA, int FB, class T> struct FCfg {
     static constexpr int NG = KE / 128;                          // scale dwords (groups of 4 blocks) per row per stage
     static constexpr int NST = T::NST;
     static constexpr int A_BYTES = TM * SBA, B_BYTES = TN * SBB;
-    static constexpr int S_BYTES = (TM + TNP) * NG * 4;          // scale dwords of one stage
-    static constexpr int SLOT = A_BYTES + B_BYTES + S_BYTES;
+    // Scale dwords of one stage, [group][256 rows] of A and [group][TN rows] of B, in copies of 1 KB: NSA of A, then B's (two groups
+    // of a 128-row B tile are one copy, a single one is half of one)
+    static constexpr int NSA = NG, NSB = (TN * NG * 4 + 1023) / 1024, NSC = NSA + NSB;
+    static constexpr int SLOT = A_BYTES + B_BYTES + NSC * 1024;
     // Stage buffers lie STRIDE apart.  The result staging area is part of the LDS array that covers the buffer of the tile's
     // last stage and never reaches into the other buffers, which already receive the next tile: with two buffers (one at
     // the start of the array, one at its end) the first or the last 64 KB, with three the first 32 KB of that buffer.
@@ -95,10 +96,10 @@ template <int FA, int FB, class T> struct FCfg {
     static constexpr int STRIDE = NST == 2 ? LDS_BYTES - SLOT : SLOT;
     static constexpr int EPI_BYTES = NST == 2 ? 64 * 1024 : 32 * 1024;
     static constexpr int epi_base(int last) { return NST == 2 ? (last ? LDS_BYTES - EPI_BYTES : 0) : last * STRIDE; }
-    static constexpr int LA = A_BYTES / 1024 / NWAVE;            // 16-byte copy instructions per wave per stage
+    static constexpr int LA = A_BYTES / 1024 / NWAVE;            // 1 KB copies of codes per wave per stage
     static constexpr int LB = B_BYTES / 1024 / NWAVE;
-    static constexpr int LS = S_BYTES / 256 / NWAVE;             // 4-byte copy instructions per wave per stage
-    static constexpr int L = LA + LB + LS;
+    static constexpr int L = LA + LB;                            // (and one of scales in waves 0 ... NSC - 1, in front of them)
+    static_assert(NSC <= NWAVE / 2, "the waves of group 0 copy the scales");
     static_assert(STRIDE % 1024 == 0 && SLOT <= STRIDE && (NST - 1) * STRIDE + SLOT <= LDS_BYTES, "stage buffers must not overlap");
     static_assert(EPI_BYTES <= (NST == 2 ? STRIDE : SLOT), "the result staging area must stay clear of the other stage buffers");
     static_assert(L * (NST - 1) <= 60, "copies in flight must be countable");
@@ -139,17 +140,22 @@ __global__ __launch_bounds__(NT) void gemm_fast_kernel(const uint8_t* __restrict
     //      to, which runs ahead of the tile being multiplied): wave-uniform base + per-lane 32-bit offset.
     //      Rows past the end of an operand re-read its last row (their products are never stored). ----
     unsigned oa[C::LA], ob[C::LB];
-    const uint8_t* sbase[C::LS];
-    int64_t sstep[C::LS];
     const uint8_t* abase;
     const uint8_t* bbase;
     // TAIL: descriptors over the tile's rows (rows past the end of an operand lie past their end) and over the grouped
-    // scale copy.  A wave's scale copies belong to one operand and scale group and to adjacent quarters.
+    // scale copy.
     v4i ra, rb, rs;
-    const int sq = wave * C::LS;
-    const bool sop = sq >= 4 * C::NG;
+    // Scales: a wave of group 0 makes one 1 KB copy per stage, 16 bytes per lane: four rows of a scale group of A, or of B (of a 128-row
+    // B tile: half of the lanes each group, or both halves the same one).  Where there are fewer than four copies the other waves
+    // repeat them.  With copies of a dword per lane in every wave it was 20 copy instructions of a stage's two waves of a SIMD
+    // instead of 17 (256 x 256, FP4); the GEMMs of a step, FP4: 70B-shaped block 6547 -> 6471 us, 7B 2929 -> 2904, FP8 the same; [16384 x
+    // 4096 x 4096] FP4 256 x 256 138.0 -> 137.3, 256 x 128 159.6 -> 158.2, [16384 x 4096 x 11008] 326.7 -> 323.0 and 383.4 -> 378.7.
+    const int sq = wave % C::NSC;
+    const bool sop = sq >= C::NSA;
+    const int sgrp = sop ? (TN == 256 ? sq - C::NSA : 0) : sq;
     const unsigned spitch = (unsigned)(sop ? b_pitch : a_pitch) * 4;
-    const unsigned os = TAIL ? scale_lane(sq % (4 * C::NG) / 4, (sop && sq % 4 * 64 >= TN ? sq % 4 - TN / 64 : sq % 4) * 64 + lane, spitch) : lane * 4;
+    const uint8_t* sbase;
+    const unsigned os = TN == 128 && sop ? scale_lane(C::NG == 2 ? lane / 32 : 0, lane % 32 * 4, spitch) : scale_lane(TAIL ? sgrp : 0, lane * 4, spitch);
     auto chunk_a = [&](int j) { constexpr int CPR = C::SBA / 16, RPI = 1024 / C::SBA; return (lane % CPR) ^ swz<C::SBA>((wave * C::LA + j) * RPI + lane / CPR); };
     auto chunk_b = [&](int j) { constexpr int CPR = C::SBB / 16, RPI = 1024 / C::SBB; return (lane % CPR) ^ swz<C::SBB>((wave * C::LB + j) * RPI + lane / CPR); };
     auto set_copy_tile = [&](int u) {
@@ -175,18 +181,8 @@ __global__ __launch_bounds__(NT) void gemm_fast_kernel(const uint8_t* __restrict
             rs = buffer_desc((sop ? b_g4 : a_g4) + row4, scale_size(ngrp, spitch, row4));
             return;
         }
-        // scale copy q of a stage: operand, scale group inside the stage, quarter of the 256 tile rows (the
-        // padded pitch of the grouped copy covers whole tiles)
-#pragma unroll
-        for (int j = 0; j < C::LS; ++j) {
-            const int q = wave * C::LS + j;
-            const int opnd = q / (4 * C::NG), grp = (q % (4 * C::NG)) / 4;
-            int quarter = q % 4;
-            if (opnd == 1 && quarter * 64 >= TN) quarter -= TN / 64;      // a 128-row B tile: fetch its rows again (unused copy)
-            const int64_t pitch = opnd == 0 ? a_pitch : b_pitch;
-            sbase[j] = (opnd == 0 ? a_g4 : b_g4) + ((int64_t)grp * pitch + (opnd == 0 ? i0 : j0) + quarter * 64) * 4;
-            sstep[j] = (int64_t)C::NG * pitch * 4;
-        }
+        // (the padded pitch of the grouped copy covers whole tiles)
+        sbase = (sop ? b_g4 : a_g4) + (int64_t)sgrp * (sop ? b_pitch : a_pitch) * 4 + (int64_t)(sop ? j0 : i0) * 4;
         abase = a_codes + (int64_t)i0 * a_row_bytes;
         bbase = b_codes + (int64_t)j0 * b_row_bytes;
     };
@@ -201,24 +197,24 @@ __global__ __launch_bounds__(NT) void gemm_fast_kernel(const uint8_t* __restrict
     };
     const unsigned lds0 = lds_addr(lds);
 
-    // copy instruction j (0 .. L-1) of this wave's share of `stage` (of the copy tile) into stage buffer `slot`
+    // copy instruction j (0 .. L-1) of this wave's share of the codes of `stage` (of the copy tile) into stage buffer `slot`
     auto issue_one = [&](int j, int stage, int slot) {
         const unsigned base = lds0 + slot * C::STRIDE;
         if (j < C::LA) {
             const unsigned dst = base + (wave * C::LA + j) * 1024;
             if constexpr (TAIL) blds16(ra, oa[j], stage * C::SBA, dst);
             else glds16(abase + (int64_t)stage * C::SBA, oa[j], dst);
-        } else if (j < C::LA + C::LB) {
+        } else {
             const int k = j - C::LA;
             const unsigned dst = base + C::A_BYTES + (wave * C::LB + k) * 1024;
             if constexpr (TAIL) blds16(rb, ob[k], stage * C::SBB, dst);
             else glds16(bbase + (int64_t)stage * C::SBB, ob[k], dst);
-        } else {
-            const int k = j - C::LA - C::LB;
-            const unsigned dst = base + C::A_BYTES + C::B_BYTES + (wave * C::LS + k) * 256;
-            if constexpr (TAIL) blds4(rs, os, scale_uniform(stage, C::NG, spitch) + k * 256, dst);
-            else glds4(sbase[k] + stage * sstep[k], os, dst);
         }
+    };
+    auto issue_scale = [&](int stage, int slot) {
+        const unsigned dst = lds0 + slot * C::STRIDE + C::A_BYTES + C::B_BYTES + sq * 1024;
+        if constexpr (TAIL) blds16(rs, os, scale_uniform(stage, C::NG, spitch), dst);
+        else glds16(sbase + (int64_t)stage * C::NG * (sop ? b_pitch : a_pitch) * 4, os, dst);
     };
     auto issue = [&](int stage, int slot) {
 #pragma unroll
@@ -271,7 +267,7 @@ __global__ __launch_bounds__(NT) void gemm_fast_kernel(const uint8_t* __restrict
 #pragma unroll
             for (int m = 0; m < MB; ++m) sa[i][m] = *reinterpret_cast<const unsigned*>(base + sca_off + q * TM * 4 + m * 128) >> (8 * g);
 #pragma unroll
-            for (int n = 0; n < NB; ++n) sb[i][n] = *reinterpret_cast<const unsigned*>(base + scb_off + q * TNP * 4 + n * 128) >> (8 * g);
+            for (int n = 0; n < NB; ++n) sb[i][n] = *reinterpret_cast<const unsigned*>(base + scb_off + q * TN * 4 + n * 128) >> (8 * g);
             // scale bytes past the last block are unspecified (a group past the last one was delivered as zeros)
             if (TAIL && (R & 127) != 0 && stage * C::NG + q == ngrp - 1) {
                 const unsigned mask = ((1u << (8 * ((R & 127) / kBlock))) - 1u) >> (8 * g);
@@ -289,11 +285,11 @@ __global__ __launch_bounds__(NT) void gemm_fast_kernel(const uint8_t* __restrict
             for (int n = 0; n < NB; ++n) fb[k][n] = read_frag<FB>(tb, n * 32 * C::SBB, offb, p * KP + k);
         }
     };
-    // The MFMAs of phase p.  With COPY the wave's L copy instructions of stage `nxt` (of the copy tile) into
+    // The MFMAs of phase p.  With COPY the wave's copy instructions of stage `nxt` (of the copy tile) into
     // buffer `nslot` are spread evenly between the phase's NM MFMAs (the sched_barriers keep them there).
     constexpr int NM = KP * MB * NB;
     auto MM = [&](auto copy_tag, int p, int nxt, int nslot) {
-        constexpr bool COPY = decltype(copy_tag)::value;
+        constexpr bool COPY = decltype(copy_tag)::value != 0, SCALES = decltype(copy_tag)::value == 2;
         constexpr int ca = FB == kFP8 ? 0 : 4, cb = FA == kFP8 ? 0 : 4;
         __builtin_amdgcn_s_setprio(1);
         int idx = 0;
@@ -310,9 +306,10 @@ __global__ __launch_bounds__(NT) void gemm_fast_kernel(const uint8_t* __restrict
                         acc[m][n] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(fb[k][n], fa[k][m], acc[m][n], ca, cb, 2, (int)sb[k / 2][n], 2, (int)sa[k / 2][m]);
                     if (COPY) {
                         __builtin_amdgcn_sched_barrier(0);
+                        if (SCALES && idx == 0) issue_scale(nxt, nslot);
 #pragma unroll
                         for (int j = 0; j < C::L; ++j)
-                            if (j * NM / C::L == idx) issue_one(j, nxt, nslot);
+                            if ((SCALES ? (j + 1) * NM / (C::L + 1) : j * NM / C::L) == idx) issue_one(j, nxt, nslot);
                         __builtin_amdgcn_sched_barrier(0);
                     }
                     ++idx;
@@ -320,8 +317,9 @@ __global__ __launch_bounds__(NT) void gemm_fast_kernel(const uint8_t* __restrict
         }
         __builtin_amdgcn_s_setprio(0);
     };
-    const std::false_type no_copy{};
-    const std::true_type with_copy{};
+    const std::integral_constant<int, 0> no_copy{};
+    const std::integral_constant<int, 1> with_copy{};
+    const std::integral_constant<int, 2> with_scales{};          // group 0
 
     // ---- result of tile u: optional sum of squares, then every wave transposes its block through its
     //      own part of the staging area at byte `ebase` of the LDS array ----
@@ -475,7 +473,10 @@ __global__ __launch_bounds__(NT) void gemm_fast_kernel(const uint8_t* __restrict
     bool first = true;
     set_copy_tile(u);
 #pragma unroll
-    for (int k = 0; k < NST - 1; ++k) issue(k, k);
+    for (int k = 0; k < NST - 1; ++k) {
+        if (wave < NWAVE / 2) issue_scale(k, k);
+        issue(k, k);
+    }
     for (;;) {
         const int un = u + (int)gridDim.x;
         const bool has_next = un < nblk;
@@ -498,7 +499,7 @@ __global__ __launch_bounds__(NT) void gemm_fast_kernel(const uint8_t* __restrict
                 const int slot = slot_of(s);
                 // the first NST - 1 stages of a later tile were waited for before the previous tile's result was stored;
                 // waiting for them here again would wait for those stores
-                if (first || s >= NST - 1) SNIP_WAIT_VM((NST - 2) * C::L);
+                if (first || s >= NST - 1) SNIP_WAIT_VM((NST - 2) * (C::L + 1));
                 SNIP_BAR();                                         // b(4s)
                 RD(slot, 0, s); SNIP_BAR();      // b(4s+1)
                 MM(copy_tag, 0, cstage, NST == 2 ? slot ^ 1 : before(slot));
@@ -517,7 +518,7 @@ __global__ __launch_bounds__(NT) void gemm_fast_kernel(const uint8_t* __restrict
                 const int cs = past ? (NST == 2 ? 0 : c - nstage) : c;
                 if ((NST == 2 ? past : c == nstage) && has_next) set_copy_tile(un);
                 cut_tail(cs);
-                stage0(with_copy, s, cs);
+                stage0(with_scales, s, cs);
                 if (NST > 2) ring = after(ring);
             }
             SNIP_BAR();                                             // b(4S)
