@@ -770,10 +770,10 @@ __device__ __forceinline__ void store_wave_sums(const float (&sums)[6], int wib,
 
 // Both orientations of one tensor from one pass over HBM (Sec. 2.2: X feeds the forward GEMM with blocks along
 // its rows and the weight-gradient GEMM with blocks down its columns; W and dY likewise).  A wave owns the same
-// units as in quant_col_kernel.  For each 32-row x 128-column tile it runs the column-block path above and then
-// reads the tile a second time with the row kernel's lane layout (a lane = 8 consecutive elements, a quad = one
-// block, 16 lanes = the tile's 128 columns of one row, 4 rows per load): those loads hit in cache, the lines
-// having just been fetched by the same wave.  Results are bit-identical to the two single-orientation kernels.
+// units as in quant_col_kernel.  A 32-row x 128-column tile goes through the column-block path above and, read with the row
+// kernel's lane layout (a lane = 8 consecutive elements, a quad = one block, 16 lanes = the tile's 128 columns of one
+// row, 4 rows per load), through the row path: from LDS, or from cache, the lines having just been fetched by the same wave or
+// workgroup.  Results are bit-identical to the two single-orientation kernels.
 // One column's block in quant_both_kernel's statistics forms: quant_one_column on unpacked elements, with the error of the
 // other format too if STATS == 2.
 template <int FMT, int RULE, int STATS>
@@ -828,6 +828,13 @@ typedef unsigned v2u_t __attribute__((ext_vector_type(2)));
 // where the scalar offset is a constant); stores of 4 and 8 bytes do not read late.
 constexpr int kPast = (int)0x80000000u;                // past the end of every descriptor
 __device__ __forceinline__ rsrc_t tile_rsrc(const void* p) { return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(p), 0, 0x7FFFFFFF, 0x00020000); }
+// Copy of 16 bytes per lane straight into LDS: lane i's land at lds + 16 i (lanes past the descriptor's end: zeros).
+__device__ __forceinline__ void copy_to_lds(rsrc_t r, uint8_t* lds, int voff, int soff)
+{
+#ifdef __HIP_DEVICE_COMPILE__          // (the host pass knows neither the builtin's size of 16 nor the address space)
+    __builtin_amdgcn_raw_ptr_buffer_load_lds(r, (__attribute__((address_space(3))) void*)lds, 16, voff, soff, 0, 0);
+#endif
+}
 __device__ __forceinline__ void step(int& soff, int by)
 {
     soff += by;
@@ -835,6 +842,7 @@ __device__ __forceinline__ void step(int& soff, int by)
 }
 
 // NW != 0: the NW waves of a workgroup share a unit of RBU tiles (wave w takes tiles w, w + NW, ...) and one staging area.
+// RAW_LDS: the tiles of a unit are copied straight into LDS, once, and the waves of rows and columns take them from there.
 // Without statistics NW more waves take the rows of the tiles (SPLIT), and the first NW the columns: 60-67 registers instead
 // of 96 put seven waves on a SIMD instead of four or five, and the two chains of a tile run side by side.  With statistics
 // a workgroup would wait for its column waves, whose work is the longer: [8192 x 4096] FP4 54 us against 41.
@@ -847,7 +855,7 @@ __device__ __forceinline__ void step(int& soff, int by)
 // [16384 x 11008] FP4 195 -> 174, FP8 214 -> 197.
 // Offsets inside a tile are 32-bit: launch_quantize_both keeps to tensors whose rows are short enough (qb_offsets_fit).
 constexpr int qb_threads(int nw, int stats) { return nw ? nw * (stats ? 64 : 128) : 256; }
-template <int FMT_R, int FMT_C, int RULE, int STATS, int NW, int RBU>      // STATS: 0 none, 1 the chosen formats' errors, 2 both formats' errors
+template <int FMT_R, int FMT_C, int RULE, int STATS, int NW, int RBU, bool RAW_LDS>      // STATS: 0 none, 1 the chosen formats' errors, 2 both formats' errors
 __global__ __launch_bounds__(qb_threads(NW, STATS), STATS ? 2 : 1) void quant_both_kernel(const uint16_t* __restrict__ x, int rows, int cols, int64_t ld,
                                                          uint8_t* __restrict__ codes_r, uint8_t* __restrict__ scales_r,
                                                          uint8_t* __restrict__ g4_r, int64_t kpitch_r,
@@ -860,8 +868,12 @@ __global__ __launch_bounds__(qb_threads(NW, STATS), STATS ? 2 : 1) void quant_bo
     constexpr int WPB = qb_threads(NW, STATS) / 64;
     constexpr int ROWB = RBU * (FMT_C == kFP8 ? 32 : 16);
     constexpr int CPR = ROWB / 16;
-    __shared__ __attribute__((aligned(16))) uint8_t stage[COOP ? 1 : kWavesPerBlock][kColsPerWave * ROWB];
+    // RAW_LDS: the raw tiles first, and the column codes in the same place once every wave has its part of them
+    constexpr int RAW = kBlock * kColsPerWave * 2;                            // bytes of a raw tile
+    __shared__ __attribute__((aligned(16))) uint8_t stage[COOP ? 1 : kWavesPerBlock][RAW_LDS && NW * RAW > kColsPerWave * ROWB ? NW * RAW : kColsPerWave * ROWB];
     __shared__ __attribute__((aligned(4))) uint8_t scale_stage[COOP ? RBU * kColsPerWave : 4];   // COOP: scale byte of (tile, column)
+    static_assert(!SPLIT || NW == RBU, "a wave of either kind has one tile");
+    static_assert(SPLIT || !RAW_LDS, "with statistics a wave reads its tile itself");
     const int lane = threadIdx.x & 63;
     const int wib = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     uint8_t* const reg = stage[COOP ? 0 : wib];
@@ -1037,19 +1049,44 @@ __global__ __launch_bounds__(qb_threads(NW, STATS), STATS ? 2 : 1) void quant_bo
             }
             if (g4_r) __builtin_amdgcn_raw_buffer_store_b32(d, tile_rsrc(g4_r + ((int64_t)cg * kpitch_r + row0) * 4), mine ? row * 4 : kPast, 0, 0);
         };
-        if (SPLIT) {
+        if (RAW_LDS) {
+            // 1 KB copies of four rows straight into LDS, dealt to all waves
+#pragma unroll
+            for (int i = 0; i < 8 * RBU / WPB; ++i) {
+                const int q = i * WPB + wib;
+                if (q < nb * 8)
+                    copy_to_lds(tile_x(q >> 3), reg + q * 1024, ract ? (lane >> 4) * pitch_x + (lane & 15) * 16 : kPast, (q & 7) * 4 * pitch_x);
+            }
+            __builtin_amdgcn_s_waitcnt(0x0F70);                // vmcnt(0)
+            __syncthreads();                                   // the raw tiles are there
+            const int k = wib < NW ? wib : wib - NW;
+            const uint8_t* raw = reg + k * RAW;
+            // (behind the second barrier, the same one for both kinds, the tiles are in registers)
             if (wib < NW) {
-                for (int k = wib; k < nb; k += NW) {
-                    unsigned cv[32];
-                    fetch_col(k, cv);
-                    work_col(k, cv);
-                }
+                unsigned cv[32];
+#pragma unroll
+                for (int i = 0; i < 32; ++i) cv[i] = *reinterpret_cast<const unsigned*>(raw + i * 256 + lane * 4);
+                __builtin_amdgcn_s_waitcnt(0xC07F);            // lgkmcnt(0)
+                __syncthreads();
+                if (k < nb) work_col(k, cv);
             } else {
-                for (int k = wib - NW; k < nb; k += NW) {
-                    uint4 rv[8];
-                    fetch_row(k, rv);
-                    work_row(k, rv);
-                }
+                uint4 rv[8];
+#pragma unroll
+                for (int j = 0; j < 8; ++j) rv[j] = *reinterpret_cast<const uint4*>(raw + j * 1024 + lane * 16);
+                __builtin_amdgcn_s_waitcnt(0xC07F);
+                __syncthreads();
+                if (k < nb) work_row(k, rv);
+            }
+        } else if (SPLIT) {
+            const int k = wib < NW ? wib : wib - NW;
+            if (wib < NW && k < nb) {
+                unsigned cv[32];
+                fetch_col(k, cv);
+                work_col(k, cv);
+            } else if (k < nb) {
+                uint4 rv[8];
+                fetch_row(k, rv);
+                work_row(k, rv);
             }
         } else {
             for (int k = COOP ? wib : 0; k < nb; k += COOP ? NW : 1) {
@@ -1434,10 +1471,10 @@ hipError_t launch_quantize(const QuantArgs& a, hipStream_t s)
     return e;
 }
 
-// Work distribution of quant_both_kernel: waves of a workgroup x tiles of the unit they share, or a wave per unit.
-enum class QbForm { k4x4, k4x8, k8x8, kWave };
+// Work distribution of quant_both_kernel: waves of a workgroup x tiles of the unit they share (Lds: RAW_LDS), or a wave per unit.
+enum class QbForm { k4x4, k4x4Lds, k4x8, kWave };
 
-template <int FMT_R, int FMT_C, int RULE, int STATS, int NW, int RBU>
+template <int FMT_R, int FMT_C, int RULE, int STATS, int NW, int RBU, bool RAW_LDS = false>
 static int launch_qb_form(const QuantBothArgs& a, double* partials, hipStream_t s)
 {
     const int64_t nrb = a.rows / kBlock;
@@ -1458,7 +1495,7 @@ static int launch_qb_form(const QuantBothArgs& a, double* partials, hipStream_t 
     // of a tile: at most kStreamBlocks workgroups with equal shares of the units then.
     const int64_t most = STATS ? kStreamBlocks / 8 : (int64_t)1 << 24, run = (units + 8 * turn - 1) / (8 * turn) * turn, share = (run + most - 1) / most;
     const int blocks = NW ? (int)(8 * ((run + share - 1) / share)) : balanced_blocks(units);
-    hipLaunchKernelGGL((quant_both_kernel<FMT_R, FMT_C, RULE, STATS, NW, RBU>), dim3(blocks), dim3(qb_threads(NW, STATS)), 0, s,
+    hipLaunchKernelGGL((quant_both_kernel<FMT_R, FMT_C, RULE, STATS, NW, RBU, RAW_LDS>), dim3(blocks), dim3(qb_threads(NW, STATS)), 0, s,
                        a.x, (int)a.rows, (int)a.cols, a.ld, a.codes_r, a.scales_r, a.g4_r, g4_pitch(a.rows),
                        a.codes_c, a.scales_c, a.g4_c, g4_pitch(a.cols), partials, (int)turn);
     return blocks;
@@ -1471,8 +1508,8 @@ static int launch_qb(const QuantBothArgs& a, double* partials, QbForm form, hipS
         if (form == QbForm::kWave) return launch_qb_form<FMT_R, FMT_C, RULE, STATS, 0, FMT_C == kFP8 ? 4 : 8>(a, partials, s);
     if constexpr (FMT_C == kFP4 && STATS != 0)
         if (form == QbForm::k4x8) return launch_qb_form<FMT_R, FMT_C, RULE, STATS, 4, 8>(a, partials, s);
-    if constexpr (FMT_C == kFP4 && STATS == 0)
-        if (form == QbForm::k8x8) return launch_qb_form<FMT_R, FMT_C, RULE, STATS, 8, 8>(a, partials, s);
+    if constexpr (STATS == 0)
+        if (form == QbForm::k4x4Lds) return launch_qb_form<FMT_R, FMT_C, RULE, STATS, 4, 4, true>(a, partials, s);
     return launch_qb_form<FMT_R, FMT_C, RULE, STATS, 4, 4>(a, partials, s);
 }
 
@@ -1480,10 +1517,13 @@ static int launch_qb(const QuantBothArgs& a, double* partials, QbForm form, hipS
 //   - four waves with a tile each (for either direction, without statistics) wherever nothing else is said: the loads of a
 //     tile are a wave's whole chain.  Against four waves with two tiles each (FP4 codes of columns): [2048 x 2048] 9.0 -> 6.4,
 //     [4096 x 4096] 15.5 -> 12.8, [8192 x 4096] 27.2 -> 21.9.
-//   - without statistics eight and eight waves for FP4 codes of columns from 56 M elements on: a unit then fills 128-byte lines
-//     of the column codes, where halves of them would reach memory one by one: [8192 x 8192] 55.9 (4 x 4) -> 52.9, [16384 x
-//     11008] 143 -> 133, [8192 x 28672] 191 -> 166, [8160 x 8160] 81.5 -> 68.4; [12288 x 4096] 41.7 against 41.3, beside FP8 rows 43.6
-//     against 44.5, [4096 x 4096] 16.5 against 17.4.
+//   - without statistics the tiles go through LDS as soon as a compute unit has more than two units: rows and columns of a
+//     tile both fetched it, which is what bound the kernel (without the rows' share [8192 x 3072] FP4 took 15.7 us of 23.3).  Direct -> LDS:
+//     [16384 x 11008] FP4 139 -> 127 (eight and eight waves to a unit, direct: 135), [32768 x 4096] 101 -> 88, FP8 rows beside FP4 113 -> 102,
+//     FP8 113 -> 108, [8192 x 28672] 206 -> 187, FP8 216 -> 199, [8160 x 8160] FP4 60.5 -> 55.8, [3072 x 3072] 12.3 -> 11.3 and 14.6 ->
+//     12.8.  With up to two units the two more barriers cost 0.1-0.4 us ([2048 x 2048] FP4 7.0 against 7.3), and with more than three
+//     and up to four, of which a compute unit takes three at once, up to 9 % ([3200 x 4096] 14.2 against 15.4, [4096 x 4096] 16.2
+//     against 16.6).
 //   - the complete statistics fill the registers (two waves per SIMD in any form), and a workgroup's barrier and sums cost
 //     8-20 %: a wave per unit as soon as that gives every SIMD work, from 28 M elements (48 M with FP4 codes of columns: eight
 //     tiles per unit): [3072 x 8192] FP8 41.2 (wave) against 38.8 (4 x 4), [8192 x 4096] 41.9 against 47.2; FP4 between
@@ -1497,19 +1537,22 @@ static int launch_qb(const QuantBothArgs& a, double* partials, QbForm form, hipS
 constexpr int64_t kTwoWavesPerSimd = 2048;
 static QbForm pick_qb_form(const QuantBothArgs& a, int stats)
 {
-    // SNIP_QUANT_BOTH_UNIT=4x4|4x8|8x8|wave in the environment, read at every call, fixes the form where it exists for the
+    // SNIP_QUANT_BOTH_UNIT=4x4|lds (or 8x8)|4x8|wave in the environment, read at every call, fixes the form where it exists for the
     // call, =workgroup keeps to a workgroup per unit; for tests and measurements
     bool group = false;
     if (const char* e = getenv("SNIP_QUANT_BOTH_UNIT")) {
         const bool fp4 = a.fmt_c == kFP4;
         const struct { const char* name; QbForm form; bool exists; } kForms[] = {
-            {"4x4", QbForm::k4x4, true}, {"4x8", QbForm::k4x8, fp4 && stats != 0}, {"8x8", QbForm::k8x8, fp4 && stats == 0}, {"wave", QbForm::kWave, stats != 0}};
+            {"4x4", QbForm::k4x4, true}, {"4x8", QbForm::k4x8, fp4 && stats != 0}, {"lds", QbForm::k4x4Lds, stats == 0}, {"8x8", QbForm::k4x4Lds, stats == 0}, {"wave", QbForm::kWave, stats != 0}};
         for (const auto& f : kForms)
             if (!strcmp(e, f.name) && f.exists) return f.form;
         group = !strcmp(e, "workgroup");
     }
     const int64_t elems = a.rows * a.cols;
-    if (stats == 0) return a.fmt_c == kFP4 && elems > ((int64_t)56 << 20) ? QbForm::k8x8 : QbForm::k4x4;
+    if (stats == 0) {
+        const int64_t units = ((a.cols + kColsPerWave - 1) / kColsPerWave) * ((a.rows / kBlock + 3) / 4), ncu = gemm_compute_units();
+        return units > 2 * ncu && !(units > 3 * ncu && units <= 4 * ncu) ? QbForm::k4x4Lds : QbForm::k4x4;
+    }
     if (stats == 1) {
         const int64_t tiles = a.fmt_c == kFP8 ? 4 : 8, waves = ((a.cols + kColsPerWave - 1) / kColsPerWave) * ((a.rows / kBlock + tiles - 1) / tiles);
         const int64_t rounds = (waves + kTwoWavesPerSimd - 1) / kTwoWavesPerSimd;
