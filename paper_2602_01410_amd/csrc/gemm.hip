@@ -230,7 +230,7 @@ __global__ __launch_bounds__(NTHREADS) void gemm_kernel(const uint8_t* __restric
                     ss = (row_ok && col < J) ? fmaf(v, v, ss) : ss;
                 }
         }
-        for (int off = 32; off > 0; off >>= 1) ss += __shfl_xor(ss, off, 64);
+        ss = wave_sum(ss);
         __shared__ float wave_ss[NTHREADS / 64];
         if (lane == 0) wave_ss[wave] = ss;
         __syncthreads();
@@ -300,8 +300,7 @@ __global__ __launch_bounds__(kNormThreads) void reduce_norm_kernel(const float* 
     double a = 0.0;
 #pragma unroll 8
     for (int64_t i = threadIdx.x; i < n; i += kNormThreads) a += (double)partials[i];
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) a += __shfl_xor(a, off, 64);
+    a = wave_sum(a);
     if ((threadIdx.x & 63) == 0) sh[threadIdx.x >> 6] = a;
     __syncthreads();
     if (threadIdx.x == 0) {

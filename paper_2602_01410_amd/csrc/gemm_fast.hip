@@ -366,7 +366,7 @@ __global__ __launch_bounds__(NT) void gemm_fast_kernel(const uint8_t* __restrict
                         }
                 }
             }
-            for (int off = 32; off > 0; off >>= 1) ss += __shfl_xor(ss, off, 64);
+            ss = wave_sum(ss);
             if (lane == 0) wave_ss[wave] = ss;
             __syncthreads();
             if (threadIdx.x == 0) {

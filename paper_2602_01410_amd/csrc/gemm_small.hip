@@ -270,7 +270,7 @@ __global__ __launch_bounds__(T::NT) void gemm_small_kernel(const uint8_t* __rest
                     ss = (row_ok && col < J) ? fmaf(v, v, ss) : ss;
                 }
         }
-        for (int off = 32; off > 0; off >>= 1) ss += __shfl_xor(ss, off, 64);
+        ss = wave_sum(ss);
         if (lane == 0) wave_ss[wave] = ss;
         __syncthreads();
         if (threadIdx.x == 0) {

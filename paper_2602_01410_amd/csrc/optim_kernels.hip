@@ -101,7 +101,7 @@ __global__ __launch_bounds__(256) void adamw_sens_kernel(const float* __restrict
         const float t = sens_any(m[i], v[i], gi, c1, c2, eps);
         acc = fmaf(t, t, acc);
     }
-    for (int off = 32; off > 0; off >>= 1) acc += __shfl_xor(acc, off, 64);
+    acc = wave_sum(acc);
     if (lane == 0) partials[wave] = acc;
 }
 

@@ -42,11 +42,6 @@ __device__ __forceinline__ unsigned pk_max_u16(unsigned a, unsigned b)
     return __builtin_bit_cast(unsigned, __builtin_elementwise_max(__builtin_bit_cast(ushort2_t, a),
                                                                   __builtin_bit_cast(ushort2_t, b)));
 }
-__device__ __forceinline__ float wave_sum(float v)
-{
-    for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);
-    return v;
-}
 __device__ __forceinline__ unsigned umax(unsigned a, unsigned b) { return a > b ? a : b; }
 
 // Scale of a group from the 15 magnitude bits of its bf16 maximum: MAX / amax in fp32, 1 for an all-zero

@@ -65,12 +65,6 @@ __device__ __forceinline__ unsigned quad_max(unsigned m)
     return m > t ? m : t;
 }
 
-__device__ __forceinline__ float wave_sum(float v)
-{
-    for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);
-    return v;
-}
-
 // E8M0 byte from the 15 magnitude bits of the block maximum; 0xFF for Inf/NaN.
 template <int FMT, int RULE>
 __device__ __forceinline__ unsigned scale_byte(unsigned amax_bits)
@@ -1292,8 +1286,7 @@ __device__ __forceinline__ double reduce_workgroup(const double (&a)[N], double 
     if (j < N) {
 #pragma unroll
         for (int k = 0; k < kReduceThreads / 64; ++k) t += sh[j][k * 64 + lane];
-#pragma unroll
-        for (int off = 32; off > 0; off >>= 1) t += __shfl_xor(t, off, 64);
+        t = wave_sum(t);
     }
     return t;
 }
