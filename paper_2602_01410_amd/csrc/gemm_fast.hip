@@ -98,7 +98,7 @@ template <int FA, int FB, class T> struct FCfg {
     static constexpr int epi_base(int last) { return NST == 2 ? (last ? LDS_BYTES - EPI_BYTES : 0) : last * STRIDE; }
     static constexpr int LA = A_BYTES / 1024 / NWAVE;            // 1 KB copies of codes per wave per stage
     static constexpr int LB = B_BYTES / 1024 / NWAVE;
-    static constexpr int L = LA + LB;                            // (and one of scales in waves 0 ... NSC - 1, in front of them)
+    static constexpr int L = LA + LB;                            // (and one of scales in the waves of group 0, in front of them)
     static_assert(NSC <= NWAVE / 2, "the waves of group 0 copy the scales");
     static_assert(STRIDE % 1024 == 0 && SLOT <= STRIDE && (NST - 1) * STRIDE + SLOT <= LDS_BYTES, "stage buffers must not overlap");
     static_assert(EPI_BYTES <= (NST == 2 ? STRIDE : SLOT), "the result staging area must stay clear of the other stage buffers");

@@ -31,8 +31,8 @@ template <> struct Fmt<kFP8> { static constexpr int emax = 8; static constexpr u
 template <> struct Fmt<kFP4> { static constexpr int emax = 2; static constexpr unsigned mmax = 0x40; };  // 6   = 1.5  * 2^2
 
 // Source loads.  A source line is read once and never again, so its load carries the streaming hint (measured:
-// quantize ROW 4.7 -> 5.8 TB/s, COL 4.0 -> 4.75 TB/s of algorithmic bytes on a 361 MB tensor).  The one-pass kernel
-// for both orientations reads every line twice, the second time out of cache: both of its reads are plain loads
+// quantize ROW 4.7 -> 5.8 TB/s, COL 4.0 -> 4.75 TB/s of algorithmic bytes on a 361 MB tensor).  Where the one-pass kernel
+// for both orientations reads every line twice, the second time out of cache, both of its reads are plain loads
 // (with the hint on either one the kernel got 4-6 % slower).
 typedef unsigned v4u_t __attribute__((ext_vector_type(4)));
 __device__ __forceinline__ uint4 ld16(const uint16_t* p)
