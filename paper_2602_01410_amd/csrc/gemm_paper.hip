@@ -19,9 +19,10 @@
 // in blocks / in tiles): [4096 x 2048 x 8192] FP8 158 -> 80 / 93, [4096 x 8192 x 2048] FP8 168 -> 108 / 112 (20 us of it the
 // output rows 16 KB apart: 89 / 101 with padded rows), [4096 x 4096 x 4096] FP4 58 / 72.  1.7 (FP8) and 2.4 (FP4) PFLOP/s with
 // B in blocks; without the copies it would be 2.3 and 3.1, without the fold 5 % more, and of the rest the matrix cores'
-// clock under random operands takes most.  Outputs with enough tiles go to gemm_paper_wide.hip (use_wide).
+// clock under random operands takes most.  Outputs with enough tiles go to gemm_paper_wide.hip (paper_pick.h).
 // Register layout of the instruction: see gemm.hip.
 #include "gemm_common.h"
+#include "paper_pick.h"
 #include <cstdlib>
 #include <cstring>
 
@@ -372,20 +373,8 @@ hipError_t launch_f(const GemmPaperArgs& a, hipStream_t s)
     return a.out_fp32 ? launch_t<FA, FB, true>(a, s) : launch_t<FA, FB, false>(a, s);
 }
 
-// Which kernel serves a call: this one or that of gemm_paper_wide.hip, by the estimate of gemm.hip's tile pick,
-//     start + full rounds * (stages * full + turn) + stages * (alone + (full - alone) * load of the last round)
-// in microseconds, a stage being 256 contraction elements for FP4 x FP4 and 128 else.  Fitted to 90 problems of 128 ... 8192 rows
-// and contraction elements and 36 around whole rounds of tiles, on operands in the caches and from memory (they differ by less
-// than the fit): the pick is on average 0.1 % (FP8) and 0.2 % (FP4) slower than the faster kernel, 10 % at worst; this kernel
-// alone would be 4.5 ... 8.5 % slower, the other alone 16 ... 28 %.
-struct PaperCost { int m; float start, turn, alone, full; };
-constexpr PaperCost kPaperCosts[2][2][2] = {           // [FP4 x FP4][B in tiles][kernel]
-    {{{128, 4.53f, 1.56f, 0.475f, 0.69f}, {256, 4.98f, 2.19f, 0.76f, 1.09f}}, {{128, 4.86f, 1.66f, 0.54f, 0.79f}, {256, 5.41f, 2.20f, 1.06f, 1.37f}}},
-    {{{128, 4.56f, 1.38f, 0.74f, 0.935f}, {256, 5.01f, 1.46f, 1.15f, 1.51f}}, {{128, 5.00f, 1.43f, 0.92f, 1.18f}, {256, 5.46f, 1.60f, 1.71f, 2.03f}}},
-};
-
-// SNIP_GEMM_PAPER_TILE=128x128|256x128 in the environment, read at every call, fixes the kernel where it can serve the call; for
-// tests and measurements.
+// This kernel or that of gemm_paper_wide.hip (paper_pick.h).  SNIP_GEMM_PAPER_TILE=128x128|256x128 in the environment, read at every
+// call, fixes the kernel where it can serve the call; for tests and measurements.
 bool use_wide(const GemmPaperArgs& a)
 {
     if (!gemm_paper_wide_eligible(a)) return false;
@@ -393,16 +382,7 @@ bool use_wide(const GemmPaperArgs& a)
         if (!strcmp(e, "256x128")) return true;
         if (!strcmp(e, "128x128")) return false;
     }
-    const bool both4 = a.fmt_a == kFP4 && a.fmt_b == kFP4;
-    const int64_t ncu = gemm_compute_units(), stages = (a.R + (both4 ? 255 : 127)) / (both4 ? 256 : 128);
-    double t[2];
-    for (int k = 0; k < 2; ++k) {
-        const PaperCost& c = kPaperCosts[both4][a.b_group == 1][k];
-        const int64_t tiles = (a.I + c.m - 1) / c.m * ((a.J + BN - 1) / BN), rounds = (tiles - 1) / ncu;
-        const double load = (double)(tiles - rounds * ncu) / (double)ncu;
-        t[k] = c.start + (double)rounds * ((double)stages * c.full + c.turn) + (double)stages * (c.alone + (c.full - c.alone) * load);
-    }
-    return t[1] < t[0];
+    return paper_wide_pays(a.I, a.J, a.R, a.fmt_a == kFP4 && a.fmt_b == kFP4, a.b_group == 1, gemm_paper_scales16(a), gemm_compute_units());
 }
 
 }  // namespace

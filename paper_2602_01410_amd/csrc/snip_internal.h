@@ -136,6 +136,8 @@ struct GemmPaperArgs {
     int64_t I, J, R;      // C[I][J] = sum_r (A[I][r] / sa) (B[J][r] / sb)
     void* c; int64_t ldc; int out_fp32;
 };
+// Every row's scales on 16 bytes: the 256 x 128 kernel then copies four slabs' at once.
+inline bool gemm_paper_scales16(const GemmPaperArgs& a) { return a.R % 512 == 0 && (((uintptr_t)a.a_scales | (uintptr_t)a.b_scales) & 15) == 0; }
 hipError_t launch_gemm_paper(const GemmPaperArgs& a, hipStream_t s);
 bool gemm_paper_wide_eligible(const GemmPaperArgs& a);
 hipError_t launch_gemm_paper_wide(const GemmPaperArgs& a, hipStream_t s);
