@@ -19,10 +19,10 @@
 // in blocks / in tiles): [4096 x 2048 x 8192] FP8 158 -> 80 / 93, [4096 x 8192 x 2048] FP8 168 -> 108 / 112 (20 us of it the
 // output rows 16 KB apart: 89 / 101 with padded rows), [4096 x 4096 x 4096] FP4 58 / 72.  1.7 (FP8) and 2.4 (FP4) PFLOP/s with
 // B in blocks; without the copies it would be 2.3 and 3.1, without the fold 5 % more, and of the rest the matrix cores'
-// clock under random operands takes most.  Outputs with enough tiles go to gemm_paper_wide.hip (paper_pick.h).
+// clock under random operands takes most.  Outputs with enough tiles go to gemm_paper_wide.hip (picks.h).
 // Register layout of the instruction: see gemm.hip.
 #include "gemm_common.h"
-#include "paper_pick.h"
+#include "picks.h"
 #include <cstdlib>
 #include <cstring>
 
@@ -373,7 +373,7 @@ hipError_t launch_f(const GemmPaperArgs& a, hipStream_t s)
     return a.out_fp32 ? launch_t<FA, FB, true>(a, s) : launch_t<FA, FB, false>(a, s);
 }
 
-// This kernel or that of gemm_paper_wide.hip (paper_pick.h).  SNIP_GEMM_PAPER_TILE=128x128|256x128 in the environment, read at every
+// This kernel or that of gemm_paper_wide.hip (picks.h).  SNIP_GEMM_PAPER_TILE=128x128|256x128 in the environment, read at every
 // call, fixes the kernel where it can serve the call; for tests and measurements.
 bool use_wide(const GemmPaperArgs& a)
 {

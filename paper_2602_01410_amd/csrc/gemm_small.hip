@@ -12,15 +12,17 @@
 //   Measured (us per call, back to back in a graph; before: the general kernel): [64 x 4096 x 4096] FP4 23.6 -> 5.2, FP8
 //   33 -> 7.0; [64 x 4096 x 11008] FP4 53 -> 8.9; [64 x 11008 x 4096] FP4 24.5 -> 6.3; [1504 x 2080 x 1568] FP4 25.3 -> 9.4,
 //   FP8 31.5 -> 11.9; [256 x 512 x 512] FP8 6.5 (256 x 128 tile) -> 3.45.
-//   Waves with one 32 x 32 block have one chain of dependent MFMAs, 160 cycles of a stage's 300; the rest was the LDS latency behind the
-//   last of them and the barrier.  The tiles of one or two such waves therefore take two stages per barrier (G) on operands of up to 10 MB and ask
-//   for the next two during the first five of eight MFMAs: operands in the caches [64 x 4096 x 11008] FP4 9.27 -> 8.33, FP8 16.0 -> 14.1,
-//   [64 x 4096 x 4096] 5.33 -> 4.96 and 7.66 -> 6.79, [1 x 2048 x 2048] FP8 5.03 -> 4.60; from memory the same (18.4 -> 18.3).  With four
-//   stages, or a ring of 12 or 16, slower (the rings' fill and LDS cost more than they hide), the 64 x 64 tile too (12.3 -> 16.7 on [1504 x
-//   2080 x 1568]: one workgroup per compute unit instead of two).  What is left is the chain and 3 us of launch, first fill and result.
+//   Waves with one 32 x 32 block have one chain of dependent MFMAs, 160 cycles of a stage's 300; the rest was the LDS latency behind
+//   the last of them and the barrier.  The tiles of one or two such waves therefore take two stages per barrier (G) on operands of
+//   up to 10 MB, from four stages on (picks.h), and ask for the next two during the first five of eight MFMAs (FP4 x FP4; else two
+//   of four): operands in the caches [64 x 4096 x 11008] FP4 9.27 -> 8.33, FP8 16.0 -> 14.1, [64 x 4096 x 4096] 5.33 -> 4.96 and 7.66 ->
+//   6.79, [1 x 2048 x 2048] FP8 5.03 -> 4.60; from memory the same (18.4 -> 18.3).  With four stages, or a ring of 12 or 16, slower (the
+//   rings' fill and LDS cost more than they hide), the 64 x 64 tile too (12.3 -> 16.7 on [1504 x 2080 x 1568]: one workgroup per
+//   compute unit instead of two).  What is left is the chain and 3 us of launch, first fill and result.
 //   Copies go through buffer descriptors: rows past the end of an operand and chunks past the end of a row deliver
 //   zeros, and the scale bytes past the last block are masked, so any contraction extent that is a multiple of 32 runs.
 #include "gemm_common.h"
+#include "picks.h"
 
 namespace snip {
 namespace {
@@ -362,16 +364,15 @@ bool gemm_small_eligible(const GemmArgs& a)
 
 hipError_t launch_gemm_small(const GemmArgs& a, GemmTile tile, hipStream_t s)
 {
-    const bool cached = gemm_operand_bytes(a) <= kColdBytes;
+    const bool both4 = a.fmt_a == kFP4 && a.fmt_b == kFP4;
+    const bool pairs = small_stages_per_barrier(gemm_operand_bytes(a) <= kColdBytes, (a.R + (both4 ? 255 : 127)) / (both4 ? 256 : 128)) == 2;
     switch (tile) {
         case GemmTile::k128x128: return launch_small_tile<SmallTile<128, 128, 64, 64, 4, 4, 1>>(a, s);
         case GemmTile::k64x64:   return launch_small_tile<SmallTile<64, 64, 32, 32, 4, 4, 1>>(a, s);
-        // Two stages per barrier where operands are likely cached.  From memory their larger steps cost 64 x 32 2-4 %, and 16 % with more
-        // tiles than compute units ([9 x 21120 x 7936] FP8 42.4 -> 49.2), 32 x 32 up to 1 %.
         case GemmTile::k64x32:
-            return cached ? launch_small_tile<SmallTile<64, 32, 32, 32, 6, 4, 2>>(a, s) : launch_small_tile<SmallTile<64, 32, 32, 32, 6, 4, 1>>(a, s);
+            return pairs ? launch_small_tile<SmallTile<64, 32, 32, 32, 6, 4, 2>>(a, s) : launch_small_tile<SmallTile<64, 32, 32, 32, 6, 4, 1>>(a, s);
         default:
-            return cached ? launch_small_tile<SmallTile<32, 32, 32, 32, 8, 4, 2>>(a, s) : launch_small_tile<SmallTile<32, 32, 32, 32, 8, 4, 1>>(a, s);
+            return pairs ? launch_small_tile<SmallTile<32, 32, 32, 32, 8, 4, 2>>(a, s) : launch_small_tile<SmallTile<32, 32, 32, 32, 8, 4, 1>>(a, s);
     }
 }
 

@@ -1,6 +1,9 @@
-// Which kernel serves a GEMM on operands of the paper's recipe, apart from the kernels so that the rule can be checked without
-// a GPU.
-//
+// Rules by which a launcher chooses between kernels, apart from these so that they can be checked without a GPU.
+#pragma once
+
+namespace snip {
+
+// ---- gemm_paper.hip / gemm_paper_wide.hip ----
 // The kernel of gemm_paper.hip (tiles of 128 x 128) or that of gemm_paper_wide.hip (256 x 128), whichever is estimated to be
 // faster,
 //     start + full rounds * turn + stages * slow * (full rounds * full + idle + (full - idle) * load of the last round)
@@ -15,10 +18,6 @@
 // are for by which the wide kernel has to be ahead.  An earlier estimate without `slow` and with `alone` for every last round took
 // it for long contractions with a little more than whole rounds, up to 25 % slower than the other ([4992 x 1792 x 7040] FP8 97 us ->
 // 122, B in tiles 114 -> 151; [3200 x 7640 x 3840] FP4 86 -> 95).
-#pragma once
-
-namespace snip {
-
 struct PaperCost { int rows; double start, turn, alone, full, tail, slow; };
 constexpr PaperCost kPaperCosts[2][2][2] = {           // [FP4 x FP4][B in tiles][kernel]
     {{{128, 4.841, 1.769, 0.483, 0.611, 0.436, 0.}, {256, 5.002, 2.250, 0.730, 1.014, 0.657, 0.104}},
@@ -41,5 +40,13 @@ inline bool paper_wide_pays(long long I, long long J, long long R, bool both4, b
     }
     return t[1] < 0.98 * t[0];
 }
+
+// ---- gemm_small.hip, tiles of 64 x 32 and 32 x 32: stages per barrier ----
+// Two where operands are likely `cached` (up to kColdBytes): from memory the larger steps cost 64 x 32 2-4 %, and 16 % with more tiles
+// than compute units ([9 x 21120 x 7936] FP8 42.4 us -> 49.2), 32 x 32 up to 1 %.  And from four stages on: pairs wait for two stages
+// before they begin and multiply a stage of zeros where the number is odd.  Pairs against single stages, averages over 368
+// problems, either tile: one stage 3.5 % slower (0.1-0.2 us of 3.0: [126 x 224 x 128] FP8 3.14 -> 3.38), two 0.7 % faster, three 1.5 %
+// slower ([98 x 832 x 320] FP8 3.59 -> 3.87), four 2.3 % faster, five the same, seven 1.8 %, eight 5 % and more than that 11 % faster.
+constexpr int small_stages_per_barrier(bool cached, long long stages) { return cached && stages >= 4 ? 2 : 1; }
 
 }  // namespace snip

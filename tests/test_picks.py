@@ -1,0 +1,42 @@
+"""The rules by which launchers choose between kernels (csrc/picks.h), compiled for the host, against what both sides take on an
+MI355X."""
+import os
+import subprocess
+
+import paper_2602_01410_amd
+
+CSRC = os.path.join(os.path.dirname(paper_2602_01410_amd.__file__), "csrc")
+
+# GEMMs of the paper's recipe that the two kernels differ on by 10 % or more: I, J, R, FP4 x FP4, B in tiles, scales on 16 bytes: us with 128 x 128, with 256 x 128 (256 compute units)
+MEASURED = [
+    # a little more than whole rounds of 256 x 128, long contractions whose scales are copied one by one
+    (4992, 1792, 7040, 0, 0, 0, 97.1, 122.0), (4992, 1792, 7040, 0, 1, 0, 114.3, 151.5), (4992, 1792, 7040, 1, 0, 0, 73.6, 90.9),
+    (4992, 1792, 7040, 1, 1, 0, 90.1, 122.7), (6911, 1368, 7040, 0, 0, 0, 100.7, 122.2), (2816, 6784, 6272, 1, 1, 0, 131.9, 166.0),
+    (4252, 6272, 8064, 0, 1, 0, 300.0, 354.6), (3200, 7640, 3840, 1, 0, 0, 86.0, 95.4), (2048, 5120, 7168, 1, 1, 1, 88.8, 102.2),
+    (3072, 3072, 7168, 0, 1, 1, 116.9, 134.7),
+    # whole rounds
+    (4096, 8192, 2048, 0, 0, 1, 98.5, 81.9), (4096, 8192, 2048, 1, 0, 1, 65.8, 52.9), (4096, 2048, 8192, 0, 0, 1, 89.0, 73.9),
+    (4096, 2048, 8192, 0, 1, 1, 100.0, 89.0), (4096, 2048, 8192, 1, 0, 1, 58.3, 47.6), (4096, 2048, 8192, 1, 1, 1, 74.0, 66.0),
+    (8192, 2048, 4096, 0, 1, 1, 103.0, 93.0), (8192, 2048, 4096, 1, 1, 1, 78.0, 68.7), (8192, 8192, 8192, 0, 1, 1, 790.0, 685.0),
+    (5120, 2560, 4608, 1, 1, 1, 79.7, 68.9),
+]
+
+# GEMMs of the small tiles: operands cached, stages: us with one stage per barrier, with two
+STAGES = [(1, 1, 3.14, 3.38), (1, 3, 3.59, 3.87), (1, 64, 14.0, 11.7), (0, 62, 42.4, 49.2)]
+
+
+def run(tmp_path, expression, args):
+    src, exe = tmp_path / "pick.cpp", tmp_path / "pick"
+    src.write_text('#include <cstdio>\n#include <cstdlib>\n#include "picks.h"\nint main(int n, char** v) { auto a = [&](int i) { return std::atoll(v[i + 1]); };\n'
+                   f'std::printf("%d", (int)({expression})); }}\n')
+    subprocess.run(["g++", "-std=c++17", f"-I{CSRC}", str(src), "-o", str(exe)], check=True, timeout=120)
+    return [int(subprocess.run([str(exe), *map(str, row)], capture_output=True, text=True, check=True, timeout=60).stdout) for row in args]
+
+
+def test_paper_kernel(tmp_path):
+    picks = run(tmp_path, "snip::paper_wide_pays(a(0), a(1), a(2), a(3), a(4), a(5), 256)", [m[:6] for m in MEASURED])
+    assert picks == [int(m[7] < m[6]) for m in MEASURED]
+
+
+def test_stages_per_barrier(tmp_path):
+    assert run(tmp_path, "snip::small_stages_per_barrier(a(0), a(1))", [m[:2] for m in STAGES]) == [2 if m[3] < m[2] else 1 for m in STAGES]
