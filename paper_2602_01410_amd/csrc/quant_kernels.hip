@@ -855,7 +855,7 @@ __global__ __launch_bounds__(qb_threads(NW, STATS), STATS ? 2 : 1) void quant_bo
                                                          uint8_t* __restrict__ g4_r, int64_t kpitch_r,
                                                          uint8_t* __restrict__ codes_c, uint8_t* __restrict__ scales_c,
                                                          uint8_t* __restrict__ g4_c, int64_t kpitch_c,
-                                                         double* __restrict__ partials, int turn)
+                                                         double* __restrict__ partials, int eighth)
 {
     constexpr bool COOP = NW != 0, SPLIT = STATS == 0;
     static_assert(COOP || !SPLIT, "a wave per unit is for the statistics");
@@ -882,16 +882,16 @@ __global__ __launch_bounds__(qb_threads(NW, STATS), STATS ? 2 : 1) void quant_bo
     const int pitch_r = FMT_R == kFP8 ? cols : cols / 2, pitch_c = FMT_C == kFP8 ? rows : rows / 2;      // bytes of a stored row
     float s0 = 0.f, se_c = 0.f, se_r = 0.f;
     float so_c = 0.f, so_r = 0.f;                         // STATS == 2: error sums of the format not chosen
-    // COOP: units go to the XCDs (workgroup id mod 8) in turns of `turn` consecutive ones, in an order that walks pairs of row
-    // units column group by column group, so that the two halves of a 128-byte line (FP4 codes of a row: 64 bytes per unit; FP4
-    // codes of a column, likewise) and the scale bytes of neighbouring units meet in one L2 (the grid is a multiple of 8
-    // workgroups).  How many: launch_qb_form.
-    const int v_end = COOP ? (units + 8 * turn - 1) / (8 * turn) * (8 * turn) : units;
+    // COOP: units go to the XCDs (workgroup id mod 8) in turns of eight consecutive ones or, with `eighth` units, in one turn each, in
+    // an order that walks pairs of row units column group by column group, so that the two halves of a 128-byte line (FP4 codes of
+    // a row: 64 bytes per unit; FP4 codes of a column, likewise) and the scale bytes of neighbouring units meet in one L2 (the
+    // grid is a multiple of 8 workgroups).  Which: launch_qb_form.  (Turns of any length would take a division here: 0.1 us of
+    // the 4.0 us of a small call.)
+    const int v_end = !COOP ? units : eighth ? 8 * eighth : (units + 63) / 64 * 64;
     for (int v = COOP ? (int)blockIdx.x : wave; v < v_end; v += COOP ? (int)gridDim.x : nwaves) {
         int ru, cg, u = v;
         if (COOP) {
-            const int i = v >> 3, c = i / turn;
-            u = (c * 8 + (v & 7)) * turn + (i - c * turn);
+            u = eighth ? (v & 7) * eighth + (v >> 3) : (v & ~63) + (v & 7) * 8 + (v >> 3 & 7);
             if (u >= units) continue;
             const int pair = u / (2 * ncg), rem = u - pair * 2 * ncg;
             const bool single = 2 * pair + 1 == nru;                  // the last pair may be one row unit
@@ -1483,14 +1483,14 @@ static int launch_qb_form(const QuantBothArgs& a, double* partials, hipStream_t 
     // 8192] FP4 105, [32768 x 4096] FP8 135.
     const int64_t near = a.cols % (4 * kBlock) != 0 ? (int64_t)24 << 20 : (int64_t)8 << 20;
     const bool eighths = a.rows * a.cols < near || (STATS == 0 && a.cols > 16384 && a.ld % 128 == 0);
-    const int64_t turn = eighths ? (units + 7) / 8 : 8;
+    const int64_t eighth = eighths ? (units + 7) / 8 : 0;
     // A workgroup per unit.  With statistics it also needs a partial-sum slot, and its waves' sums cost as much as a sixth
     // of a tile: at most kStreamBlocks workgroups with equal shares of the units then.
-    const int64_t most = STATS ? kStreamBlocks / 8 : (int64_t)1 << 24, run = (units + 8 * turn - 1) / (8 * turn) * turn, share = (run + most - 1) / most;
+    const int64_t most = STATS ? kStreamBlocks / 8 : (int64_t)1 << 24, run = eighths ? eighth : (units + 63) / 64 * 8, share = (run + most - 1) / most;
     const int blocks = NW ? (int)(8 * ((run + share - 1) / share)) : balanced_blocks(units);
     hipLaunchKernelGGL((quant_both_kernel<FMT_R, FMT_C, RULE, STATS, NW, RBU, RAW_LDS>), dim3(blocks), dim3(qb_threads(NW, STATS)), 0, s,
                        a.x, (int)a.rows, (int)a.cols, a.ld, a.codes_r, a.scales_r, a.g4_r, g4_pitch(a.rows),
-                       a.codes_c, a.scales_c, a.g4_c, g4_pitch(a.cols), partials, (int)turn);
+                       a.codes_c, a.scales_c, a.g4_c, g4_pitch(a.cols), partials, (int)eighth);
     return blocks;
 }
 
