@@ -49,4 +49,22 @@ inline bool paper_wide_pays(long long I, long long J, long long R, bool both4, b
 // slower ([98 x 832 x 320] FP8 3.59 -> 3.87), four 2.3 % faster, five the same, seven 1.8 %, eight 5 % and more than that 11 % faster.
 constexpr int small_stages_per_barrier(bool cached, long long stages) { return cached && stages >= 4 ? 2 : 1; }
 
+// ---- quant_kernels.hip, quantize for both orientations: the order in which units go to the XCDs ----
+// An eighth of the tensor each (true) or turns of eight units.  us per call, dealt one by one / turns of eight / eighths:
+//   - below 8 M elements the tensor fits the L2s: eighths, which lead by a little ([1504 x 2080] FP4 6.4 / 5.9 / 5.8, FP8 6.6 / 6.3 /
+//     6.1), up to 24 M where rows hold no whole number of four blocks, so that scale bytes share dwords and lines with the
+//     neighbours' at odd places ([2432 x 4896] FP4 13.0 / 12.7 / 12.9, FP8 15.4 / 15.6 / 15.3, with all statistics 22.6 / 21.8 / 21.6).
+//   - larger tensors: turns of eight; far apart, the eighths meet in few memory channels.  [16384 x 11008] FP4 131 / 128 / 133, [32768 x
+//     4096] 100.5 / 87.9 / 103 and FP8 116 / 107 / 131, [16384 x 8192] 97.5 / 89.8 / 99.8, [8160 x 8160] 72.7 / 54.2 / 69.4 and 98.8 / 82.3 / 89.6,
+//     [2048 x 22016] 37.9 / 35.8 / 38.8 and 42.6 / 42.2 / 46.4, [6144 x 22016] 104 / 100 / 104 and 119 / 118 / 124; with all statistics
+//     [11008 x 4096] 52.4 / 50.4 / 50.6, [4096 x 4096] 23.3 / 23.7 / 27.7.
+//   - but where the stored columns lie whole multiples of 4096 bytes apart, the column groups of a turn meet in few channels too:
+//     for more than 16384 columns eighths again, without statistics, where rows start on whole lines.  [8192 x 28672] FP4 181 / 166 /
+//     168, FP8 214 / 206 / 198, [8192 x 32768] 218 / 200 / 186 and 254 / 262 / 223, [4096 x 28672] FP8 107 / 104 / 103, beside FP4 rows
+//     103 / 100 / 98.  (FP8 with 16384 columns and less also gains, 2-4 % from 8192 rows on; FP4 loses 2 %.)
+constexpr bool qb_eighths(long long rows, long long cols, long long ld, long long column_bytes, bool stats)
+{
+    return rows * cols < (cols % 128 != 0 ? 24ll << 20 : 8ll << 20) || (!stats && cols > 16384 && ld % 128 == 0 && column_bytes % 4096 == 0);
+}
+
 }  // namespace snip

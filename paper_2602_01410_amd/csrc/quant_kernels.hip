@@ -15,6 +15,7 @@
 //             (exact in fp32) is squared and summed in fp32 per lane, then per wave, and the
 //             per-wave partials are summed in double by a single-block kernel in fixed order.
 #include "snip_internal.h"
+#include "picks.h"
 #include <cstdlib>
 #include <cstring>
 
@@ -1472,17 +1473,10 @@ static int launch_qb_form(const QuantBothArgs& a, double* partials, hipStream_t 
 {
     const int64_t nrb = a.rows / kBlock;
     const int64_t units = ((a.cols + kColsPerWave - 1) / kColsPerWave) * ((nrb + RBU - 1) / RBU);
-    // Order of the units (see quant_both_kernel): in turns of eight (two row units by four column groups) from 8 M elements on, 24 M
-    // if rows hold no whole number of four blocks; an eighth of the tensor each below, where it fits the L2s ([1504 x 2080] FP4 5.7
-    // against 7.8 us), and without statistics for rows of more than 16384 columns that start on whole lines of 256 bytes
-    // ([8192 x 28672] FP4 169 against 175, FP8 214 against 212; [4096 x 16384] 53.5 against 51.8).  Dealt one by one, half lines of
-    // codes and dwords of scales reach memory from two L2s: 37 % more bytes written than there are for [16384 x 11008] FP4.  us per call,
-    // dealt -> turns of eight: that 139 -> 132, FP8 164 -> 160, [8192 x 4096] 30.2 -> 27.6, 33.7 -> 32.0, [32768 x 4096] 101 -> 94, 120 -> 112,
-    // [16384 x 8192] 105 -> 93.5, 125 -> 119, [8160 x 8160] 66 -> 67, 91 -> 82; [4096 x 4096] 16.6 -> 16.3; with all statistics [11008 x
-    // 4096] FP4 55.0 -> 50.8, [3072 x 8192] 33.2 -> 31.6; inside the step of a 70B-shaped block FP4 817 -> 783, FP8 191 -> 184.  Eighths of large tensors, far apart, meet in few memory channels: [16384 x
-    // 8192] FP4 105, [32768 x 4096] FP8 135.
-    const int64_t near = a.cols % (4 * kBlock) != 0 ? (int64_t)24 << 20 : (int64_t)8 << 20;
-    const bool eighths = a.rows * a.cols < near || (STATS == 0 && a.cols > 16384 && a.ld % 128 == 0);
+    // Order of the units (see quant_both_kernel): turns of eight (two row units by four column groups) or an eighth of the tensor
+    // each (picks.h).  Dealt one by one, half lines of codes and dwords of scales reach memory from two L2s: 37 % more bytes
+    // written than there are for [16384 x 11008] FP4.
+    const bool eighths = qb_eighths(a.rows, a.cols, a.ld, FMT_C == kFP8 ? a.rows : a.rows / 2, STATS != 0);
     const int64_t eighth = eighths ? (units + 7) / 8 : 0;
     // A workgroup per unit.  With statistics it also needs a partial-sum slot, and its waves' sums cost as much as a sixth
     // of a tile: at most kStreamBlocks workgroups with equal shares of the units then.

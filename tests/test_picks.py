@@ -24,6 +24,11 @@ MEASURED = [
 # GEMMs of the small tiles: operands cached, stages: us with one stage per barrier, with two
 STAGES = [(1, 1, 3.14, 3.38), (1, 3, 3.59, 3.87), (1, 64, 14.0, 11.7), (0, 62, 42.4, 49.2)]
 
+# one-pass quantize: rows, columns, bytes of a stored column, statistics: us with turns of eight units, with an eighth per XCD
+ORDERS = [(1504, 2080, 752, 0, 5.9, 5.8), (2432, 4896, 1216, 1, 21.8, 21.6), (32768, 4096, 16384, 0, 87.9, 103.0), (8160, 8160, 8160, 0, 82.3, 89.6),
+          (2048, 22016, 1024, 0, 35.8, 38.8), (6144, 22016, 6144, 0, 118.4, 124.5), (8192, 32768, 4096, 0, 199.9, 186.2), (8192, 28672, 8192, 0, 206.3, 198.5),
+          (4096, 4096, 2048, 1, 23.7, 27.7)]
+
 
 def run(tmp_path, expression, args):
     src, exe = tmp_path / "pick.cpp", tmp_path / "pick"
@@ -40,3 +45,8 @@ def test_paper_kernel(tmp_path):
 
 def test_stages_per_barrier(tmp_path):
     assert run(tmp_path, "snip::small_stages_per_barrier(a(0), a(1))", [m[:2] for m in STAGES]) == [2 if m[3] < m[2] else 1 for m in STAGES]
+
+
+def test_unit_order(tmp_path):
+    picks = run(tmp_path, "snip::qb_eighths(a(0), a(1), a(1), a(2), a(3))", [m[:4] for m in ORDERS])
+    assert picks == [int(m[5] < m[4]) for m in ORDERS]
