@@ -1,6 +1,9 @@
-"""GPU parity of snip_gemm_paper where its kernel changes what it does: odd and even numbers of 128-element slabs (FP4 x FP4
+"""GPU parity of snip_gemm_paper where its kernels change what they do: odd and even numbers of 128-element slabs (FP4 x FP4
 takes two per stage), fewer slabs than stage buffers, ragged tiles, more tiles than compute units, every pair of scaling
-groups.  Against the float64 product of the oracle's dequantized operands."""
+groups.  Both kernels (SNIP_GEMM_PAPER_TILE; 256 x 128 where it can serve the call) against the float64 product of the oracle's
+dequantized operands."""
+import itertools
+
 import numpy as np
 import pytest
 import torch
@@ -27,8 +30,8 @@ def operand(snip, rng, rows, cols, fmt, group):
 
 @pytest.mark.parametrize("groups", [(T, T), (T, B), (B, T), (B, B)])
 @pytest.mark.parametrize("fmts", [(0, 0), (1, 1), (0, 1), (1, 0)])
-@pytest.mark.parametrize("shape", [(1, 1, 128), (128, 128, 256), (130, 72, 384), (257, 391, 640), (96, 300, 1152), (2200, 2050, 384)])
-def test_gemm_paper(shape, fmts, groups):
+@pytest.mark.parametrize("shape", [(1, 1, 128), (128, 128, 256), (130, 72, 384), (257, 391, 640), (96, 300, 1152), (2200, 2050, 384), (4352, 2200, 640)])
+def test_gemm_paper(shape, fmts, groups, monkeypatch):
     snip = require_gpu()
     I, J, R = shape
     rng = np.random.default_rng([I, J, R, *fmts, *groups])
@@ -41,7 +44,9 @@ def test_gemm_paper(shape, fmts, groups):
     # A factor taken from a wrong row, column or slab is off by a multiple of the magnitudes.
     mags = np.abs(a) @ np.abs(b).T
     ld = (J + 7) // 8 * 8
-    for dtype, tdtype, own in ((snip.OUT_FP32, torch.float32, 0.0), (snip.OUT_BF16, torch.bfloat16, 2.0 ** -8)):
+    outs = ((snip.OUT_FP32, torch.float32, 0.0), (snip.OUT_BF16, torch.bfloat16, 2.0 ** -8))
+    for tile, (dtype, tdtype, own) in itertools.product(("128x128", "256x128"), outs):
+        monkeypatch.setenv("SNIP_GEMM_PAPER_TILE", tile)
         buf = torch.full((I, ld), 7.0, dtype=tdtype, device="cuda")
         snip.snip_gemm_paper(*qa, *qb, out=buf[:, :J], out_dtype=dtype)
         torch.cuda.synchronize()
@@ -52,10 +57,11 @@ def test_gemm_paper(shape, fmts, groups):
 
 @pytest.mark.parametrize("group_a", [T, B])
 @pytest.mark.parametrize("fmts", [(0, 0), (1, 1), (0, 1), (1, 0)])
-def test_non_finite_group_stays_in_its_column(fmts, group_a):
+def test_non_finite_group_stays_in_its_column(fmts, group_a, monkeypatch):
     # More tiles than compute units: a workgroup's second tile must not see the factors of its first one's last slab.  One
     # infinity per 128 rows of B, in the last slab, always at another offset (two tiles with the same one would hide it).
     snip = require_gpu()
+    monkeypatch.setenv("SNIP_GEMM_PAPER_TILE", "128x128")
     n, R = 17 * 128, 256
     if (n // 128) ** 2 <= torch.cuda.get_device_properties(0).multi_processor_count:
         pytest.fail("the shape needs more tiles")

@@ -1,7 +1,7 @@
 """GPU parity of the 256 x 128 tile of snip_gemm_paper where it changes what it does: three stages (the least it takes) and
 more, odd numbers of slabs, chunks of scales that do not fill a fetch or do not start on 16 bytes, ragged tiles, more tiles than
-compute units.  Products, factors and their order are those of the 128 x 128 tile, so the bits have to be the same; that one is
-checked against the oracle (test_gpu_gemm_paper.py)."""
+compute units.  Products, factors and their order are those of the 128 x 128 tile, so the bits have to be the same; both are checked
+against the oracle too (test_gpu_gemm_paper.py)."""
 import pytest
 import torch
 
@@ -43,6 +43,20 @@ def test_same_bits_as_the_small_tile(shape, fmts, groups, monkeypatch):
     for dtype in (snip.OUT_FP32, snip.OUT_BF16):
         small, wide = both_tiles(snip, monkeypatch, qa, qb, I, J, dtype)
         assert torch.equal(small, wide)
+
+
+# Three stages and four (FP8 and mixed formats; FP4 x FP4 has three in 640 above): a tile of less than one fetch of scales and of
+# exactly one, alone and with a second tile per workgroup
+@pytest.mark.parametrize("groups", [(T, T), (T, B)])
+@pytest.mark.parametrize("fmts", [(0, 0), (0, 1), (1, 0)])
+@pytest.mark.parametrize("shape", [(300, 200, 384), (300, 200, 512), (4352, 2200, 384), (4352, 2200, 512)])
+def test_short_contractions(shape, fmts, groups, monkeypatch):
+    snip = require_gpu()
+    I, J, R = shape
+    gen = torch.Generator(device="cuda").manual_seed(I + J + R)
+    qa, qb = operand(snip, gen, I, R, fmts[0], groups[0]), operand(snip, gen, J, R, fmts[1], groups[1])
+    small, wide = both_tiles(snip, monkeypatch, qa, qb, I, J, snip.OUT_FP32)
+    assert torch.equal(small, wide)
 
 
 @pytest.mark.parametrize("groups", [(T, T), (T, B)])
