@@ -171,9 +171,9 @@ typedef enum { SNIP_STATS_CHOSEN_FORMAT = 0, SNIP_STATS_BOTH_FORMATS = 1 } snip_
  *             Sec. 4.2) together with its two quantized orientations from one read.  Ignored
  *             without statistics outputs.
  * A 128-column unit is worked on by one workgroup or, in calls with statistics on large tensors, by
- * one wave; the environment variable SNIP_QUANT_BOTH_UNIT=4x4|4x8|8x8|wave (waves of a workgroup x
- * 32-row tiles of the unit they share, or a wave per unit), read at every call, fixes the form where it
- * exists for the call, =workgroup rules out a wave per unit; for tests and measurements (codes and scales
+ * one wave; the environment variable SNIP_QUANT_BOTH_UNIT=4x4|lds|4x8|wave (waves of a workgroup x
+ * 32-row tiles of the unit they share; lds: 4x4 with the tiles copied into LDS first; a wave per unit),
+ * read at every call, fixes the form where it exists for the call, =workgroup rules out a wave per unit; for tests and measurements (codes and scales
  * do not depend on it; the statistics are summed in another fixed order). */
 snip_status snip_quantize_both(const void* x, int64_t rows, int64_t cols, int64_t ld,
                                snip_scale_rule rule, const snip_qtensor* out_row,

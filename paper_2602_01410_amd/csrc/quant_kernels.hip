@@ -1506,11 +1506,11 @@ static int launch_qb(const QuantBothArgs& a, double* partials, QbForm form, hipS
 //     [4096 x 4096] 15.5 -> 12.8, [8192 x 4096] 27.2 -> 21.9.
 //   - without statistics the tiles go through LDS as soon as a compute unit has more than two units: rows and columns of a
 //     tile both fetched it, which is what bound the kernel (without the rows' share [8192 x 3072] FP4 took 15.7 us of 23.3).  Direct -> LDS:
-//     [16384 x 11008] FP4 139 -> 127 (eight and eight waves to a unit, direct: 135), [32768 x 4096] 101 -> 88, FP8 rows beside FP4 113 -> 102,
-//     FP8 113 -> 108, [8192 x 28672] 206 -> 187, FP8 216 -> 199, [8160 x 8160] FP4 60.5 -> 55.8, [3072 x 3072] 12.3 -> 11.3 and 14.6 ->
-//     12.8.  With up to two units the two more barriers cost 0.1-0.4 us ([2048 x 2048] FP4 7.0 against 7.3), and with more than three
-//     and up to four, of which a compute unit takes three at once, up to 9 % ([3200 x 4096] 14.2 against 15.4, [4096 x 4096] 16.2
-//     against 16.6).
+//     [16384 x 11008] FP4 140 -> 127, FP8 162 -> 160, [32768 x 4096] 101 -> 88 and 112 -> 106, FP8 rows beside FP4 columns 106 -> 98, [8192 x
+//     28672] 191 -> 169 and 215 -> 199, FP4 rows beside FP8 207 -> 186, [8160 x 8160] 59.8 -> 55.1 and 81.8 -> 80.6, [3072 x 3072] 12.5 ->
+//     11.4 and 15.0 -> 13.1.  With up to two units the two more barriers cost 0.3-0.45 us ([2048 x 2048] FP4 5.9 against 6.3, FP8 6.9
+//     against 7.3), and with more than three and up to four, of which a compute unit takes three at once, up to 8 % ([3200 x 4096]
+//     14.4 against 15.2, mixed 15.9 against 17.2; [4096 x 4096] 16.2 against 16.3).
 //   - the complete statistics fill the registers (two waves per SIMD in any form), and a workgroup's barrier and sums cost
 //     8-20 %: a wave per unit as soon as that gives every SIMD work, from 28 M elements (48 M with FP4 codes of columns: eight
 //     tiles per unit): [3072 x 8192] FP8 41.2 (wave) against 38.8 (4 x 4), [8192 x 4096] 41.9 against 47.2; FP4 between
@@ -1524,13 +1524,13 @@ static int launch_qb(const QuantBothArgs& a, double* partials, QbForm form, hipS
 constexpr int64_t kTwoWavesPerSimd = 2048;
 static QbForm pick_qb_form(const QuantBothArgs& a, int stats)
 {
-    // SNIP_QUANT_BOTH_UNIT=4x4|lds (or 8x8)|4x8|wave in the environment, read at every call, fixes the form where it exists for the
+    // SNIP_QUANT_BOTH_UNIT=4x4|lds|4x8|wave in the environment, read at every call, fixes the form where it exists for the
     // call, =workgroup keeps to a workgroup per unit; for tests and measurements
     bool group = false;
     if (const char* e = getenv("SNIP_QUANT_BOTH_UNIT")) {
         const bool fp4 = a.fmt_c == kFP4;
         const struct { const char* name; QbForm form; bool exists; } kForms[] = {
-            {"4x4", QbForm::k4x4, true}, {"4x8", QbForm::k4x8, fp4 && stats != 0}, {"lds", QbForm::k4x4Lds, stats == 0}, {"8x8", QbForm::k4x4Lds, stats == 0}, {"wave", QbForm::kWave, stats != 0}};
+            {"4x4", QbForm::k4x4, true}, {"4x8", QbForm::k4x8, fp4 && stats != 0}, {"lds", QbForm::k4x4Lds, stats == 0}, {"wave", QbForm::kWave, stats != 0}};
         for (const auto& f : kForms)
             if (!strcmp(e, f.name) && f.exists) return f.form;
         group = !strcmp(e, "workgroup");

@@ -20,12 +20,12 @@ def gemm_tile(request, monkeypatch):
     return request.param
 
 
-@pytest.fixture(params=["wave", "4x4", "4x8", "8x8"])
+@pytest.fixture(params=["wave", "4x4", "4x8", "lds"])
 def quant_both_unit(request, monkeypatch):
     """Runs a test of the one-pass two-orientation quantize once per work distribution (a wave per 128-column unit, or
-    workgroups of 4 or 8 waves that share a unit of 4 or 8 tiles): the library reads SNIP_QUANT_BOTH_UNIT at every call.
-    4x4 exists for every call, wave with statistics, 4x8 for FP4 columns with statistics, 8x8 for FP4 columns
-    without; elsewhere the library keeps to its own choice."""
+    workgroups of 4 waves that share a unit of 4 or 8 tiles): the library reads SNIP_QUANT_BOTH_UNIT at every call.
+    4x4 exists for every call, wave with statistics, 4x8 for FP4 columns with statistics, lds (4x4 with the tiles copied
+    into LDS first) without statistics; elsewhere the library keeps to its own choice."""
     monkeypatch.setenv("SNIP_QUANT_BOTH_UNIT", request.param)
     return request.param
 

@@ -10,10 +10,10 @@ from gpu_util import host, require_gpu
 pytestmark = pytest.mark.gpu
 
 
-def check(rows, cols, fr, fc, rule, stats):
+def check(rows, cols, fr, fc, rule, stats, pad=8):
     snip = require_gpu()
     gen = torch.Generator(device="cuda").manual_seed(rows * 31 + cols)
-    x = torch.randn((rows, cols + 8), generator=gen, device="cuda", dtype=torch.float32).bfloat16()[:, :cols]
+    x = torch.randn((rows, cols + pad), generator=gen, device="cuda", dtype=torch.float32).bfloat16()[:, :cols]
     qr, qc = snip.alloc_qtensor(rows, cols, fr), snip.alloc_qtensor(cols, rows, fc)
     for q in (qr, qc):
         q.codes.fill_(0xA5)
@@ -49,12 +49,12 @@ def test_small(shape, fmts, stats, quant_both_unit):
 
 
 # the library's own choice: four waves with two tiles each (12 M ... 48 M elements, FP4 columns; 48 M = 50331648: just below and
-# just above), a wave per unit (beyond, FP8 columns from 28 M), eight waves with a tile each (beyond the memory-side cache) and
-# the limited occupancy of FP8 columns beside FP4 rows; with the written formats' statistics a wave per unit from 56 M on, where
-# it fills its rounds, or four waves with two tiles each
+# just above), a wave per unit (beyond, FP8 columns from 28 M); without statistics tiles through LDS, with rows of more than 16384
+# columns in either order of the units; with the written formats' statistics a wave per unit from 56 M on, where it fills its
+# rounds, or four waves with two tiles each
 @pytest.mark.parametrize("shape,fmts,stats", [((3232, 4128), (1, 1), 2), ((3232, 4128), (0, 1), 2), ((8224, 6112), (1, 1), 2), ((8224, 6176), (1, 1), 2),
                                               ((8224, 4128), (0, 0), 2), ((8224, 6176), (1, 0), 0), ((16672, 8096), (1, 1), 0),
-                                              ((16672, 8096), (0, 1), 0), ((16672, 8096), (0, 0), 0), ((16672, 8096), (1, 1), 1),
+                                              ((16672, 8096), (0, 1), 0), ((16672, 8096), (0, 0), 0), ((16672, 8096), (1, 1), 1), ((4096, 16512), (0, 0), 0), ((2080, 16512), (1, 1), 0),
                                               ((8192, 7392), (1, 1), 1), ((8192, 7392), (0, 0), 1), ((8224, 8224), (0, 1), 1), ((3232, 6624), (0, 1), 1)])
 def test_large(shape, fmts, stats):
-    check(*shape, *fmts, 1 if stats == 0 else 0, stats)
+    check(*shape, *fmts, 1 if stats == 0 else 0, stats, 128 if shape[1] > 16384 else 8)
