@@ -5,10 +5,14 @@
 //   What bounds the 128 x 128 tile of gemm_paper.hip is its copies (32 KB per 4.2 MFLOP) and one compute wave per SIMD, whose
 //   LDS latencies and barrier nothing covers.  Here eight waves of 64 x 64 (4 x 2) share a tile of 256 x 128 (24 KB per 4.2
 //   MFLOP) and alternate, as in gemm_fast.hip: of the two waves of a SIMD one reads its operands of a stage from LDS while the
-//   other issues its MFMAs and folds the products of the blocks before, one phase apart, workgroup barriers between (the
-//   schedule, the barriers b(..) and the reasons why the buffers are free when they are refilled: gemm_fast.hip, 256 x 128).
-//   Three stage buffers of 128 code bytes per row.  A wave issues its global->LDS copies behind its operand reads: here its MFMA
-//   phase is full of vector instructions (between the MFMAs FP4 with B in blocks took 3-7 % longer, FP8 the same).
+//   other issues its MFMAs and folds the products of the blocks before, one phase apart, workgroup barriers between:
+//       b(4s)    group 0 (waves 0-3) R(s)    group 1 M(s - 1)
+//       b(4s+1)  group 0 M(s)                group 1 R(s)             b(4s+4) follows
+//   Three stage buffers of 128 code bytes per row.  In R(s) a wave issues its global->LDS copies of stage s + 2 behind its operand
+//   reads, into the buffer of stage s - 1: that was read last in group 1's R(s - 1), which waits for its reads before b(4s).  (Here
+//   the MFMA phase is full of vector instructions: with the copies between the MFMAs, as in gemm_fast.hip, FP4 with B in blocks took
+//   3-7 % longer, FP8 the same.)  Stage s + 1 has landed at b(4s+4): group 0 waits in front of that barrier for all but its copies
+//   of stage s + 2, group 1 behind its own issue of them.
 //   The fold takes 16 (B in 128 x 128 blocks: one factor per lane and slab) or 32 (a factor per column) vector instructions
 //   per 32 x 32 block beside 2 x 64 (FP8) or 2 x 32 (FP4) cycles of MFMA; an instruction takes 4.3 cycles and an MFMA blocks
 //   their issue for about 20, so that with a factor per column the vector instructions are what bounds it.
@@ -284,7 +288,7 @@ __global__ __launch_bounds__(NT) void gemm_paper_wide_kernel(const uint8_t* __re
             fold_block(c1, c1, 0, 16);
         }
     };
-    // The MFMAs of a stage, the fold and, between them, the wave's copies of stage `nxt` into buffer `nslot`.
+    // The MFMAs of a stage and, between them, the fold.
     auto MM = [&]() __attribute__((always_inline)) {
         if (!B_BLOCK) __builtin_amdgcn_s_setprio(1);             // (with a block's single factor it slows the other wave's divisions down: FP4 50.1 -> 54.8 us)
         slab(c0);
@@ -372,8 +376,10 @@ __global__ __launch_bounds__(NT) void gemm_paper_wide_kernel(const uint8_t* __re
         }
         clear();
         if (wave < NWAVE / 2) {
-            // group 0 issues its code copies of stage s + 2 during M(s), and in the first stage of a chunk the scale copies of the
-            // next chunk (of the next tile's first one) in front of them: behind the wait of any later stage they have landed
+            // group 0 issues its code copies of stage s + 2 in R(s), and the scale copies of the next chunk (or of the next tile's
+            // first one) in front of M(s) of a chunk's first stage s.  These are its newest copies at the wait of stage s + 1, which
+            // may leave them in flight; that of stage s + 2 (the first that can read them), the one before `convert` and the one
+            // behind the last stage do not.
             for (int s = 0; s < nstage; ++s) {
                 const int c = s + NST - 1, cs = c >= nstage ? c - nstage : c;
                 const int in_chunk = s & (SPC - 1);
@@ -400,7 +406,7 @@ __global__ __launch_bounds__(NT) void gemm_paper_wide_kernel(const uint8_t* __re
             SNIP_WAIT_VM(0);                                        // own shares of the next tile's first stages and scales
             convert(cbuf);
         } else {
-            // group 1 issues its copies of stage s + 3 during M(s), those of stage 2 while it idles through the tile's first phase
+            // group 1 issues its copies of stage s + 2 in R(s), a phase after group 0, and none in the tile's first phase
             auto stage1 = [&](int s, int cstage) {
                 SNIP_BAR();                                         // b(4s+1)
                 RD(ring, s, cbuf, cstage, before(ring));
