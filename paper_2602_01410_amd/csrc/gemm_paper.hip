@@ -280,55 +280,11 @@ __global__ __launch_bounds__(NT) void gemm_paper_kernel(const uint8_t* __restric
         }
     };
 
-    // Result of a tile: every wave turns its 64 x 64 block through its own 4 KB of LDS, 32 rows x 128 bytes at a time.
-    constexpr int ESZ = OUT_F32 ? 4 : 2;
-    uint8_t* const reg = lds + C::OFF_E + wave * C::EPI;
+    uint8_t* const reg = lds + C::OFF_E + wave * C::EPI;         // result staging of the wave
     auto store_tile = [&](int u) {
         int ti, tj;
         tile_of(u, ntile, tiles_i, tiles_j, ti, tj);
-        const int i0 = ti * BM + wm * WTM, j0 = tj * BN + wn * WTN;
-        // 16-byte piece c of row r sits at position c ^ (r / 2 % 8) (bf16: a piece is written in two halves)
-#pragma unroll
-        for (int m = 0; m < MB; ++m)
-#pragma unroll
-            for (int h = 0; h < (OUT_F32 ? NB : 1); ++h) {
-                const int f = (r32 >> 1) & 7;
-                if (OUT_F32) {
-#pragma unroll
-                    for (int q = 0; q < 4; ++q)
-                        *reinterpret_cast<float4*>(reg + r32 * 128 + (((q * 2 + g) ^ f) * 16)) =
-                            make_float4(acc[m][h][4 * q], acc[m][h][4 * q + 1], acc[m][h][4 * q + 2], acc[m][h][4 * q + 3]);
-                } else {
-#pragma unroll
-                    for (int n = 0; n < NB; ++n)
-#pragma unroll
-                        for (int q = 0; q < 4; ++q) {
-                            const float2_t lo = {acc[m][n][4 * q], acc[m][n][4 * q + 1]}, hi = {acc[m][n][4 * q + 2], acc[m][n][4 * q + 3]};
-                            const bf16x2 blo = __builtin_convertvector(lo, bf16x2), bhi = __builtin_convertvector(hi, bf16x2);
-                            *reinterpret_cast<uint2*>(reg + r32 * 128 + (((n * 4 + q) ^ f) * 16) + 8 * g) =
-                                make_uint2(__builtin_bit_cast(unsigned, blo), __builtin_bit_cast(unsigned, bhi));
-                        }
-                }
-#pragma unroll
-                for (int it = 0; it < 4; ++it) {
-                    const int row = it * 8 + lane / 8, c = lane % 8;
-                    const uint4 v = *reinterpret_cast<const uint4*>(reg + row * 128 + ((c ^ ((row >> 1) & 7)) * 16));
-                    const int i = i0 + m * 32 + row, j = j0 + h * 32 + c * (16 / ESZ);
-                    if (i < I) {
-                        uint8_t* p = reinterpret_cast<uint8_t*>(c_out) + ((int64_t)i * ldc + j) * ESZ;
-                        if (j + 16 / ESZ <= J) {
-                            *reinterpret_cast<uint4*>(p) = v;
-                        } else {
-                            const unsigned w[4] = {v.x, v.y, v.z, v.w};
-                            for (int e = 0; e < 16 / ESZ; ++e)
-                                if (j + e < J) {
-                                    if (OUT_F32) reinterpret_cast<unsigned*>(p)[e] = w[e];
-                                    else reinterpret_cast<uint16_t*>(p)[e] = (uint16_t)(w[e >> 1] >> (16 * (e & 1)));
-                                }
-                        }
-                    }
-                }
-            }
+        store_block64<OUT_F32>(acc, reg, lane, c_out, ldc, ti * BM + wm * WTM, tj * BN + wn * WTN, I, J, false, false);
     };
 
     SNIP_BAR();                                              // stage 0 is complete

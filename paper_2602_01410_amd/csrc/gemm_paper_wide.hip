@@ -296,56 +296,10 @@ __global__ __launch_bounds__(NT) void gemm_paper_wide_kernel(const uint8_t* __re
         if (!B_BLOCK) __builtin_amdgcn_s_setprio(0);
     };
 
-    // ---- result of a tile: every wave turns its 64 x 64 block through its own 4 KB of the last stage's buffer, 32 rows x 128
-    // bytes at a time; 16-byte piece c of row r sits at position c ^ (r / 2 % 8) (bf16: a piece is written in two halves)
-    constexpr int ESZ = OUT_F32 ? 4 : 2;
+    // ---- result of a tile, staged in the last stage's buffer
     auto store_tile = [&](int ti0, int tj0, int slot) __attribute__((always_inline)) {
-        uint8_t* const reg = lds + slot * C::SLOT + wave * C::EPI;
-        const int i0 = ti0 + wm * WTM, j0 = tj0 + wn * WTN;
-        const bool interior = ti0 + TM <= I && tj0 + TN <= J;
-        const int f = (r32 >> 1) & 7;
-#pragma unroll
-        for (int m = 0; m < MB; ++m)
-#pragma unroll
-            for (int h = 0; h < (OUT_F32 ? NB : 1); ++h) {
-                if (OUT_F32) {
-#pragma unroll
-                    for (int q = 0; q < 4; ++q)
-                        *reinterpret_cast<float4*>(reg + r32 * 128 + (((q * 2 + g) ^ f) * 16)) =
-                            make_float4(acc[m][h][4 * q], acc[m][h][4 * q + 1], acc[m][h][4 * q + 2], acc[m][h][4 * q + 3]);
-                } else {
-#pragma unroll
-                    for (int n = 0; n < NB; ++n)
-#pragma unroll
-                        for (int q = 0; q < 4; ++q) {
-                            const float2_t lo = {acc[m][n][4 * q], acc[m][n][4 * q + 1]}, hi = {acc[m][n][4 * q + 2], acc[m][n][4 * q + 3]};
-                            const bf16x2 blo = __builtin_convertvector(lo, bf16x2), bhi = __builtin_convertvector(hi, bf16x2);
-                            *reinterpret_cast<uint2*>(reg + r32 * 128 + (((n * 4 + q) ^ f) * 16) + 8 * g) =
-                                make_uint2(__builtin_bit_cast(unsigned, blo), __builtin_bit_cast(unsigned, bhi));
-                        }
-                }
-#pragma unroll
-                for (int it = 0; it < 4; ++it) {
-                    const int row = it * 8 + lane / 8, c = lane % 8;
-                    const v4u v = *reinterpret_cast<const v4u*>(reg + row * 128 + ((c ^ ((row >> 1) & 7)) * 16));
-                    const int i = i0 + m * 32 + row, j = j0 + h * 32 + c * (16 / ESZ);
-                    uint8_t* p = reinterpret_cast<uint8_t*>(c_out) + ((int64_t)i * ldc + j) * ESZ;
-                    if (interior) {
-                        if (stream_out) __builtin_nontemporal_store(v, reinterpret_cast<v4u*>(p));
-                        else *reinterpret_cast<v4u*>(p) = v;
-                    } else if (i < I) {
-                        if (j + 16 / ESZ <= J) {
-                            *reinterpret_cast<v4u*>(p) = v;
-                        } else if (j < J) {
-                            for (int e = 0; e < 16 / ESZ; ++e)
-                                if (j + e < J) {
-                                    if (OUT_F32) reinterpret_cast<unsigned*>(p)[e] = v[e];
-                                    else reinterpret_cast<uint16_t*>(p)[e] = (uint16_t)(v[e >> 1] >> (16 * (e & 1)));
-                                }
-                        }
-                    }
-                }
-            }
+        store_block64<OUT_F32>(acc, lds + slot * C::SLOT + wave * C::EPI, lane, c_out, ldc, ti0 + wm * WTM, tj0 + wn * WTN, I, J,
+                               ti0 + TM <= I && tj0 + TN <= J, stream_out != 0);
     };
 
     auto after = [](int slot) { return slot == NST - 1 ? 0 : slot + 1; };

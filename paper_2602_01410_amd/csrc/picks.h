@@ -14,7 +14,7 @@ namespace snip {
 // Fitted to 21564 problems (128 ... 16384 rows, contractions of 384 ... 8192: random, around whole rounds, multiples of 256 ... 1024;
 // FP8 x FP8 and FP4 x FP4, B in blocks and in tiles, operands in the caches and from memory, which differ by less than the
 // fit).  On 5632 others the pick is on average 0.15 % slower than the faster kernel, 10 % at worst, and 128 x 128 alone 3.9 %; on
-// 10408 more, mixed formats among them, 0.6 % are more than 3 % slower than with 128 x 128 alone, 11 % at worst, which is what the 2 %
+// 20066 more, mixed formats among them, 0.5 % are more than 3 % slower than with 128 x 128 alone, 11 % at worst, which is what the 2 %
 // are for by which the wide kernel has to be ahead.  An earlier estimate without `slow` and with `alone` for every last round took
 // it for long contractions with a little more than whole rounds, up to 25 % slower than the other ([4992 x 1792 x 7040] FP8 97 us ->
 // 122, B in tiles 114 -> 151; [3200 x 7640 x 3840] FP4 86 -> 95).
