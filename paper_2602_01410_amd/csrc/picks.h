@@ -1,5 +1,6 @@
 // Rules by which a launcher chooses between kernels, apart from these so that they can be checked without a GPU.
 #pragma once
+#include "copy_ranges.h"      // SNIP_HD
 
 namespace snip {
 
@@ -49,7 +50,27 @@ inline bool paper_wide_pays(long long I, long long J, long long R, bool both4, b
 // slower ([98 x 832 x 320] FP8 3.59 -> 3.87), four 2.3 % faster, five the same, seven 1.8 %, eight 5 % and more than that 11 % faster.
 constexpr int small_stages_per_barrier(bool cached, long long stages) { return cached && stages >= 4 ? 2 : 1; }
 
-// ---- quant_kernels.hip, quantize for both orientations: the order in which units go to the XCDs ----
+// ---- quant_kernels.hip, quantize for both orientations: the order of the units among the XCDs ----
+// A unit is a row unit (RBU tiles of 32 rows) of a column group (128 columns).  Workgroup ids go to the XCDs in turn (id mod 8); units
+// go to them in turns of eight consecutive ones or, if `eighth` is not 0, `eighth` units each.  Consecutive units walk pairs of row units
+// column group by column group (a turn is two row units by four column groups), so that the two halves of a 128-byte line (FP4
+// codes of a row: 64 bytes per unit; FP4 codes of a column, likewise) and the scale bytes of neighbours meet in one L2.  Dealt one by
+// one, 37 % more bytes reached memory than there are for [16384 x 11008] FP4.  (Turns of any length would take a division in qb_unit: 0.1
+// us of the 4.0 us of a small call.)
+// In turns, what row units the pairs leave over, and a last one with fewer tiles, are walked by themselves behind all others: where
+// there are a few more units than fit at once, whole ones at the end are a round of their own (all statistics, [1344 x 11264] FP4 28.6 us
+// instead of 24.2, [2912 x 5632] 29.0 instead of 26.0, [800 x 27392] 36.2 instead of 32.9).  With eighths one XCD would have nearly all
+// the short ones ([160 x 25984] FP4 7.1 instead of 6.4): they stay in their pairs.
+struct QbPlace { int ru, cg; };
+SNIP_HD constexpr int qb_unit(int v, int eighth) { return eighth ? (v & 7) * eighth + (v >> 3) : (v & ~63) + (v & 7) * 8 + (v >> 3 & 7); }
+SNIP_HD constexpr int qb_pairs(int whole_row_units, int row_units, int eighth) { return (eighth ? row_units : whole_row_units) / 2; }
+SNIP_HD constexpr QbPlace qb_place(int u, int pairs, int ncg)
+{
+    const int paired = pairs * 2 * ncg;
+    const bool in_pair = u < paired;
+    const int band = in_pair ? 2 * ncg : ncg, from = in_pair ? u : u - paired, k = from / band, rem = from - k * band;
+    return in_pair ? QbPlace{2 * k + (rem & 1), rem >> 1} : QbPlace{2 * pairs + k, rem};
+}
 // An eighth of the tensor each (true) or turns of eight units.  us per call, dealt one by one / turns of eight / eighths:
 //   - below 8 M elements the tensor fits the L2s: eighths, which lead by a little ([1504 x 2080] FP4 6.4 / 5.9 / 5.8, FP8 6.6 / 6.3 /
 //     6.1), up to 24 M where rows hold no whole number of four blocks, so that scale bytes share dwords and lines with the

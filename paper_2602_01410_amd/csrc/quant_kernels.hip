@@ -883,25 +883,14 @@ __global__ __launch_bounds__(qb_threads(NW, STATS), STATS ? 2 : 1) void quant_bo
     const int pitch_r = FMT_R == kFP8 ? cols : cols / 2, pitch_c = FMT_C == kFP8 ? rows : rows / 2;      // bytes of a stored row
     float s0 = 0.f, se_c = 0.f, se_r = 0.f;
     float so_c = 0.f, so_r = 0.f;                         // STATS == 2: error sums of the format not chosen
-    // COOP: units go to the XCDs (workgroup id mod 8) in turns of eight consecutive ones or, with `eighth` units, in one turn each, in
-    // an order that walks pairs of row units column group by column group, so that the two halves of a 128-byte line (FP4 codes of
-    // a row: 64 bytes per unit; FP4 codes of a column, likewise) and the scale bytes of neighbouring units meet in one L2 (the
-    // grid is a multiple of 8 workgroups).  Which: launch_qb_form.  (Turns of any length would take a division here: 0.1 us of
-    // the 4.0 us of a small call.)
+    // COOP: the order of the units (qb_place and qb_eighths in picks.h; the grid is a multiple of 8 workgroups); else row unit by row unit
+    const int pairs = COOP ? qb_pairs(nrb / RBU, nru, eighth) : 0;
     const int v_end = !COOP ? units : eighth ? 8 * eighth : (units + 63) / 64 * 64;
     for (int v = COOP ? (int)blockIdx.x : wave; v < v_end; v += COOP ? (int)gridDim.x : nwaves) {
-        int ru, cg, u = v;
-        if (COOP) {
-            u = eighth ? (v & 7) * eighth + (v >> 3) : (v & ~63) + (v & 7) * 8 + (v >> 3 & 7);
-            if (u >= units) continue;
-            const int pair = u / (2 * ncg), rem = u - pair * 2 * ncg;
-            const bool single = 2 * pair + 1 == nru;                  // the last pair may be one row unit
-            ru = 2 * pair + (single ? 0 : rem & 1);
-            cg = single ? rem : rem >> 1;
-        } else {
-            ru = u / ncg;
-            cg = u - ru * ncg;
-        }
+        const int u = COOP ? qb_unit(v, eighth) : v;
+        if (COOP && u >= units) continue;
+        const QbPlace place = qb_place(u, pairs, ncg);
+        const int ru = place.ru, cg = place.cg;
         const int c0 = cg * kColsPerWave;
         const bool act = c0 + lane * 2 < cols;                        // column direction: this lane's 2 columns
         const bool ract = c0 + (lane & 15) * 8 < cols;                // row direction: this lane's 8 columns
@@ -1473,9 +1462,7 @@ static int launch_qb_form(const QuantBothArgs& a, double* partials, hipStream_t 
 {
     const int64_t nrb = a.rows / kBlock;
     const int64_t units = ((a.cols + kColsPerWave - 1) / kColsPerWave) * ((nrb + RBU - 1) / RBU);
-    // Order of the units (see quant_both_kernel): turns of eight (two row units by four column groups) or an eighth of the tensor
-    // each (picks.h).  Dealt one by one, half lines of codes and dwords of scales reach memory from two L2s: 37 % more bytes
-    // written than there are for [16384 x 11008] FP4.
+    // order of the units (picks.h)
     const bool eighths = qb_eighths(a.rows, a.cols, a.ld, FMT_C == kFP8 ? a.rows : a.rows / 2, STATS != 0);
     const int64_t eighth = eighths ? (units + 7) / 8 : 0;
     // A workgroup per unit.  With statistics it also needs a partial-sum slot, and its waves' sums cost as much as a sixth

@@ -50,3 +50,45 @@ def test_stages_per_barrier(tmp_path):
 def test_unit_order(tmp_path):
     picks = run(tmp_path, "snip::qb_eighths(a(0), a(1), a(1), a(2), a(3))", [m[:4] for m in ORDERS])
     assert picks == [int(m[5] < m[4]) for m in ORDERS]
+
+
+ORDER_PROGRAM = r"""
+#include <algorithm>
+#include <cstdio>
+#include <vector>
+#include "picks.h"
+using namespace snip;
+#define CHECK(c) do { if (!(c)) { std::printf("line %d: %s (row units %d, whole %d, column groups %d, eighth %d)\n", __LINE__, #c, nru, whole, ncg, eighth); return 1; } } while (0)
+int main()
+{
+    for (int nru = 1; nru <= 21; ++nru) for (int whole = nru - 1; whole <= nru; ++whole) for (int ncg = 1; ncg <= 40; ++ncg) for (int in_turns = 0; in_turns < 2; ++in_turns) {
+        const int units = nru * ncg, eighth = in_turns ? 0 : (units + 7) / 8, end = eighth ? 8 * eighth : (units + 63) / 64 * 64;
+        const int pairs = qb_pairs(whole, nru, eighth);
+        std::vector<int> seen(units, 0);
+        for (int v = 0; v < end; ++v) {
+            const int u = qb_unit(v, eighth);
+            if (u >= units) continue;
+            const QbPlace p = qb_place(u, pairs, ncg);
+            CHECK(u >= 0 && p.ru >= 0 && p.ru < nru && p.cg >= 0 && p.cg < ncg);
+            ++seen[p.ru * ncg + p.cg];
+            // short units come last, of all or, in eighths, of their pair
+            if (in_turns) CHECK((u >= whole * ncg) == (p.ru >= whole));
+            // an XCD's eight in a row are two row units by four column groups
+            if (in_turns && u % 8 == 0 && u + 7 < pairs * 2 * ncg && u % (2 * ncg) + 7 < 2 * ncg) {
+                const QbPlace q = qb_place(u + 7, pairs, ncg);
+                CHECK(p.ru % 2 == 0 && q.ru == p.ru + 1 && q.cg == p.cg + 3 && qb_unit(v + 56, eighth) == u + 7);
+            }
+        }
+        CHECK(std::all_of(seen.begin(), seen.end(), [](int n) { return n == 1; }));
+    }
+    return 0;
+}
+"""
+
+
+def test_every_unit_once_and_short_ones_last(tmp_path):
+    src, exe = tmp_path / "order.cpp", tmp_path / "order"
+    src.write_text(ORDER_PROGRAM)
+    subprocess.run(["g++", "-std=c++17", "-O2", f"-I{CSRC}", str(src), "-o", str(exe)], check=True, timeout=120)
+    res = subprocess.run([str(exe)], capture_output=True, text=True, timeout=120)
+    assert res.returncode == 0, res.stdout
