@@ -61,15 +61,27 @@ constexpr int small_stages_per_barrier(bool cached, long long stages) { return c
 // there are a few more units than fit at once, whole ones at the end are a round of their own (all statistics, [1344 x 11264] FP4 28.6 us
 // instead of 24.2, [2912 x 5632] 29.0 instead of 26.0, [800 x 27392] 36.2 instead of 32.9).  With eighths one XCD would have nearly all
 // the short ones ([160 x 25984] FP4 7.1 instead of 6.4): they stay in their pairs.
+// Where the stored columns are no whole number of 128-byte lines, every row unit shares lines of every column with the next one, and
+// bands of four row units instead of two (a turn of four by two) leave fewer of them to two L2s: FP4 columns beside FP8 rows, pairs
+// -> four, [86080 x 2048] 155 -> 129, [52000 x 2048] 96.7 -> 81.1, [28608 x 6144] 159 -> 137, [8160 x 11008] 90.4 -> 84.2, [25760 x 1984] 49.2 ->
+// 43.7; on average 2 % below 64 M elements and 6 % above, at worst 6.5 % slower.  Not where the last column group is a part of one:
+// the rows' lines run on into the next group, and a turn of four by two splits more of these ([22624 x 8288] FP4 161 -> 174), unless
+// bands of four bring the same columns to the same XCD again (16 groups or an odd multiple).  Nor at a multiple of 32 groups or near
+// one, where pairs do that already ([8160 x 8160] FP4 54.3 -> 60.9, [2624 x 16000] 36.1 -> 38.5).
 struct QbPlace { int ru, cg; };
 SNIP_HD constexpr int qb_unit(int v, int eighth) { return eighth ? (v & 7) * eighth + (v >> 3) : (v & ~63) + (v & 7) * 8 + (v >> 3 & 7); }
-SNIP_HD constexpr int qb_pairs(int whole_row_units, int row_units, int eighth) { return (eighth ? row_units : whole_row_units) / 2; }
-SNIP_HD constexpr QbPlace qb_place(int u, int pairs, int ncg)
+SNIP_HD constexpr int qb_bands(int whole_row_units, int row_units, int eighth, int log2) { return (eighth ? row_units : whole_row_units) >> log2; }
+SNIP_HD constexpr QbPlace qb_place(int u, int bands, int log2, int ncg)
 {
-    const int paired = pairs * 2 * ncg;
-    const bool in_pair = u < paired;
-    const int band = in_pair ? 2 * ncg : ncg, from = in_pair ? u : u - paired, k = from / band, rem = from - k * band;
-    return in_pair ? QbPlace{2 * k + (rem & 1), rem >> 1} : QbPlace{2 * pairs + k, rem};
+    const int banded = (bands * ncg) << log2;
+    const bool in_band = u < banded;
+    const int band = in_band ? ncg << log2 : ncg, from = in_band ? u : u - banded, k = from / band, rem = from - k * band;
+    return in_band ? QbPlace{(k << log2) + (rem & ((1 << log2) - 1)), rem >> log2} : QbPlace{(bands << log2) + k, rem};
+}
+constexpr int qb_band_log2(long long cols, long long column_bytes)
+{
+    const long long phase = (cols + 127) / 128 % 32;
+    return column_bytes % 128 != 0 && (phase == 16 || (cols % 128 == 0 && phase >= 4 && phase <= 28)) ? 2 : 1;
 }
 // An eighth of the tensor each (true) or turns of eight units.  us per call, dealt one by one / turns of eight / eighths:
 //   - below 8 M elements the tensor fits the L2s: eighths, which lead by a little ([1504 x 2080] FP4 6.4 / 5.9 / 5.8, FP8 6.6 / 6.3 /

@@ -856,7 +856,7 @@ __global__ __launch_bounds__(qb_threads(NW, STATS), STATS ? 2 : 1) void quant_bo
                                                          uint8_t* __restrict__ g4_r, int64_t kpitch_r,
                                                          uint8_t* __restrict__ codes_c, uint8_t* __restrict__ scales_c,
                                                          uint8_t* __restrict__ g4_c, int64_t kpitch_c,
-                                                         double* __restrict__ partials, int eighth)
+                                                         double* __restrict__ partials, int eighth, int band_log2)
 {
     constexpr bool COOP = NW != 0, SPLIT = STATS == 0;
     static_assert(COOP || !SPLIT, "a wave per unit is for the statistics");
@@ -884,12 +884,12 @@ __global__ __launch_bounds__(qb_threads(NW, STATS), STATS ? 2 : 1) void quant_bo
     float s0 = 0.f, se_c = 0.f, se_r = 0.f;
     float so_c = 0.f, so_r = 0.f;                         // STATS == 2: error sums of the format not chosen
     // COOP: the order of the units (qb_place and qb_eighths in picks.h; the grid is a multiple of 8 workgroups); else row unit by row unit
-    const int pairs = COOP ? qb_pairs(nrb / RBU, nru, eighth) : 0;
+    const int bands = COOP ? qb_bands(nrb / RBU, nru, eighth, band_log2) : 0;
     const int v_end = !COOP ? units : eighth ? 8 * eighth : (units + 63) / 64 * 64;
     for (int v = COOP ? (int)blockIdx.x : wave; v < v_end; v += COOP ? (int)gridDim.x : nwaves) {
         const int u = COOP ? qb_unit(v, eighth) : v;
         if (COOP && u >= units) continue;
-        const QbPlace place = qb_place(u, pairs, ncg);
+        const QbPlace place = qb_place(u, bands, band_log2, ncg);
         const int ru = place.ru, cg = place.cg;
         const int c0 = cg * kColsPerWave;
         const bool act = c0 + lane * 2 < cols;                        // column direction: this lane's 2 columns
@@ -1463,7 +1463,9 @@ static int launch_qb_form(const QuantBothArgs& a, double* partials, hipStream_t 
     const int64_t nrb = a.rows / kBlock;
     const int64_t units = ((a.cols + kColsPerWave - 1) / kColsPerWave) * ((nrb + RBU - 1) / RBU);
     // order of the units (picks.h)
-    const bool eighths = qb_eighths(a.rows, a.cols, a.ld, FMT_C == kFP8 ? a.rows : a.rows / 2, STATS != 0);
+    const int64_t column_bytes = FMT_C == kFP8 ? a.rows : a.rows / 2;
+    const bool eighths = qb_eighths(a.rows, a.cols, a.ld, column_bytes, STATS != 0);
+    const int band_log2 = eighths ? 1 : qb_band_log2(a.cols, column_bytes);
     const int64_t eighth = eighths ? (units + 7) / 8 : 0;
     // A workgroup per unit.  With statistics it also needs a partial-sum slot, and its waves' sums cost as much as a sixth
     // of a tile: at most kStreamBlocks workgroups with equal shares of the units then.
@@ -1471,7 +1473,7 @@ static int launch_qb_form(const QuantBothArgs& a, double* partials, hipStream_t 
     const int blocks = NW ? (int)(8 * ((run + share - 1) / share)) : balanced_blocks(units);
     hipLaunchKernelGGL((quant_both_kernel<FMT_R, FMT_C, RULE, STATS, NW, RBU, RAW_LDS>), dim3(blocks), dim3(qb_threads(NW, STATS)), 0, s,
                        a.x, (int)a.rows, (int)a.cols, a.ld, a.codes_r, a.scales_r, a.g4_r, g4_pitch(a.rows),
-                       a.codes_c, a.scales_c, a.g4_c, g4_pitch(a.cols), partials, (int)eighth);
+                       a.codes_c, a.scales_c, a.g4_c, g4_pitch(a.cols), partials, (int)eighth, band_log2);
     return blocks;
 }
 

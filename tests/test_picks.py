@@ -29,6 +29,10 @@ ORDERS = [(1504, 2080, 752, 0, 5.9, 5.8), (2432, 4896, 1216, 1, 21.8, 21.6), (32
           (2048, 22016, 1024, 0, 35.8, 38.8), (6144, 22016, 6144, 0, 118.4, 124.5), (8192, 32768, 4096, 0, 199.9, 186.2), (8192, 28672, 8192, 0, 206.3, 198.5),
           (4096, 4096, 2048, 1, 23.7, 27.7)]
 
+# ... in turns: columns, bytes of a stored column: us with pairs of row units, with four
+BANDS = [(2048, 43040, 154.8, 129.0), (2048, 26000, 96.7, 81.1), (6144, 14304, 159.4, 137.0), (11008, 4080, 90.4, 84.2), (1984, 12880, 49.2, 43.7),
+         (8160, 4080, 54.3, 60.9), (11008, 8192, 127.6, 130.7), (4096, 16384, 87.2, 89.6), (8288, 11312, 160.6, 174.1)]
+
 
 def run(tmp_path, expression, args):
     src, exe = tmp_path / "pick.cpp", tmp_path / "pick"
@@ -52,6 +56,11 @@ def test_unit_order(tmp_path):
     assert picks == [int(m[5] < m[4]) for m in ORDERS]
 
 
+def test_bands(tmp_path):
+    picks = run(tmp_path, "snip::qb_band_log2(a(0), a(1))", [m[:2] for m in BANDS])
+    assert picks == [1 + int(m[3] < m[2]) for m in BANDS]
+
+
 ORDER_PROGRAM = r"""
 #include <algorithm>
 #include <cstdio>
@@ -61,22 +70,22 @@ using namespace snip;
 #define CHECK(c) do { if (!(c)) { std::printf("line %d: %s (row units %d, whole %d, column groups %d, eighth %d)\n", __LINE__, #c, nru, whole, ncg, eighth); return 1; } } while (0)
 int main()
 {
-    for (int nru = 1; nru <= 21; ++nru) for (int whole = nru - 1; whole <= nru; ++whole) for (int ncg = 1; ncg <= 40; ++ncg) for (int in_turns = 0; in_turns < 2; ++in_turns) {
+    for (int nru = 1; nru <= 21; ++nru) for (int whole = nru - 1; whole <= nru; ++whole) for (int ncg = 1; ncg <= 40; ++ncg) for (int in_turns = 0; in_turns < 2; ++in_turns) for (int log2 = 1; log2 <= 1 + in_turns; ++log2) {
         const int units = nru * ncg, eighth = in_turns ? 0 : (units + 7) / 8, end = eighth ? 8 * eighth : (units + 63) / 64 * 64;
-        const int pairs = qb_pairs(whole, nru, eighth);
+        const int bands = qb_bands(whole, nru, eighth, log2), band = 1 << log2;
         std::vector<int> seen(units, 0);
         for (int v = 0; v < end; ++v) {
             const int u = qb_unit(v, eighth);
             if (u >= units) continue;
-            const QbPlace p = qb_place(u, pairs, ncg);
+            const QbPlace p = qb_place(u, bands, log2, ncg);
             CHECK(u >= 0 && p.ru >= 0 && p.ru < nru && p.cg >= 0 && p.cg < ncg);
             ++seen[p.ru * ncg + p.cg];
             // short units come last, of all or, in eighths, of their pair
             if (in_turns) CHECK((u >= whole * ncg) == (p.ru >= whole));
-            // an XCD's eight in a row are two row units by four column groups
-            if (in_turns && u % 8 == 0 && u + 7 < pairs * 2 * ncg && u % (2 * ncg) + 7 < 2 * ncg) {
-                const QbPlace q = qb_place(u + 7, pairs, ncg);
-                CHECK(p.ru % 2 == 0 && q.ru == p.ru + 1 && q.cg == p.cg + 3 && qb_unit(v + 56, eighth) == u + 7);
+            // an XCD's eight in a row are two row units by four column groups, or four by two
+            if (in_turns && u % 8 == 0 && u + 7 < bands * band * ncg && u % (band * ncg) + 7 < band * ncg && u % (band * ncg) % band == 0) {
+                const QbPlace q = qb_place(u + 7, bands, log2, ncg);
+                CHECK(p.ru % band == 0 && q.ru == p.ru + band - 1 && q.cg == p.cg + 8 / band - 1 && qb_unit(v + 56, eighth) == u + 7);
             }
         }
         CHECK(std::all_of(seen.begin(), seen.end(), [](int n) { return n == 1; }));
