@@ -100,4 +100,18 @@ constexpr bool qb_eighths(long long rows, long long cols, long long ld, long lon
     return rows * cols < (cols % 128 != 0 ? 24ll << 20 : 8ll << 20) || (!stats && cols > 16384 && ld % 128 == 0 && column_bytes % 4096 == 0);
 }
 
+// ---- ... whether its tiles go through LDS, without statistics ----
+// As soon as a compute unit has more than two units: rows and columns of a tile both fetched it, which is what bound the kernel
+// (without the rows' share [8192 x 3072] FP4 took 15.7 us of 23.3).  Direct -> LDS: [16384 x 11008] FP4 140 -> 127, FP8 162 -> 160, [32768 x
+// 4096] 101 -> 88 and 112 -> 106, FP8 rows beside FP4 columns 106 -> 98, [8192 x 28672] 191 -> 169 and 215 -> 199, FP4 rows beside FP8
+// 207 -> 186, [8160 x 8160] 59.8 -> 55.1 and 81.8 -> 80.6, [3072 x 3072] 12.5 -> 11.4 and 15.0 -> 13.1.  With up to two units the two more
+// barriers cost 0.3-0.45 us ([2048 x 2048] FP4 5.9 against 6.3, FP8 6.9 against 7.3), and with more than three and up to four, of
+// which a compute unit takes three at once, up to 8 % ([3200 x 4096] 14.4 against 15.2, mixed 15.9 against 17.2; [4096 x 4096] 16.2
+// against 16.3).  Half a column group and less is too little to fetch for that: [140800 x 32] FP4 9.2 against 10.2, [68736 x 64] 7.1
+// against 7.8, [262144 x 32] 14.5 against 15.5; with 96 columns they are even (8.9 and 8.8 on [68736 x 96]).
+constexpr bool qb_through_lds(long long cols, long long units, long long ncu)
+{
+    return cols > 64 && units > 2 * ncu && !(units > 3 * ncu && units <= 4 * ncu);
+}
+
 }  // namespace snip

@@ -1493,13 +1493,7 @@ static int launch_qb(const QuantBothArgs& a, double* partials, QbForm form, hipS
 //   - four waves with a tile each (for either direction, without statistics) wherever nothing else is said: the loads of a
 //     tile are a wave's whole chain.  Against four waves with two tiles each (FP4 codes of columns): [2048 x 2048] 9.0 -> 6.4,
 //     [4096 x 4096] 15.5 -> 12.8, [8192 x 4096] 27.2 -> 21.9.
-//   - without statistics the tiles go through LDS as soon as a compute unit has more than two units: rows and columns of a
-//     tile both fetched it, which is what bound the kernel (without the rows' share [8192 x 3072] FP4 took 15.7 us of 23.3).  Direct -> LDS:
-//     [16384 x 11008] FP4 140 -> 127, FP8 162 -> 160, [32768 x 4096] 101 -> 88 and 112 -> 106, FP8 rows beside FP4 columns 106 -> 98, [8192 x
-//     28672] 191 -> 169 and 215 -> 199, FP4 rows beside FP8 207 -> 186, [8160 x 8160] 59.8 -> 55.1 and 81.8 -> 80.6, [3072 x 3072] 12.5 ->
-//     11.4 and 15.0 -> 13.1.  With up to two units the two more barriers cost 0.3-0.45 us ([2048 x 2048] FP4 5.9 against 6.3, FP8 6.9
-//     against 7.3), and with more than three and up to four, of which a compute unit takes three at once, up to 8 % ([3200 x 4096]
-//     14.4 against 15.2, mixed 15.9 against 17.2; [4096 x 4096] 16.2 against 16.3).
+//   - without statistics the tiles go through LDS where qb_through_lds (picks.h) says so.
 //   - the complete statistics fill the registers (two waves per SIMD in any form), and a workgroup's barrier and sums cost
 //     8-20 %: a wave per unit as soon as that gives every SIMD work, from 28 M elements (48 M with FP4 codes of columns: eight
 //     tiles per unit): [3072 x 8192] FP8 41.2 (wave) against 38.8 (4 x 4), [8192 x 4096] 41.9 against 47.2; FP4 between
@@ -1526,8 +1520,8 @@ static QbForm pick_qb_form(const QuantBothArgs& a, int stats)
     }
     const int64_t elems = a.rows * a.cols;
     if (stats == 0) {
-        const int64_t units = ((a.cols + kColsPerWave - 1) / kColsPerWave) * ((a.rows / kBlock + 3) / 4), ncu = gemm_compute_units();
-        return units > 2 * ncu && !(units > 3 * ncu && units <= 4 * ncu) ? QbForm::k4x4Lds : QbForm::k4x4;
+        const int64_t units = ((a.cols + kColsPerWave - 1) / kColsPerWave) * ((a.rows / kBlock + 3) / 4);
+        return qb_through_lds(a.cols, units, gemm_compute_units()) ? QbForm::k4x4Lds : QbForm::k4x4;
     }
     if (stats == 1) {
         const int64_t tiles = a.fmt_c == kFP8 ? 4 : 8, waves = ((a.cols + kColsPerWave - 1) / kColsPerWave) * ((a.rows / kBlock + tiles - 1) / tiles);

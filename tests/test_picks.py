@@ -33,6 +33,10 @@ ORDERS = [(1504, 2080, 752, 0, 5.9, 5.8), (2432, 4896, 1216, 1, 21.8, 21.6), (32
 BANDS = [(2048, 43040, 154.8, 129.0), (2048, 26000, 96.7, 81.1), (6144, 14304, 159.4, 137.0), (11008, 4080, 90.4, 84.2), (1984, 12880, 49.2, 43.7),
          (8160, 4080, 54.3, 60.9), (11008, 8192, 127.6, 130.7), (4096, 16384, 87.2, 89.6), (8288, 11312, 160.6, 174.1)]
 
+# ... columns, units: us with tiles read directly, through LDS
+LDS = [(32, 1100, 9.24, 10.23), (64, 537, 7.08, 7.79), (96, 537, 8.87, 8.84), (11008, 11008, 140.5, 126.9), (4096, 8192, 101.2, 87.7), (2048, 256, 5.9, 6.3),
+       (3072, 576, 12.5, 11.4), (4096, 800, 14.4, 15.2)]
+
 
 def run(tmp_path, expression, args):
     src, exe = tmp_path / "pick.cpp", tmp_path / "pick"
@@ -59,6 +63,11 @@ def test_unit_order(tmp_path):
 def test_bands(tmp_path):
     picks = run(tmp_path, "snip::qb_band_log2(a(0), a(1))", [m[:2] for m in BANDS])
     assert picks == [1 + int(m[3] < m[2]) for m in BANDS]
+
+
+def test_through_lds(tmp_path):
+    picks = run(tmp_path, "snip::qb_through_lds(a(0), a(1), 256)", [m[:2] for m in LDS])
+    assert picks == [int(m[3] < m[2]) for m in LDS]
 
 
 ORDER_PROGRAM = r"""
