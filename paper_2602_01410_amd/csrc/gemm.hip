@@ -352,10 +352,10 @@ int gemm_compute_units()
 // pairs), `tail` at least `alone`: a lower one fits some long contractions better and picks tiles whose last round is a
 // quarter full ([2048 x 2304 x 3072] FP8 37 us with 128 x 128 for 26 with 256 x 128).  On 1233 other problems the pick is on
 // average 0.2 % (cached, up to 10 MB) and 0.5 % (from memory, more) slower than the fastest tile, 20 % at worst (rows of few
-// tokens by very wide weights, where the tables are rough).  The cached stages of 64 x 32 and 32 x 32 were lowered by hand when
-// these took up two stages per barrier; with the table as it is, 368 cached problems of 1 ... 1024 rows and 1 ... 86 stages, many of
-// them odd or cut, come out 0.6 % slower on average than with the fastest tile (one stage 0.8 %, three 1.4 %, six and more 0.4 %), 16 %
-// at worst ([241 x 10048 x 320] FP8 x FP4: 128 x 128, 7.4 us, for 64 x 64, 6.4).
+// tokens by very wide weights, where the tables are rough).  The cached stages of 64 x 32 and 32 x 32 were lowered by hand
+// when 32 x 32 took up two stages per barrier; with the tables and kernels as they are, 2600 problems of up to 10 MB (1 ... 1024 rows,
+// contractions of 96 ... 16384, many cut) come out 0.13 % slower on average than with the fastest small tile, from the caches and from
+// memory, 20 % at worst ([608 x 6752 x 2048] FP8 x FP4: 128 x 128 for 64 x 64).
 struct TileCost { GemmTile tile; int m, n; float start, turn, alone[2], full[2], tail[2]; };      // [0]: FP4 x FP4, [1]: others
 static const TileCost kTileCosts[2][6] = {{
     {GemmTile::kBig,      256, 256, 7.7f, 4.5f, {0.61f, 0.62f}, {1.90f, 1.42f}, {0.61f, 0.62f}},

@@ -13,11 +13,12 @@
 //   33 -> 7.0; [64 x 4096 x 11008] FP4 53 -> 8.9; [64 x 11008 x 4096] FP4 24.5 -> 6.3; [1504 x 2080 x 1568] FP4 25.3 -> 9.4,
 //   FP8 31.5 -> 11.9; [256 x 512 x 512] FP8 6.5 (256 x 128 tile) -> 3.45.
 //   Waves with one 32 x 32 block have one chain of dependent MFMAs, 160 cycles of a stage's 300; the rest was the LDS latency behind
-//   the last of them and the barrier.  The tiles of one or two such waves therefore take two stages per barrier (G) on operands of
-//   up to 10 MB, from four stages on (picks.h), and ask for the next two during the first five of eight MFMAs (FP4 x FP4; else two
-//   of four): operands in the caches [64 x 4096 x 11008] FP4 9.27 -> 8.33, FP8 16.0 -> 14.1, [64 x 4096 x 4096] 5.33 -> 4.96 and 7.66 ->
-//   6.79, [1 x 2048 x 2048] FP8 5.03 -> 4.60; from memory the same (18.4 -> 18.3).  With four stages, or a ring of 12 or 16, slower (the
-//   rings' fill and LDS cost more than they hide), the 64 x 64 tile too (12.3 -> 16.7 on [1504 x 2080 x 1568]: one workgroup per
+//   the last of them and the barrier.  The 32 x 32 tile therefore takes two stages per barrier (G) on operands of up to 10 MB, from
+//   four stages on (picks.h), and asks for the next two during the first five of eight MFMAs (FP4 x FP4; else two of four): operands
+//   in the caches [64 x 4096 x 4096] FP4 5.40 -> 4.95, FP8 7.24 -> 6.76, [64 x 4096 x 11008] 9.02 -> 7.94 and 14.4 -> 13.8, [1 x 2048 x 2048] FP8
+//   4.84 -> 4.63; from memory the same (6.15 and 6.22).  64 x 32 keeps one: with two it gained 3-6 % from the caches ([224 x 1696 x 4224]
+//   FP8 8.01 -> 7.75) and lost 2-10 % from memory (10.5 -> 11.0, FP8 x FP4 9.6 -> 10.4).  With four stages, or a ring of 12 or 16, slower
+//   (the rings' fill and LDS cost more than they hide), the 64 x 64 tile too (12.3 -> 16.7 on [1504 x 2080 x 1568]: one workgroup per
 //   compute unit instead of two).  What is left is the chain and 3 us of launch, first fill and result.
 //   Copies go through buffer descriptors: rows past the end of an operand and chunks past the end of a row deliver
 //   zeros, and the scale bytes past the last block are masked, so any contraction extent that is a multiple of 32 runs.
@@ -372,8 +373,7 @@ hipError_t launch_gemm_small(const GemmArgs& a, GemmTile tile, hipStream_t s)
     switch (tile) {
         case GemmTile::k128x128: return launch_small_tile<SmallTile<128, 128, 64, 64, 4, 4, 1>>(a, s);
         case GemmTile::k64x64:   return launch_small_tile<SmallTile<64, 64, 32, 32, 4, 4, 1>>(a, s);
-        case GemmTile::k64x32:
-            return pairs ? launch_small_tile<SmallTile<64, 32, 32, 32, 6, 4, 2>>(a, s) : launch_small_tile<SmallTile<64, 32, 32, 32, 6, 4, 1>>(a, s);
+        case GemmTile::k64x32:   return launch_small_tile<SmallTile<64, 32, 32, 32, 6, 4, 1>>(a, s);
         default:
             return pairs ? launch_small_tile<SmallTile<32, 32, 32, 32, 8, 4, 2>>(a, s) : launch_small_tile<SmallTile<32, 32, 32, 32, 8, 4, 1>>(a, s);
     }

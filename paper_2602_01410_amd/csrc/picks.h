@@ -42,12 +42,11 @@ inline bool paper_wide_pays(long long I, long long J, long long R, bool both4, b
     return t[1] < 0.98 * t[0];
 }
 
-// ---- gemm_small.hip, tiles of 64 x 32 and 32 x 32: stages per barrier ----
-// Two where operands are likely `cached` (up to kColdBytes): from memory the larger steps cost 64 x 32 2-4 %, and 16 % with more tiles
-// than compute units ([9 x 21120 x 7936] FP8 42.4 us -> 49.2), 32 x 32 up to 1 %.  And from four stages on: pairs wait for two stages
-// before they begin and multiply a stage of zeros where the number is odd.  Pairs against single stages, averages over 368
-// problems, either tile: one stage 3.5 % slower (0.1-0.2 us of 3.0: [126 x 224 x 128] FP8 3.14 -> 3.38), two 0.7 % faster, three 1.5 %
-// slower ([98 x 832 x 320] FP8 3.59 -> 3.87), four 2.3 % faster, five the same, seven 1.8 %, eight 5 % and more than that 11 % faster.
+// ---- gemm_small.hip, tile of 32 x 32: stages per barrier ----
+// Two where operands are likely `cached` (up to kColdBytes): from memory the larger steps cost up to 3 %.  And from four stages on:
+// pairs wait for two stages before they begin and multiply a stage of zeros where the number is odd.  Single stages against pairs,
+// mean of 2600 calls with operands of up to 10 MB, in the caches: up to three stages 1.6 % faster ([126 x 224 x 128] FP8 3.26 us and
+// 3.38), four to seven 0.6 % slower, eight to fifteen 2.8 %, sixteen to 31 6.6 %, beyond that 10 %.
 constexpr int small_stages_per_barrier(bool cached, long long stages) { return cached && stages >= 4 ? 2 : 1; }
 
 // ---- quant_kernels.hip, quantize for both orientations: the order of the units among the XCDs ----

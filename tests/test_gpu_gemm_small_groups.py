@@ -1,5 +1,5 @@
-"""The GEMM tiles that take two pipeline stages per barrier: every number of stages around their ring, whole last stages and
-cut ones, bit for bit against the general kernel (which the oracle checks)."""
+"""The small GEMM tiles of one or two waves, of which 32 x 32 takes two pipeline stages per barrier: every number of stages around
+their rings, whole last stages and cut ones, bit for bit against the general kernel (which the oracle checks)."""
 import pytest
 import torch
 

@@ -21,8 +21,8 @@ MEASURED = [
     (5120, 2560, 4608, 1, 1, 1, 79.7, 68.9),
 ]
 
-# GEMMs of the small tiles: operands cached, stages: us with one stage per barrier, with two
-STAGES = [(1, 1, 3.14, 3.38), (1, 3, 3.59, 3.87), (1, 64, 14.0, 11.7), (0, 62, 42.4, 49.2)]
+# GEMMs of the 32 x 32 tile: operands cached, stages: us with one stage per barrier, with two
+STAGES = [(1, 1, 3.26, 3.38), (1, 3, 3.52, 3.60), (1, 16, 5.40, 4.95), (1, 32, 7.24, 6.76), (0, 62, 37.2, 38.5)]
 
 # one-pass quantize: rows, columns, bytes of a stored column, statistics: us with turns of eight units, with an eighth per XCD
 ORDERS = [(1504, 2080, 752, 0, 5.9, 5.8), (2432, 4896, 1216, 1, 21.8, 21.6), (32768, 4096, 16384, 0, 87.9, 103.0), (8160, 8160, 8160, 0, 82.3, 89.6),
