@@ -197,18 +197,34 @@ __global__ __launch_bounds__(NT) void gemm_fast_kernel(const uint8_t* __restrict
     };
     const unsigned lds0 = lds_addr(lds);
 
-    // copy instruction j (0 .. L-1) of this wave's share of the codes of `stage` (of the copy tile) into stage buffer `slot`
-    auto issue_one = [&](int j, int stage, int slot) {
-        const unsigned base = lds0 + slot * C::STRIDE;
+    // Where this wave's share of the codes lies in stage buffer `slot`.  The empty statements keep it in one scalar register (two for
+    // unequal shares): the compiler would otherwise form the place of every copy ahead of all loops, spill these, and fetch each
+    // back with a vector instruction between the MFMAs, which hold such up for about 20 cycles.  Formed in front of the operand
+    // reads; behind the barrier in front of the MFMAs FP8 took 1-4 % longer.  Cached operands, fp32 results, cut last stage, us: FP4
+    // [5376 x 1152 x 11648] 52.2 -> 49.2, [407 x 14080 x 14976] 67.5 -> 62.5, FP8 [2784 x 2368 x 10560] 77.1 -> 73.5; mean of 24 problems FP4
+    // 2.5 % (bf16 results 0.5 %), FP8 1 % (0.4 %), FP8 x FP4 0.2 % (1 %); from memory the same.
+    struct Share { unsigned a, b; };
+    auto share = [&](int slot) {
+        Share d;
+        d.a = lds0 + wave * C::LA * 1024 + slot * C::STRIDE;
+        asm volatile("" : "+s"(d.a));
+        if (C::LA == C::LB) {
+            d.b = d.a + C::A_BYTES;
+        } else {
+            d.b = lds0 + C::A_BYTES + wave * C::LB * 1024 + slot * C::STRIDE;
+            asm volatile("" : "+s"(d.b));
+        }
+        return d;
+    };
+    // copy instruction j (0 .. L-1) of this wave's share of the codes of `stage` (of the copy tile)
+    auto issue_one = [&](int j, int stage, Share to) {
         if (j < C::LA) {
-            const unsigned dst = base + (wave * C::LA + j) * 1024;
-            if constexpr (TAIL) blds16(ra, oa[j], stage * C::SBA, dst);
-            else glds16(abase + (int64_t)stage * C::SBA, oa[j], dst);
+            if constexpr (TAIL) blds16(ra, oa[j], stage * C::SBA, to.a + j * 1024);
+            else glds16(abase + (int64_t)stage * C::SBA, oa[j], to.a + j * 1024);
         } else {
             const int k = j - C::LA;
-            const unsigned dst = base + C::A_BYTES + (wave * C::LB + k) * 1024;
-            if constexpr (TAIL) blds16(rb, ob[k], stage * C::SBB, dst);
-            else glds16(bbase + (int64_t)stage * C::SBB, ob[k], dst);
+            if constexpr (TAIL) blds16(rb, ob[k], stage * C::SBB, to.b + k * 1024);
+            else glds16(bbase + (int64_t)stage * C::SBB, ob[k], to.b + k * 1024);
         }
     };
     auto issue_scale = [&](int stage, int slot) {
@@ -217,8 +233,9 @@ __global__ __launch_bounds__(NT) void gemm_fast_kernel(const uint8_t* __restrict
         else glds16(sbase + (int64_t)stage * C::NG * (sop ? b_pitch : a_pitch) * 4, os, dst);
     };
     auto issue = [&](int stage, int slot) {
+        const Share to = share(slot);
 #pragma unroll
-        for (int j = 0; j < C::L; ++j) issue_one(j, stage, slot);
+        for (int j = 0; j < C::L; ++j) issue_one(j, stage, to);
     };
 
     // ---- per-lane LDS read offsets ----
@@ -288,7 +305,7 @@ __global__ __launch_bounds__(NT) void gemm_fast_kernel(const uint8_t* __restrict
     // The MFMAs of phase p.  With COPY the wave's copy instructions of stage `nxt` (of the copy tile) into
     // buffer `nslot` are spread evenly between the phase's NM MFMAs (the sched_barriers keep them there).
     constexpr int NM = KP * MB * NB;
-    auto MM = [&](auto copy_tag, int p, int nxt, int nslot) {
+    auto MM = [&](auto copy_tag, int p, int nxt, int nslot, Share to) {
         constexpr bool COPY = decltype(copy_tag)::value != 0, SCALES = decltype(copy_tag)::value == 2;
         constexpr int ca = FB == kFP8 ? 0 : 4, cb = FA == kFP8 ? 0 : 4;
         __builtin_amdgcn_s_setprio(1);
@@ -309,7 +326,7 @@ __global__ __launch_bounds__(NT) void gemm_fast_kernel(const uint8_t* __restrict
                         if (SCALES && idx == 0) issue_scale(nxt, nslot);
 #pragma unroll
                         for (int j = 0; j < C::L; ++j)
-                            if ((SCALES ? (j + 1) * NM / (C::L + 1) : j * NM / C::L) == idx) issue_one(j, nxt, nslot);
+                            if ((SCALES ? (j + 1) * NM / (C::L + 1) : j * NM / C::L) == idx) issue_one(j, nxt, to);
                         __builtin_amdgcn_sched_barrier(0);
                     }
                     ++idx;
@@ -501,12 +518,14 @@ __global__ __launch_bounds__(NT) void gemm_fast_kernel(const uint8_t* __restrict
                 // waiting for them here again would wait for those stores
                 if (first || s >= NST - 1) SNIP_WAIT_VM((NST - 2) * (C::L + 1));
                 SNIP_BAR();                                         // b(4s)
+                const int to = NST == 2 ? slot ^ 1 : before(slot);
+                const Share at = share(to);
                 RD(slot, 0, s); SNIP_BAR();      // b(4s+1)
-                MM(copy_tag, 0, cstage, NST == 2 ? slot ^ 1 : before(slot));
+                MM(copy_tag, 0, cstage, to, at);
                 if (PH == 2) {
                     SNIP_BAR();                                     // b(4s+2)
                     RD(slot, 1, s); SNIP_BAR();  // b(4s+3)
-                    MM(no_copy, 1, 0, 0);
+                    MM(no_copy, 1, 0, 0, Share());
                 }
             };
             // Every stage carries copies, so that the MFMA code exists once (two variants of it merging in front
@@ -530,12 +549,13 @@ __global__ __launch_bounds__(NT) void gemm_fast_kernel(const uint8_t* __restrict
             auto stage1 = [&](auto copy_tag, int s, int cstage) {
                 const int slot = slot_of(s);
                 SNIP_BAR();                                         // b(4s+1)
-                RD(slot, 0, s);
                 if (PH == 2) {
+                    RD(slot, 0, s);
                     SNIP_BAR();                  // b(4s+2)
-                    MM(no_copy, 0, 0, 0); SNIP_BAR();               // b(4s+3)
-                    RD(slot, 1, s);
+                    MM(no_copy, 0, 0, 0, Share()); SNIP_BAR();      // b(4s+3)
                 }
+                const Share at = decltype(copy_tag)::value ? share(slot) : Share();
+                RD(slot, PH - 1, s);
                 if (NST == 2) {
                     __builtin_amdgcn_s_waitcnt(0x0070);             // vmcnt(0) and lgkmcnt(0)
                 } else {
@@ -543,7 +563,7 @@ __global__ __launch_bounds__(NT) void gemm_fast_kernel(const uint8_t* __restrict
                     __builtin_amdgcn_s_waitcnt(0xC07F);             // lgkmcnt(0)
                 }
                 SNIP_BAR();                                         // b(4s+4)
-                MM(copy_tag, PH - 1, cstage, slot);
+                MM(copy_tag, PH - 1, cstage, slot, at);
             };
             if (first) SNIP_WAIT_VM((NST - 2) * C::L);
             SNIP_BAR();                                             // b(0)

@@ -1,6 +1,12 @@
-"""A global->LDS copy waits until earlier ones have read the offsets that a vector instruction is about to write, so the stage loop
-of the small GEMM tiles has to skip the cut of a last stage with a branch: no loop of the built library selects offsets between its
-barrier and the copies that use them (64 x 32, [123 x 2240 x 17024] FP8: 28.9 us with selects, 23.0 with a branch)."""
+"""What the compiler makes of the GEMM kernels' copies, looked up in the built library.
+
+A global->LDS copy waits until earlier ones have read the offsets that a vector instruction is about to write, so the stage loop
+of the small GEMM tiles has to skip the cut of a last stage with a branch: no loop selects offsets between its barrier and the copies
+that use them (64 x 32, [123 x 2240 x 17024] FP8: 28.9 us with selects, 23.0 with a branch).
+
+The large tiles issue their copies between MFMAs, which hold a vector instruction up for about 20 cycles: hardly any spilled scalar
+register is fetched back (v_readlane) there (256 x 128, [407 x 14080 x 14976] FP4 with fp32 results: 67.5 us with up to 39 of them in
+a kernel, 62.5 with up to 16)."""
 import os
 import re
 import subprocess
@@ -41,10 +47,32 @@ def test_scan_finds_a_select():
     assert selects_before_copies(loop) == ([], 1)
 
 
+def fetched_between_mfmas(lines):
+    """Kernel of the large tiles -> v_readlanes between s_setprio 1 and 0, the MFMA phases."""
+    counts, function, inside = {}, "", False
+    for line in lines:
+        if line.endswith(">:"):
+            function, inside = line, False
+            if "gemm_fast_kernel" in line:
+                counts[function] = 0
+            continue
+        ins = line.split("//")[0].split()
+        if ins and function in counts:
+            if ins[0] == "s_setprio":
+                inside = ins[1] == "1"
+            counts[function] += inside and ins[0] == "v_readlane_b32"
+    return counts
+
+
+def test_scan_counts_between_mfmas():
+    body = ["0000 <_Z16gemm_fast_kernelv>:", " v_readlane_b32 s1, v2, 3", " s_setprio 1", " v_readlane_b32 s1, v2, 3 // x", " s_setprio 0", " v_readlane_b32 s1, v2, 3"]
+    assert list(fetched_between_mfmas(body).values()) == [1]
+
+
 def test_library(tmp_path):
     if not os.path.exists(OBJDUMP):
         pytest.skip("no disassembler")
-    copies = 0
+    copies, fetched = 0, {}
     for i, obj in enumerate(code_objects(snip.LIB_PATH)):
         path = tmp_path / f"{i}.co"
         path.write_bytes(obj)
@@ -52,4 +80,6 @@ def test_library(tmp_path):
         found, n = selects_before_copies(out)
         assert found == []
         copies += n
+        fetched.update(fetched_between_mfmas(out))
     assert copies > 100
+    assert len(fetched) > 10 and max(fetched.values()) <= 20
