@@ -202,10 +202,18 @@ __global__ __launch_bounds__(NT) void gemm_fast_kernel(const uint8_t* __restrict
     // back with a vector instruction between the MFMAs, which hold such up for about 20 cycles.  Formed in front of the operand
     // reads; behind the barrier in front of the MFMAs FP8 took 1-4 % longer.  Cached operands, fp32 results, cut last stage, us: FP4
     // [5376 x 1152 x 11648] 52.2 -> 49.2, [407 x 14080 x 14976] 67.5 -> 62.5, FP8 [2784 x 2368 x 10560] 77.1 -> 73.5; mean of 24 problems FP4
-    // 2.5 % (bf16 results 0.5 %), FP8 1 % (0.4 %), FP8 x FP4 0.2 % (1 %); from memory the same.
+    // 2.5 % (bf16 results 0.5 %), FP8 1 % (0.4 %), FP8 x FP4 0.2 % (1 %); from memory the same.  Kernels of whole stages with bf16
+    // results have a third of the spills and nothing to gain, and with 256 x 256 and FP4 lost three lane registers of the result
+    // store's ragged path to scratch ([4960 x 1760 x 512] 10.9 -> 11.8 us, [6944 x 2016 x 512] 12.0 -> 13.0).
+    constexpr bool HELD = TAIL || OUT_F32;
     struct Share { unsigned a, b; };
     auto share = [&](int slot) {
         Share d;
+        if constexpr (!HELD) {
+            d.a = lds0 + slot * C::STRIDE;
+            d.b = d.a + C::A_BYTES;
+            return d;
+        }
         d.a = lds0 + wave * C::LA * 1024 + slot * C::STRIDE;
         asm volatile("" : "+s"(d.a));
         if (C::LA == C::LB) {
@@ -218,6 +226,7 @@ __global__ __launch_bounds__(NT) void gemm_fast_kernel(const uint8_t* __restrict
     };
     // copy instruction j (0 .. L-1) of this wave's share of the codes of `stage` (of the copy tile)
     auto issue_one = [&](int j, int stage, Share to) {
+        if constexpr (!HELD) to = Share{to.a + wave * C::LA * 1024, to.b + wave * C::LB * 1024};
         if (j < C::LA) {
             if constexpr (TAIL) blds16(ra, oa[j], stage * C::SBA, to.a + j * 1024);
             else glds16(abase + (int64_t)stage * C::SBA, oa[j], to.a + j * 1024);
