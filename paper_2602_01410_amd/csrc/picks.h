@@ -108,6 +108,10 @@ constexpr bool qb_eighths(long long rows, long long cols, long long ld, long lon
 // which a compute unit takes three at once, up to 8 % ([3200 x 4096] 14.4 against 15.2, mixed 15.9 against 17.2; [4096 x 4096] 16.2
 // against 16.3).  Half a column group and less is too little to fetch for that: [140800 x 32] FP4 9.2 against 10.2, [68736 x 64] 7.1
 // against 7.8, [262144 x 32] 14.5 against 15.5; with 96 columns they are even (8.9 and 8.8 on [68736 x 96]).
+// Where the line lies is decided on tensors that come from memory and results that go there, as in a step of a model; mean of 1200 calls of
+// 1.6 ... 9 units per compute unit, LDS against direct: up to two units 1.0 % slower, three 10.6 % faster ([2432 x 4224] FP8 12.3 us and 11.2,
+// [1536 x 5760] FP4 14.9 and 11.8), four 1.9 % faster (10 % slower ... 14 % faster), beyond that 3.8-5.5 % faster.  On one buffer again and
+// again, all in the caches, the direct form is faster throughout, by 8.5 % up to two units and 4-5 % beyond (8.3 and 8.9, 9.1 and 9.9).
 constexpr bool qb_through_lds(long long cols, long long units, long long ncu)
 {
     return cols > 64 && units > 2 * ncu && !(units > 3 * ncu && units <= 4 * ncu);
