@@ -94,9 +94,16 @@ constexpr int qb_band_log2(long long cols, long long column_bytes)
 //     for more than 16384 columns eighths again, without statistics, where rows start on whole lines.  [8192 x 28672] FP4 181 / 166 /
 //     168, FP8 214 / 206 / 198, [8192 x 32768] 218 / 200 / 186 and 254 / 262 / 223, [4096 x 28672] FP8 107 / 104 / 103, beside FP4 rows
 //     103 / 100 / 98.  (FP8 with 16384 columns and less also gains, 2-4 % from 8192 rows on; FP4 loses 2 %.)
+//   - and for such rows with FP8 columns of whole 128-byte lines from 160 M elements on, where row units share no line of a column:
+//     turns / eighths [10496 x 23808] FP8 227 / 212, [12544 x 21504] beside FP4 rows 224 / 210; 111 calls of 192 ... 420 M 3.5 % on average,
+//     17 of 160 ... 192 M 1.5 %.  Below 144 M turns lead by 3 % ([4224 x 30080] FP8 107 / 114).  Columns that are no whole lines gain
+//     7 % from turns (77 calls), FP4 ones that are 1 %.
 constexpr bool qb_eighths(long long rows, long long cols, long long ld, long long column_bytes, bool stats)
 {
-    return rows * cols < (cols % 128 != 0 ? 24ll << 20 : 8ll << 20) || (!stats && cols > 16384 && ld % 128 == 0 && column_bytes % 4096 == 0);
+    const bool fp8_columns = column_bytes == rows;
+    return rows * cols < (cols % 128 != 0 ? 24ll << 20 : 8ll << 20) ||
+           (!stats && cols > 16384 && ld % 128 == 0 &&
+            (column_bytes % 4096 == 0 || (fp8_columns && column_bytes % 128 == 0 && rows * cols >= 160ll << 20)));
 }
 
 // ---- ... whether its tiles go through LDS, without statistics ----

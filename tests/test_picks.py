@@ -27,7 +27,7 @@ STAGES = [(1, 1, 3.26, 3.38), (1, 3, 3.52, 3.60), (1, 16, 5.40, 4.95), (1, 32, 7
 # one-pass quantize: rows, columns, bytes of a stored column, statistics: us with turns of eight units, with an eighth per XCD
 ORDERS = [(1504, 2080, 752, 0, 5.9, 5.8), (2432, 4896, 1216, 1, 21.8, 21.6), (32768, 4096, 16384, 0, 87.9, 103.0), (8160, 8160, 8160, 0, 82.3, 89.6),
           (2048, 22016, 1024, 0, 35.8, 38.8), (6144, 22016, 6144, 0, 118.4, 124.5), (8192, 32768, 4096, 0, 199.9, 186.2), (8192, 28672, 8192, 0, 206.3, 198.5),
-          (4096, 4096, 2048, 1, 23.7, 27.7)]
+          (4096, 4096, 2048, 1, 23.7, 27.7), (10496, 23808, 10496, 0, 226.9, 211.6), (12544, 21504, 12544, 0, 224.4, 210.3), (4224, 30080, 4224, 0, 107.2, 113.6)]
 
 # ... in turns: columns, bytes of a stored column: us with pairs of row units, with four
 BANDS = [(2048, 43040, 154.8, 129.0), (2048, 26000, 96.7, 81.1), (6144, 14304, 159.4, 137.0), (11008, 4080, 90.4, 84.2), (1984, 12880, 49.2, 43.7),
