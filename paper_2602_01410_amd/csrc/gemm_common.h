@@ -121,12 +121,35 @@ __device__ __forceinline__ void tile_of(int u, int nblk, int tiles_i, int tiles_
     tj = rem / rows_in_band;
 }
 
+// 16 bytes of a result, streaming ("nt"): nothing on this path reads a result again, and plain stores take room in the memory-side
+// cache (256 MB) from the quantized operands of the GEMMs that follow and leave the L2s dirty lines, which the end of a kernel
+// writes out with the chip idle: from the last store of a launch (17 MB) to the first instruction of the next one it was 3.4 us with plain
+// stores and is 1.5 with these.  Plain -> streaming, us: [4096 x 2048 x 2048] FP4 16.0 -> 13.7, FP8 22.4 -> 18.8, [8192 x 3072 x 3072] FP4 58.5 ->
+// 51.9, [2048 x 4096 x 4096] FP8 39.7 -> 36.2, fp32 42.2 -> 36.8; random calls on operands from memory 7 % on average (30 % ... -3 %), on one
+// buffer again and again 2 %; followed by a quantize call that reads the result 0 and 0.5 %.  Write-through besides ("sc1 nt") shortens
+// the gap to 1.3 us, but tiles that follow each other wait for it (blocks of the 70B and 7B shapes 0.4 % slower, 1B 0.4 % faster).
+// Rows that do not start on 64 bytes leave parts of 64-byte pieces at the edges of every tile, which memory takes singly: plain stores
+// there (paper recipe, streaming against plain, operands from memory: [7040 x 5200 x 256] FP4 32.5 us and 27.9, 63 calls +2 %; rows on 64
+// bytes, 9 calls, -3 %, whole lines, 27 calls above 1 M elements, -7 %).
+__device__ __forceinline__ bool streams_result(int64_t ldc, bool f32) { return (ldc & (f32 ? 15 : 31)) == 0; }
+// (The empty statements keep the compiler from making one plain store of the two kinds.)
+__device__ __forceinline__ void store16(v4u v, uint8_t* p, bool stream = true)
+{
+    if (stream) {
+        __builtin_nontemporal_store(v, reinterpret_cast<v4u*>(p));
+    } else {
+        asm volatile("");
+        *reinterpret_cast<v4u*>(p) = v;
+        asm volatile("");
+    }
+}
+
 // Result of a wave's 64 x 64 block with its corner at (i0, j0), of a kernel whose first MFMA operand is the B tile: turned through
 // 4 KB of LDS of the wave's own, 32 rows x 128 bytes at a time.  16-byte piece c of row r sits at position c ^ (r / 2 % 8) (bf16: a
-// piece is written in two halves).  `interior`: no row or column lies outside; `stream_out`: streaming stores there.
+// piece is written in two halves).  `interior`: no row or column lies outside; `stream`: see store16.
 template <bool OUT_F32>
 __device__ __forceinline__ void store_block64(const v16f (&acc)[2][2], uint8_t* reg, int lane, void* c_out, int64_t ldc, int i0, int j0,
-                                              int I, int J, bool interior, bool stream_out)
+                                              int I, int J, bool interior, bool stream)
 {
     constexpr int ESZ = OUT_F32 ? 4 : 2;
     const int r32 = lane & 31, g = lane >> 5, f = (r32 >> 1) & 7;
@@ -157,11 +180,10 @@ __device__ __forceinline__ void store_block64(const v16f (&acc)[2][2], uint8_t* 
                 const int i = i0 + m * 32 + row, j = j0 + h * 32 + c * (16 / ESZ);
                 uint8_t* p = reinterpret_cast<uint8_t*>(c_out) + ((int64_t)i * ldc + j) * ESZ;
                 if (interior) {
-                    if (stream_out) __builtin_nontemporal_store(v, reinterpret_cast<v4u*>(p));
-                    else *reinterpret_cast<v4u*>(p) = v;
+                    store16(v, p, stream);
                 } else if (i < I) {
                     if (j + 16 / ESZ <= J) {
-                        *reinterpret_cast<v4u*>(p) = v;
+                        store16(v, p, stream);
                     } else if (j < J) {
                         for (int e = 0; e < 16 / ESZ; ++e)
                             if (j + e < J) {

@@ -116,8 +116,7 @@ __global__ __launch_bounds__(NT) void gemm_fast_kernel(const uint8_t* __restrict
                                                        const uint8_t* __restrict__ b_codes,
                                                        const uint8_t* __restrict__ b_g4,
                                                        int I, int J, int R, void* __restrict__ c_out, int64_t ldc,
-                                                       int tiles_i, int tiles_j, float* __restrict__ norm_partials,
-                                                       int stream_out)
+                                                       int tiles_i, int tiles_j, float* __restrict__ norm_partials)
 {
     using C = FCfg<FA, FB, T>;
     constexpr int TM = T::TM, TN = T::TN, WTM = T::WTM, WTN = T::WTN, WGN = T::WGN, MB = T::MB, NB = T::NB;
@@ -353,7 +352,7 @@ __global__ __launch_bounds__(NT) void gemm_fast_kernel(const uint8_t* __restrict
         int ti, tj;
         tile_of(u, nblk, tiles_i, tiles_j, ti, tj);
         const int i0 = ti * TM, j0 = tj * TN;
-        const bool interior = i0 + TM <= I && j0 + TN <= J;
+        const bool interior = i0 + TM <= I && j0 + TN <= J, stream = streams_result(ldc, OUT_F32);
         // optional: sum of squares of the tile as it will be stored (rounded to the output type), elements
         // outside the matrix excluded; one partial per tile, combined by a second kernel.  Interior tiles take
         // the short path: bf16 pairs are squared and added by v_dot2c_f32_bf16.
@@ -440,13 +439,10 @@ __global__ __launch_bounds__(NT) void gemm_fast_kernel(const uint8_t* __restrict
                         }
                     }
             }
-            // read back row-contiguous: 64 lanes cover 64 / CPR rows per instruction.  All workgroups finish a tile
-            // at about the same time: 32 MB per round of tiles, the size of all L2s together.  When operands and
-            // output together fit the memory-side cache, plain stores are absorbed there fastest (2.1-2.7 us per tile
-            // for the later group of waves against 3-5 us); when they do not, streaming stores keep the output from
-            // pushing the operands out (8-10 % on the FP8 GEMMs with 180 MB operands).  The launcher decides.
+            // read back row-contiguous: 64 lanes cover 64 / CPR rows per instruction (stores: store16)
             constexpr int RPI = 64 / CPR;
-            if (interior) {
+            constexpr bool TWO = !OUT_F32;          // (plain stores of fp32 results here too spill registers)
+            if (interior && (TWO || stream)) {
                 // whole tile inside the matrix (wave-uniform): no per-lane tests, one wave-uniform base per
                 // instruction plus a 32-bit lane offset
                 const unsigned lane_off = (unsigned)((lane / CPR) * (int)ldc * ESZ + (lane % CPR) * 16);
@@ -457,11 +453,8 @@ __global__ __launch_bounds__(NT) void gemm_fast_kernel(const uint8_t* __restrict
                     const int row = it * RPI + lane / CPR;
                     const int c = lane % CPR;
                     const int f = spread(row);
-                    const uint4 v = *reinterpret_cast<const uint4*>(reg + row * ROWB + ((c ^ f) * 16));
-                    const v4u vv = {v.x, v.y, v.z, v.w};
-                    uint8_t* p = const_cast<uint8_t*>(cb) + (int64_t)(it * RPI) * ldc * ESZ + lane_off;
-                    if (stream_out) __builtin_nontemporal_store(vv, reinterpret_cast<v4u*>(p));
-                    else *reinterpret_cast<v4u*>(p) = vv;
+                    const v4u v = *reinterpret_cast<const v4u*>(reg + row * ROWB + ((c ^ f) * 16));
+                    store16(v, const_cast<uint8_t*>(cb) + (int64_t)(it * RPI) * ldc * ESZ + lane_off, !TWO || stream);
                 }
             } else {
                 for (int it = 0; it < ROWS_PER_PASS / RPI; ++it) {
@@ -474,7 +467,7 @@ __global__ __launch_bounds__(NT) void gemm_fast_kernel(const uint8_t* __restrict
                     if (i < I) {
                         uint8_t* p = reinterpret_cast<uint8_t*>(c_out) + ((int64_t)i * ldc + j) * ESZ;
                         if (j + 16 / ESZ <= J) {
-                            *reinterpret_cast<uint4*>(p) = v;
+                            store16(v4u{v.x, v.y, v.z, v.w}, p, stream);
                         // (lanes past the last column would walk through the tests below: 1 us of a tile with two passes; cached
                         // operands, [7936 x 544 x 640] FP8 10.3 -> 8.9 us, [416 x 9440 x 1152] 12.0 -> 10.7)
                         } else if (j < J) {
@@ -607,17 +600,12 @@ hipError_t launch_fast_t(const GemmArgs& a, hipStream_t s)
     // one workgroup per compute unit (the LDS array admits no second one), each walking its share of the tiles
     const int ncu = gemm_compute_units();
     const dim3 grid((unsigned)(ti * tj < ncu ? ti * tj : ncu)), block(NT);
-    // streaming output stores when operands + output exceed what the memory-side cache (256 MB) can hold next to
-    // everything else in flight
-    const double bytes = (double)a.I * a.R * (FA == kFP8 ? 1.0 : 0.5) + (double)a.J * a.R * (FB == kFP8 ? 1.0 : 0.5) +
-                         (double)a.I * a.J * (a.out_fp32 ? 4.0 : 2.0);
-    int stream_out = bytes > 200e6;
     if (a.out_fp32)
         hipLaunchKernelGGL((gemm_fast_kernel<FA, FB, true, T, TAIL>), grid, block, 0, s, a.a_codes, a.a_scales_g4, a.b_codes, a.b_scales_g4,
-                           (int)a.I, (int)a.J, (int)a.R, a.c, a.ldc, ti, tj, a.norm_partials, stream_out);
+                           (int)a.I, (int)a.J, (int)a.R, a.c, a.ldc, ti, tj, a.norm_partials);
     else
         hipLaunchKernelGGL((gemm_fast_kernel<FA, FB, false, T, TAIL>), grid, block, 0, s, a.a_codes, a.a_scales_g4, a.b_codes, a.b_scales_g4,
-                           (int)a.I, (int)a.J, (int)a.R, a.c, a.ldc, ti, tj, a.norm_partials, stream_out);
+                           (int)a.I, (int)a.J, (int)a.R, a.c, a.ldc, ti, tj, a.norm_partials);
     return hipGetLastError();
 }
 template <int FA, int FB, class T>

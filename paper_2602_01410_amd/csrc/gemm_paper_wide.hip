@@ -57,8 +57,7 @@ template <int FA, int FB> struct WideCfg {
 template <int FA, int FB, bool OUT_F32, bool B_BLOCK>
 __global__ __launch_bounds__(NT) void gemm_paper_wide_kernel(const uint8_t* __restrict__ a_codes, const float* __restrict__ a_scales, int a_shift,
                                                              const uint8_t* __restrict__ b_codes, const float* __restrict__ b_scales,
-                                                             int I, int J, int R, void* __restrict__ c_out, int64_t ldc, int tiles_i, int tiles_j,
-                                                             int stream_out)
+                                                             int I, int J, int R, void* __restrict__ c_out, int64_t ldc, int tiles_i, int tiles_j)
 {
     using C = WideCfg<FA, FB>;
     constexpr int NG = C::NG, KS = C::KS, SPC = C::SPC;
@@ -299,7 +298,7 @@ __global__ __launch_bounds__(NT) void gemm_paper_wide_kernel(const uint8_t* __re
     // ---- result of a tile, staged in the last stage's buffer
     auto store_tile = [&](int ti0, int tj0, int slot) __attribute__((always_inline)) {
         store_block64<OUT_F32>(acc, lds + slot * C::SLOT + wave * C::EPI, lane, c_out, ldc, ti0 + wm * WTM, tj0 + wn * WTN, I, J,
-                               ti0 + TM <= I && tj0 + TN <= J, stream_out != 0);
+                               ti0 + TM <= I && tj0 + TN <= J, streams_result(ldc, OUT_F32));
     };
 
     auto after = [](int slot) { return slot == NST - 1 ? 0 : slot + 1; };
@@ -397,15 +396,13 @@ hipError_t launch_t(const GemmPaperArgs& a, hipStream_t s)
     const int ti = (int)((a.I + TM - 1) / TM), tj = (int)((a.J + TN - 1) / TN);
     const int ncu = gemm_compute_units();
     const dim3 grid((unsigned)(ti * tj < ncu ? ti * tj : ncu)), block(NT);
-    // as in gemm_fast.hip: streaming stores where operands and output exceed what the memory-side cache can hold
-    const double bytes = (double)a.I * a.R * (FA == kFP8 ? 1.0 : 0.5) + (double)a.J * a.R * (FB == kFP8 ? 1.0 : 0.5) + (double)a.I * a.J * (OUT_F32 ? 4.0 : 2.0);
-    const int stream_out = bytes > 200e6, a_shift = a.a_group == 1 ? 0 : 7;
+    const int a_shift = a.a_group == 1 ? 0 : 7;
     if (a.b_group != 1)
         hipLaunchKernelGGL((gemm_paper_wide_kernel<FA, FB, OUT_F32, true>), grid, block, 0, s, a.a_codes, a.a_scales, a_shift, a.b_codes, a.b_scales,
-                           (int)a.I, (int)a.J, (int)a.R, a.c, a.ldc, ti, tj, stream_out);
+                           (int)a.I, (int)a.J, (int)a.R, a.c, a.ldc, ti, tj);
     else
         hipLaunchKernelGGL((gemm_paper_wide_kernel<FA, FB, OUT_F32, false>), grid, block, 0, s, a.a_codes, a.a_scales, a_shift, a.b_codes, a.b_scales,
-                           (int)a.I, (int)a.J, (int)a.R, a.c, a.ldc, ti, tj, stream_out);
+                           (int)a.I, (int)a.J, (int)a.R, a.c, a.ldc, ti, tj);
     return hipGetLastError();
 }
 

@@ -312,6 +312,7 @@ __global__ __launch_bounds__(T::NT) void gemm_small_kernel(const uint8_t* __rest
                 }
             }
     }
+    const bool stream = streams_result(ldc, OUT_F32);
 #pragma unroll
     for (int it = 0; it < WTM / RPI; ++it) {
         const int row = it * RPI + lane / CPR, c = lane % CPR;
@@ -320,7 +321,7 @@ __global__ __launch_bounds__(T::NT) void gemm_small_kernel(const uint8_t* __rest
         if (i < I) {
             uint8_t* p = reinterpret_cast<uint8_t*>(c_out) + ((int64_t)i * ldc + j) * ESZ;
             if (j + 16 / ESZ <= J) {
-                *reinterpret_cast<uint4*>(p) = v;
+                store16(v4u{v.x, v.y, v.z, v.w}, p, stream);
             } else {
                 const unsigned w[4] = {v.x, v.y, v.z, v.w};
                 for (int e = 0; e < 16 / ESZ; ++e)

@@ -7,7 +7,10 @@ that use them (64 x 32, [123 x 2240 x 17024] FP8: 28.9 us with selects, 23.0 wit
 The large tiles issue their copies between MFMAs, which hold a vector instruction up for about 20 cycles: hardly any spilled scalar
 register is fetched back (v_readlane) there (256 x 128, [407 x 14080 x 14976] FP4 with fp32 results: 67.5 us with up to 39 of them in
 a kernel, 62.5 with up to 16), and lane registers are not spilled to make room (256 x 256, [4960 x 1760 x 512] FP4 with bf16 results:
-11.8 us with four of them and seven loads from scratch, 10.9 with one)."""
+11.8 us with four of them and seven loads from scratch, 10.9 with one).
+
+Results are stored streaming ("nt") or, where rows start off 64 bytes, plain: both kinds are there in every kernel (the compiler makes
+one plain store of two branches that differ in nothing else, [4096 x 2048 x 2048] FP4 16.0 us instead of 13.7)."""
 import os
 import re
 import subprocess
@@ -87,10 +90,29 @@ def test_scan_counts_scratch_loads():
     assert list(loads_from_scratch(body).values()) == [1]
 
 
+def result_stores(lines):
+    """GEMM kernel that takes grouped scales or the paper's -> 16-byte stores, streaming and plain."""
+    counts, function = {}, ""
+    for line in lines:
+        if line.endswith(">:"):
+            function = line
+        ins = line.split("//")[0].split()
+        if ins and re.search(r"gemm_(fast|small|paper|paper_wide)_kernel", function) and ins[0] == "global_store_dwordx4":
+            kinds = counts.setdefault(function, [0, 0])
+            kinds[0 if "nt" in ins else 1] += 1
+    return counts
+
+
+def test_scan_counts_result_stores():
+    body = ["0000 <_Z16gemm_fast_kernelv>:", " global_store_dwordx4 v0, v[2:5], s[0:1] nt // x", " global_store_dwordx4 v0, v[2:5], s[0:1] // nt", "0100 <_Z1kv>:",
+            " global_store_dwordx4 v0, v[2:5], s[0:1]"]
+    assert list(result_stores(body).values()) == [[1, 1]]
+
+
 def test_library(tmp_path):
     if not os.path.exists(OBJDUMP):
         pytest.skip("no disassembler")
-    copies, fetched, scratch = 0, {}, {}
+    copies, fetched, scratch, stores = 0, {}, {}, {}
     for i, obj in enumerate(code_objects(snip.LIB_PATH)):
         path = tmp_path / f"{i}.co"
         path.write_bytes(obj)
@@ -100,6 +122,8 @@ def test_library(tmp_path):
         copies += n
         fetched.update(fetched_between_mfmas(out))
         scratch.update(loads_from_scratch(out))
+        stores.update(result_stores(out))
     assert copies > 100
     assert len(fetched) > 10 and max(fetched.values()) <= 20
     assert scratch.keys() == fetched.keys() and max(scratch.values()) <= 3
+    assert len(stores) > 60 and all(streaming > 0 and plain > 0 for streaming, plain in stores.values())
