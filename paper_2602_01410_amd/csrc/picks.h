@@ -124,4 +124,17 @@ constexpr bool qb_through_lds(long long cols, long long units, long long ncu)
     return cols > 64 && units > 2 * ncu && !(units > 3 * ncu && units <= 4 * ncu);
 }
 
+// ---- ... whether the forms for large tensors (through LDS; a wave per unit) stream their codes past the caches ----
+// From 64 M elements on, of which both orientations' codes fill half of the memory-side cache (256 MB) and more: they would not be there
+// any more when a GEMM wants them, and leave their place to those of smaller tensors and to what the GEMMs read.  Plain -> streaming:
+// all statistics [16384 x 11008] FP4 157 -> 152 us, the 19 quantize calls of a 7B-shaped block 1392 -> 1344, those of a 70B-shaped one 1546 ->
+// 1490.  Smaller tensors' codes are still there: streamed from 16 M elements on, the quantize calls of 1B- and 3B-shaped blocks gain 2 and
+// 8 % and the whole blocks 1.5 %, but 40 steps of one linear lose 1.8 % on average (14 % at worst, [2176 x 8960 x 1024] 102 us -> 117).
+// And where every stored row starts on 64 bytes: pieces of 64 bytes reach memory by themselves ([12384 x 10656] FP4, rows of 5328 bytes,
+// 161 us -> 196).
+constexpr bool qb_streams(long long rows, long long cols, bool fp8_rows, bool fp8_columns)
+{
+    return rows * cols >= 64ll << 20 && (fp8_rows ? cols : cols / 2) % 64 == 0 && (fp8_columns ? rows : rows / 2) % 64 == 0;
+}
+
 }  // namespace snip

@@ -824,10 +824,11 @@ typedef unsigned v2u_t __attribute__((ext_vector_type(2)));
 constexpr int kPast = (int)0x80000000u;                // past the end of every descriptor
 __device__ __forceinline__ rsrc_t tile_rsrc(const void* p) { return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(p), 0, 0x7FFFFFFF, 0x00020000); }
 // Copy of 16 bytes per lane straight into LDS: lane i's land at lds + 16 i (lanes past the descriptor's end: zeros).
+template <int POLICY>
 __device__ __forceinline__ void copy_to_lds(rsrc_t r, uint8_t* lds, int voff, int soff)
 {
 #ifdef __HIP_DEVICE_COMPILE__          // (the host pass knows neither the builtin's size of 16 nor the address space)
-    __builtin_amdgcn_raw_ptr_buffer_load_lds(r, (__attribute__((address_space(3))) void*)lds, 16, voff, soff, 0, 0);
+    __builtin_amdgcn_raw_ptr_buffer_load_lds(r, (__attribute__((address_space(3))) void*)lds, 16, voff, soff, 0, POLICY);
 #endif
 }
 __device__ __forceinline__ void step(int& soff, int by)
@@ -849,8 +850,14 @@ __device__ __forceinline__ void step(int& soff, int by)
 // 11008] FP4 141 -> 133, FP8 177 -> 165; with all statistics [4096 x 4096] FP4 27.0 -> 24.8, [16384 x 4096] 77 -> 68, FP8 81.5 -> 76,
 // [16384 x 11008] FP4 195 -> 174, FP8 214 -> 197.
 // Offsets inside a tile are 32-bit: launch_quantize_both keeps to tensors whose rows are short enough (qb_offsets_fit).
+// Cache policies of buffer instructions: streaming ("nt") and write-through ("sc1").  A tile that goes through LDS is read once and
+// streamed, so that sources leave the memory-side cache to the codes: 40 steps of one linear 0.9 % on average, 6 % at most (plain stores
+// of codes; all three: with the statistics' below).  Codes of a workgroup per unit with statistics are written through: at the end of a
+// kernel the L2s write out what is dirty with the chip idle ([1504 x 2080] 9.1 us -> 8.4, [4096 x 4096] 22.5 -> 20.8, a step 1504 x 2080 x
+// 1568 58.9 -> 57.3, 2048 x 4096 x 4096 165.9 -> 162.3).  Without statistics and LDS it makes no difference.  Large tensors: qb_streams.
+constexpr int kStream = 2, kThrough = 16;
 constexpr int qb_threads(int nw, int stats) { return nw ? nw * (stats ? 64 : 128) : 256; }
-template <int FMT_R, int FMT_C, int RULE, int STATS, int NW, int RBU, bool RAW_LDS>      // STATS: 0 none, 1 the chosen formats' errors, 2 both formats' errors
+template <int FMT_R, int FMT_C, int RULE, int STATS, int NW, int RBU, bool RAW_LDS, bool STREAM>      // STATS: 0 none, 1 the chosen formats' errors, 2 both formats' errors
 __global__ __launch_bounds__(qb_threads(NW, STATS), STATS ? 2 : 1) void quant_both_kernel(const uint16_t* __restrict__ x, int rows, int cols, int64_t ld,
                                                          uint8_t* __restrict__ codes_r, uint8_t* __restrict__ scales_r,
                                                          uint8_t* __restrict__ g4_r, int64_t kpitch_r,
@@ -859,7 +866,8 @@ __global__ __launch_bounds__(qb_threads(NW, STATS), STATS ? 2 : 1) void quant_bo
                                                          double* __restrict__ partials, int eighth, int band_log2)
 {
     constexpr bool COOP = NW != 0, SPLIT = STATS == 0;
-    static_assert(COOP || !SPLIT, "a wave per unit is for the statistics");
+    constexpr int STORE = STREAM ? kStream | kThrough : COOP && STATS ? kThrough : 0;
+    static_assert(!STREAM || RAW_LDS || !COOP, "codes are streamed by the forms for large tensors");
     constexpr int WPB = qb_threads(NW, STATS) / 64;
     constexpr int ROWB = RBU * (FMT_C == kFP8 ? 32 : 16);
     constexpr int CPR = ROWB / 16;
@@ -990,13 +998,13 @@ __global__ __launch_bounds__(qb_threads(NW, STATS), STATS ? 2 : 1) void quant_bo
                     unsigned e0 = STATS ? enc8x4<RULE>(x8, sc, byte) : enc8<RULE>(w[0], w[1], sc, byte);
                     unsigned e1 = STATS ? enc8x4<RULE>(x8 + 4, sc, byte) : enc8<RULE>(w[2], w[3], sc, byte);
                     if (bad) { e0 = 0; e1 = 0; }
-                    __builtin_amdgcn_raw_buffer_store_b64(v2u_t{e0, e1}, sc_codes, voff, soff, 0);
+                    __builtin_amdgcn_raw_buffer_store_b64(v2u_t{e0, e1}, sc_codes, voff, soff, STORE);
                     if (STATS) { err8x4(x8, e0, sc, se_r); err8x4(x8 + 4, e1, sc, se_r); }
                     if (STATS == 2) err4x8(x8, enc4x8(x8, sco), sco, so_r);
                 } else {
                     unsigned e4 = STATS ? enc4x8(x8, sc) : enc4(w[0], w[1], w[2], w[3], sc);
                     if (bad) e4 = 0;
-                    __builtin_amdgcn_raw_buffer_store_b32(e4, sc_codes, voff, soff, 0);
+                    __builtin_amdgcn_raw_buffer_store_b32(e4, sc_codes, voff, soff, STORE);
                     if (STATS) err4x8(x8, e4, sc, se_r);
                     if (STATS == 2) {
                         err8x4(x8, enc8x4<RULE>(x8, sco, other), sco, so_r);
@@ -1039,7 +1047,7 @@ __global__ __launch_bounds__(qb_threads(NW, STATS), STATS ? 2 : 1) void quant_bo
             for (int i = 0; i < 8 * RBU / WPB; ++i) {
                 const int q = i * WPB + wib;
                 if (q < nb * 8)
-                    copy_to_lds(tile_x(q >> 3), reg + q * 1024, ract ? (lane >> 4) * pitch_x + (lane & 15) * 16 : kPast, (q & 7) * 4 * pitch_x);
+                    copy_to_lds<kStream>(tile_x(q >> 3), reg + q * 1024, ract ? (lane >> 4) * pitch_x + (lane & 15) * 16 : kPast, (q & 7) * 4 * pitch_x);
             }
             __builtin_amdgcn_s_waitcnt(0x0F70);                // vmcnt(0)
             __syncthreads();                                   // the raw tiles are there
@@ -1115,7 +1123,7 @@ __global__ __launch_bounds__(qb_threads(NW, STATS), STATS ? 2 : 1) void quant_bo
             const int row = it * (64 / CPR) + l / CPR;
             const v4u_t q = *reinterpret_cast<const v4u_t*>(reg + row * ROWB + ((chunk ^ ((row >> 1) & (CPR - 1))) * 16));
             // (no scalar offset in a 16-byte store: see tile_rsrc)
-            __builtin_amdgcn_raw_buffer_store_b128(q, sc_codes, c0 + row < cols && blk < nb ? lane_off + it * (64 / CPR) * pitch_c : kPast, 0, 0);
+            __builtin_amdgcn_raw_buffer_store_b128(q, sc_codes, c0 + row < cols && blk < nb ? lane_off + it * (64 / CPR) * pitch_c : kPast, 0, STORE);
         }
         if (COOP) __syncthreads();                             // the staging areas go to the next unit
     }
@@ -1457,7 +1465,7 @@ hipError_t launch_quantize(const QuantArgs& a, hipStream_t s)
 // Work distribution of quant_both_kernel: waves of a workgroup x tiles of the unit they share (Lds: RAW_LDS), or a wave per unit.
 enum class QbForm { k4x4, k4x4Lds, k4x8, kWave };
 
-template <int FMT_R, int FMT_C, int RULE, int STATS, int NW, int RBU, bool RAW_LDS = false>
+template <int FMT_R, int FMT_C, int RULE, int STATS, int NW, int RBU, bool RAW_LDS = false, bool STREAM = false>
 static int launch_qb_form(const QuantBothArgs& a, double* partials, hipStream_t s)
 {
     const int64_t nrb = a.rows / kBlock;
@@ -1471,7 +1479,7 @@ static int launch_qb_form(const QuantBothArgs& a, double* partials, hipStream_t 
     // of a tile: at most kStreamBlocks workgroups with equal shares of the units then.
     const int64_t most = STATS ? kStreamBlocks / 8 : (int64_t)1 << 24, run = eighths ? eighth : (units + 63) / 64 * 8, share = (run + most - 1) / most;
     const int blocks = NW ? (int)(8 * ((run + share - 1) / share)) : balanced_blocks(units);
-    hipLaunchKernelGGL((quant_both_kernel<FMT_R, FMT_C, RULE, STATS, NW, RBU, RAW_LDS>), dim3(blocks), dim3(qb_threads(NW, STATS)), 0, s,
+    hipLaunchKernelGGL((quant_both_kernel<FMT_R, FMT_C, RULE, STATS, NW, RBU, RAW_LDS, STREAM>), dim3(blocks), dim3(qb_threads(NW, STATS)), 0, s,
                        a.x, (int)a.rows, (int)a.cols, a.ld, a.codes_r, a.scales_r, a.g4_r, g4_pitch(a.rows),
                        a.codes_c, a.scales_c, a.g4_c, g4_pitch(a.cols), partials, (int)eighth, band_log2);
     return blocks;
@@ -1480,12 +1488,17 @@ static int launch_qb_form(const QuantBothArgs& a, double* partials, hipStream_t 
 template <int FMT_R, int FMT_C, int RULE, int STATS>
 static int launch_qb(const QuantBothArgs& a, double* partials, QbForm form, hipStream_t s)
 {
+    const bool stream = qb_streams(a.rows, a.cols, FMT_R == kFP8, FMT_C == kFP8);
     if constexpr (STATS != 0)
-        if (form == QbForm::kWave) return launch_qb_form<FMT_R, FMT_C, RULE, STATS, 0, FMT_C == kFP8 ? 4 : 8>(a, partials, s);
+        if (form == QbForm::kWave)
+            return stream ? launch_qb_form<FMT_R, FMT_C, RULE, STATS, 0, FMT_C == kFP8 ? 4 : 8, false, true>(a, partials, s)
+                          : launch_qb_form<FMT_R, FMT_C, RULE, STATS, 0, FMT_C == kFP8 ? 4 : 8>(a, partials, s);
     if constexpr (FMT_C == kFP4 && STATS != 0)
         if (form == QbForm::k4x8) return launch_qb_form<FMT_R, FMT_C, RULE, STATS, 4, 8>(a, partials, s);
     if constexpr (STATS == 0)
-        if (form == QbForm::k4x4Lds) return launch_qb_form<FMT_R, FMT_C, RULE, STATS, 4, 4, true>(a, partials, s);
+        if (form == QbForm::k4x4Lds)
+            return stream ? launch_qb_form<FMT_R, FMT_C, RULE, STATS, 4, 4, true, true>(a, partials, s)
+                          : launch_qb_form<FMT_R, FMT_C, RULE, STATS, 4, 4, true>(a, partials, s);
     return launch_qb_form<FMT_R, FMT_C, RULE, STATS, 4, 4>(a, partials, s);
 }
 

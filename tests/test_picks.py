@@ -37,6 +37,9 @@ BANDS = [(2048, 43040, 154.8, 129.0), (2048, 26000, 96.7, 81.1), (6144, 14304, 1
 LDS = [(32, 1100, 9.24, 10.23), (64, 537, 7.08, 7.79), (96, 537, 8.87, 8.84), (11008, 11008, 140.5, 126.9), (4096, 8192, 101.2, 87.7), (2048, 256, 5.9, 6.3),
        (3072, 576, 12.5, 11.4), (4096, 800, 14.4, 15.2)]
 
+# ... forms for large tensors: rows, columns, FP8 rows, FP8 columns, us with codes stored plainly, streamed.  (The second: what a step of one linear takes.)
+STREAMED = [(16384, 11008, 0, 0, 157.0, 152.0), (2176, 8960, 0, 0, 102.4, 117.0), (12384, 10656, 0, 0, 160.8, 196.3)]
+
 
 def run(tmp_path, expression, args):
     src, exe = tmp_path / "pick.cpp", tmp_path / "pick"
@@ -68,6 +71,11 @@ def test_bands(tmp_path):
 def test_through_lds(tmp_path):
     picks = run(tmp_path, "snip::qb_through_lds(a(0), a(1), 256)", [m[:2] for m in LDS])
     assert picks == [int(m[3] < m[2]) for m in LDS]
+
+
+def test_streamed_codes(tmp_path):
+    picks = run(tmp_path, "snip::qb_streams(a(0), a(1), a(2), a(3))", [m[:4] for m in STREAMED])
+    assert picks == [int(m[5] < m[4]) for m in STREAMED]
 
 
 ORDER_PROGRAM = r"""
