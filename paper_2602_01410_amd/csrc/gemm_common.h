@@ -146,10 +146,10 @@ __device__ __forceinline__ void store16(v4u v, uint8_t* p, bool stream = true)
 
 // Result of a wave's 64 x 64 block with its corner at (i0, j0), of a kernel whose first MFMA operand is the B tile: turned through
 // 4 KB of LDS of the wave's own, 32 rows x 128 bytes at a time.  16-byte piece c of row r sits at position c ^ (r / 2 % 8) (bf16: a
-// piece is written in two halves).  `interior`: no row or column lies outside; `stream`: see store16.
-template <bool OUT_F32>
+// piece is written in two halves).  `interior`: no row or column lies outside; STREAM: see store16.
+template <bool OUT_F32, bool STREAM>
 __device__ __forceinline__ void store_block64(const v16f (&acc)[2][2], uint8_t* reg, int lane, void* c_out, int64_t ldc, int i0, int j0,
-                                              int I, int J, bool interior, bool stream)
+                                              int I, int J, bool interior)
 {
     constexpr int ESZ = OUT_F32 ? 4 : 2;
     const int r32 = lane & 31, g = lane >> 5, f = (r32 >> 1) & 7;
@@ -180,10 +180,10 @@ __device__ __forceinline__ void store_block64(const v16f (&acc)[2][2], uint8_t* 
                 const int i = i0 + m * 32 + row, j = j0 + h * 32 + c * (16 / ESZ);
                 uint8_t* p = reinterpret_cast<uint8_t*>(c_out) + ((int64_t)i * ldc + j) * ESZ;
                 if (interior) {
-                    store16(v, p, stream);
+                    store16(v, p, STREAM);
                 } else if (i < I) {
                     if (j + 16 / ESZ <= J) {
-                        store16(v, p, stream);
+                        store16(v, p, STREAM);
                     } else if (j < J) {
                         for (int e = 0; e < 16 / ESZ; ++e)
                             if (j + e < J) {

@@ -287,7 +287,9 @@ __global__ __launch_bounds__(NT) void gemm_paper_kernel(const uint8_t* __restric
     auto store_tile = [&](int u) {
         int ti, tj;
         tile_of(u, ntile, tiles_i, tiles_j, ti, tj);
-        store_block64<OUT_F32>(acc, reg, lane, c_out, ldc, ti * BM + wm * WTM, tj * BN + wn * WTN, I, J, false, stream);
+        const int i0 = ti * BM + wm * WTM, j0 = tj * BN + wn * WTN;
+        if (stream) store_block64<OUT_F32, true>(acc, reg, lane, c_out, ldc, i0, j0, I, J, false);
+        else store_block64<OUT_F32, false>(acc, reg, lane, c_out, ldc, i0, j0, I, J, false);
     };
 
     SNIP_BAR();                                              // stage 0 is complete

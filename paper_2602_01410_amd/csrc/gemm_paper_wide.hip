@@ -297,8 +297,11 @@ __global__ __launch_bounds__(NT) void gemm_paper_wide_kernel(const uint8_t* __re
 
     // ---- result of a tile, staged in the last stage's buffer
     auto store_tile = [&](int ti0, int tj0, int slot) __attribute__((always_inline)) {
-        store_block64<OUT_F32>(acc, lds + slot * C::SLOT + wave * C::EPI, lane, c_out, ldc, ti0 + wm * WTM, tj0 + wn * WTN, I, J,
-                               ti0 + TM <= I && tj0 + TN <= J, streams_result(ldc, OUT_F32));
+        uint8_t* const reg = lds + slot * C::SLOT + wave * C::EPI;
+        const int ti = ti0 + wm * WTM, tj = tj0 + wn * WTN;
+        const bool interior = ti0 + TM <= I && tj0 + TN <= J;
+        if (streams_result(ldc, OUT_F32)) store_block64<OUT_F32, true>(acc, reg, lane, c_out, ldc, ti, tj, I, J, interior);
+        else store_block64<OUT_F32, false>(acc, reg, lane, c_out, ldc, ti, tj, I, J, interior);
     };
 
     auto after = [](int slot) { return slot == NST - 1 ? 0 : slot + 1; };
