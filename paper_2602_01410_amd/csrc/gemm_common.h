@@ -41,10 +41,15 @@ __device__ __forceinline__ void glds4(const uint8_t* base, unsigned lane_off, un
 // The same with a buffer descriptor as source, per-lane offset `lane_off` + wave-uniform `soff`: a lane whose offset lies at
 // or past the descriptor's size - soff delivers zeros (kNoSource is past every size used here; soff: see copy_ranges.h).
 constexpr unsigned kNoSource = 0x80000000u;
+template <bool STREAM = false>
 __device__ __forceinline__ void blds16(v4i rsrc, unsigned lane_off, unsigned soff, unsigned lds)
 {
-    asm volatile("s_mov_b32 m0, %3\n\ts_nop 3\n\tbuffer_load_dwordx4 %0, %1, %2 offen lds"
-                 : : "v"(lane_off), "s"(rsrc), "s"(soff), "s"(lds) : "memory", "m0");
+    if constexpr (STREAM)
+        asm volatile("s_mov_b32 m0, %3\n\ts_nop 3\n\tbuffer_load_dwordx4 %0, %1, %2 offen nt lds"
+                     : : "v"(lane_off), "s"(rsrc), "s"(soff), "s"(lds) : "memory", "m0");
+    else
+        asm volatile("s_mov_b32 m0, %3\n\ts_nop 3\n\tbuffer_load_dwordx4 %0, %1, %2 offen lds"
+                     : : "v"(lane_off), "s"(rsrc), "s"(soff), "s"(lds) : "memory", "m0");
 }
 __device__ __forceinline__ void blds4(v4i rsrc, unsigned lane_off, unsigned soff, unsigned lds)
 {

@@ -56,7 +56,7 @@ template <int FA, int FB, class T> struct SmallCfg {
     static_assert(LDS_BYTES <= 159 * 1024, "LDS budget");
 };
 
-template <int FA, int FB, bool OUT_F32, class T>
+template <int FA, int FB, bool OUT_F32, class T, bool STREAM_B>
 __global__ __launch_bounds__(T::NT) void gemm_small_kernel(const uint8_t* __restrict__ a_codes, const uint8_t* __restrict__ a_g4,
                                                            const uint8_t* __restrict__ b_codes, const uint8_t* __restrict__ b_g4,
                                                            int I, int J, int R, void* __restrict__ c_out, int64_t ldc,
@@ -131,7 +131,7 @@ __global__ __launch_bounds__(T::NT) void gemm_small_kernel(const uint8_t* __rest
 #pragma unroll
             for (int j = 0; j < C::LA; ++j) blds16(ra, oa[j], ca.uniform, base + qa(j) * 1024);
 #pragma unroll
-            for (int j = 0; j < C::LB; ++j) blds16(rb, ob[j], cb.uniform, base + C::OFF_B + qb(j) * 1024);
+            for (int j = 0; j < C::LB; ++j) blds16<STREAM_B>(rb, ob[j], cb.uniform, base + C::OFF_B + qb(j) * 1024);
 #pragma unroll
             for (int j = 0; j < C::LS; ++j) {
                 const CopyRange cs = scale_range(st, nstage, ngrp, C::NG, spitch[j], srow0[j]);
@@ -338,18 +338,25 @@ __global__ __launch_bounds__(T::NT) void gemm_small_kernel(const uint8_t* __rest
     if (streams_result(ldc, OUT_F32)) store(std::true_type()); else store(std::false_type());
 }
 
-template <int FA, int FB, class T>
-hipError_t launch_small_t(const GemmArgs& a, hipStream_t s)
+template <int FA, int FB, class T, bool STREAM_B>
+hipError_t launch_small_s(const GemmArgs& a, hipStream_t s)
 {
     const int ti = (int)((a.I + T::BM - 1) / T::BM), tj = (int)((a.J + T::BN - 1) / T::BN);
     const dim3 grid((unsigned)(ti * tj)), block(T::NT);
     if (a.out_fp32)
-        hipLaunchKernelGGL((gemm_small_kernel<FA, FB, true, T>), grid, block, 0, s, a.a_codes, a.a_scales_g4, a.b_codes, a.b_scales_g4,
+        hipLaunchKernelGGL((gemm_small_kernel<FA, FB, true, T, STREAM_B>), grid, block, 0, s, a.a_codes, a.a_scales_g4, a.b_codes, a.b_scales_g4,
                            (int)a.I, (int)a.J, (int)a.R, a.c, a.ldc, ti, tj, a.norm_partials);
     else
-        hipLaunchKernelGGL((gemm_small_kernel<FA, FB, false, T>), grid, block, 0, s, a.a_codes, a.a_scales_g4, a.b_codes, a.b_scales_g4,
+        hipLaunchKernelGGL((gemm_small_kernel<FA, FB, false, T, STREAM_B>), grid, block, 0, s, a.a_codes, a.a_scales_g4, a.b_codes, a.b_scales_g4,
                            (int)a.I, (int)a.J, (int)a.R, a.c, a.ldc, ti, tj, a.norm_partials);
     return hipGetLastError();
+}
+template <int FA, int FB, class T>
+hipError_t launch_small_t(const GemmArgs& a, hipStream_t s)
+{
+    if constexpr (T::BM <= 64 && T::G == 1)
+        if (small_streams_b(a.I <= T::BM, a.J * a.R / (FB == kFP8 ? 1 : 2))) return launch_small_s<FA, FB, T, true>(a, s);
+    return launch_small_s<FA, FB, T, false>(a, s);
 }
 
 template <class T>

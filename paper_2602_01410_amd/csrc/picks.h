@@ -49,6 +49,15 @@ inline bool paper_wide_pays(long long I, long long J, long long R, bool both4, b
 // 3.38), four to seven 0.6 % slower, eight to fifteen 2.8 %, sixteen to 31 6.6 %, beyond that 10 %.
 constexpr int small_stages_per_barrier(bool cached, long long stages) { return cached && stages >= 4 ? 2 : 1; }
 
+// ---- gemm_small.hip: whether the codes of B are streamed ----
+// Where one row of tiles reads them, once (few tokens through a weight); other tile rows would find them in L2 (all calls of the small
+// tiles streamed, a step of 1024 x 2048 x 2048: 38 us -> 46).  From 20 MB on: a block with such weights has 90 MB of them, so the
+// memory-side cache (256 MB) keeps them for no second use, and streamed they come faster and leave it to the smaller ones.  Forward of
+// 7B-shaped blocks in FP4, 64 tokens 64.0 us -> 56.9, one token 55.1 -> 50.7, 70B-shaped 109 -> 99; streamed from 8 MB on 64 tokens took 60.7.
+// Smaller weights may be in that cache, and streaming would bring them from memory again (8 tokens, hidden 3584, FP4, three blocks
+// in turn: 47.8 us and 56.9).
+constexpr bool small_streams_b(bool one_row, long long bytes) { return one_row && bytes >= 20ll << 20; }
+
 // ---- quant_kernels.hip, quantize for both orientations: the order of the units among the XCDs ----
 // A unit is a row unit (RBU tiles of 32 rows) of a column group (128 columns).  Workgroup ids go to the XCDs in turn (id mod 8); units
 // go to them in turns of eight consecutive ones or, if `eighth` is not 0, `eighth` units each.  Consecutive units walk pairs of row units

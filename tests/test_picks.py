@@ -40,6 +40,9 @@ LDS = [(32, 1100, 9.24, 10.23), (64, 537, 7.08, 7.79), (96, 537, 8.87, 8.84), (1
 # ... forms for large tensors: rows, columns, FP8 rows, FP8 columns, us with codes stored plainly, streamed.  (The second: what a step of one linear takes.)
 STREAMED = [(16384, 11008, 0, 0, 157.0, 152.0), (2176, 8960, 0, 0, 102.4, 117.0), (12384, 10656, 0, 0, 160.8, 196.3)]
 
+# GEMMs of the small tiles: one row of tiles, bytes of B's codes, us of a forward with B read plainly, streamed
+B_STREAMED = [(1, 11008 * 2048, 64.0, 56.9), (1, 9536 * 1792, 47.8, 56.9), (0, 11008 * 2048, 38.0, 46.0)]
+
 
 def run(tmp_path, expression, args):
     src, exe = tmp_path / "pick.cpp", tmp_path / "pick"
@@ -76,6 +79,11 @@ def test_through_lds(tmp_path):
 def test_streamed_codes(tmp_path):
     picks = run(tmp_path, "snip::qb_streams(a(0), a(1), a(2), a(3))", [m[:4] for m in STREAMED])
     assert picks == [int(m[5] < m[4]) for m in STREAMED]
+
+
+def test_streamed_weights(tmp_path):
+    picks = run(tmp_path, "snip::small_streams_b(a(0), a(1))", [m[:2] for m in B_STREAMED])
+    assert picks == [int(m[3] < m[2]) for m in B_STREAMED]
 
 
 ORDER_PROGRAM = r"""
