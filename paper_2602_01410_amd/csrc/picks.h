@@ -133,6 +133,13 @@ constexpr bool qb_through_lds(long long cols, long long units, long long ncu)
     return cols > 64 && units > 2 * ncu && !(units > 3 * ncu && units <= 4 * ncu);
 }
 
+// ---- ... whether the waves of rows leave the columns' stores to those of columns, without statistics or LDS ----
+// With up to one unit per compute unit, where a call is one tile's chain: [256 x 512] FP4 3.7 us -> 3.45, [1024 x 1024] 4.2 -> 3.95, FP8 4.3 ->
+// 4.0, [1504 x 2080] 5.8 -> 5.5, [2048 x 2048] 6.5 -> 6.3 and 7.56 -> 7.53; six launches of a 256 x 512 x 512 step 20.8 -> 20.0.  Beyond that half of
+// the waves store 16 KB of FP8 columns too slowly ([4096 x 2048] 10.8 -> 11.4, [2048 x 5632] 11.4 -> 12.2, FP4 9.5 -> 9.6 and 10.1 -> 9.9;
+// through LDS [8192 x 3072] 21.9 -> 23.3).
+constexpr bool qb_rows_apart(long long units, long long ncu) { return units <= ncu; }
+
 // ---- ... whether the forms for large tensors (through LDS; a wave per unit) stream their codes past the caches ----
 // From 64 M elements on, of which both orientations' codes fill half of the memory-side cache (256 MB) and more: they would not be there
 // any more when a GEMM wants them, and leave their place to those of smaller tensors and to what the GEMMs read.  Plain -> streaming:

@@ -842,6 +842,9 @@ __device__ __forceinline__ void step(int& soff, int by)
 // Without statistics NW more waves take the rows of the tiles (SPLIT), and the first NW the columns: 60-67 registers instead
 // of 96 put seven waves on a SIMD instead of four or five, and the two chains of a tile run side by side.  With statistics
 // a workgroup would wait for its column waves, whose work is the longer: [8192 x 4096] FP4 54 us against 41.
+// APART: a row takes its wave 1.0 us of work where a column takes 0.4 (time stamps, [2048 x 2048] FP4), and the waves of rows stand in
+// front of the barrier behind which the columns' codes are stored.  They meet it on their way, after three of their eight
+// steps, when the columns are done, and leave the columns' stores to the others (qb_rows_apart, picks.h).
 // NW == 0 (with statistics): a wave per unit, four of them in a workgroup.  Same bytes out.
 // Without statistics bound by memory (and by launch and one tile's chain below 4 M elements), with them by vector arithmetic.
 // Vector instructions per tile of 4096 elements, FP4: 765 -> 464 without statistics, 1800 -> 1480 with all of them, when
@@ -857,7 +860,7 @@ __device__ __forceinline__ void step(int& soff, int by)
 // 1568 58.9 -> 57.3, 2048 x 4096 x 4096 165.9 -> 162.3).  Without statistics and LDS it makes no difference.  Large tensors: qb_streams.
 constexpr int kStream = 2, kThrough = 16;
 constexpr int qb_threads(int nw, int stats) { return nw ? nw * (stats ? 64 : 128) : 256; }
-template <int FMT_R, int FMT_C, int RULE, int STATS, int NW, int RBU, bool RAW_LDS, bool STREAM>      // STATS: 0 none, 1 the chosen formats' errors, 2 both formats' errors
+template <int FMT_R, int FMT_C, int RULE, int STATS, int NW, int RBU, bool RAW_LDS, bool STREAM, bool APART>      // STATS: 0 none, 1 the chosen formats' errors, 2 both formats' errors
 __global__ __launch_bounds__(qb_threads(NW, STATS), STATS ? 2 : 1) void quant_both_kernel(const uint16_t* __restrict__ x, int rows, int cols, int64_t ld,
                                                          uint8_t* __restrict__ codes_r, uint8_t* __restrict__ scales_r,
                                                          uint8_t* __restrict__ g4_r, int64_t kpitch_r,
@@ -868,7 +871,9 @@ __global__ __launch_bounds__(qb_threads(NW, STATS), STATS ? 2 : 1) void quant_bo
     constexpr bool COOP = NW != 0, SPLIT = STATS == 0;
     constexpr int STORE = STREAM ? kStream | kThrough : COOP && STATS ? kThrough : 0;
     static_assert(!STREAM || RAW_LDS || !COOP, "codes are streamed by the forms for large tensors");
-    constexpr int WPB = qb_threads(NW, STATS) / 64;
+    constexpr int WPB = qb_threads(NW, STATS) / 64, CW = APART ? NW : WPB;    // waves of a workgroup, those that store the columns
+    static_assert(!APART || (SPLIT && !RAW_LDS), "waves of rows and of columns, each with its own loads");
+    constexpr int kRowsMeet = 3;
     constexpr int ROWB = RBU * (FMT_C == kFP8 ? 32 : 16);
     constexpr int CPR = ROWB / 16;
     // RAW_LDS: the raw tiles first, and the column codes in the same place once every wave has its part of them
@@ -981,6 +986,7 @@ __global__ __launch_bounds__(qb_threads(NW, STATS), STATS ? 2 : 1) void quant_bo
             int d_lo = 0, d_hi = 0;
 #pragma unroll
             for (int j = 0; j < 8; ++j) {
+                if (APART && j == kRowsMeet) __builtin_amdgcn_s_barrier();      // the one in front of the columns' stores
                 const unsigned w[4] = {rv[j].x, rv[j].y, rv[j].z, rv[j].w};
                 float x8[8];
                 unsigned am;
@@ -1079,6 +1085,8 @@ __global__ __launch_bounds__(qb_threads(NW, STATS), STATS ? 2 : 1) void quant_bo
                 uint4 rv[8];
                 fetch_row(k, rv);
                 work_row(k, rv);
+            } else if (APART && wib >= NW) {
+                __builtin_amdgcn_s_barrier();
             }
         } else {
             for (int k = COOP ? wib : 0; k < nb; k += COOP ? NW : 1) {
@@ -1090,40 +1098,42 @@ __global__ __launch_bounds__(qb_threads(NW, STATS), STATS ? 2 : 1) void quant_bo
                 work_row(k, rv);
             }
         }
-        if (COOP) {
-            __syncthreads();                                   // all tiles of the unit are staged
-            for (int g = wib; 4 * g < nb; g += WPB) {
-                const int last = min(3, nb - 1 - 4 * g);
-                unsigned lo = 0, hi = 0;
-                for (int i = 0; i <= last; ++i) {
-                    const unsigned v = *reinterpret_cast<const uint16_t*>(scale_stage + (4 * g + i) * kColsPerWave + 2 * lane);
-                    lo |= (v & 0xFFu) << (8 * i);
-                    hi |= (v >> 8) << (8 * i);
+        if (!APART || wib < NW) {                              // (the rows' waves have met this barrier on their way)
+            if (COOP) {
+                __syncthreads();                                   // all tiles of the unit are staged
+                for (int g = wib; 4 * g < nb; g += CW) {
+                    const int last = min(3, nb - 1 - 4 * g);
+                    unsigned lo = 0, hi = 0;
+                    for (int i = 0; i <= last; ++i) {
+                        const unsigned v = *reinterpret_cast<const uint16_t*>(scale_stage + (4 * g + i) * kColsPerWave + 2 * lane);
+                        lo |= (v & 0xFFu) << (8 * i);
+                        hi |= (v >> 8) << (8 * i);
+                    }
+                    store_col_scales(rb0 + 4 * g, last, lo, hi);
                 }
-                store_col_scales(rb0 + 4 * g, last, lo, hi);
+                // Rows of no whole number of dwords: bytes, four lanes to a column, the columns dealt to the waves (a lane for two whole
+                // columns, in one wave, is four times the requests).
+                if ((nrb & 3) != 0)
+                    for (int p = wib; p < (nb + 3) / 4 * 8; p += CW) {
+                        int l = lane;
+                        asm volatile("" : "+v"(l));
+                        const int blk = p / 8 * 4 + (l & 3), col = p % 8 * 16 + (l >> 2);
+                        __builtin_amdgcn_raw_buffer_store_b8(scale_stage[blk * kColsPerWave + col], tile_rsrc(scales_c + (int64_t)c0 * nrb + rb0),
+                                                             blk < nb && c0 + col < cols ? col * nrb + blk : kPast, 0, 0);
+                    }
             }
-            // Rows of no whole number of dwords: bytes, four lanes to a column, the columns dealt to the waves (a lane for two whole
-            // columns, in one wave, is four times the requests).
-            if ((nrb & 3) != 0)
-                for (int p = wib; p < (nb + 3) / 4 * 8; p += WPB) {
-                    int l = lane;
-                    asm volatile("" : "+v"(l));
-                    const int blk = p / 8 * 4 + (l & 3), col = p % 8 * 16 + (l >> 2);
-                    __builtin_amdgcn_raw_buffer_store_b8(scale_stage[blk * kColsPerWave + col], tile_rsrc(scales_c + (int64_t)c0 * nrb + rb0),
-                                                         blk < nb && c0 + col < cols ? col * nrb + blk : kPast, 0, 0);
-                }
-        }
-        const rsrc_t sc_codes = tile_rsrc(codes_c + (int64_t)c0 * pitch_c + (int64_t)ru * ROWB);
-        int l = lane;
-        if (!COOP) asm volatile("" : "+v"(l));                 // (computed here: kept over the tiles, the addresses below spill registers)
-        const int chunk = l % CPR, blk = FMT_C == kFP8 ? chunk >> 1 : chunk;
-        const int lane_off = (l / CPR) * pitch_c + chunk * 16;
+            const rsrc_t sc_codes = tile_rsrc(codes_c + (int64_t)c0 * pitch_c + (int64_t)ru * ROWB);
+            int l = lane;
+            if (!COOP) asm volatile("" : "+v"(l));                 // (computed here: kept over the tiles, the addresses below spill registers)
+            const int chunk = l % CPR, blk = FMT_C == kFP8 ? chunk >> 1 : chunk;
+            const int lane_off = (l / CPR) * pitch_c + chunk * 16;
 #pragma unroll
-        for (int it = COOP ? wib : 0; it < kColsPerWave * CPR / 64; it += COOP ? WPB : 1) {
-            const int row = it * (64 / CPR) + l / CPR;
-            const v4u_t q = *reinterpret_cast<const v4u_t*>(reg + row * ROWB + ((chunk ^ ((row >> 1) & (CPR - 1))) * 16));
-            // (no scalar offset in a 16-byte store: see tile_rsrc)
-            __builtin_amdgcn_raw_buffer_store_b128(q, sc_codes, c0 + row < cols && blk < nb ? lane_off + it * (64 / CPR) * pitch_c : kPast, 0, STORE);
+            for (int it = COOP ? wib : 0; it < kColsPerWave * CPR / 64; it += COOP ? CW : 1) {
+                const int row = it * (64 / CPR) + l / CPR;
+                const v4u_t q = *reinterpret_cast<const v4u_t*>(reg + row * ROWB + ((chunk ^ ((row >> 1) & (CPR - 1))) * 16));
+                // (no scalar offset in a 16-byte store: see tile_rsrc)
+                __builtin_amdgcn_raw_buffer_store_b128(q, sc_codes, c0 + row < cols && blk < nb ? lane_off + it * (64 / CPR) * pitch_c : kPast, 0, STORE);
+            }
         }
         if (COOP) __syncthreads();                             // the staging areas go to the next unit
     }
@@ -1465,7 +1475,7 @@ hipError_t launch_quantize(const QuantArgs& a, hipStream_t s)
 // Work distribution of quant_both_kernel: waves of a workgroup x tiles of the unit they share (Lds: RAW_LDS), or a wave per unit.
 enum class QbForm { k4x4, k4x4Lds, k4x8, kWave };
 
-template <int FMT_R, int FMT_C, int RULE, int STATS, int NW, int RBU, bool RAW_LDS = false, bool STREAM = false>
+template <int FMT_R, int FMT_C, int RULE, int STATS, int NW, int RBU, bool RAW_LDS = false, bool STREAM = false, bool APART = false>
 static int launch_qb_form(const QuantBothArgs& a, double* partials, hipStream_t s)
 {
     const int64_t nrb = a.rows / kBlock;
@@ -1479,7 +1489,7 @@ static int launch_qb_form(const QuantBothArgs& a, double* partials, hipStream_t 
     // of a tile: at most kStreamBlocks workgroups with equal shares of the units then.
     const int64_t most = STATS ? kStreamBlocks / 8 : (int64_t)1 << 24, run = eighths ? eighth : (units + 63) / 64 * 8, share = (run + most - 1) / most;
     const int blocks = NW ? (int)(8 * ((run + share - 1) / share)) : balanced_blocks(units);
-    hipLaunchKernelGGL((quant_both_kernel<FMT_R, FMT_C, RULE, STATS, NW, RBU, RAW_LDS, STREAM>), dim3(blocks), dim3(qb_threads(NW, STATS)), 0, s,
+    hipLaunchKernelGGL((quant_both_kernel<FMT_R, FMT_C, RULE, STATS, NW, RBU, RAW_LDS, STREAM, APART>), dim3(blocks), dim3(qb_threads(NW, STATS)), 0, s,
                        a.x, (int)a.rows, (int)a.cols, a.ld, a.codes_r, a.scales_r, a.g4_r, g4_pitch(a.rows),
                        a.codes_c, a.scales_c, a.g4_c, g4_pitch(a.cols), partials, (int)eighth, band_log2);
     return blocks;
@@ -1499,6 +1509,9 @@ static int launch_qb(const QuantBothArgs& a, double* partials, QbForm form, hipS
         if (form == QbForm::k4x4Lds)
             return stream ? launch_qb_form<FMT_R, FMT_C, RULE, STATS, 4, 4, true, true>(a, partials, s)
                           : launch_qb_form<FMT_R, FMT_C, RULE, STATS, 4, 4, true>(a, partials, s);
+    if constexpr (STATS == 0)
+        if (qb_rows_apart(((a.cols + kColsPerWave - 1) / kColsPerWave) * ((a.rows / kBlock + 3) / 4), gemm_compute_units()))
+            return launch_qb_form<FMT_R, FMT_C, RULE, STATS, 4, 4, false, false, true>(a, partials, s);
     return launch_qb_form<FMT_R, FMT_C, RULE, STATS, 4, 4>(a, partials, s);
 }
 

@@ -43,6 +43,9 @@ STREAMED = [(16384, 11008, 0, 0, 157.0, 152.0), (2176, 8960, 0, 0, 102.4, 117.0)
 # GEMMs of the small tiles: one row of tiles, bytes of B's codes, us of a forward with B read plainly, streamed
 B_STREAMED = [(1, 11008 * 2048, 64.0, 56.9), (1, 9536 * 1792, 47.8, 56.9), (0, 11008 * 2048, 38.0, 46.0)]
 
+# ... direct: units, us with columns stored by all waves, by those of columns
+APART = [(8, 3.70, 3.45), (204, 5.80, 5.48), (256, 6.53, 6.33), (512, 10.81, 11.39), (704, 11.40, 12.16)]
+
 
 def run(tmp_path, expression, args):
     src, exe = tmp_path / "pick.cpp", tmp_path / "pick"
@@ -84,6 +87,11 @@ def test_streamed_codes(tmp_path):
 def test_streamed_weights(tmp_path):
     picks = run(tmp_path, "snip::small_streams_b(a(0), a(1))", [m[:2] for m in B_STREAMED])
     assert picks == [int(m[3] < m[2]) for m in B_STREAMED]
+
+
+def test_rows_apart(tmp_path):
+    picks = run(tmp_path, "snip::qb_rows_apart(a(0), 256)", [m[:1] for m in APART])
+    assert picks == [int(m[2] < m[1]) for m in APART]
 
 
 ORDER_PROGRAM = r"""
