@@ -136,7 +136,6 @@ __device__ __forceinline__ void tile_of(int u, int nblk, int tiles_i, int tiles_
 // Rows that do not start on 64 bytes leave parts of 64-byte pieces at the edges of every tile, which memory takes singly: plain stores
 // there (paper recipe, streaming against plain, operands from memory: [7040 x 5200 x 256] FP4 32.5 us and 27.9, 63 calls +2 %; rows on 64
 // bytes, 9 calls, -3 %, whole lines, 27 calls above 1 M elements, -7 %).
-__device__ __forceinline__ bool streams_result(int64_t ldc, bool f32) { return (ldc & (f32 ? 15 : 31)) == 0; }
 // (The empty statements keep the compiler from making one plain store of the two kinds.)
 __device__ __forceinline__ void store16(v4u v, uint8_t* p, bool stream = true)
 {

@@ -40,9 +40,9 @@
 // launch before it, 1.9 until the first stage is there, eight stages of 0.72 (the first) to 1.0 us, 2.4 for the result; the shader
 // clock falls from 2.4 GHz to 1.65 within the first 4 us of stages.
 //
-// Registers: 256 vector registers (256 x 256), 198-246 (256 x 128; 193-215 with two buffers).  Scalar registers run out and spill to
-// lanes of vector registers: 27-28 for bf16 outputs and 65-71 for fp32 (256 x 256; 256 x 128 20-31 and 64-71, with two buffers 21-23
-// and 61-63), 46-63 and 88-99 with TAIL (59-73 and 97-116, 52-62 and 89-100), of which a stage restores up to six.
+// Registers: 256 vector registers (256 x 256), 200-246 (256 x 128; 193-215 with two buffers).  Scalar registers run out and spill to
+// lanes of vector registers: 23-25 for bf16 outputs and 58-65 for fp32 (256 x 256; 256 x 128 20-26 and 60-65, with two buffers 17-19
+// and 57-59), 50-62 and 84-97 with TAIL (63-71 and 93-102, 50-62 and 85-96), of which a stage restores up to six.
 //
 // See gemm.hip for the register layout of v_mfma_scale_f32_32x32x64_f8f6f4.
 #include "gemm_common.h"
@@ -113,7 +113,10 @@ template <int FA, int FB, class T> struct FCfg {
 // for chunks past the end of a row, and the scale bytes past the last block are masked.  It is a variant of its own
 // because descriptors and masks cost the whole-stage form 10-14 % (16384 x 4096 x 4096, FP4 134 -> 147 us, FP8 202 -> 233;
 // scalar registers spill); against the general kernel it is 3.5-4 times as fast (4096 x 4096 x 4128, FP4 190 -> 46 us).
-template <int FA, int FB, bool OUT_F32, class T, bool TAIL>
+// STREAM: result stores (store16).  Kernels of their own too: with both kinds in one, whole tiles of fp32 results had to share the
+// stores of ragged ones where they are plain, for want of scalar registers (rows off 64 bytes, operands from memory: [4096 x 2048 x 2048]
+// FP4 21.6 us -> 19.5, FP8 27.0 -> 26.1, [8192 x 3072 x 3072] FP4 71.8 -> 70.1).
+template <int FA, int FB, bool OUT_F32, class T, bool TAIL, bool STREAM>
 __global__ __launch_bounds__(NT) void gemm_fast_kernel(const uint8_t* __restrict__ a_codes,
                                                        const uint8_t* __restrict__ a_g4,
                                                        const uint8_t* __restrict__ b_codes,
@@ -190,8 +193,9 @@ __global__ __launch_bounds__(NT) void gemm_fast_kernel(const uint8_t* __restrict
     };
     // A workgroup's last copies, which nobody reads, all from one place: they are waited for before the result is stored, and take L2
     // and power beside the last MFMAs.  From memory, graphs: 3B-shaped block 2146 us -> 2133, backward of 8192 x 8192 x 3072 283.8 -> 281.3.
-    // (Not where fp32 results of a cut contraction leave no scalar registers: 35 spilled ones fetched between MFMAs.)
-    constexpr bool QUIET = !(TAIL && OUT_F32);
+    // (Not where fp32 results leave no scalar registers: of a cut contraction, 35 spilled ones fetched between MFMAs, of FP8 times FP4 in
+    // 256 x 128, 28.)
+    constexpr bool QUIET = !(OUT_F32 && (TAIL || (FA == kFP8 && FB == kFP4 && TN == 128)));
     auto copy_nothing = [&]() {
 #pragma unroll
         for (int j = 0; j < C::LA; ++j) oa[j] = TAIL ? kNoSource : 0u;
@@ -365,7 +369,7 @@ __global__ __launch_bounds__(NT) void gemm_fast_kernel(const uint8_t* __restrict
         int ti, tj;
         tile_of(u, nblk, tiles_i, tiles_j, ti, tj);
         const int i0 = ti * TM, j0 = tj * TN;
-        const bool interior = i0 + TM <= I && j0 + TN <= J, stream = streams_result(ldc, OUT_F32);
+        const bool interior = i0 + TM <= I && j0 + TN <= J;
         // optional: sum of squares of the tile as it will be stored (rounded to the output type), elements
         // outside the matrix excluded; one partial per tile, combined by a second kernel.  Interior tiles take
         // the short path: bf16 pairs are squared and added by v_dot2c_f32_bf16.
@@ -454,8 +458,7 @@ __global__ __launch_bounds__(NT) void gemm_fast_kernel(const uint8_t* __restrict
             }
             // read back row-contiguous: 64 lanes cover 64 / CPR rows per instruction (stores: store16)
             constexpr int RPI = 64 / CPR;
-            constexpr bool TWO = !OUT_F32;          // (plain stores of fp32 results here too spill registers)
-            if (interior && (TWO || stream)) {
+            if (interior) {
                 // whole tile inside the matrix (wave-uniform): no per-lane tests, one wave-uniform base per
                 // instruction plus a 32-bit lane offset
                 const unsigned lane_off = (unsigned)((lane / CPR) * (int)ldc * ESZ + (lane % CPR) * 16);
@@ -467,7 +470,7 @@ __global__ __launch_bounds__(NT) void gemm_fast_kernel(const uint8_t* __restrict
                     const int c = lane % CPR;
                     const int f = spread(row);
                     const v4u v = *reinterpret_cast<const v4u*>(reg + row * ROWB + ((c ^ f) * 16));
-                    store16(v, const_cast<uint8_t*>(cb) + (int64_t)(it * RPI) * ldc * ESZ + lane_off, !TWO || stream);
+                    store16(v, const_cast<uint8_t*>(cb) + (int64_t)(it * RPI) * ldc * ESZ + lane_off, STREAM);
                 }
             } else {
                 for (int it = 0; it < ROWS_PER_PASS / RPI; ++it) {
@@ -480,7 +483,7 @@ __global__ __launch_bounds__(NT) void gemm_fast_kernel(const uint8_t* __restrict
                     if (i < I) {
                         uint8_t* p = reinterpret_cast<uint8_t*>(c_out) + ((int64_t)i * ldc + j) * ESZ;
                         if (j + 16 / ESZ <= J) {
-                            store16(v4u{v.x, v.y, v.z, v.w}, p, stream);
+                            store16(v4u{v.x, v.y, v.z, v.w}, p, STREAM);
                         // (lanes past the last column would walk through the tests below: 1 us of a tile with two passes; cached
                         // operands, [7936 x 544 x 640] FP8 10.3 -> 8.9 us, [416 x 9440 x 1152] 12.0 -> 10.7)
                         } else if (j < J) {
@@ -618,25 +621,23 @@ __global__ __launch_bounds__(NT) void gemm_fast_kernel(const uint8_t* __restrict
     }
 }
 
-template <int FA, int FB, class T, bool TAIL>
+template <int FA, int FB, bool OUT_F32, class T, bool TAIL>
 hipError_t launch_fast_t(const GemmArgs& a, hipStream_t s)
 {
     const int ti = (int)((a.I + T::TM - 1) / T::TM), tj = (int)((a.J + T::TN - 1) / T::TN);
     // one workgroup per compute unit (the LDS array admits no second one), each walking its share of the tiles
     const int ncu = gemm_compute_units();
     const dim3 grid((unsigned)(ti * tj < ncu ? ti * tj : ncu)), block(NT);
-    if (a.out_fp32)
-        hipLaunchKernelGGL((gemm_fast_kernel<FA, FB, true, T, TAIL>), grid, block, 0, s, a.a_codes, a.a_scales_g4, a.b_codes, a.b_scales_g4,
-                           (int)a.I, (int)a.J, (int)a.R, a.c, a.ldc, ti, tj, a.norm_partials);
-    else
-        hipLaunchKernelGGL((gemm_fast_kernel<FA, FB, false, T, TAIL>), grid, block, 0, s, a.a_codes, a.a_scales_g4, a.b_codes, a.b_scales_g4,
-                           (int)a.I, (int)a.J, (int)a.R, a.c, a.ldc, ti, tj, a.norm_partials);
+    auto* const kernel = gemm_streams(a) ? gemm_fast_kernel<FA, FB, OUT_F32, T, TAIL, true> : gemm_fast_kernel<FA, FB, OUT_F32, T, TAIL, false>;
+    hipLaunchKernelGGL(kernel, grid, block, 0, s, a.a_codes, a.a_scales_g4, a.b_codes, a.b_scales_g4,
+                       (int)a.I, (int)a.J, (int)a.R, a.c, a.ldc, ti, tj, a.norm_partials);
     return hipGetLastError();
 }
 template <int FA, int FB, class T>
 hipError_t launch_fast_f(const GemmArgs& a, hipStream_t s)
 {
-    return a.R % FCfg<FA, FB, T>::KE == 0 ? launch_fast_t<FA, FB, T, false>(a, s) : launch_fast_t<FA, FB, T, true>(a, s);
+    if (a.R % FCfg<FA, FB, T>::KE == 0) return a.out_fp32 ? launch_fast_t<FA, FB, true, T, false>(a, s) : launch_fast_t<FA, FB, false, T, false>(a, s);
+    return a.out_fp32 ? launch_fast_t<FA, FB, true, T, true>(a, s) : launch_fast_t<FA, FB, false, T, true>(a, s);
 }
 
 template <class T>

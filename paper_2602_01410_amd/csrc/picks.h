@@ -49,6 +49,9 @@ inline bool paper_wide_pays(long long I, long long J, long long R, bool both4, b
 // 3.38), four to seven 0.6 % slower, eight to fifteen 2.8 %, sixteen to 31 6.6 %, beyond that 10 %.
 constexpr int small_stages_per_barrier(bool cached, long long stages) { return cached && stages >= 4 ? 2 : 1; }
 
+// ---- GEMMs: whether the result is stored streaming (store16 in gemm_common.h) ----
+constexpr bool streams_result(long long ldc, bool f32) { return ldc * (f32 ? 4 : 2) % 64 == 0; }
+
 // ---- gemm_small.hip: whether the codes of B are streamed ----
 // Where one row of tiles reads them, once (few tokens through a weight); other tile rows would find them in L2 (all calls of the small
 // tiles streamed, a step of 1024 x 2048 x 2048: 38 us -> 46).  From 20 MB on: a block with such weights has 90 MB of them, so the

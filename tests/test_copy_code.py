@@ -9,8 +9,10 @@ register is fetched back (v_readlane) there (256 x 128, [407 x 14080 x 14976] FP
 a kernel, 62.5 with up to 16), and lane registers are not spilled to make room (256 x 256, [4960 x 1760 x 512] FP4 with bf16 results:
 11.8 us with four of them and seven loads from scratch, 10.9 with one).
 
-Results are stored streaming ("nt") or, where rows start off 64 bytes, plain: both kinds are there in every kernel (the compiler makes
-one plain store of two branches that differ in nothing else, [4096 x 2048 x 2048] FP4 16.0 us instead of 13.7)."""
+Results are stored streaming ("nt") or plain, by kernels of their own or by two branches of one, of which the compiler makes one plain store
+if they differ in nothing else ([4096 x 2048 x 2048] FP4 16.0 us instead of 13.7).  So the stores are counted: as many of either kind as
+a wave's part of the tile takes, twice that where whole tiles have stores without tests of their own ([4096 x 2048 x 2048] FP4, fp32
+results on rows off 64 bytes, plain: 21.6 us on the stores of ragged tiles, 19.5 on those of whole ones)."""
 import os
 import re
 import subprocess
@@ -103,10 +105,32 @@ def result_stores(lines):
     return counts
 
 
-def test_scan_counts_result_stores():
-    body = ["0000 <_Z16gemm_fast_kernelv>:", " global_store_dwordx4 v0, v[2:5], s[0:1] nt // x", " global_store_dwordx4 v0, v[2:5], s[0:1] // nt", "0100 <_Z1kv>:",
-            " global_store_dwordx4 v0, v[2:5], s[0:1]"]
-    assert list(result_stores(body).values()) == [[1, 1]]
+def wanted_stores(function):
+    """What result_stores has to find in a kernel, by its mangled name: either of the pairs returned."""
+    kernel, args = re.search(r"(gemm_(?:fast|small|paper_wide|paper)_kernel)(.*)", function).groups()
+    f32 = re.match(r"ILi\dELi\dELb(\d)E", args).group(1) == "1"
+    tile = re.search(r"Tile\w*?ILi\d+ELi\d+ELi(\d+)ELi(\d+)E", args)         # rows and columns of a workgroup, of a wave (the paper's recipe: 64 x 64)
+    rows, columns = map(int, tile.groups()) if tile else (64, 64)
+    n = rows * columns * (4 if f32 else 2) // 1024                              # a wave stores 1 KB at a time
+    if kernel == "gemm_fast_kernel":
+        return [2 * n, 0], [0, 2 * n]
+    return ([2 * n, 2 * n],) if kernel == "gemm_paper_wide_kernel" else ([n, n],)
+
+
+FAST = "0000 <_ZN4snip12_GLOBAL__N_116gemm_fast_kernelILi0ELi0ELb%dENS0_7TileCfgILi256ELi128ELi64ELi64ELi3ELi1EEELb0ELb1EEEvPKh>:"
+SMALL = "0000 <_ZN4snip12_GLOBAL__N_117gemm_small_kernelILi0ELi0ELb0ENS0_9SmallTileILi32ELi32ELi32ELi32ELi8ELi4ELi2EEELb0EEEvPKh>:"
+
+
+@pytest.mark.parametrize("function, streaming, plain, good", [
+    (FAST % 0, 16, 0, True), (FAST % 0, 0, 16, True), (FAST % 1, 32, 0, True), (FAST % 1, 0, 32, True), (SMALL, 2, 2, True),
+    (FAST % 0, 8, 8, False),            # streaming for ragged tiles only
+    (FAST % 1, 0, 16, False),           # no stores without tests for whole tiles
+    (SMALL, 0, 2, False)])              # one plain store of two branches
+def test_scan_counts_result_stores(function, streaming, plain, good):
+    body = [function] + [" global_store_dwordx4 v0, v[2:5], s[0:1] nt // x"] * streaming + [" global_store_dwordx4 v0, v[2:5], s[0:1] // nt"] * plain
+    found = result_stores(body + ["0100 <_Z1kv>:", " global_store_dwordx4 v0, v[2:5], s[0:1]"])
+    assert list(found.values()) == [[streaming, plain]]
+    assert (found[function] in wanted_stores(function)) == good
 
 
 def test_library(tmp_path):
@@ -126,4 +150,6 @@ def test_library(tmp_path):
     assert copies > 100
     assert len(fetched) > 10 and max(fetched.values()) <= 20
     assert scratch.keys() == fetched.keys() and max(scratch.values()) <= 3
-    assert len(stores) > 60 and all(streaming > 0 and plain > 0 for streaming, plain in stores.values())
+    assert len(stores) > 60 and {f: n for f, n in stores.items() if n not in wanted_stores(f)} == {}
+    fast = [n for f, n in stores.items() if "gemm_fast_kernel" in f]
+    assert sum(n[0] > 0 for n in fast) == sum(n[1] > 0 for n in fast) == len(fast) // 2
