@@ -133,9 +133,7 @@ __device__ __forceinline__ void tile_of(int u, int nblk, int tiles_i, int tiles_
 // 51.9, [2048 x 4096 x 4096] FP8 39.7 -> 36.2, fp32 42.2 -> 36.8; random calls on operands from memory 7 % on average (30 % ... -3 %), on one
 // buffer again and again 2 %; followed by a quantize call that reads the result 0 and 0.5 %.  Write-through besides ("sc1 nt") shortens
 // the gap to 1.3 us, but tiles that follow each other wait for it (blocks of the 70B and 7B shapes 0.4 % slower, 1B 0.4 % faster).
-// Rows that do not start on 64 bytes leave parts of 64-byte pieces at the edges of every tile, which memory takes singly: plain stores
-// there (paper recipe, streaming against plain, operands from memory: [7040 x 5200 x 256] FP4 32.5 us and 27.9, 63 calls +2 %; rows on 64
-// bytes, 9 calls, -3 %, whole lines, 27 calls above 1 M elements, -7 %).
+// Which results: streams_result (picks.h).
 // (The empty statements keep the compiler from making one plain store of the two kinds.)
 __device__ __forceinline__ void store16(v4u v, uint8_t* p, bool stream = true)
 {

@@ -59,7 +59,7 @@ __device__ __forceinline__ void glds16_at(uint64_t src, unsigned lds)
 template <int FA, int FB, bool OUT_F32, bool B_BLOCK>
 __global__ __launch_bounds__(NT) void gemm_paper_kernel(const uint8_t* __restrict__ a_codes, const float* __restrict__ a_scales, int a_group,
                                                         const uint8_t* __restrict__ b_codes, const float* __restrict__ b_scales, int b_group,
-                                                        int I, int J, int R, void* __restrict__ c_out, int64_t ldc, int tiles_i, int tiles_j)
+                                                        int I, int J, int R, void* __restrict__ c_out, int64_t ldc, int tiles_i, int tiles_j, int stream_out)
 {
     using C = PaperCfg<FA, FB>;
     constexpr int NG = C::NG, KS = C::KS;
@@ -281,14 +281,11 @@ __global__ __launch_bounds__(NT) void gemm_paper_kernel(const uint8_t* __restric
     };
 
     uint8_t* const reg = lds + C::OFF_E + wave * C::EPI;         // result staging of the wave
-    // Small results plain too: at the end of a short kernel memory answers later than the caches ([832 x 768 x 256] FP4 5.3 us and 5.6; 1 %
-    // on average below 1 M elements, above 4-6 % the other way).
-    const bool stream = streams_result(ldc, OUT_F32) && (int64_t)I * J >= 1 << 20;
     auto store_tile = [&](int u) {
         int ti, tj;
         tile_of(u, ntile, tiles_i, tiles_j, ti, tj);
         const int i0 = ti * BM + wm * WTM, j0 = tj * BN + wn * WTN;
-        if (stream) store_block64<OUT_F32, true>(acc, reg, lane, c_out, ldc, i0, j0, I, J, false);
+        if (stream_out) store_block64<OUT_F32, true>(acc, reg, lane, c_out, ldc, i0, j0, I, J, false);
         else store_block64<OUT_F32, false>(acc, reg, lane, c_out, ldc, i0, j0, I, J, false);
     };
 
@@ -319,12 +316,15 @@ hipError_t launch_t(const GemmPaperArgs& a, hipStream_t s)
     const int ti = (int)((a.I + BM - 1) / BM), tj = (int)((a.J + BN - 1) / BN);
     const int ncu = gemm_compute_units();
     const dim3 grid((unsigned)(ti * tj < ncu ? ti * tj : ncu)), block(NT);
+    // Small results plain too: at the end of a short kernel memory answers later than the caches ([832 x 768 x 256] FP4 5.3 us and 5.6; 1 %
+    // on average below 1 M elements, above 4-6 % the other way).
+    const int stream_out = gemm_streams(a) && a.I * a.J >= 1 << 20;
     if (a.b_group != 1)
         hipLaunchKernelGGL((gemm_paper_kernel<FA, FB, OUT_F32, true>), grid, block, 0, s, a.a_codes, a.a_scales, a.a_group, a.b_codes,
-                           a.b_scales, a.b_group, (int)a.I, (int)a.J, (int)a.R, a.c, a.ldc, ti, tj);
+                           a.b_scales, a.b_group, (int)a.I, (int)a.J, (int)a.R, a.c, a.ldc, ti, tj, stream_out);
     else
         hipLaunchKernelGGL((gemm_paper_kernel<FA, FB, OUT_F32, false>), grid, block, 0, s, a.a_codes, a.a_scales, a.a_group, a.b_codes,
-                           a.b_scales, a.b_group, (int)a.I, (int)a.J, (int)a.R, a.c, a.ldc, ti, tj);
+                           a.b_scales, a.b_group, (int)a.I, (int)a.J, (int)a.R, a.c, a.ldc, ti, tj, stream_out);
     return hipGetLastError();
 }
 

@@ -57,7 +57,7 @@ template <int FA, int FB> struct WideCfg {
 template <int FA, int FB, bool OUT_F32, bool B_BLOCK>
 __global__ __launch_bounds__(NT) void gemm_paper_wide_kernel(const uint8_t* __restrict__ a_codes, const float* __restrict__ a_scales, int a_shift,
                                                              const uint8_t* __restrict__ b_codes, const float* __restrict__ b_scales,
-                                                             int I, int J, int R, void* __restrict__ c_out, int64_t ldc, int tiles_i, int tiles_j)
+                                                             int I, int J, int R, void* __restrict__ c_out, int64_t ldc, int tiles_i, int tiles_j, int stream_out)
 {
     using C = WideCfg<FA, FB>;
     constexpr int NG = C::NG, KS = C::KS, SPC = C::SPC;
@@ -300,7 +300,7 @@ __global__ __launch_bounds__(NT) void gemm_paper_wide_kernel(const uint8_t* __re
         uint8_t* const reg = lds + slot * C::SLOT + wave * C::EPI;
         const int ti = ti0 + wm * WTM, tj = tj0 + wn * WTN;
         const bool interior = ti0 + TM <= I && tj0 + TN <= J;
-        if (streams_result(ldc, OUT_F32)) store_block64<OUT_F32, true>(acc, reg, lane, c_out, ldc, ti, tj, I, J, interior);
+        if (stream_out) store_block64<OUT_F32, true>(acc, reg, lane, c_out, ldc, ti, tj, I, J, interior);
         else store_block64<OUT_F32, false>(acc, reg, lane, c_out, ldc, ti, tj, I, J, interior);
     };
 
@@ -399,13 +399,13 @@ hipError_t launch_t(const GemmPaperArgs& a, hipStream_t s)
     const int ti = (int)((a.I + TM - 1) / TM), tj = (int)((a.J + TN - 1) / TN);
     const int ncu = gemm_compute_units();
     const dim3 grid((unsigned)(ti * tj < ncu ? ti * tj : ncu)), block(NT);
-    const int a_shift = a.a_group == 1 ? 0 : 7;
+    const int a_shift = a.a_group == 1 ? 0 : 7, stream_out = gemm_streams(a);
     if (a.b_group != 1)
         hipLaunchKernelGGL((gemm_paper_wide_kernel<FA, FB, OUT_F32, true>), grid, block, 0, s, a.a_codes, a.a_scales, a_shift, a.b_codes, a.b_scales,
-                           (int)a.I, (int)a.J, (int)a.R, a.c, a.ldc, ti, tj);
+                           (int)a.I, (int)a.J, (int)a.R, a.c, a.ldc, ti, tj, stream_out);
     else
         hipLaunchKernelGGL((gemm_paper_wide_kernel<FA, FB, OUT_F32, false>), grid, block, 0, s, a.a_codes, a.a_scales, a_shift, a.b_codes, a.b_scales,
-                           (int)a.I, (int)a.J, (int)a.R, a.c, a.ldc, ti, tj);
+                           (int)a.I, (int)a.J, (int)a.R, a.c, a.ldc, ti, tj, stream_out);
     return hipGetLastError();
 }
 

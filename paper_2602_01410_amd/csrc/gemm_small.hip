@@ -60,7 +60,7 @@ template <int FA, int FB, bool OUT_F32, class T, bool STREAM_B>
 __global__ __launch_bounds__(T::NT) void gemm_small_kernel(const uint8_t* __restrict__ a_codes, const uint8_t* __restrict__ a_g4,
                                                            const uint8_t* __restrict__ b_codes, const uint8_t* __restrict__ b_g4,
                                                            int I, int J, int R, void* __restrict__ c_out, int64_t ldc,
-                                                           int tiles_i, int tiles_j, float* __restrict__ norm_partials)
+                                                           int tiles_i, int tiles_j, float* __restrict__ norm_partials, int stream_out)
 {
     using C = SmallCfg<FA, FB, T>;
     constexpr int BM = T::BM, BN = T::BN, WTM = T::WTM, WTN = T::WTN, MB = T::MB, NB = T::NB, NST = T::NST, NP = T::NP, G = T::G;
@@ -335,7 +335,7 @@ __global__ __launch_bounds__(T::NT) void gemm_small_kernel(const uint8_t* __rest
             }
         }
     };
-    if (streams_result(ldc, OUT_F32)) store(std::true_type()); else store(std::false_type());
+    if (stream_out) store(std::true_type()); else store(std::false_type());
 }
 
 template <int FA, int FB, class T, bool STREAM_B>
@@ -345,10 +345,10 @@ hipError_t launch_small_s(const GemmArgs& a, hipStream_t s)
     const dim3 grid((unsigned)(ti * tj)), block(T::NT);
     if (a.out_fp32)
         hipLaunchKernelGGL((gemm_small_kernel<FA, FB, true, T, STREAM_B>), grid, block, 0, s, a.a_codes, a.a_scales_g4, a.b_codes, a.b_scales_g4,
-                           (int)a.I, (int)a.J, (int)a.R, a.c, a.ldc, ti, tj, a.norm_partials);
+                           (int)a.I, (int)a.J, (int)a.R, a.c, a.ldc, ti, tj, a.norm_partials, (int)gemm_streams(a));
     else
         hipLaunchKernelGGL((gemm_small_kernel<FA, FB, false, T, STREAM_B>), grid, block, 0, s, a.a_codes, a.a_scales_g4, a.b_codes, a.b_scales_g4,
-                           (int)a.I, (int)a.J, (int)a.R, a.c, a.ldc, ti, tj, a.norm_partials);
+                           (int)a.I, (int)a.J, (int)a.R, a.c, a.ldc, ti, tj, a.norm_partials, (int)gemm_streams(a));
     return hipGetLastError();
 }
 template <int FA, int FB, class T>

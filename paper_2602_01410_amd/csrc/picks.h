@@ -50,7 +50,13 @@ inline bool paper_wide_pays(long long I, long long J, long long R, bool both4, b
 constexpr int small_stages_per_barrier(bool cached, long long stages) { return cached && stages >= 4 ? 2 : 1; }
 
 // ---- GEMMs: whether the result is stored streaming (store16 in gemm_common.h) ----
-constexpr bool streams_result(long long ldc, bool f32) { return ldc * (f32 ? 4 : 2) % 64 == 0; }
+// Result at address `at`, rows `ldc` elements apart.  Rows that do not all start on 64 bytes leave parts of 64-byte pieces at the edges
+// of every tile, which memory takes singly: plain stores there.  Streaming against plain, operands from memory, us: pitch off 64 bytes (paper
+// recipe) [7040 x 5200 x 256] FP4 32.5 and 27.9, 63 calls +2 %; rows on 64 bytes, 9 calls, -3 %, whole lines, 27 calls above 1 M elements,
+// -7 %.  Pitch on 64 bytes, start 16 or 32 bytes past that: [4096 x 2048 x 2048] FP4, fp32, 28.6 and 21.8, [8192 x 3072 x 3072] 94.6 and 73.2,
+// [4096 x 4096 x 4096] bf16 42.7 and 39.9, [1024 x 1024 x 1024] 4.64 and 4.23, paper recipe [4096 x 8192 x 2048] FP8 99.5 and 91.9; 44 random calls with
+// bf16 results, 512 ... 12288 rows, the same on average, 19 % slower ([1472 x 12576 x 512]) to 25 % faster ([1952 x 1408 x 4096] FP8).
+constexpr bool streams_result(unsigned long long at, long long ldc, bool f32) { return ((at | (unsigned long long)ldc * (f32 ? 4 : 2)) & 63) == 0; }
 
 // ---- gemm_small.hip: whether the codes of B are streamed ----
 // Where one row of tiles reads them, once (few tokens through a weight); other tile rows would find them in L2 (all calls of the small

@@ -108,7 +108,7 @@ inline double gemm_operand_bytes(const GemmArgs& a)
     return (double)a.I * a.R * (a.fmt_a == kFP8 ? 1.0 : 0.5) + (double)a.J * a.R * (a.fmt_b == kFP8 ? 1.0 : 0.5);
 }
 // Whether the result is stored streaming.
-template <class Args> bool gemm_streams(const Args& a) { return streams_result(a.ldc, a.out_fp32); }
+template <class Args> bool gemm_streams(const Args& a) { return streams_result((uintptr_t)a.c, a.ldc, a.out_fp32); }
 constexpr double kColdBytes = 10e6;      // operands of more than that are taken to come from memory (the tables in gemm.hip say why)
 // Upper bound of the number of partials either GEMM kernel writes for an I x J output (128 x 128 tiles).
 inline int64_t gemm_norm_partials(int64_t I, int64_t J) { return ((I + 127) / 128) * ((J + 127) / 128); }

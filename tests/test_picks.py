@@ -43,6 +43,10 @@ STREAMED = [(16384, 11008, 0, 0, 157.0, 152.0), (2176, 8960, 0, 0, 102.4, 117.0)
 # GEMMs of the small tiles: one row of tiles, bytes of B's codes, us of a forward with B read plainly, streamed
 B_STREAMED = [(1, 11008 * 2048, 64.0, 56.9), (1, 9536 * 1792, 47.8, 56.9), (0, 11008 * 2048, 38.0, 46.0)]
 
+# GEMM results: address, pitch in elements, fp32, us stored plainly, streamed
+RESULTS = [(0, 2080, 0, 15.1, 13.1), (0, 5200, 0, 27.9, 32.5), (0, 2064, 1, 17.99, 16.92), (16, 2064, 1, 21.79, 29.02), (32, 3088, 1, 73.07, 94.35),
+           (16, 4128, 0, 39.89, 42.70), (32, 1056, 0, 4.23, 4.63), (16, 1056, 0, 4.23, 4.64)]
+
 # ... direct: units, us with columns stored by all waves, by those of columns
 APART = [(8, 3.70, 3.45), (204, 5.80, 5.48), (256, 6.53, 6.33), (512, 10.81, 11.39), (704, 11.40, 12.16)]
 
@@ -87,6 +91,11 @@ def test_streamed_codes(tmp_path):
 def test_streamed_weights(tmp_path):
     picks = run(tmp_path, "snip::small_streams_b(a(0), a(1))", [m[:2] for m in B_STREAMED])
     assert picks == [int(m[3] < m[2]) for m in B_STREAMED]
+
+
+def test_streamed_results(tmp_path):
+    picks = run(tmp_path, "snip::streams_result(a(0), a(1), a(2))", [m[:3] for m in RESULTS])
+    assert picks == [int(m[4] < m[3]) for m in RESULTS]
 
 
 def test_rows_apart(tmp_path):
