@@ -126,14 +126,13 @@ __device__ __forceinline__ void tile_of(int u, int nblk, int tiles_i, int tiles_
     tj = rem / rows_in_band;
 }
 
-// 16 bytes of a result, streaming ("nt"): nothing on this path reads a result again, and plain stores take room in the memory-side
-// cache (256 MB) from the quantized operands of the GEMMs that follow and leave the L2s dirty lines, which the end of a kernel
-// writes out with the chip idle: from the last store of a launch (17 MB) to the first instruction of the next one it was 3.4 us with plain
-// stores and is 1.5 with these.  Plain -> streaming, us: [4096 x 2048 x 2048] FP4 16.0 -> 13.7, FP8 22.4 -> 18.8, [8192 x 3072 x 3072] FP4 58.5 ->
-// 51.9, [2048 x 4096 x 4096] FP8 39.7 -> 36.2, fp32 42.2 -> 36.8; random calls on operands from memory 7 % on average (30 % ... -3 %), on one
-// buffer again and again 2 %; followed by a quantize call that reads the result 0 and 0.5 %.  Write-through besides ("sc1 nt") shortens
-// the gap to 1.3 us, but tiles that follow each other wait for it (blocks of the 70B and 7B shapes 0.4 % slower, 1B 0.4 % faster).
-// Which results: streams_result (picks.h).
+// 16 bytes of a result, streaming ("nt") or plain.  Plain stores take room in the memory-side cache (256 MB) from the quantized
+// operands of the GEMMs that follow and leave the L2s dirty lines, which the end of a kernel writes out with the chip idle: from the last
+// store of a launch (17 MB) to the first instruction of the next one it was 3.4 us with plain stores and is 1.5 with these.  Plain ->
+// streaming, GEMMs alone, us: [4096 x 2048 x 2048] FP4 16.0 -> 13.7, FP8 22.4 -> 18.8, [8192 x 3072 x 3072] FP4 58.5 -> 51.9, [2048 x 4096 x 4096]
+// FP8 39.7 -> 36.2, fp32 42.2 -> 36.8; random calls on operands from memory 7 % on average (30 % ... -3 %), on one buffer again and again 2 %.
+// Write-through besides ("sc1 nt") shortens the gap to 1.3 us, but tiles that follow each other wait for it (blocks of the 70B and 7B
+// shapes 0.4 % slower, 1B 0.4 % faster).  Which results, and what their readers pay: streams_result (picks.h).
 // (The empty statements keep the compiler from making one plain store of the two kinds.)
 __device__ __forceinline__ void store16(v4u v, uint8_t* p, bool stream = true)
 {

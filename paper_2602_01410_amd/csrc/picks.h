@@ -56,6 +56,15 @@ constexpr int small_stages_per_barrier(bool cached, long long stages) { return c
 // -7 %.  Pitch on 64 bytes, start 16 or 32 bytes past that: [4096 x 2048 x 2048] FP4, fp32, 28.6 and 21.8, [8192 x 3072 x 3072] 94.6 and 73.2,
 // [4096 x 4096 x 4096] bf16 42.7 and 39.9, [1024 x 1024 x 1024] 4.64 and 4.23, paper recipe [4096 x 8192 x 2048] FP8 99.5 and 91.9; 44 random calls with
 // bf16 results, 512 ... 12288 rows, the same on average, 19 % slower ([1472 x 12576 x 512]) to 25 % faster ([1952 x 1408 x 4096] FP8).
+// No limit of size: whoever reads a result at once takes back a part of what streaming it gains, or more than that, as it then comes from memory,
+// but a step gains.  GEMM alone, followed by a quantize call and by an elementwise pass that read the result, operands from memory, plain ->
+// streaming, us: [64 x 4096 x 4096] FP4, 0.5 MB, 4.65 -> 4.67, 8.15 -> 8.41 and 6.85 -> 6.90; [512 x 2048 x 2048] 2 MB 4.88 -> 4.92, 8.75 -> 9.27 and
+// 7.30 -> 7.54; [4096 x 2048 x 2048] 17 MB 15.7 -> 13.2, 23.5 -> 23.0 and 21.9 -> 22.2, fp32 17.5 -> 16.9 and (elementwise) 28.1 -> 32.0; [8192 x 8192 x
+// 3072] 134 MB 107.2 -> 105.9, 133 -> 147 and 157 -> 160; [16384 x 11008 x 4096] 368 -> 350, 460 -> 442 and 470 -> 461.  Training steps of one to four blocks in
+// which elementwise passes read every Y and dX as soon as it is there, 64 ... 16384 tokens, hidden 1024 ... 8192, take 0.2 ... 5 % less
+// (21 steps, mean 2.5), with every dW read at once too 0.1 % (twelve, -1.6 ... +1.6), with fp32 dW that wait 1 ... 9 % less (eight), with no reader 2 ... 11 %.
+// Limits tried: plain below 1 MB, 1 % less for 64 tokens of hidden 2048 with readers, 1 % more for forwards of 64 tokens without; below 4 MB up to 3 %
+// more without readers; plain from 56 MB or 200 MB on, 1 % less to 1.5 % more.
 constexpr bool streams_result(unsigned long long at, long long ldc, bool f32) { return ((at | (unsigned long long)ldc * (f32 ? 4 : 2)) & 63) == 0; }
 
 // ---- gemm_small.hip: whether the codes of B are streamed ----
