@@ -159,16 +159,25 @@ constexpr bool qb_through_lds(long long cols, long long units, long long ncu)
 constexpr bool qb_rows_apart(long long units, long long ncu) { return units <= ncu; }
 
 // ---- ... whether the forms for large tensors (through LDS; a wave per unit) stream their codes past the caches ----
-// From 64 M elements on, of which both orientations' codes fill half of the memory-side cache (256 MB) and more: they would not be there
-// any more when a GEMM wants them, and leave their place to those of smaller tensors and to what the GEMMs read.  Plain -> streaming:
-// all statistics [16384 x 11008] FP4 157 -> 152 us, the 19 quantize calls of a 7B-shaped block 1392 -> 1344, those of a 70B-shaped one 1546 ->
-// 1490.  Smaller tensors' codes are still there: streamed from 16 M elements on, the quantize calls of 1B- and 3B-shaped blocks gain 2 and
-// 8 % and the whole blocks 1.5 %, but 40 steps of one linear lose 1.8 % on average (14 % at worst, [2176 x 8960 x 1024] 102 us -> 117).
-// And where every stored row starts on 64 bytes: pieces of 64 bytes reach memory by themselves ([12384 x 10656] FP4, rows of 5328 bytes,
-// 161 us -> 196).
-constexpr bool qb_streams(long long rows, long long cols, bool fp8_rows, bool fp8_columns)
+// From 128 MB of codes in both orientations on, half of the memory-side cache (256 MB), and of FP4 codes alone from 256 MB on: they would
+// not be there any more when a GEMM wants them, and leave their place to those of smaller tensors and to what the GEMMs read.  Plain ->
+// streaming, us: steps of one linear, gradients of [16384 x 4096] FP8 (128 MB) 294 -> 278, [4096 x 16384] 301 -> 285, [16384 x 11008] FP8 rows and FP4
+// columns (258 MB) 1050 -> 1013; but [8192 x 8192] FP8 395 -> 413.  Steps of blocks, 7B-shaped, 16384 tokens, FP8 7937 -> 7912 (9788 -> 9706 with readers of
+// every Y and dX), rows and columns of both formats 7163 -> 7155 (9054 -> 8992), 70B-shaped FP8 15783 -> 15725; FP4, tensors of 256 MB ([32768 x 8192])
+// 3606 -> 3572.  Less is slower: FP4 gradients of [16384 x 4096] (64 MB) 184 -> 193, in both formats (96 MB) 247 -> 262, blocks in FP4 with tensors of 172 MB
+// 4638 -> 4675 and with 224 MB 8966 -> 9021; streamed from 16 M elements on, 40 steps of one linear lose 1.8 % on average (14 % at worst, [2176 x 8960 x
+// 1024] 102 us -> 117).
+// With statistics the codes come more slowly, and it pays from 64 M elements on: steps of one linear with gradients of 64 M ... 172 M elements, FP8
+// 2.4 % less on average (eight, 0.6 ... 6.7), both formats 1.0 % (sixteen, 4.3 ... -1.8), FP4 the same (eight, 1.6 ... -2.2); [4096 x 16384] FP8 336 -> 313, FP4 rows and FP8
+// columns 302 -> 290.
+// And where every stored row starts on 64 bytes, by pitch and by address: pieces of 64 bytes reach memory by themselves ([12384 x 10656]
+// FP4, rows of 5328 bytes, 161 us -> 196).
+constexpr bool qb_streams(long long rows, long long cols, bool fp8_rows, bool fp8_columns, bool stats, unsigned long long at_rows = 0, unsigned long long at_columns = 0)
 {
-    return rows * cols >= 64ll << 20 && (fp8_rows ? cols : cols / 2) % 64 == 0 && (fp8_columns ? rows : rows / 2) % 64 == 0;
+    const long long row = fp8_rows ? cols : cols / 2, column = fp8_columns ? rows : rows / 2;        // bytes
+    if (((at_rows | at_columns | (unsigned long long)row | (unsigned long long)column) & 63) != 0) return false;
+    if (stats) return rows * cols >= 64ll << 20;
+    return rows * row + cols * column >= (fp8_rows || fp8_columns ? 128ll << 20 : 256ll << 20);
 }
 
 }  // namespace snip

@@ -1498,7 +1498,7 @@ static int launch_qb_form(const QuantBothArgs& a, double* partials, hipStream_t 
 template <int FMT_R, int FMT_C, int RULE, int STATS>
 static int launch_qb(const QuantBothArgs& a, double* partials, QbForm form, hipStream_t s)
 {
-    const bool stream = qb_streams(a.rows, a.cols, FMT_R == kFP8, FMT_C == kFP8);
+    const bool stream = qb_streams(a.rows, a.cols, FMT_R == kFP8, FMT_C == kFP8, STATS != 0, (uintptr_t)a.codes_r, (uintptr_t)a.codes_c);
     if constexpr (STATS != 0)
         if (form == QbForm::kWave)
             return stream ? launch_qb_form<FMT_R, FMT_C, RULE, STATS, 0, FMT_C == kFP8 ? 4 : 8, false, true>(a, partials, s)

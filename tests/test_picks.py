@@ -37,8 +37,13 @@ BANDS = [(2048, 43040, 154.8, 129.0), (2048, 26000, 96.7, 81.1), (6144, 14304, 1
 LDS = [(32, 1100, 9.24, 10.23), (64, 537, 7.08, 7.79), (96, 537, 8.87, 8.84), (11008, 11008, 140.5, 126.9), (4096, 8192, 101.2, 87.7), (2048, 256, 5.9, 6.3),
        (3072, 576, 12.5, 11.4), (4096, 800, 14.4, 15.2)]
 
-# ... forms for large tensors: rows, columns, FP8 rows, FP8 columns, us with codes stored plainly, streamed.  (The second: what a step of one linear takes.)
-STREAMED = [(16384, 11008, 0, 0, 157.0, 152.0), (2176, 8960, 0, 0, 102.4, 117.0), (12384, 10656, 0, 0, 160.8, 196.3)]
+# ... forms for large tensors: rows, columns, FP8 rows, FP8 columns, statistics, us with codes stored plainly, streamed: of the quantize call ([12384 x
+# 10656]), of a step of one linear, of a block ([16384 x 11008] FP4, [8192 x 28672], [32768 x 8192])
+STREAMED = [(16384, 11008, 0, 0, 0, 4638., 4675.), (8192, 28672, 0, 0, 0, 8966., 9021.), (32768, 8192, 0, 0, 0, 3606., 3572.),
+            (16384, 4096, 0, 0, 0, 184.4, 192.5), (16384, 4096, 0, 1, 0, 246.6, 262.0), (16384, 4096, 1, 0, 0, 249.9, 252.0), (16384, 4096, 1, 1, 0, 294.0, 278.3),
+            (4096, 16384, 1, 1, 0, 301.4, 284.9), (16384, 11008, 1, 0, 0, 1050., 1013.), (16384, 11008, 0, 1, 0, 1041., 1021.),
+            (16384, 4096, 1, 1, 1, 318.9, 308.6), (4096, 16384, 1, 1, 1, 336.0, 313.4), (4096, 16384, 0, 1, 1, 302.4, 289.6), (8192, 8192, 1, 0, 1, 434.6, 425.0),
+            (2176, 8960, 0, 0, 0, 102.4, 117.0), (12384, 10656, 0, 0, 0, 160.8, 196.3), (12384, 10656, 0, 0, 1, 160.8, 196.3)]
 
 # GEMMs of the small tiles: one row of tiles, bytes of B's codes, us of a forward with B read plainly, streamed
 B_STREAMED = [(1, 11008 * 2048, 64.0, 56.9), (1, 9536 * 1792, 47.8, 56.9), (0, 11008 * 2048, 38.0, 46.0)]
@@ -84,8 +89,11 @@ def test_through_lds(tmp_path):
 
 
 def test_streamed_codes(tmp_path):
-    picks = run(tmp_path, "snip::qb_streams(a(0), a(1), a(2), a(3))", [m[:4] for m in STREAMED])
-    assert picks == [int(m[5] < m[4]) for m in STREAMED]
+    rule = "snip::qb_streams(a(0), a(1), a(2), a(3), a(4), a(5), a(6))"
+    assert run(tmp_path, rule, [(*m[:5], 0, 0) for m in STREAMED]) == [int(m[6] < m[5]) for m in STREAMED]
+    # codes that start off 64 bytes have rows off 64 bytes, whatever their pitch
+    for stats in (0, 1):
+        assert run(tmp_path, rule, [(16384, 11008, 1, 1, stats, *at) for at in ((4096, 64), (16, 0), (0, 48), (32, 32))]) == [1, 0, 0, 0]
 
 
 def test_streamed_weights(tmp_path):
