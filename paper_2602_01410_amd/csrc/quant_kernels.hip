@@ -1472,8 +1472,9 @@ hipError_t launch_quantize(const QuantArgs& a, hipStream_t s)
     return e;
 }
 
-// Work distribution of quant_both_kernel: waves of a workgroup x tiles of the unit they share (Lds: RAW_LDS), or a wave per unit.
-enum class QbForm { k4x4, k4x4Lds, k4x8, kWave };
+// Work distribution of quant_both_kernel: waves of a workgroup x tiles of the unit they share (Apart: APART, Lds: RAW_LDS), or a wave
+// per unit.
+enum class QbForm { k4x4, k4x4Apart, k4x4Lds, k4x8, kWave };
 
 template <int FMT_R, int FMT_C, int RULE, int STATS, int NW, int RBU, bool RAW_LDS = false, bool STREAM = false, bool APART = false>
 static int launch_qb_form(const QuantBothArgs& a, double* partials, hipStream_t s)
@@ -1510,8 +1511,7 @@ static int launch_qb(const QuantBothArgs& a, double* partials, QbForm form, hipS
             return stream ? launch_qb_form<FMT_R, FMT_C, RULE, STATS, 4, 4, true, true>(a, partials, s)
                           : launch_qb_form<FMT_R, FMT_C, RULE, STATS, 4, 4, true>(a, partials, s);
     if constexpr (STATS == 0)
-        if (qb_rows_apart(((a.cols + kColsPerWave - 1) / kColsPerWave) * ((a.rows / kBlock + 3) / 4), gemm_compute_units()))
-            return launch_qb_form<FMT_R, FMT_C, RULE, STATS, 4, 4, false, false, true>(a, partials, s);
+        if (form == QbForm::k4x4Apart) return launch_qb_form<FMT_R, FMT_C, RULE, STATS, 4, 4, false, false, true>(a, partials, s);
     return launch_qb_form<FMT_R, FMT_C, RULE, STATS, 4, 4>(a, partials, s);
 }
 
@@ -1533,22 +1533,26 @@ static int launch_qb(const QuantBothArgs& a, double* partials, QbForm form, hipS
 constexpr int64_t kTwoWavesPerSimd = 2048;
 static QbForm pick_qb_form(const QuantBothArgs& a, int stats)
 {
+    QbForm direct = QbForm::k4x4;
+    bool through_lds = false;
+    if (stats == 0) {
+        const int64_t units = ((a.cols + kColsPerWave - 1) / kColsPerWave) * ((a.rows / kBlock + 3) / 4), ncu = gemm_compute_units();
+        if (qb_rows_apart(units, ncu)) direct = QbForm::k4x4Apart;
+        through_lds = qb_through_lds(a.cols, units, ncu);
+    }
     // SNIP_QUANT_BOTH_UNIT=4x4|lds|4x8|wave in the environment, read at every call, fixes the form where it exists for the
     // call, =workgroup keeps to a workgroup per unit; for tests and measurements
     bool group = false;
     if (const char* e = getenv("SNIP_QUANT_BOTH_UNIT")) {
         const bool fp4 = a.fmt_c == kFP4;
         const struct { const char* name; QbForm form; bool exists; } kForms[] = {
-            {"4x4", QbForm::k4x4, true}, {"4x8", QbForm::k4x8, fp4 && stats != 0}, {"lds", QbForm::k4x4Lds, stats == 0}, {"wave", QbForm::kWave, stats != 0}};
+            {"4x4", direct, true}, {"4x8", QbForm::k4x8, fp4 && stats != 0}, {"lds", QbForm::k4x4Lds, stats == 0}, {"wave", QbForm::kWave, stats != 0}};
         for (const auto& f : kForms)
             if (!strcmp(e, f.name) && f.exists) return f.form;
         group = !strcmp(e, "workgroup");
     }
     const int64_t elems = a.rows * a.cols;
-    if (stats == 0) {
-        const int64_t units = ((a.cols + kColsPerWave - 1) / kColsPerWave) * ((a.rows / kBlock + 3) / 4);
-        return qb_through_lds(a.cols, units, gemm_compute_units()) ? QbForm::k4x4Lds : QbForm::k4x4;
-    }
+    if (stats == 0) return through_lds ? QbForm::k4x4Lds : direct;
     if (stats == 1) {
         const int64_t tiles = a.fmt_c == kFP8 ? 4 : 8, waves = ((a.cols + kColsPerWave - 1) / kColsPerWave) * ((a.rows / kBlock + tiles - 1) / tiles);
         const int64_t rounds = (waves + kTwoWavesPerSimd - 1) / kTwoWavesPerSimd;
