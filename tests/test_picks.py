@@ -45,8 +45,9 @@ STREAMED = [(16384, 11008, 0, 0, 0, 4638., 4675.), (8192, 28672, 0, 0, 0, 8966.,
             (16384, 4096, 1, 1, 1, 318.9, 308.6), (4096, 16384, 1, 1, 1, 336.0, 313.4), (4096, 16384, 0, 1, 1, 302.4, 289.6), (8192, 8192, 1, 0, 1, 434.6, 425.0),
             (2176, 8960, 0, 0, 0, 102.4, 117.0), (12384, 10656, 0, 0, 0, 160.8, 196.3), (12384, 10656, 0, 0, 1, 160.8, 196.3)]
 
-# GEMMs of the small tiles: one row of tiles, bytes of B's codes, us of a forward with B read plainly, streamed
-B_STREAMED = [(1, 11008 * 2048, 64.0, 56.9), (1, 9536 * 1792, 47.8, 56.9), (0, 11008 * 2048, 38.0, 46.0)]
+# GEMMs of the small tiles: one row of tiles, bytes of B's codes, us with B read plainly, streamed: forwards of three blocks in turn, one GEMM on
+# weights in turn (90 MB and 541 MB; 268 MB)
+B_STREAMED = [(1, 11008 * 2048, 62.9, 56.4), (1, 9536 * 1792, 47.8, 56.9), (0, 11008 * 2048, 9.24, 12.46), (0, 11008 * 2048, 11.25, 13.10), (0, 16384 * 4096, 19.54, 25.88)]
 
 # GEMM results: address, pitch in elements, fp32, us stored plainly, streamed
 RESULTS = [(0, 2080, 0, 15.1, 13.1), (0, 5200, 0, 27.9, 32.5), (0, 2064, 1, 17.99, 16.92), (16, 2064, 1, 21.79, 29.02), (32, 3088, 1, 73.07, 94.35),
