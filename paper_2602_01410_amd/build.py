@@ -14,8 +14,8 @@ MICROBENCH = os.path.join(_HERE, "snip_microbench")
 OBJDIR = os.path.join(_HERE, "_build")          # object files (not tracked)
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
          "-Wno-unused-command-line-argument"]
-# Arguments of a kernel come in scalar registers instead of out of memory: 0.3 us at the start of every launch (forward of 64 tokens, 7B-shaped,
-# 65.7 us -> 63.8, 1B-shaped block 712 -> 707, paper recipe 1024 x 1024 x 1024 51.6 -> 50.2).  Not for the large GEMM tiles: they run out of scalar
+# Arguments of a kernel come in scalar registers instead of out of memory: 0.15-0.2 us at the start of a launch (forward of 64 tokens, 7B-shaped,
+# eleven launches, 65.7 us -> 63.8, paper recipe 1024 x 1024 x 1024, nine, 51.6 -> 50.2; 1B-shaped block 712 -> 707).  Not for the large GEMM tiles: they run out of scalar
 # registers, and two kernels would fetch more spilled ones between the MFMAs.
 PRELOAD = ["-mllvm", "-amdgpu-kernarg-preload-count=16"]
 NO_PRELOAD = ("gemm_fast.hip",)

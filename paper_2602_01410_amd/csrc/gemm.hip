@@ -353,9 +353,12 @@ int gemm_compute_units()
 // quarter full ([2048 x 2304 x 3072] FP8 37 us with 128 x 128 for 26 with 256 x 128).  On 1233 other problems the pick is on
 // average 0.2 % (cached, up to 10 MB) and 0.5 % (from memory, more) slower than the fastest tile, 20 % at worst (rows of few
 // tokens by very wide weights, where the tables are rough).  The cached stages of 64 x 32 and 32 x 32 were lowered by hand
-// when 32 x 32 took up two stages per barrier; with the tables and kernels as they are, 2600 problems of up to 10 MB (1 ... 1024 rows,
-// contractions of 96 ... 16384, many cut) come out 0.13 % slower on average than with the fastest small tile, from the caches and from
-// memory, 20 % at worst ([608 x 6752 x 2048] FP8 x FP4: 128 x 128 for 64 x 64).
+// when 32 x 32 took up two stages per barrier.
+// That was before results were streamed, arguments preloaded (small tiles) and 64 x 64 replaced by 32 x 64 up to 32 rows, which the row of
+// 64 x 64 now prices.  With the kernels as they are, 150 other problems (half of them of 1 ... 32 rows, the rest of up to 4096, 64 ... 16384 columns,
+// contractions of 96 ... 16384, all format pairs), cached and from memory, the pick against the fastest tile: up to 32 rows 0.5 % slower on
+// average and 6 % at worst with up to 10 MB of operands, 2.3 % and 14 % with more; beyond 32 rows 1.9 % (cached) and 1.1 % (from memory), 22 % at
+// worst, and with more than 10 MB 5 % and 0.8 %, 14 % at worst.
 struct TileCost { GemmTile tile; int m, n; float start, turn, alone[2], full[2], tail[2]; };      // [0]: FP4 x FP4, [1]: others
 static const TileCost kTileCosts[2][6] = {{
     {GemmTile::kBig,      256, 256, 7.7f, 4.5f, {0.61f, 0.62f}, {1.90f, 1.42f}, {0.61f, 0.62f}},

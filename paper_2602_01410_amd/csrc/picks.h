@@ -68,12 +68,16 @@ constexpr int small_stages_per_barrier(bool cached, long long stages) { return c
 constexpr bool streams_result(unsigned long long at, long long ldc, bool f32) { return ((at | (unsigned long long)ldc * (f32 ? 4 : 2)) & 63) == 0; }
 
 // ---- gemm_small.hip: whether the codes of B are streamed ----
-// Where one row of tiles reads them, once (few tokens through a weight); other tile rows would find them in L2 (all calls of the small
-// tiles streamed, a step of 1024 x 2048 x 2048: 38 us -> 46).  From 20 MB on: a block with such weights has 90 MB of them, so the
-// memory-side cache (256 MB) keeps them for no second use, and streamed they come faster and leave it to the smaller ones.  Forward of
-// 7B-shaped blocks in FP4, 64 tokens 64.0 us -> 56.9, one token 55.1 -> 50.7, 70B-shaped 109 -> 99; streamed from 8 MB on 64 tokens took 60.7.
+// Where one row of tiles reads them, once (few tokens through a weight); other tile rows would find them in L2 ([65 x 11008 x 4096] FP4, two rows
+// of 64 x 64, four weights in turn 9.2 us -> 12.5, 24 of them, from memory, 11.3 -> 13.1).  From 20 MB on: a block with such weights has 90 MB
+// of them, so the memory-side cache (256 MB) keeps them for no second use, and streamed they come faster and leave it to the smaller ones.
+// What that is worth follows from how much is read in turn, which a call does not see.  Plain -> streaming, [1 x 11008 x 4096] and [64 x 11008 x 4096]
+// FP4 (22.5 MB), us: one weight again and again 5.13 -> 5.14 and 6.16 -> 6.24, four 5.95 -> 6.11 and 6.50 -> 8.16, eight 5.95 -> 6.30 and 6.51 -> 8.34, sixteen
+// (361 MB) 6.78 -> 6.40 and 8.77 -> 8.45; FP8 (45 MB) four 9.16 -> 10.2 and 10.1 -> 14.0, sixteen 11.8 -> 10.6 and 14.8 -> 14.3.  Forwards of blocks, four shapes of
+// 7B to 13B, one and 64 tokens: one block again and again 3 ... 21 % slower (7B-shaped FP4 47.6 -> 49.1 and 52.9 -> 59.8), three in turn 1 ... 14 %
+// faster (52.9 -> 48.5 and 62.9 -> 56.4), eight 0 ... 7 % (53.5 -> 53.1 and 64.4 -> 64.4).  A program has all blocks of a model in turn.
 // Smaller weights may be in that cache, and streaming would bring them from memory again (8 tokens, hidden 3584, FP4, three blocks
-// in turn: 47.8 us and 56.9).
+// in turn: 47.8 us and 56.9; streamed from 8 MB on 64 tokens through 7B-shaped blocks took 60.7).
 constexpr bool small_streams_b(bool one_row, long long bytes) { return one_row && bytes >= 20ll << 20; }
 
 // ---- quant_kernels.hip, quantize for both orientations: the order of the units among the XCDs ----

@@ -854,10 +854,10 @@ __device__ __forceinline__ void step(int& soff, int by)
 // [16384 x 11008] FP4 195 -> 174, FP8 214 -> 197.
 // Offsets inside a tile are 32-bit: launch_quantize_both keeps to tensors whose rows are short enough (qb_offsets_fit).
 // Cache policies of buffer instructions: streaming ("nt") and write-through ("sc1").  A tile that goes through LDS is read once and
-// streamed, so that sources leave the memory-side cache to the codes: 40 steps of one linear 0.9 % on average, 6 % at most (plain stores
-// of codes; all three: with the statistics' below).  Codes of a workgroup per unit with statistics are written through: at the end of a
-// kernel the L2s write out what is dirty with the chip idle ([1504 x 2080] 9.1 us -> 8.4, [4096 x 4096] 22.5 -> 20.8, a step 1504 x 2080 x
-// 1568 58.9 -> 57.3, 2048 x 4096 x 4096 165.9 -> 162.3).  Without statistics and LDS it makes no difference.  Large tensors: qb_streams.
+// streamed, so that sources leave the memory-side cache to the codes: alone, 40 steps of one linear come out the same on average (7 % faster
+// to 4 % slower).  Codes of a workgroup per unit with statistics are written through: at the end of a kernel the L2s write out what is dirty
+// with the chip idle (20 steps of one linear 2.3 % on average, 0 ... 5; [1504 x 2080] 9.1 us -> 8.4, [4096 x 4096] 22.5 -> 20.8, a step 1504 x 2080 x 1568
+// 59.9 -> 58.7, 2048 x 4096 x 4096 163.2 -> 160.1).  Without statistics and LDS it makes no difference.  Large tensors: qb_streams.
 constexpr int kStream = 2, kThrough = 16;
 constexpr int qb_threads(int nw, int stats) { return nw ? nw * (stats ? 64 : 128) : 256; }
 template <int FMT_R, int FMT_C, int RULE, int STATS, int NW, int RBU, bool RAW_LDS, bool STREAM, bool APART>      // STATS: 0 none, 1 the chosen formats' errors, 2 both formats' errors
